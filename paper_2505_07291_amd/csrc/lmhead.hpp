@@ -148,14 +148,16 @@ __device__ __forceinline__ void lm_tile_of(int L, int tiles_m, int tiles_n, int 
 struct LmSplit {
     int full, rest, s2;
 };
-__device__ __forceinline__ LmSplit lm_plan_split(int tiles, int k_tiles, int max_items, int n_cu)
+__host__ __device__ inline LmSplit lm_plan_split(int tiles, int k_tiles, int max_items, int n_cu)
 {
     LmSplit sp;
     sp.rest = max_items > 0 ? tiles % n_cu : 0;
     sp.full = tiles - sp.rest;
     sp.s2 = 1;
     if (sp.rest == 0) return sp;
-    const int lim = min(min(LM_SPLIT_MAX, k_tiles / 8), max_items / sp.rest);
+    int lim = LM_SPLIT_MAX;
+    if (k_tiles / 8 < lim) lim = k_tiles / 8;
+    if (max_items / sp.rest < lim) lim = max_items / sp.rest;
     float best = 1.f;
     for (int S = 2; S <= lim; ++S) {
         const float cost = (float)((sp.rest * S + n_cu - 1) / n_cu) / (float)S + 0.002f * (float)S;
@@ -165,6 +167,24 @@ __device__ __forceinline__ LmSplit lm_plan_split(int tiles, int k_tiles, int max
         }
     }
     return sp;
+}
+
+// Workgroups that cover every plan a product of at most tiles_m tile rows can get (the device knows
+// how many there really are): whole tiles and parts, each kind rounded up to the 8 XCDs.  The plans
+// repeat with the tile count modulo n_cu while the whole tiles only grow, so the last n_cu row
+// counts hold the largest.  A workgroup without work is not free - it takes all 160 KB of a CU's
+// LDS, so only one at a time gets in, about 5 us each: launched for the most parts any plan could
+// have (32 for each of n_cu tiles, 8192 workgroups) they cost 0.15 to 0.2 ms a product whatever its
+// size (dL/dH of 612 x 50304 x 768: 236 us, 53 us with this bound).
+inline long long lm_split_grid(int tiles_m, int tiles_n, int k_tiles, int max_items, int n_cu)
+{
+    long long most = 8;
+    for (int t = tiles_m > n_cu ? tiles_m - n_cu + 1 : 1; t <= tiles_m; ++t) {
+        const LmSplit sp = lm_plan_split(t * tiles_n, k_tiles, max_items, n_cu);
+        const long long g = ((long long)(sp.full + 7) / 8 + (sp.rest * sp.s2 + 7) / 8) * 8;
+        if (g > most) most = g;
+    }
+    return most;
 }
 
 // Workgroup -> tile (and part).  Each XCD takes a contiguous run of the whole tiles, then a
@@ -1008,11 +1028,10 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
     }
     p.tiles_n = (p.N + LM_BN - 1) / LM_BN;
     if (p.group_m <= 0) p.group_m = LM_GROUP_M;
-    // upper bound: every tile whole, plus the most parts a plan can have (fewer than n_cu tiles cut)
-    const long long tiles = (long long)((p.M + LM_BM - 1) / LM_BM) * p.tiles_n;
-    const long long items = EPI == LM_EPI_BF16 && p.split_items > 0
-                                ? (long long)(p.n_cu > 0 ? p.n_cu : 256) * LM_SPLIT_MAX : 0;
-    const long long grid = ((tiles + 7) / 8 + (items + 7) / 8) * 8;
+    const int tiles_m = (p.M + LM_BM - 1) / LM_BM;
+    const long long grid = EPI == LM_EPI_BF16 && p.split_items > 0
+                               ? lm_split_grid(tiles_m, p.tiles_n, p.K / LM_BK, p.split_items, p.n_cu > 0 ? p.n_cu : 256)
+                               : ((long long)tiles_m * p.tiles_n + 7) / 8 * 8;
     hipLaunchKernelGGL((lm_gemm_nt<EPI, STORE_Z, AUX, AKM, BKM>), dim3((unsigned)grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
     return hipGetLastError();
 }
