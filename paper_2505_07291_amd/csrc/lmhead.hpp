@@ -793,51 +793,71 @@ __global__ void __launch_bounds__(256) lm_gather_rows(const __bf16 *in, long lon
 }
 
 // Merges the tile partials of each compact row, then the objective's once-per-row arithmetic.
-// A workgroup takes 16 compact rows; 16 lanes share a row, each merging every 16th tile, and
-// their results meet in LDS in lane order (fixed order: the bits repeat from run to run).
-constexpr int LM_CMB_ROWS = 16, LM_CMB_LANES = 16;
+// A workgroup takes 16 compact rows; 64 lanes share a row, lane l merging tiles l, l + 64, ..., and
+// their results meet in LDS in lane order (fixed order: the bits repeat from run to run).  What
+// bounds it is latency - the partials of 1056 rows and 594 tiles are 5 MB - so every lane reads all
+// of its partials into registers at once (up to LM_CMB_KEEP tiles, V = 196608; tiles beyond them are
+// read twice) and the maximum and the sums are taken from there.  16 lanes to a row, each walking 37
+// tiles twice, took 48 us on that batch.
+constexpr int LM_CMB_ROWS = 16, LM_CMB_LANES = 64, LM_CMB_KEEP = 12;
 template <bool AUX>
 __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowParams p, LmRows w)
 {
     __shared__ float sh_m[LM_CMB_LANES][LM_CMB_ROWS + 1], sh_s[LM_CMB_LANES][LM_CMB_ROWS + 1];
-    __shared__ float sh_w[LM_CMB_LANES][LM_CMB_ROWS + 1];
+    __shared__ float sh_w[AUX ? LM_CMB_LANES : 1][LM_CMB_ROWS + 1];
     const int rl = threadIdx.x % LM_CMB_ROWS, tl = threadIdx.x / LM_CMB_ROWS;
     int base, count;
     lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, base, count);
+    if ((long long)blockIdx.x * LM_CMB_ROWS >= count) return;  // whole workgroup alike
     const long long il = (long long)blockIdx.x * LM_CMB_ROWS + rl;  // row inside the chunk: the partials' index
     const long long i = base + il;                                  // compact row: the per-row arrays' index
     const bool live = il < count;
+    float pm[LM_CMB_KEEP], ps[LM_CMB_KEEP], pw[AUX ? LM_CMB_KEEP : 1];
+    const int tiles = live ? w.tiles_n : 0;
+#pragma unroll
+    for (int j = 0; j < LM_CMB_KEEP; ++j) {
+        const int t = tl + j * LM_CMB_LANES;
+        const long long at = (long long)t * w.part_stride + il;
+        pm[j] = t < tiles ? w.part_m[at] : -INFINITY;
+        ps[j] = t < tiles ? w.part_s[at] : 0.f;
+        if constexpr (AUX) pw[j] = t < tiles ? w.part_w[at] : 0.f;
+    }
+    const float zy = live ? w.zy[i] : 0.f;
     float mz = -INFINITY;  // maximum over the tiles, in units of z
-    if (live)
-        for (int t = tl; t < w.tiles_n; t += LM_CMB_LANES) mz = fmaxf(mz, w.part_m[(long long)t * w.part_stride + il]);
+#pragma unroll
+    for (int j = 0; j < LM_CMB_KEEP; ++j) mz = fmaxf(mz, pm[j]);
+    for (int t = tl + LM_CMB_KEEP * LM_CMB_LANES; t < tiles; t += LM_CMB_LANES)
+        mz = fmaxf(mz, w.part_m[(long long)t * w.part_stride + il]);
     sh_m[tl][rl] = mz;
     __syncthreads();
-#pragma unroll
+#pragma unroll 16
     for (int l = 0; l < LM_CMB_LANES; ++l) mz = fmaxf(mz, sh_m[l][rl]);
-    const float zy = live ? w.zy[i] : 0.f;
     const float mx = fmaxf(mz, zy);  // the sampled token may be the row's maximum
     const float mk = mx * p.k;
     float s = 0.f, ws = 0.f;
-    if (live)
-        for (int t = tl; t < w.tiles_n; t += LM_CMB_LANES) {
-            const float mt = w.part_m[(long long)t * w.part_stride + il];
-            if (mt == -INFINITY) continue;
-            const float st = w.part_s[(long long)t * w.part_stride + il];
-            if constexpr (AUX) {
-                const float d = (mt - mx) * p.k;
-                const float f = __builtin_amdgcn_exp2f(d);
-                s = fmaf(st, f, s);
-                ws = fmaf(f, fmaf(d, st, w.part_w[(long long)t * w.part_stride + il]), ws);
-            } else {
-                s = fmaf(st, __builtin_amdgcn_exp2f(fmaf(mt, p.k, -mk)), s);
-            }
+    auto add = [&](float mt, float st, float wt) __attribute__((always_inline)) {
+        if (mt == -INFINITY) return;
+        if constexpr (AUX) {
+            const float d = (mt - mx) * p.k;
+            const float f = __builtin_amdgcn_exp2f(d);
+            s = fmaf(st, f, s);
+            ws = fmaf(f, fmaf(d, st, wt), ws);
+        } else {
+            s = fmaf(st, __builtin_amdgcn_exp2f(fmaf(mt, p.k, -mk)), s);
         }
+    };
+#pragma unroll
+    for (int j = 0; j < LM_CMB_KEEP; ++j) add(pm[j], ps[j], AUX ? pw[AUX ? j : 0] : 0.f);
+    for (int t = tl + LM_CMB_KEEP * LM_CMB_LANES; t < tiles; t += LM_CMB_LANES) {
+        const long long at = (long long)t * w.part_stride + il;
+        add(w.part_m[at], w.part_s[at], AUX ? w.part_w[at] : 0.f);
+    }
     sh_s[tl][rl] = s;
     if constexpr (AUX) sh_w[tl][rl] = ws;
     __syncthreads();
     if (tl != 0 || !live) return;
     float s_excl = 0.f, w_excl = 0.f;
-#pragma unroll
+#pragma unroll 16
     for (int l = 0; l < LM_CMB_LANES; ++l) {
         s_excl += sh_s[l][rl];
         if constexpr (AUX) w_excl += sh_w[l][rl];
