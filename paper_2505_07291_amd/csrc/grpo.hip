@@ -74,6 +74,7 @@ struct RowParams {
     float lo, hi, delta, grad_scale;
     int bwd;  // 0: log-probs only (grpo_logprobs_fwd), 1: objective + gradient
     const int *order;  // optional: the rows in the order they are handed out (grpo_order_rows), else 0, 1, 2, ...
+    int queued;       // rows come from the queue in the workspace (0: strided over the grid)
     int queue_chunk;  // rows taken from the queue per increment
     int queue_parts;  // counters in use (1 or kQueueParts)
     // auxiliary terms (kernels instantiated with AUX only)
@@ -872,10 +873,13 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     // With a workspace (objective + gradient) rows are handed out through a counter in
     // it, one at a time, to whichever workgroup is free: masked rows cost a third of a
     // live row, and a fixed assignment leaves some workgroups with all the live ones.
-    // Without a workspace (log-probs only) rows are strided over the grid.
-    const bool queued = p.hdr != nullptr;
-    long long strided_next = blockIdx.x;
-    unsigned grabs = 0;
+    // Without a workspace (log-probs only), and in small batches (launch_cached), rows are
+    // strided over the grid, the rows of round i by workgroups turned by i * 5/8 of the
+    // grid: response lengths that divide the grid would otherwise give one workgroup the
+    // same, masked, position of every response.
+    const bool queued = p.queued != 0;
+    long long strided_base = 0;
+    unsigned turn = blockIdx.x, grabs = 0;
     // very narrow rows are also handed out several at a time
     const long long chunk = p.queue_chunk;
     long long chunk_next = 0, chunk_end = 0;  // positions inside the current partition
@@ -885,9 +889,11 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     int part = (int)((blockIdx.x / 8) % nparts), parts_done = 0;
     auto grab = [&]() -> long long {
         if (!queued) {
-            const long long r = strided_next;
-            strided_next += gridDim.x;
-            return r;
+            const long long r = strided_base + turn;
+            strided_base += gridDim.x;
+            turn += gridDim.x / 8 * 5;
+            if (turn >= gridDim.x) turn -= gridDim.x;
+            return r;  // only the last round has positions past the batch: they end the workgroup's work
         }
         for (;;) {
             if (chunk_next < chunk_end) {
@@ -1734,9 +1740,16 @@ int cu_count()
 }
 
 template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false>
-void launch_cached(const RowParams &p, int blocks_per_cu, hipStream_t st)
+void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
 {
+    RowParams p = p_in;
     long long grid = (long long)cu_count() * blocks_per_cu;
+    // Batches of so few rows that the queue costs more than the balance it gives: with at most one
+    // row for each workgroup there is nothing to balance; narrow rows, which are queued several at a
+    // time, leave workgroups without any until there are several chunks for each, and a workgroup
+    // that finds the queue empty has asked all its counters in turn.  512 fp32 rows of 1024 entries
+    // (64 chunks of 8, 512 workgroups): 25 us through the queue, 5 us strided.
+    if (p.n_tokens <= grid || (p.queue_chunk > 1 && p.n_tokens <= 4 * grid)) p.queued = 0;
     if (grid > p.n_tokens) grid = p.n_tokens;
     // dynamic LDS: the waiting gradient slots, or the LDS-resident part of the row
     constexpr unsigned lds_bytes = (unsigned)(NL + row_stash_slots(BLOCK, NV, NL)) * BLOCK * 16u;
@@ -1827,6 +1840,7 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
         p.queue_chunk = (int)(c < 1 ? 1 : (c > 64 ? 64 : c));
         p.queue_parts = row_bytes < 200 * 1024 ? kQueueParts : 1;
     }
+    p.queued = p.hdr != nullptr;
     const long long nvec = (p.vocab + Elem<DT>::EPV - 1) / Elem<DT>::EPV;
     switch (plan_rows(nvec, p.vocab % Elem<DT>::EPV != 0)) {
 #define GRPO_ROW_CASE(ID, BLOCK, NV, TAIL, NL, RSTP, RSTA, REM, PERCU)                              \

@@ -175,7 +175,7 @@ __host__ __device__ inline LmSplit lm_plan_split(int tiles, int k_tiles, int max
 // counts hold the largest.  A workgroup without work is not free - it takes all 160 KB of a CU's
 // LDS, so only one at a time gets in, about 5 us each: launched for the most parts any plan could
 // have (32 for each of n_cu tiles, 8192 workgroups) they cost 0.15 to 0.2 ms a product whatever its
-// size (dL/dH of 612 x 50304 x 768: 236 us, 53 us with this bound).
+// size (dL/dH of 612 x 50304 x 768: 236 us, 92 us with this bound).
 inline long long lm_split_grid(int tiles_m, int tiles_n, int k_tiles, int max_items, int n_cu)
 {
     long long most = 8;
