@@ -88,7 +88,8 @@ size_t grpo_workspace_bytes(int64_t n_tokens);
  *     With streamed_remainder = 1 the vectors beyond them are read twice.
  *     ragged_tail_slot = 1: the instantiation also serves a vocabulary that ends
  *     inside a 16-byte vector.  workgroups_per_cu of them share a compute unit.
- *   streaming = 1: the row is read twice (online maximum and sum, then the gradient).
+ *   streaming = 1: the row is read twice, in batches (online maximum and sum, then the gradient;
+ *     the last batches, still in registers then, only once).
  * Errors: GRPO_ERR_DTYPE, GRPO_ERR_SHAPE (vocab outside [1, 2^28]), GRPO_ERR_NULL.
  */
 typedef struct grpo_row_plan {

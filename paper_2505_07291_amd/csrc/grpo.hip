@@ -770,7 +770,7 @@ __device__ __forceinline__ void online_rescale(float m, float s, float w, float 
 {
     const float dlt = (m - mx) * k;
     const float sc_ = __builtin_amdgcn_exp2f(dlt);
-    scaled = (m > -INFINITY) ? s * sc_ : 0.f;
+    scaled = (m > -INFINITY) ? s * sc_ : s;  // no maximum seen: s is 0, or NaN
     scaledw = (AUX && m > -INFINITY && s > 0.f) ? sc_ * fmaf(dlt, s, w) : 0.f;
 }
 
@@ -1229,35 +1229,153 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     }
 }
 
-// ---------------------------------------------------------------------------
-// Streaming row kernel for rows too wide for the register file: an online
-// (max, sum) pass and a gradient pass, i.e. 2 reads + 1 write.
-// ---------------------------------------------------------------------------
-template <grpo_dtype DT, int BLOCK, bool AUX>
-__global__ void __launch_bounds__(BLOCK) grpo_rows_streamed(RowParams p)
+// One batch of vectors joined into a lane's online statistics: running maximum m (in logit units),
+// sum s of the exponentials relative to it, and for the entropy w = sum e a.  One comparison with
+// the running maximum for the whole batch.  As long as a lane has seen no maximum (all -inf, or
+// NaN, which the maximum skips) its exponents are taken relative to 0: -inf adds nothing, NaN poisons s.
+template <grpo_dtype DT, bool AUX, int U>
+__device__ __forceinline__ void online_batch(u32x4 (&z)[U], float k, float &m, float &s, float &w)
 {
-    constexpr int EPV = Elem<DT>::EPV;
-    constexpr int BYTES = Elem<DT>::BYTES;
+    constexpr int EPW = Elem<DT>::EPV / 4;
+    float vm = m;
+#pragma unroll
+    for (int u = 0; u < U; ++u) vm = vec_max_into<DT>(vm, z[u]);
+    if (vm > m) {
+        // new reference: every exponent so far moves by dlt, every term by 2^dlt
+        const float dlt = (m - vm) * k;  // -inf the first time: s and w are 0 (s: or NaN) and stay so
+        const float sc_ = __builtin_amdgcn_exp2f(dlt);
+        if constexpr (AUX) w = (s > 0.f) ? sc_ * fmaf(dlt, s, w) : 0.f;
+        s *= sc_;
+        m = vm;
+    }
+    const float ref = m > -INFINITY ? m : 0.f, mk_t = ref * k;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        forget(z[u]);  // see the register-resident kernel: the widening is done anew
+        float part = 0.f, partw = 0.f;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            float f[EPW];
+            unpack_word<DT>(z[u][d], f);
+#pragma unroll
+            for (int e = 0; e < EPW; ++e) {
+                const float a = AUX ? fmaxf((f[e] - ref) * k, kExpFloor) : fmaf(f[e], k, -mk_t);
+                const float ex = __builtin_amdgcn_exp2f(a);
+                part += ex;
+                if constexpr (AUX) partw = fmaf(ex, a, partw);
+            }
+        }
+        s += part;
+        if constexpr (AUX) w += partw;
+        VECTOR_FENCE();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Streaming row kernel for rows the register-resident kernel cannot hold: an online (max, sum)
+// pass and a gradient pass, each reading the row.
+//
+// Bound: HBM, if enough loads are in flight and the second read does not go there.  Two workgroups
+// of 512 lanes share a CU.  A lane works in batches of four vectors through two register buffers, even
+// batches in A, odd ones in B: while one is reduced the other's loads are in flight, up to 128 KB
+// per CU.  The gradient pass walks the batches backwards: the last two are still in the buffers and
+// are not read again, the ones before them are the most recent in the caches, and the buffers it
+// frees last take the first two batches of the next row.  The loads are ordinary ones: 512 rows of
+// 300 KB in flight fit the memory-side cache, non-temporal reads pass it by (380 us instead of 321,
+// 530 instead of 461 on the two batches below).  Loads stand in front of the stores of the same step.
+// Rows come from the queue, live ones first, like the resident kernel's.
+// Whole step, against one vector in flight per lane and rows strided over the grid (which gave
+// some workgroups the live head of every response and others its masked tail): 4096 x 50257 fp32
+// 410 -> 321 us, 4096 x 152069 bf16 529 -> 461 us.  Batches of five and six: 318 and 355, 470 and 497.
+// ---------------------------------------------------------------------------
+constexpr int kStreamBlock = 512, kStreamPerCu = 2, kStreamBatch = 4;
+template <grpo_dtype DT, bool AUX>
+__global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams p)
+{
+    constexpr int EPV = Elem<DT>::EPV, BYTES = Elem<DT>::BYTES, BLOCK = kStreamBlock, U = kStreamBatch;
+    constexpr unsigned SLAB = BLOCK * 16u;  // bytes one slot of the workgroup covers
     __shared__ float lds_max[BLOCK / 64];
     __shared__ float lds_sum[BLOCK / 64];
     __shared__ float lds_sumw[BLOCK / 64];
+    __shared__ long long lds_row[2];
     const int tid = threadIdx.x;
     const int nvec_full = (int)(p.vocab / EPV);
     const int tail = (int)(p.vocab % EPV);
-    const int nvec = nvec_full + (tail ? 1 : 0);
+    const int nb = (nvec_full + U * BLOCK - 1) / (U * BLOCK);  // batches; at least 2 (the plan's widths)
+    const bool queued = p.queued != 0;
+    long long strided_next = blockIdx.x;
+    unsigned grabs = 0;
+    auto acquire = [&](long long &y) -> long long {
+        for (;;) {
+            long long r;
+            if (queued) {
+                const unsigned slot = grabs++ & 1u;  // alternating, as in the resident kernel
+                if (tid == 0) lds_row[slot] = (long long)atomicAdd(queue_counters(p.hdr), 1ull);
+                lds_barrier();
+                r = uniform(lds_row[slot]);
+            } else {
+                r = strided_next;
+                strided_next += gridDim.x;
+            }
+            if (r >= p.n_tokens) return p.n_tokens;
+            if (p.order) r = uniform((long long)p.order[r]);
+            if (row_is_live<DT, BLOCK>(p, r, nvec_full, tail, y)) return r;
+        }
+    };
+    u32x4 A[U], B[U];
+    float zy = 0.f, tz = -INFINITY;  // the sampled token's logit; lane i < tail: entry i of the ragged last vector
+    // the lane's number and byte offset, opaque at every use (see the resident kernel: kept for every
+    // slot of every batch they would fill the registers)
+    auto lane = [&]() __attribute__((always_inline)) {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        return t;
+    };
+    unsigned noff = (unsigned)tid * 16u;
+    auto load_slot = [&](u32x4 &z, const char *zrow, int slot) __attribute__((always_inline)) {
+        z = neg_inf_vec<DT>();
+        if (slot * BLOCK + lane() < nvec_full) z = *(const u32x4 *)(zrow + (size_t)slot * SLAB + noff);
+    };
+    auto load_batch = [&](u32x4 (&buf)[U], const char *zrow, int b) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) load_slot(buf[u], zrow, b * U + u);
+    };
+    auto load_first = [&](const char *zrow, long long y) __attribute__((always_inline)) {
+        load_batch(A, zrow, 0);
+        load_batch(B, zrow, 1);
+        zy = load_elem<DT>(zrow, y);
+        if (tid < tail) tz = load_elem<DT>(zrow, (long long)nvec_full * EPV + tid);
+    };
 
-    for (long long row = blockIdx.x; row < p.n_tokens; row += gridDim.x) {
-        long long y;
-        if (!row_is_live<DT, BLOCK>(p, row, nvec_full, tail, y)) continue;
+    long long y = 0, y_next = 0;
+    long long row = acquire(y);
+    if (row < p.n_tokens) load_first((const char *)p.logits + row * p.row_stride * BYTES, y);
+
+    while (row < p.n_tokens) {
         const char *zrow = (const char *)p.logits + row * p.row_stride * BYTES;
-        const float zy = load_elem<DT>(zrow, y);
+        const long long next = acquire(y_next);
+        const bool has_next = next < p.n_tokens;
+        const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
         const int vy = (int)(y / EPV);
         const int ey = (int)(y % EPV);
 
         float m = -INFINITY, s = 0.f, w = 0.f;
-        for (int v = tid; v < nvec; v += BLOCK) {
-            const u32x4 z = load_vec<DT>(zrow, v, nvec_full, tail);
-            online_vec<DT, AUX>(z, v == vy, ey, p.k, m, s, w);
+        auto stat_step = [&](u32x4 (&buf)[U], int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)  // the sampled token's logit stays out of the sums
+                if ((b * U + u) == vy / BLOCK && lane() == vy % BLOCK && vy < nvec_full) set_neg_inf<DT>(buf[u], ey);
+            online_batch<DT, AUX, U>(buf, p.k, m, s, w);
+            if (b + 2 < nb) load_batch(buf, zrow, b + 2);
+        };
+        for (int b = 0; b < nb; b += 2) {
+            stat_step(A, b);
+            if (b + 1 < nb) stat_step(B, b + 1);
+        }
+        u32x4 tv[1] = {neg_inf_vec<DT>()};  // the ragged last vector, one entry per lane
+        if (tail) {
+            if (tid < tail && !(vy == nvec_full && tid == ey))
+                tv[0][0] = DT == GRPO_BF16 ? (kNegInfF32 | (as_u32(tz) >> 16)) : as_u32(tz);
+            online_batch<DT, AUX, 1>(tv, p.k, m, s, w);
         }
         const float mx = fmaxf(block_max<BLOCK>(m, lds_max), zy);
         const float mk = mx * p.k;
@@ -1276,29 +1394,63 @@ __global__ void __launch_bounds__(BLOCK) grpo_rows_streamed(RowParams p)
             sc = row_scalars(p, row, zy, mk, s_excl);
         }
         if (tid == 0) write_row_outputs(p, row, sc.logp, sc.J, sc.flags);
-        // the LDS arrays are reused by the next row: one barrier separates this row's
-        // reads of lds_sum from the next row's writes of lds_max/lds_sum
-        lds_barrier();
-        if (!p.bwd) continue;
+        lds_barrier();  // this row's reads of the LDS arrays, the next one's writes
 
         char *grow = (char *)p.grad + row * p.row_stride * BYTES;
-        if (sc.c == 0.f && (!AUX || sc.b == 0.f)) {
-            zero_row<DT, BLOCK>(grow, nvec_full, tail, tid);
-            continue;
-        }
-        const float q = -sc.c * p.inv_T;
-        const float gy = (sc.c * p.inv_T) * (sc.s_excl / sc.s) + (AUX ? sc.gy_ent : 0.f);
-        for (int v = tid; v < nvec; v += BLOCK) {
-            u32x4 z = load_vec<DT>(zrow, v, nvec_full, tail);
-            float g[EPV];
-            if constexpr (AUX) {
-                const u32x4 pk = grad_vec_aux<DT>(z, p.k, sc.mx, sc.log2s, sc.q2, sc.bq, v == vy, ey, gy);
-                unpack<DT>(pk, g);  // exact: the values are already rounded
-            } else {
-                grad_vec<DT>(z, p.k, sc.shift, q, v == vy, ey, gy, g);
+        if (!p.bwd || (sc.c == 0.f && (!AUX || sc.b == 0.f))) {
+            if (has_next) load_first(zrow_next, y_next);
+            if (p.bwd) zero_row<DT, BLOCK>(grow, nvec_full, tail, tid);
+        } else {
+            const float q = -sc.c * p.inv_T;
+            const float gy = (sc.c * p.inv_T) * (sc.s_excl / sc.s) + (AUX ? sc.gy_ent : 0.f);
+            auto grad_of = [&](u32x4 &z, bool has_y, int e) __attribute__((always_inline)) {
+                if constexpr (AUX) {
+                    z = grad_vec_aux<DT>(z, p.k, sc.mx, sc.log2s, sc.q2, sc.bq, has_y, e, gy);
+                } else {
+                    float g[EPV];
+                    grad_vec<DT>(z, p.k, sc.shift, q, has_y, e, gy, g);
+                    z = pack<DT>(g);
+                }
+            };
+            auto grad_step = [&](u32x4 (&buf)[U], int b) __attribute__((always_inline)) {
+                u32x4 out[U];
+                const bool more = b >= 2 || has_next;  // A is done with batch 0, B with batch 1: the next row's
+                const char *from = b >= 2 ? zrow : zrow_next;
+                const int b_load = b >= 2 ? b - 2 : b;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    forget(buf[u]);
+                    out[u] = buf[u];
+                    grad_of(out[u], (b * U + u) * BLOCK + lane() == vy, ey);
+                    order_after(noff, out[u]);
+                    if (more) load_slot(buf[u], from, b_load * U + u);
+                    VECTOR_FENCE();
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if ((b * U + u) * BLOCK + lane() < nvec_full)
+                        st16(grow + (size_t)(b * U + u) * SLAB + noff, out[u]);
+            };
+            for (int b = (nb - 1) | 1; b > 0; b -= 2) {
+                if (b < nb) grad_step(B, b);
+                grad_step(A, b - 1);
             }
-            store_vec<DT>(grow, v, nvec_full, tail, g);
+            if (tail) {
+                grad_of(tv[0], vy == nvec_full && tid == ey, 0);
+                if (tid < tail) {
+                    if constexpr (DT == GRPO_BF16)
+                        ((unsigned short *)grow)[(long long)nvec_full * EPV + tid] = (unsigned short)(tv[0][0] & 0xffffu);
+                    else
+                        ((unsigned *)grow)[(long long)nvec_full * EPV + tid] = tv[0][0];
+                }
+            }
+            if (has_next) {
+                zy = load_elem<DT>(zrow_next, y_next);
+                if (tid < tail) tz = load_elem<DT>(zrow_next, (long long)nvec_full * EPV + tid);
+            }
         }
+        row = next;
+        y = y_next;
     }
 }
 
@@ -1851,9 +2003,12 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
         GRPO_ROW_KERNELS(GRPO_ROW_CASE)
 #undef GRPO_ROW_CASE
     default: {
-        long long grid = (long long)cu_count() * 2;
-        if (grid > p.n_tokens) grid = p.n_tokens;
-        hipLaunchKernelGGL((grpo_rows_streamed<DT, 1024, AUX>), dim3((unsigned)grid), dim3(1024), 0, st, p);
+        long long grid = (long long)cu_count() * kStreamPerCu;
+        if (p.n_tokens <= grid) {
+            p.queued = 0;
+            grid = p.n_tokens;
+        }
+        hipLaunchKernelGGL((grpo_rows_streamed<DT, AUX>), dim3((unsigned)grid), dim3(kStreamBlock), 0, st, p);
     }
     }
 }
@@ -2058,8 +2213,8 @@ grpo_status grpo_row_kernel_plan(grpo_dtype dtype_arg, int64_t vocab, grpo_row_p
 #undef GRPO_ROW_CASE
     default:
         r.streaming = 1;
-        r.lanes = 1024;
-        r.workgroups_per_cu = 2;
+        r.lanes = kStreamBlock;
+        r.workgroups_per_cu = kStreamPerCu;
     }
     const int64_t capacity = (int64_t)r.lanes * (r.register_slots + r.lds_slots);
     r.resident_vectors = r.streaming ? 0 : (r.vectors < capacity ? r.vectors : capacity);

@@ -1,0 +1,30 @@
+"""Row widths and batch sizes at which the row kernels change what they do, against the fp64 oracle
+(log-probs, loss and counters of every row, gradients of sampled rows, in place as well): tolerances and
+comparison are those of the other shapes (run_shape_case)."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import run_shape_case
+
+pytestmark = pytest.mark.gpu
+
+
+def sampled(rows, seed):
+    rng = np.random.default_rng(seed)
+    return np.unique(np.concatenate([np.arange(min(rows, 6)), np.arange(max(0, rows - 6), rows),
+                                     rng.choice(rows, size=min(rows, 40), replace=False)]))
+
+
+# the streaming kernel works in batches of 2048 vectors through two buffers: an even and an odd number
+# of whole batches, one vector more, and one less; ragged, so that no resident kernel takes them
+@pytest.mark.parametrize("dtype,epv", [("bf16", 8), ("f32", 4)])
+@pytest.mark.parametrize("vectors", [10 * 2048, 10 * 2048 + 1, 11 * 2048, 9 * 2048 - 1])
+def test_streamed_rows_around_whole_batches(dtype, epv, vectors):
+    vocab = vectors * epv + epv - 1
+    run_shape_case(dtype, vocab, vocab + 1, 600, grad_rows=sampled(600, vectors))
+
+
+# narrow rows: at most one row for each workgroup, up to four, and more (through the queue)
+@pytest.mark.parametrize("rows", [1, 7, 2048, 2049, 8192, 8193])
+def test_narrow_rows_strided_and_queued(rows):
+    run_shape_case("f32", 1024, 1024, rows, grad_rows=sampled(rows, rows))
