@@ -190,40 +190,6 @@ __device__ __forceinline__ u32x4 neg_inf_vec()
     return v;
 }
 
-// Vector number v of a row: full vectors come as one 16-byte load; the ragged last
-// vector (vocab not a multiple of EPV) is gathered element by element and padded
-// with -inf, which contributes exp2(-inf) = 0 and never wins the max; vectors past
-// the row are all -inf.
-template <grpo_dtype DT>
-__device__ __forceinline__ u32x4 load_vec(const char *row, int v, int nvec_full, int tail)
-{
-    constexpr int EPV = Elem<DT>::EPV;
-    if (v < nvec_full) return ld16(row + (unsigned)v * 16u);
-    u32x4 out = neg_inf_vec<DT>();
-    if (v == nvec_full && tail) {
-        float f[EPV];
-#pragma unroll
-        for (int i = 0; i < EPV; ++i)
-            f[i] = (i < tail) ? load_elem<DT>(row, (long long)v * EPV + i) : -INFINITY;
-        out = pack<DT>(f);  // exact: the values are already representable
-    }
-    return out;
-}
-
-template <grpo_dtype DT>
-__device__ __forceinline__ void store_vec(char *row, int v, int nvec_full, int tail,
-                                          const float (&g)[Elem<DT>::EPV])
-{
-    constexpr int EPV = Elem<DT>::EPV;
-    if (v < nvec_full) {
-        st16(row + (unsigned)v * 16u, pack<DT>(g));
-    } else if (v == nvec_full && tail) {
-#pragma unroll
-        for (int i = 0; i < EPV; ++i)
-            if (i < tail) store_elem<DT>(row, (long long)v * EPV + i, g[i]);
-    }
-}
-
 template <grpo_dtype DT, int BLOCK>
 __device__ __forceinline__ void zero_row(char *row, int nvec_full, int tail, int tid)
 {
@@ -862,12 +828,10 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     const unsigned toff = (unsigned)tid * 16u;
     const int nvec_full = (int)(p.vocab / EPV);
     const int tail = (int)(p.vocab % EPV);
-    // The ragged last vector (vocab not a multiple of EPV) lives in one extra slot
-    // that only the first wavefront carries: lane 0 holds the elements, padded with
-    // -inf.  Full rows never enter those branches.
-    // (The widest instantiation has no registers to spare for that slot and is built
-    // without it; ragged rows of that width take the streaming kernel.)
-    const bool tail_wave = TAIL && tail != 0 && tid < 64;
+    // The ragged last vector (vocab not a multiple of EPV): lane i < tail holds its entry i, one
+    // register (tz; the other lanes' are -inf) and one exponential more per pass, against the four of
+    // a slot of its own.  Rows without a ragged end never enter those branches.
+    const bool ragged = TAIL && tail != 0;
 
     // ---- which row next ----
     // With a workspace (objective + gradient) rows are handed out through a counter in
@@ -935,8 +899,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     u32x4 buf[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) buf[i] = neg_inf_vec<DT>();
-    u32x4 tbuf = neg_inf_vec<DT>();
-    float zy = 0.f;
+    float zy = 0.f, tz = -INFINITY;
 
     // The lane's number and byte offset as the slot loops use them.  In the instantiations with
     // LDS-resident slots they are made opaque at every use: otherwise the compiler keeps the
@@ -995,7 +958,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         for (int j = 0; j < NL; ++j) fetch_lds_slot(zrow, j);
     };
     auto fetch_rest = [&](const char *zrow, long long y) {
-        if (tail_wave && tid == 0) tbuf = load_vec<DT>(zrow, nvec_full, nvec_full, tail);
+        if (ragged && tid < tail) tz = load_elem<DT>(zrow, (long long)nvec_full * EPV + tid);
         zy = load_elem<DT>(zrow, y);
     };
 
@@ -1025,7 +988,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             for (int i = 0; i < NV; ++i)
                 if (i == vy / BLOCK) set_neg_inf<DT>(buf[i], ey);
         }
-        if (tail_wave && tid == 0 && vy == nvec_full) set_neg_inf<DT>(tbuf, ey);
+        if (ragged && vy == nvec_full && tid == ey) tz = -INFINITY;
 
         // reference maximum over j != y, then joined with z_y
         float mx = -INFINITY;
@@ -1045,7 +1008,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                 VECTOR_FENCE();
             }
         }
-        if (tail_wave) mx = vec_max_into<DT>(mx, tbuf);
+        if (ragged) mx = fmaxf(mx, tz);
         // the part of the row that is not resident: online statistics, first read
         const char *zrow_cur = (const char *)p.logits + row * p.row_stride * BYTES;
         float rem_m = -INFINITY, rem_s = 0.f, rem_w = 0.f;
@@ -1099,11 +1062,13 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             }
             VECTOR_FENCE();
         }
-        if (tail_wave) {
-            if constexpr (AUX)
-                acc += exp_sum_vec_aux<DT>(tbuf, p.k, mx, accw);
-            else
-                acc += exp_sum_vec<DT>(tbuf, p.k, mk);
+        if (ragged) {
+            const float a = AUX ? fmaxf((tz - mx) * p.k, kExpFloor) : fmaf(tz, p.k, -mk);
+            const float ex = __builtin_amdgcn_exp2f(a);
+            if (tid < tail) {  // (the other lanes' -inf is no number against a maximum of -inf)
+                acc += ex;
+                if constexpr (AUX) accw = fmaf(ex, a, accw);
+            }
         }
         if constexpr (REM) {
             float scaled, scaledw;
@@ -1203,15 +1168,16 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                     if (v < nvec_full) st16(grow + (size_t)(NV + j) * SLAB + lane_off(), packed);
                     VECTOR_FENCE();
                 }
-                if (tail_wave && tid == 0) {
-                    float g[EPV];
+                if (ragged && tid < tail) {
+                    float g;
                     if constexpr (AUX) {
-                        const u32x4 pk = grad_vec_aux<DT>(tbuf, p.k, sc.mx, sc.log2s, sc.q2, sc.bq, vy == nvec_full, ey, gy);
-                        unpack<DT>(pk, g);  // the tail is stored element by element
+                        const float a = fmaxf(fmaf(tz - sc.mx, p.k, -sc.log2s), kExpFloor);
+                        g = __builtin_amdgcn_exp2f(a) * fmaf(sc.bq, a, sc.q2);
                     } else {
-                        grad_vec<DT>(tbuf, p.k, sc.shift, q, vy == nvec_full, ey, gy, g);
+                        g = __builtin_amdgcn_exp2f(fmaf(tz, p.k, -sc.shift)) * q;
                     }
-                    store_vec<DT>(grow, nvec_full, nvec_full, tail, g);
+                    if (vy == nvec_full && tid == ey) g = gy;
+                    store_elem<DT>(grow, (long long)nvec_full * EPV + tid, g);
                 }
                 if (has_next) fetch_rest(zrow_next, y_next);
 #pragma unroll
@@ -1935,6 +1901,8 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
     X(6, 512, 20, false, 0, 2, 2, false, 1)                   \
     X(7, 1024, 10, true, 0, -1, -1, false, 1)                 \
     X(8, 512, 26, false, 0, 8, 8, false, 1)                   \
+    X(16, 512, 26, true, 0, 8, 8, false, 1)                   \
+    X(17, 512, 32, true, 0, 14, 14, false, 1)                 \
     X(9, 512, 32, false, 0, 14, 14, false, 1)                 \
     X(10, 512, 38, false, 0, -1, -1, false, 1)                \
     X(11, 512, 44, false, 0, 10, 8, false, 1)                 \
@@ -1966,11 +1934,12 @@ int plan_rows(long long nvec, bool ragged)
     if (nvec <= 512 * 16) return 5;
     if (nvec <= 512 * 20 && !ragged) return 6;  // all 20 gradient slots wait: 18 in LDS, 2 in registers
     if (nvec <= 1024 * 10) return 7;
-    if (ragged) return kRowStreaming;
     // 512 lanes with twice the registers, in several widths: the arithmetic of a pass runs over
-    // every slot of the instantiation, used or not
-    if (nvec <= 512 * 26) return 8;
-    if (nvec <= 512 * 32) return 9;
+    // every slot of the instantiation, used or not.  Ragged rows as well up to 32 slots (step on
+    // 4096 x 50257 fp32: 290 us, streamed 326); wider ones are streamed.
+    if (nvec <= 512 * 26) return ragged ? 16 : 8;
+    if (nvec <= 512 * 32) return ragged ? 17 : 9;
+    if (ragged) return kRowStreaming;
     if (nvec <= 512 * 38) return 10;
     if (nvec <= 512 * 44) return 11;
     // wider than the registers: the last slots of the row live in LDS

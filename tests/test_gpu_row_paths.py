@@ -28,3 +28,11 @@ def test_streamed_rows_around_whole_batches(dtype, epv, vectors):
 @pytest.mark.parametrize("rows", [1, 7, 2048, 2049, 8192, 8193])
 def test_narrow_rows_strided_and_queued(rows):
     run_shape_case("f32", 1024, 1024, rows, grad_rows=sampled(rows, rows))
+
+
+# ragged rows that stay in registers: the last vector of a width, and the first one past it
+@pytest.mark.parametrize("dtype,epv", [("bf16", 8), ("f32", 4)])
+@pytest.mark.parametrize("vectors", [10240, 26 * 512 - 1, 26 * 512, 32 * 512 - 1, 32 * 512])
+def test_ragged_rows_around_the_resident_widths(dtype, epv, vectors):
+    vocab = vectors * epv + 1
+    run_shape_case(dtype, vocab, (vectors + 1) * epv, 300, grad_rows=sampled(300, vectors))
