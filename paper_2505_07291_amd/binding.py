@@ -368,7 +368,8 @@ def grpo_filter_groups(rewards, group_size=None, group_offsets=None, stream=None
     keep = torch.empty(n_groups, dtype=torch.uint8, device=dev)
     kept = torch.empty(n_groups, dtype=torch.int32, device=dev)
     n_kept = torch.empty(1, dtype=torch.int32, device=dev)
-    rk = torch.zeros(R, dtype=torch.uint8, device=dev)
+    # groups of one size own every rollout; with offsets some may belong to none and keep their 0
+    rk = (torch.empty if group_offsets is None else torch.zeros)(R, dtype=torch.uint8, device=dev)
     rc = lib().grpo_filter_groups(_ptr(rewards), R, _ptr(group_offsets), n_groups, gs, _ptr(keep),
                                   _ptr(kept), _ptr(n_kept), _ptr(rk), _stream(stream))
     if rc != GRPO_OK:

@@ -22,6 +22,7 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -38,7 +39,6 @@ struct WsHeader {
     long long M;   // rows with mask != 0
     int error;     // sticky data-error word (bit 0: token id out of range)
     unsigned fin_ticket;  // blocks of grpo_finalize that have delivered their partial sums
-    unsigned live_fill, masked_fill;  // entries grpo_order_rows has reserved at either end of the order array
 };
 // The row queue: up to kQueueParts counters, each on a 128-byte line of its own, follow
 // the 256-byte header.  With P counters in use, counter q hands out the rows q, q + P,
@@ -47,7 +47,8 @@ struct WsHeader {
 // not for 64 KB rows.  Narrow rows therefore use eight interleaved partitions, each
 // started on by an eighth of the workgroups and then stolen from in turn, which keeps
 // single-row granularity; wide rows use one counter, which measured 4-6 % faster there.
-constexpr int kFinSegment = 4096;  // rows one workgroup of grpo_finalize / grpo_order_rows takes: four per lane
+constexpr int kOrderRows = 4096;    // rows one workgroup of grpo_prepare orders: four per lane
+constexpr int kFinSegment = 16384;  // rows one workgroup of grpo_finalize takes: sixteen per lane
 constexpr int kQueueParts = 8;
 constexpr int kQueueStride = 16;  // in unsigned long long: 128 bytes
 constexpr size_t kHeaderBytes = 256 + (size_t)kQueueParts * kQueueStride * 8;
@@ -73,7 +74,7 @@ struct RowParams {
     float inv_T;  // 1 / T
     float lo, hi, delta, grad_scale;
     int bwd;  // 0: log-probs only (grpo_logprobs_fwd), 1: objective + gradient
-    const int *order;  // optional: the rows in the order they are handed out (grpo_order_rows), else 0, 1, 2, ...
+    const int *order;  // optional: the rows in the order they are handed out (grpo_prepare), else 0, 1, 2, ...
     int queued;       // rows come from the queue in the workspace (0: strided over the grid)
     int queue_chunk;  // rows taken from the queue per increment
     int queue_parts;  // counters in use (1 or kQueueParts)
@@ -243,6 +244,42 @@ __device__ __forceinline__ float wave_sum(float v)
     v += dpp_move<0x142, 0xa>(0.f, v);
     v += dpp_move<0x143, 0xc>(0.f, v);
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_move(int identity, int v)
+{
+    return __builtin_amdgcn_update_dpp(identity, v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ int wave_sum(int v)
+{
+    v += dpp_move<0xB1, 0xf>(0, v);
+    v += dpp_move<0x4E, 0xf>(0, v);
+    v += dpp_move<0x141, 0xf>(0, v);
+    v += dpp_move<0x140, 0xf>(0, v);
+    v += dpp_move<0x142, 0xa>(0, v);
+    v += dpp_move<0x143, 0xc>(0, v);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_move(double v)  // 0 where the row mask leaves a lane out
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)dpp_move<CTRL, ROW_MASK>(0, (int)b);
+    const unsigned hi = (unsigned)dpp_move<CTRL, ROW_MASK>(0, (int)(b >> 32));
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum_dpp(double v)
+{
+    v += dpp_move<0xB1, 0xf>(v);
+    v += dpp_move<0x4E, 0xf>(v);
+    v += dpp_move<0x141, 0xf>(v);
+    v += dpp_move<0x140, 0xf>(v);
+    v += dpp_move<0x142, 0xa>(v);
+    v += dpp_move<0x143, 0xc>(v);
+    const long long b = __builtin_bit_cast(long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, 63);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)hi << 32) | lo));
 }
 __device__ __forceinline__ double wave_sum(double v)
 {
@@ -1424,107 +1461,111 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
 // Small kernels around the row kernel
 // ---------------------------------------------------------------------------
 
-// Counts the unmasked rows and fixes the denominator before any row is processed.
-__global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask,
-                                                     const float *token_w, long long n,
-                                                     double denom, WsHeader *hdr)
+// How many of the rows [r0, r1) take part (mask not 0, weight not 0): this lane's share of them.
+__device__ __forceinline__ int count_live(const unsigned char *mask, const float *token_w, long long r0, long long r1)
 {
-    __shared__ long long lds[16];
-    long long cnt = 0;
+    int cnt = 0;
     if (mask && !token_w) {
         // the mask alone: 16 bytes per lane and step between the first and the last 16-byte
         // boundary inside it, single bytes before and after (the counts are integers: any order)
-        const long long head = ((16 - (long long)((unsigned long long)mask & 15u)) & 15);
+        const unsigned char *m = mask + r0;
+        const long long n = r1 - r0;
+        const long long head = ((16 - (long long)((unsigned long long)m & 15u)) & 15);
         const long long lead = head < n ? head : n;
         const long long nvec = (n - lead) / 16;
-        for (long long i = threadIdx.x; i < lead; i += 1024) cnt += mask[i] ? 1 : 0;
+        for (long long i = threadIdx.x; i < lead; i += 1024) cnt += m[i] ? 1 : 0;
         for (long long v = threadIdx.x; v < nvec; v += 1024) {
-            const u32x4 w = *(const u32x4 *)(mask + lead + 16 * v);
+            const u32x4 w = *(const u32x4 *)(m + lead + 16 * v);
 #pragma unroll
             for (int d = 0; d < 4; ++d)  // bit 7 of every byte that is not zero, then count them
                 cnt += __builtin_popcount((w[d] | ((w[d] & 0x7f7f7f7fu) + 0x7f7f7f7fu)) & 0x80808080u);
         }
-        for (long long i = lead + 16 * nvec + threadIdx.x; i < n; i += 1024) cnt += mask[i] ? 1 : 0;
+        for (long long i = lead + 16 * nvec + threadIdx.x; i < n; i += 1024) cnt += m[i] ? 1 : 0;
     } else if (mask || token_w) {
-        for (long long i = threadIdx.x; i < n; i += 1024)
+        for (long long i = r0 + threadIdx.x; i < r1; i += 1024)
             cnt += ((!mask || mask[i]) && (!token_w || token_w[i] != 0.f)) ? 1 : 0;
     }
-    cnt = wave_sum(cnt);
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = cnt;
-    if (threadIdx.x < kQueueParts) queue_counters(hdr)[threadIdx.x * kQueueStride] = 0ull;
+    return cnt;
+}
+
+// Counts the unmasked rows, fixes the denominator and resets the queue before any row is processed;
+// with `order`, also writes the order in which the row kernels hand out the rows of a batch with
+// masked rows: first the rows that take part (mask 1 and weight not 0), then the masked ones, which
+// only need zeros.  Handed out in index order, masked rows between live ones cost more than their
+// bytes: the same rows with the masked ones at the end ran 5 to 8 % faster at V = 152064 (the zero fill
+// of a masked row and the read-compute-write cycle of a live row share the memory system badly).
+// One workgroup per 4096 rows: an ordered compaction inside the workgroup, behind the rows it counts
+// before its own.  Every workgroup counts the whole mask itself, at 16 bytes a lane: for the 16 KB of
+// 16384 rows that is one step, against a launch of its own for the counting (2 to 5 us) and two
+// atomics on the way.  order[0 .. M) are the live rows in increasing order, order[M .. n) the masked
+// ones (written from the end).
+__global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask, const float *token_w, long long n,
+                                                     double denom, WsHeader *hdr, int *order)
+{
+    __shared__ long long lds_before[16], lds_rest[16];
+    __shared__ int wave_l[16], wave_m[16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const long long seg0 = (long long)blockIdx.x * kOrderRows < n ? (long long)blockIdx.x * kOrderRows : n;
+    const int cb = wave_sum(count_live(mask, token_w, 0, seg0));
+    const int cr = wave_sum(count_live(mask, token_w, seg0, n));
+    if (lane == 0) {
+        lds_before[wv] = cb;
+        lds_rest[wv] = cr;
+    }
+    if (blockIdx.x == 0 && tid < kQueueParts) queue_counters(hdr)[tid * kQueueStride] = 0ull;
+    const long long r0 = seg0 + tid * 4ll;  // four consecutive rows per lane
+    bool live[4], valid[4];
+    int cl = 0, cm = 0, il = 0, im = 0;
+    if (order) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const long long r = r0 + e;
+            valid[e] = r < n && r < seg0 + kOrderRows;
+            live[e] = valid[e] && (!mask || mask[r] != 0) && (!token_w || token_w[r] != 0.f);
+            cl += live[e] ? 1 : 0;
+            cm += (valid[e] && !live[e]) ? 1 : 0;
+        }
+        il = cl, im = cm;  // inclusive scans inside the wavefront
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int ul = __shfl_up(il, o, 64), um = __shfl_up(im, o, 64);
+            if (lane >= o) {
+                il += ul;
+                im += um;
+            }
+        }
+        if (lane == 63) {
+            wave_l[wv] = il;
+            wave_m[wv] = im;
+        }
+    }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        long long M = 0;
-        for (int i = 0; i < 16; ++i) M += lds[i];
-        if (!mask && !token_w) M = n;
+    long long before = 0, rest = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        before += lds_before[i];
+        rest += lds_rest[i];
+    }
+    if (blockIdx.x == 0 && tid == 0) {
+        const long long M = (!mask && !token_w) ? n : before + rest;
         const double D = denom > 0.0 ? denom : (double)M;
         hdr->D = D;
         hdr->inv_D = D > 0.0 ? 1.0 / D : 0.0;
         hdr->M = M;
         hdr->error = 0;
         hdr->fin_ticket = 0u;
-        hdr->live_fill = 0u;
-        hdr->masked_fill = 0u;
     }
-}
-
-// The order in which grpo_rows_cached hands out the rows of a batch with masked rows: first the
-// rows that take part (mask 1 and weight not 0), then the masked ones, which only need zeros.
-// Handed out in index order, masked rows between live ones cost more than their bytes: the same
-// rows with the masked ones at the end ran 5 to 8 % faster at V = 152064 (the zero fill of a masked
-// row and the read-compute-write cycle of a live row share the memory system badly).
-// One workgroup per 4096 rows: an ordered compaction inside the workgroup, a range of the output
-// reserved with one atomic per class.  order[0 .. M) are the live rows, order[M .. n) the masked
-// ones (written from the end).  Which workgroup gets which range varies from run to run; no
-// output depends on the order rows are processed in.
-__global__ void __launch_bounds__(1024) grpo_order_rows(const unsigned char *mask, const float *token_w,
-                                                       long long n, WsHeader *hdr, int *order)
-{
-    __shared__ int wave_l[16], wave_m[16];
-    __shared__ unsigned base_l, base_m;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const long long r0 = (long long)blockIdx.x * kFinSegment + tid * 4ll;  // four consecutive rows per lane
-    bool live[4], valid[4];
-    int cl = 0, cm = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const long long r = r0 + e;
-        valid[e] = r < n;
-        live[e] = valid[e] && (!mask || mask[r] != 0) && (!token_w || token_w[r] != 0.f);
-        cl += live[e] ? 1 : 0;
-        cm += (valid[e] && !live[e]) ? 1 : 0;
-    }
-    int il = cl, im = cm;  // inclusive scans inside the wavefront
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int ul = __shfl_up(il, o, 64), um = __shfl_up(im, o, 64);
-        if (lane >= o) {
-            il += ul;
-            im += um;
-        }
-    }
-    if (lane == 63) {
-        wave_l[wv] = il;
-        wave_m[wv] = im;
-    }
-    __syncthreads();
-    int before_l = 0, before_m = 0, tot_l = 0, tot_m = 0;
+    if (!order) return;
+    int before_l = 0, before_m = 0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) {
         if (w < wv) {
             before_l += wave_l[w];
             before_m += wave_m[w];
         }
-        tot_l += wave_l[w];
-        tot_m += wave_m[w];
     }
-    if (tid == 0) {
-        base_l = tot_l ? atomicAdd(&hdr->live_fill, (unsigned)tot_l) : 0u;
-        base_m = tot_m ? atomicAdd(&hdr->masked_fill, (unsigned)tot_m) : 0u;
-    }
-    __syncthreads();
-    long long pl = (long long)base_l + before_l + (il - cl);
-    long long pm = (long long)base_m + before_m + (im - cm);
+    long long pl = before + before_l + (il - cl);
+    long long pm = (seg0 - before) + before_m + (im - cm);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (live[e])
@@ -1548,20 +1589,25 @@ __global__ void grpo_reset_queue(WsHeader *hdr)
 // total = policy + kl_coef * mean kl - ent_coef * mean H, policy, mean kl, mean H.
 //
 // One workgroup per segment of kFinSegment rows: it sums its rows (a fixed assignment of rows to
-// lanes, wavefronts combined in order), leaves the partial sums in the workspace and draws a
-// ticket; the workgroup that draws the last ticket adds the partials in segment order and writes
-// the results.  Which workgroup that is varies from run to run, what it computes does not: the
-// sums are bitwise reproducible.  (A single workgroup took 13 us for 16384 rows and 0.1 ms for
-// 131072; the segments take about as long as one of them.)
+// lanes, wavefronts combined in a fixed order), and unless it is the only one leaves the partial sums
+// in the workspace and draws a ticket; the workgroup that draws the last ticket adds the partials in
+// segment order and writes the results.  Which workgroup that is varies from run to run, what it
+// computes does not: the sums are bitwise reproducible.
+// Bound by latency, so what counts is how few dependent steps there are: all of a lane's loads are
+// issued at once, sums across lanes are DPP steps on 32-bit halves, the four counters of a workgroup
+// travel as 16-bit fields of two words (at most 16384 each), and up to 16384 rows need no ticket (with
+// segments of 4096 rows, seven shuffled sums and a walk over 16 wavefronts: 6.8 us for 512 rows, 17 us for 16384;
+// now 3.6 and 4.6 us).
 struct FinPartial {
     double s[3];
     long long c[4];
     long long pad;
 };
 static_assert(sizeof(FinPartial) == 64, "one partial per 64 bytes");
-constexpr size_t fin_partials_bytes(long long n)
+static_assert(kFinSegment < 65536, "counters of a segment fit 16 bits");
+constexpr size_t fin_partials_bytes(long long n)  // sized for segments of 4096 rows
 {
-    return (((size_t)((n + kFinSegment - 1) / kFinSegment) * sizeof(FinPartial)) + 255) / 256 * 256;
+    return (((size_t)((n + 4095) / 4096) * sizeof(FinPartial)) + 255) / 256 * 256;
 }
 
 __global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const float *KL_ws,
@@ -1571,87 +1617,99 @@ __global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const f
                                                       float ent_coef, float *loss_out,
                                                       long long *counts_out, int *error_out)
 {
-    __shared__ double lds_j[16][3];
-    __shared__ long long lds_c[16][4];
+    __shared__ double lds_s[3][16];
+    __shared__ int lds_c[2][16];
+    __shared__ long long lds_c4[4][16];
     __shared__ unsigned lds_ticket;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const bool aux = KL_ws != nullptr;
     const long long nseg = (n + kFinSegment - 1) / kFinSegment;  // 0 for an empty batch: one block, no rows
-    // sums x over the block in a fixed order: lanes inside a wavefront, then the wavefronts in turn
-    auto block_totals = [&](double (&sj)[3], long long (&c)[4]) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q) sj[q] = wave_sum(sj[q]);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) c[q] = wave_sum(c[q]);
-        __syncthreads();  // the arrays may still be read from the previous use
-        if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) lds_j[threadIdx.x >> 6][q] = sj[q];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) lds_c[threadIdx.x >> 6][q] = c[q];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 3; ++q) sj[q] = 0.0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) c[q] = 0;
-#pragma unroll 2  // all 16 at once would read 224 registers' worth of partial sums first, and spill
-        for (int w = 0; w < 16; ++w) {  // wavefront by wavefront, in order
-#pragma unroll
-            for (int q = 0; q < 3; ++q) sj[q] += lds_j[w][q];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) c[q] += lds_c[w][q];
-        }
-    };
-
-    double sj[3] = {0.0, 0.0, 0.0};
-    long long c[4] = {0, 0, 0, 0};
-    auto count = [&](int fl) {
-        c[0] += (fl & kFlagClipHigh) ? 1 : 0;
-        c[1] += (fl & kFlagClipLow) ? 1 : 0;
-        c[2] += (fl & kFlagDelta) ? 1 : 0;
-        c[3] += (fl & kFlagOutOfBand) ? 1 : 0;
-    };
-    // this block's segment: four rows per lane (the arrays start on 256-byte boundaries and a
-    // segment is a multiple of four rows), the batch's last n % 4 rows one by one
+    // this block's segment, four consecutive rows per lane and step (the arrays start on 256-byte
+    // boundaries and a segment is a multiple of four rows), the batch's last n % 4 rows one by one
     const long long seg0 = (long long)blockIdx.x * kFinSegment;
     const long long seg1 = seg0 + kFinSegment < n ? seg0 + kFinSegment : n;
-    const long long i = seg0 + threadIdx.x * 4ll;
-    if (i + 3 < seg1) {
-        const float4 j = *(const float4 *)(J_ws + i);
-        sj[0] += (double)j.x;
-        sj[0] += (double)j.y;
-        sj[0] += (double)j.z;
-        sj[0] += (double)j.w;
-        if (aux) {
-            const float4 kl = *(const float4 *)(KL_ws + i), h = *(const float4 *)(H_ws + i);
-            sj[1] += (double)kl.x;
-            sj[1] += (double)kl.y;
-            sj[1] += (double)kl.z;
-            sj[1] += (double)kl.w;
-            sj[2] += (double)h.x;
-            sj[2] += (double)h.y;
-            sj[2] += (double)h.z;
-            sj[2] += (double)h.w;
-        }
-        const unsigned fl4 = *(const unsigned *)(flags_ws + i);
+    constexpr int STEPS = kFinSegment / 4096;
+    f32x4 j[STEPS], kl[STEPS], h[STEPS];
+    unsigned fl[STEPS];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) count((int)((fl4 >> (8 * b)) & 0xffu));
-    } else {
-        for (long long r = i; r < seg1; ++r) {  // at most three rows, in one lane of the last segment
-            sj[0] += (double)J_ws[r];
+    for (int q = 0; q < STEPS; ++q) {
+        const long long i = seg0 + q * 4096ll + tid * 4ll;
+        j[q] = kl[q] = h[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        fl[q] = 0u;
+        if (i + 3 < seg1) {
+            j[q] = *(const f32x4 *)(J_ws + i);
+            fl[q] = *(const unsigned *)(flags_ws + i);
             if (aux) {
-                sj[1] += (double)KL_ws[r];
-                sj[2] += (double)H_ws[r];
+                kl[q] = *(const f32x4 *)(KL_ws + i);
+                h[q] = *(const f32x4 *)(H_ws + i);
             }
-            count(flags_ws[r]);
+        } else if (i < seg1) {  // at most three rows, in one lane of the last segment
+#pragma unroll
+            for (int e = 0; e < 3; ++e) {
+                if (e >= (int)(seg1 - i)) break;
+                j[q][e] = J_ws[i + e];
+                fl[q] |= (unsigned)flags_ws[i + e] << (8 * e);
+                if (aux) {
+                    kl[q][e] = KL_ws[i + e];
+                    h[q][e] = H_ws[i + e];
+                }
+            }
         }
     }
-    block_totals(sj, c);
+    double s[3] = {0.0, 0.0, 0.0};
+    int c01 = 0, c23 = 0;  // two counters each, 16 bits
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            s[0] += (double)j[q][e];
+            if (aux) {
+                s[1] += (double)kl[q][e];
+                s[2] += (double)h[q][e];
+            }
+        }
+        static_assert(kFlagClipHigh == 1 && kFlagClipLow == 2 && kFlagDelta == 4 && kFlagOutOfBand == 8, "bit positions");
+        c01 += __builtin_popcount(fl[q] & 0x01010101u) + (__builtin_popcount(fl[q] & 0x02020202u) << 16);
+        c23 += __builtin_popcount(fl[q] & 0x04040404u) + (__builtin_popcount(fl[q] & 0x08080808u) << 16);
+    }
+    // totals of the workgroup, in every lane of its first wavefront
+    auto block_totals = [&]() {
+        s[0] = wave_sum_dpp(s[0]);
+        if (aux) {
+            s[1] = wave_sum_dpp(s[1]);
+            s[2] = wave_sum_dpp(s[2]);
+        }
+        if (lane == 0) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) lds_s[q][wv] = s[q];
+        }
+    };
+    auto first_wave_sums = [&]() {
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            if (q == 0 || aux) s[q] = wave_sum_dpp(lane < 16 ? lds_s[q][lane & 15] : 0.0);
+    };
+    block_totals();
+    c01 = wave_sum(c01);
+    c23 = wave_sum(c23);
+    if (lane == 0) {
+        lds_c[0][wv] = c01;
+        lds_c[1][wv] = c23;
+    }
+    __syncthreads();
+    long long c[4] = {0, 0, 0, 0};
+    if (wv == 0) {
+        first_wave_sums();
+        c01 = wave_sum(lane < 16 ? lds_c[0][lane & 15] : 0);
+        c23 = wave_sum(lane < 16 ? lds_c[1][lane & 15] : 0);
+        c[0] = c01 & 0xffff, c[1] = (unsigned)c01 >> 16;
+        c[2] = c23 & 0xffff, c[3] = (unsigned)c23 >> 16;
+    }
     if (nseg > 1) {
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             FinPartial pt;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) pt.s[q] = sj[q];
+            for (int q = 0; q < 3; ++q) pt.s[q] = s[q];
 #pragma unroll
             for (int q = 0; q < 4; ++q) pt.c[q] = c[q];
             pt.pad = 0;
@@ -1663,22 +1721,33 @@ __global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const f
         if (lds_ticket != (unsigned)(nseg - 1)) return;  // whole workgroup alike
         __threadfence();  // the last ticket: every partial has been delivered; read them afresh
 #pragma unroll
-        for (int q = 0; q < 3; ++q) sj[q] = 0.0;
+        for (int q = 0; q < 3; ++q) s[q] = 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) c[q] = 0;
-        for (long long sgm = threadIdx.x; sgm < nseg; sgm += 1024) {  // lane l: segments l, l + 1024, ...
+        for (long long sgm = tid; sgm < nseg; sgm += 1024) {  // lane l: segments l, l + 1024, ...
             const volatile FinPartial *pp = partials + sgm;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) sj[q] += pp->s[q];
+            for (int q = 0; q < 3; ++q) s[q] += pp->s[q];
 #pragma unroll
             for (int q = 0; q < 4; ++q) c[q] += pp->c[q];
         }
-        block_totals(sj, c);
+        block_totals();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            c[q] = wave_sum(c[q]);
+            if (lane == 0) lds_c4[q][wv] = c[q];
+        }
+        __syncthreads();
+        if (wv == 0) {
+            first_wave_sums();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) c[q] = wave_sum(lane < 16 ? lds_c4[q][lane & 15] : 0ll);
+        }
     }
-    if (threadIdx.x == 0) {
-        const double policy = 0.0 - sj[0] * hdr->inv_D;
+    if (tid == 0) {
+        const double policy = 0.0 - s[0] * hdr->inv_D;
         if (aux) {
-            const double klm = sj[1] * hdr->inv_D, hm = sj[2] * hdr->inv_D;
+            const double klm = s[1] * hdr->inv_D, hm = s[2] * hdr->inv_D;
             loss_out[0] = (float)(policy + (double)kl_coef * klm - (double)ent_coef * hm);
             loss_out[1] = (float)policy;
             loss_out[2] = (float)klm;
@@ -1738,6 +1807,62 @@ __global__ void __launch_bounds__(256) grpo_adv_to_tokens(const float *adv, long
     }
 }
 
+// Both in one launch, for a batch of few groups of one size: every workgroup computes all advantages
+// (16 lanes to a group of up to 16 rollouts, 64 to a larger one; the sums run over the lanes in the
+// same order as above) and looks its tokens up in LDS; the first one also writes adv_out.  Two launches
+// of 2 to 5 us each became one of the same length.  Up to 1024 rollouts and four rounds of groups: beyond
+// them the repeated work costs more than the launch.
+constexpr int kAdvRollouts = 1024, kAdvTokens = 4096;
+__global__ void __launch_bounds__(1024) grpo_adv_fused(const float *rewards, int n_rollouts, int n_groups, int group_size,
+                                                       double eps_std, int ddof, float *adv_out,
+                                                       const int *rollout_of_token, long long n_tokens, float *adv_tok)
+{
+    __shared__ float adv[kAdvRollouts];
+    const int W = group_size <= 16 ? 16 : 64;  // lanes to a group
+    const int l = threadIdx.x & (W - 1);
+    int tok[kAdvTokens / 1024];
+#pragma unroll
+    for (int q = 0; q < kAdvTokens / 1024; ++q) {
+        const long long t = (long long)blockIdx.x * kAdvTokens + q * 1024 + threadIdx.x;
+        tok[q] = t < n_tokens ? rollout_of_token[t] : -1;
+    }
+    for (int g0 = 0; g0 < n_groups; g0 += 1024 / W) {
+        const int g = g0 + (int)threadIdx.x / W;
+        const int b = g * group_size, e = g < n_groups ? b + group_size : b;
+        auto sum_lanes = [&](double v) {
+            if (W == 64) {
+                v += __shfl_xor(v, 32, 64);
+                v += __shfl_xor(v, 16, 64);
+            }
+#pragma unroll
+            for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+            return v;
+        };
+        double sum = 0.0;
+        for (int i = b + l; i < e; i += W) sum += (double)rewards[i];
+        const double mu = sum_lanes(sum) / (double)group_size;
+        double ss = 0.0;
+        for (int i = b + l; i < e; i += W) {
+            const double d = (double)rewards[i] - mu;
+            ss += d * d;
+        }
+        ss = sum_lanes(ss);
+        const double sigma = (group_size - ddof > 0) ? sqrt(ss / (double)(group_size - ddof)) : 0.0;
+        const double den = sigma + eps_std;
+        for (int i = b + l; i < e; i += W) {
+            const float A = den > 0.0 ? (float)(((double)rewards[i] - mu) / den) : 0.f;
+            adv[i] = A;
+            if (blockIdx.x == 0) adv_out[i] = A;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kAdvTokens / 1024; ++q) {
+        const long long t = (long long)blockIdx.x * kAdvTokens + q * 1024 + threadIdx.x;
+        if (t < n_tokens) adv_tok[t] = (tok[q] >= 0 && tok[q] < n_rollouts) ? adv[tok[q]] : NAN;
+    }
+}
+
 // r_total = r_task - alpha |l_target - l_y| (section 3.1).  The length difference is formed
 // in integers, so it is exact.
 __global__ void __launch_bounds__(256) grpo_total_rewards_k(const float *task, const int *len,
@@ -1773,6 +1898,39 @@ __global__ void __launch_bounds__(64) grpo_filter_flag(const float *rewards, lon
         if (rollout_keep)
             for (long long i = b + lane; i < e; i += 64) rollout_keep[i] = (unsigned char)differs;
     }
+}
+
+// Flags and compaction in one launch for up to 1024 groups of one size of up to 64: a lane to a group
+// (its rewards lie next to one another), the kept ones counted ahead of each lane.
+constexpr int kFilterGroups = 1024, kFilterSize = 64;
+__global__ void __launch_bounds__(kFilterGroups) grpo_filter_fused(const float *rewards, int n_groups, int group_size,
+                                                                   unsigned char *keep, unsigned char *rollout_keep,
+                                                                   int *kept_groups, int *n_kept)
+{
+    __shared__ int wave_tot[kFilterGroups / 64];
+    const int g = threadIdx.x, lane = g & 63, wv = g >> 6;
+    const int b = g * group_size;
+    bool differs = false;
+    if (g < n_groups) {
+        const float first = rewards[b];
+        for (int i = 0; i < group_size; ++i) differs |= rewards[b + i] != first;
+        keep[g] = differs ? 1 : 0;
+        if (rollout_keep)
+            for (int i = 0; i < group_size; ++i) rollout_keep[b + i] = differs ? 1 : 0;
+    }
+    const unsigned long long kept = __ballot(differs);
+    const int ahead = __popcll(kept & ((1ull << lane) - 1ull));
+    if (lane == 0) wave_tot[wv] = __popcll(kept);
+    __syncthreads();
+    int before = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < kFilterGroups / 64; ++w) {
+        if (w < wv) before += wave_tot[w];
+        total += wave_tot[w];
+    }
+    if (differs) kept_groups[before + ahead] = g;
+    if (g >= total && g < n_groups) kept_groups[g] = -1;
+    if (g == 0) *n_kept = total;
 }
 
 // Ordered compaction of the kept group indices: one workgroup walks the flags in chunks
@@ -1812,29 +1970,55 @@ __global__ void __launch_bounds__(1024) grpo_filter_compact(const unsigned char 
     if (tid == 0) *n_kept = total;
 }
 
-// Packed (variable-length) batches: rollout i owns rows [cu[i], cu[i+1]).  First every
-// row gets "no rollout, weight 0", then each rollout stamps its range.
-__global__ void __launch_bounds__(256) grpo_packed_clear(long long n_tokens, float *weights,
-                                                         int *rollout_of_token)
+// Packed (variable-length) batches: rollout i owns rows [cu[i], cu[i+1]).  A wavefront takes 256
+// consecutive rows: it finds the rollouts of its first and of its last row together, 64 lanes
+// probing at once (two rounds for 4096 rollouts), and each lane then searches between those two.
+// How many of the R + 1 entries of cu are <= t (they do not decrease; if they do, the result is
+// some number in range).
+__device__ __forceinline__ long long count_le(const long long *cu, long long R, long long t)
 {
-    for (long long t = (long long)blockIdx.x * 256 + threadIdx.x; t < n_tokens;
-         t += (long long)gridDim.x * 256) {
-        if (weights) weights[t] = 0.f;
-        if (rollout_of_token) rollout_of_token[t] = -1;
+    long long lo = 0, len = R + 1;
+    for (;;) {
+        const long long step = (len + 63) / 64;
+        const long long at = lo + (long long)((threadIdx.x & 63) + 1) * step - 1;  // last entry of this lane's piece
+        const int cnt = __popcll(__ballot(at < lo + len && cu[at < lo + len ? at : lo] <= t));
+        lo += cnt * step;
+        len -= cnt * step;
+        if (step == 1 || len <= 0) return lo;
+        if (len > step) len = step;
     }
 }
-__global__ void __launch_bounds__(256) grpo_packed_stamp(const long long *cu, long long n_rollouts,
-                                                         long long n_tokens, int sample_level,
-                                                         float *weights, int *rollout_of_token)
+__global__ void __launch_bounds__(256) grpo_packed_rows(const long long *cu, long long n_rollouts, long long n_tokens,
+                                                        int sample_level, float *weights, int *rollout_of_token)
 {
-    for (long long i = blockIdx.x; i < n_rollouts; i += gridDim.x) {
-        long long b = cu[i], e = cu[i + 1];
-        b = b < 0 ? 0 : (b > n_tokens ? n_tokens : b);
-        e = e < b ? b : (e > n_tokens ? n_tokens : e);
-        const float w = sample_level ? (float)(1.0 / (double)(e - b)) : 1.f;
-        for (long long t = b + threadIdx.x; t < e; t += 256) {
+    const int lane = threadIdx.x & 63;
+    for (long long t0 = ((long long)blockIdx.x * 4 + (threadIdx.x >> 6)) * 256; t0 < n_tokens; t0 += (long long)gridDim.x * 1024) {
+        const long long t1 = (t0 + 256 < n_tokens ? t0 + 256 : n_tokens) - 1;
+        const long long c0 = n_rollouts > 0 ? count_le(cu, n_rollouts, t0) : 0;
+        const long long c1 = n_rollouts > 0 ? count_le(cu, n_rollouts, t1) : 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const long long t = t0 + q * 64 + lane;
+            if (t > t1) break;
+            long long lo = c0, hi = c1;  // entries <= t: between those of the first and of the last row
+            while (lo < hi) {
+                const long long mid = (lo + hi) >> 1;
+                if (cu[mid] <= t)
+                    lo = mid + 1;
+                else
+                    hi = mid;
+            }
+            float w = 0.f;
+            int r = -1;
+            if (lo > 0 && lo <= n_rollouts) {
+                long long b = cu[lo - 1], e = cu[lo];
+                b = b < 0 ? 0 : (b > n_tokens ? n_tokens : b);
+                e = e < b ? b : (e > n_tokens ? n_tokens : e);
+                r = (int)(lo - 1);
+                w = sample_level ? (float)(1.0 / (double)(e - b)) : 1.f;
+            }
             if (weights) weights[t] = w;
-            if (rollout_of_token) rollout_of_token[t] = (int)i;
+            if (rollout_of_token) rollout_of_token[t] = r;
         }
     }
 }
@@ -2052,8 +2236,12 @@ grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens,
     int *order = (int *)((char *)partials + fin_partials_bytes(n_tokens));
     hipStream_t st = (hipStream_t)stream;
 
-    hipLaunchKernelGGL(grpo_prepare, dim3(1), dim3(1024), 0, st, mask, aux ? token_weights : nullptr,
-                       (long long)n_tokens, denom, hdr);
+    // rows of 32 KB and more, some of them masked, more of them than CUs: the live rows first, then the masked ones
+    if (!((mask || (aux && token_weights)) && n_tokens <= 0x7fffffffll && n_tokens > cu_count() &&
+          vocab * (dtype == GRPO_BF16 ? 2 : 4) >= kOrderMinRowBytes))
+        order = nullptr;
+    hipLaunchKernelGGL(grpo_prepare, dim3(order ? (unsigned)((n_tokens + kOrderRows - 1) / kOrderRows) : 1u), dim3(1024), 0,
+                       st, mask, aux ? token_weights : (const float *)nullptr, (long long)n_tokens, denom, hdr, order);
     if (n_tokens > 0) {
         RowParams p = {};
         p.logits = logits;
@@ -2076,13 +2264,7 @@ grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens,
         p.delta = delta;
         p.grad_scale = grad_scale;
         p.bwd = 1;
-        // rows of 32 KB and more, some of them masked: the live rows first, then the masked ones
-        if ((mask || (aux && token_weights)) && n_tokens <= 0x7fffffffll &&
-            vocab * (dtype == GRPO_BF16 ? 2 : 4) >= kOrderMinRowBytes) {
-            p.order = order;
-            hipLaunchKernelGGL(grpo_order_rows, dim3(fin_blocks(n_tokens)), dim3(1024), 0, st, mask,
-                               aux ? token_weights : (const float *)nullptr, (long long)n_tokens, hdr, order);
-        }
+        p.order = order;
         if (aux) {
             p.ref_lp = kl_coef != 0.f ? ref_logprobs : nullptr;
             p.token_w = token_weights;
@@ -2212,6 +2394,13 @@ grpo_status grpo_group_advantages(const float *rewards, int64_t n_rollouts,
     hipStream_t st = (hipStream_t)stream;
     const bool any_work = (n_groups > 0 && n_rollouts > 0) || (rollout_of_token && n_tokens > 0);
     if (!any_work) return GRPO_OK;
+    if (!group_offsets && n_groups > 0 && n_rollouts > 0 && rollout_of_token && n_tokens > 0 &&
+        n_rollouts <= kAdvRollouts && n_groups <= (group_size <= 16 ? 4 * 64 : 4 * 16)) {
+        hipLaunchKernelGGL(grpo_adv_fused, dim3((unsigned)((n_tokens + kAdvTokens - 1) / kAdvTokens)), dim3(1024), 0, st,
+                           rewards, (int)n_rollouts, (int)n_groups, (int)group_size, (double)eps_std, ddof, adv_out,
+                           rollout_of_token, (long long)n_tokens, adv_tok_out);
+        return hipGetLastError() == hipSuccess ? GRPO_OK : GRPO_ERR_HIP;
+    }
     if (n_groups > 0 && n_rollouts > 0) {
         const unsigned grid = (unsigned)(n_groups < 4096 ? n_groups : 4096);
         hipLaunchKernelGGL(grpo_group_adv, dim3(grid), dim3(64), 0, st, rewards, (long long)n_rollouts,
@@ -2254,6 +2443,11 @@ grpo_status grpo_filter_groups(const float *rewards, int64_t n_rollouts, const i
     if (n_groups > 0 && (!keep_out || !kept_groups_out)) return GRPO_ERR_NULL;
     if (n_groups > 0 && n_rollouts > 0 && !rewards) return GRPO_ERR_NULL;
     hipStream_t st = (hipStream_t)stream;
+    if (!group_offsets && n_groups > 0 && n_groups <= kFilterGroups && group_size <= kFilterSize) {
+        hipLaunchKernelGGL(grpo_filter_fused, dim3(1), dim3(kFilterGroups), 0, st, rewards, (int)n_groups, (int)group_size,
+                           keep_out, rollout_keep_out, kept_groups_out, n_kept_out);
+        return hipGetLastError() == hipSuccess ? GRPO_OK : GRPO_ERR_HIP;
+    }
     if (n_groups > 0) {
         const unsigned grid = (unsigned)(n_groups < 4096 ? n_groups : 4096);
         hipLaunchKernelGGL(grpo_filter_flag, dim3(grid), dim3(64), 0, st, rewards, (long long)n_rollouts,
@@ -2274,16 +2468,10 @@ grpo_status grpo_packed_layout(const int64_t *cu_seqlens, int64_t n_rollouts, in
     if (!weights_out && !rollout_of_token_out) return GRPO_ERR_NULL;
     if (n_tokens == 0) return GRPO_OK;
     hipStream_t st = (hipStream_t)stream;
-    long long blocks = (n_tokens + 255) / 256;
+    long long blocks = (n_tokens + 1023) / 1024;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(grpo_packed_clear, dim3((unsigned)blocks), dim3(256), 0, st, (long long)n_tokens,
-                       weights_out, rollout_of_token_out);
-    if (n_rollouts > 0) {
-        const unsigned grid = (unsigned)(n_rollouts < 4096 ? n_rollouts : 4096);
-        hipLaunchKernelGGL(grpo_packed_stamp, dim3(grid), dim3(256), 0, st, (const long long *)cu_seqlens,
-                           (long long)n_rollouts, (long long)n_tokens, sample_level ? 1 : 0, weights_out,
-                           rollout_of_token_out);
-    }
+    hipLaunchKernelGGL(grpo_packed_rows, dim3((unsigned)blocks), dim3(256), 0, st, (const long long *)cu_seqlens,
+                       (long long)n_rollouts, (long long)n_tokens, sample_level ? 1 : 0, weights_out, rollout_of_token_out);
     return hipGetLastError() == hipSuccess ? GRPO_OK : GRPO_ERR_HIP;
 }
 

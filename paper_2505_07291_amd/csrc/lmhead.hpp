@@ -44,7 +44,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int LM_BM = 256, LM_BN = 256, LM_BK = 64;
@@ -1201,7 +1200,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
 
     if (bwd)
         hipLaunchKernelGGL(grpo_prepare, dim3(1), dim3(1024), 0, st, mask, aux ? token_weights : (const float *)nullptr,
-                           (long long)n_tokens, denom, hdr);
+                           (long long)n_tokens, denom, hdr, (int *)nullptr);
     if (n_tokens > 0) {
         const int M = (int)n_tokens, V = (int)vocab, D = (int)d_model;
         const int Mc = (int)std::min<int64_t>(cap, n_tokens);  // most rows a chunk can have
