@@ -499,54 +499,84 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     // row 8 (v / 4) + 4 (l / 32) + v % 4.
     const int cl = lane & 31, g = lane >> 5;
     const int wrow = wm * (LM_FA * 32), wcol = wn * (LM_FB * 32);
-    if (EPI == LM_EPI_F32 && p.accumulate) {
-        // C += result.  All loads of a block row first, then the sums and stores: element by element the
-        // dependent load in front of every store made this epilogue take 2 ms longer than the plain store
-        // (dL/dW of the second and later chunks).
+    // Where a wavefront's part lies inside the matrix whole - every part but those of the last tile row:
+    // N is a multiple of 64 here, so a part's 64 columns are all inside or all outside - its stores need no
+    // checks: a scalar address per row and one 32-bit offset per lane.  With a row and a column test, a 64-bit
+    // address and a branch for each of 128 stores the epilogue was bound by its 2200 instructions a wavefront
+    // (FIGURES).
+    if constexpr (EPI == LM_EPI_F32) {
+        if (col0 + wcol >= p.N) return;
+        const bool whole = row0 + wrow + LM_FA * 32 <= M && col0 + wcol + LM_FB * 32 <= p.N && p.ldc < (1ll << 28);
+        if (whole) {
+            char *cw = (char *)p.C + ((long long)(row0 + wrow) * p.ldc + col0 + wcol) * 4;
+            const unsigned voff = (unsigned)((4 * g * p.ldc + cl) * 4);
+            const long long pitch = p.ldc * 4;
 #pragma unroll
-        for (int i = 0; i < LM_FA; ++i) {
-            float old[16][LM_FB];
+            for (int i = 0; i < LM_FA; ++i) {
+                float old[16][LM_FB];
+                if (p.accumulate) {
+                    // C += result: all loads of a block row first, then the sums and stores (a dependent load in
+                    // front of every store made this epilogue take 2 ms longer than the plain store)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + wrow + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+                    for (int v = 0; v < 16; ++v)
 #pragma unroll
-                for (int j = 0; j < LM_FB; ++j) {
-                    const int col = col0 + wcol + j * 32 + cl;
-                    old[v][j] = (row < M && col < p.N) ? ((const float *)p.C)[(long long)row * p.ldc + col] : 0.f;
+                        for (int j = 0; j < LM_FB; ++j)
+                            old[v][j] = *(const float *)(cw + (i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 128 + voff);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+#pragma unroll
+                        for (int j = 0; j < LM_FB; ++j) old[v][j] = -0.f;  // x + -0 is x, whatever x
                 }
-            }
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + wrow + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+                for (int v = 0; v < 16; ++v)
 #pragma unroll
-                for (int j = 0; j < LM_FB; ++j) {
-                    const int col = col0 + wcol + j * 32 + cl;
-                    if (row < M && col < p.N) ((float *)p.C)[(long long)row * p.ldc + col] = old[v][j] + acc[i][j][v];
-                }
+                    for (int j = 0; j < LM_FB; ++j)
+                        *(float *)(cw + (i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 128 + voff) = old[v][j] + acc[i][j][v];
             }
+            return;
         }
-        return;
-    }
-    if (EPI == LM_EPI_BF16 || EPI == LM_EPI_F32) {
 #pragma unroll
         for (int i = 0; i < LM_FA; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = row0 + wrow + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
                 if (row >= M) continue;
-                const long long orow = (EPI == LM_EPI_BF16 && p.c_rows) ? p.c_rows[row] : row;
 #pragma unroll
                 for (int j = 0; j < LM_FB; ++j) {
                     const int col = col0 + wcol + j * 32 + cl;
                     if (col >= p.N) continue;
-                    if (EPI == LM_EPI_BF16 && parts > 1) {
-                        p.split_ws[(((long long)rest_index * parts + part) << 16) + (row - row0) * LM_BN + (col - col0)] =
-                            acc[i][j][v];
-                    } else if (EPI == LM_EPI_BF16) {
-                        ((__bf16 *)p.C)[orow * p.ldc + col] = (__bf16)acc[i][j][v];
-                    } else {
-                        ((float *)p.C)[orow * p.ldc + col] = acc[i][j][v];
-                    }
+                    float *at = (float *)p.C + (long long)row * p.ldc + col;
+                    *at = p.accumulate ? *at + acc[i][j][v] : acc[i][j][v];
+                }
+            }
+        return;
+    }
+    if constexpr (EPI == LM_EPI_BF16) {
+        if (parts > 1) {
+            // the partial block is dense and read only where rows and columns exist: stored whole
+            char *bw = (char *)(p.split_ws + (((long long)rest_index * parts + part) << 16) + wrow * LM_BN + wcol);
+            const unsigned voff = (unsigned)((4 * g * LM_BN + cl) * 4);
+#pragma unroll
+            for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+#pragma unroll
+                    for (int j = 0; j < LM_FB; ++j)
+                        *(float *)(bw + ((i * 32 + 8 * (v >> 2) + (v & 3)) * LM_BN + j * 32) * 4 + voff) = acc[i][j][v];
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = row0 + wrow + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+                if (row >= M) continue;
+                const long long orow = p.c_rows ? p.c_rows[row] : row;
+#pragma unroll
+                for (int j = 0; j < LM_FB; ++j) {
+                    const int col = col0 + wcol + j * 32 + cl;
+                    if (col < p.N) ((__bf16 *)p.C)[orow * p.ldc + col] = (__bf16)acc[i][j][v];
                 }
             }
         return;
@@ -600,12 +630,19 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             // 16 lanes per row, four rows per instruction; the columns between N and the row
             // pitch of Z receive the products with the clamped operand rows: never read
             const int rr = lane >> 4, c4 = (lane & 15) * 4;
+            char *zw = (char *)(p.Z + (long long)(row0 + rbase) * p.ldz + col0 + wcol);  // ldz < 2^23: see lm_bwd_vocab_ok
+            const unsigned voff = (unsigned)((rr * p.ldz + c4) * 4);
+            if (row0 + rbase + 64 <= M) {
 #pragma unroll
-            for (int it = 0; it < 16; ++it) {
-                const int rl = it * 4 + rr;
-                const int row = row0 + rbase + rl;
-                const f32x4 zq = *(const f32x4 *)(stage + rl * LM_EPI_PITCH + c4);
-                if (row < M) *(f32x4 *)(p.Z + (long long)row * p.ldz + col0 + wcol + c4) = zq;
+                for (int it = 0; it < 16; ++it)
+                    *(f32x4 *)(zw + it * 4 * (p.ldz * 4) + voff) =
+                        *(const f32x4 *)(stage + (it * 4 + rr) * LM_EPI_PITCH + c4);
+            } else {
+#pragma unroll
+                for (int it = 0; it < 16; ++it)
+                    if (row0 + rbase + it * 4 + rr < M)
+                        *(f32x4 *)(zw + it * 4 * (p.ldz * 4) + voff) =
+                            *(const f32x4 *)(stage + (it * 4 + rr) * LM_EPI_PITCH + c4);
             }
         }
         // lane = row: take the sampled token's logit out, blank what lies outside the matrix
