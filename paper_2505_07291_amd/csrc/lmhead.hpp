@@ -829,14 +829,16 @@ __global__ void __launch_bounds__(256) lm_gather_rows(const __bf16 *in, long lon
 }
 
 // Merges the tile partials of each compact row, then the objective's once-per-row arithmetic.
-// A workgroup takes 16 compact rows; 64 lanes share a row, lane l merging tiles l, l + 64, ..., and
-// their results meet in LDS in lane order (fixed order: the bits repeat from run to run).  What
+// A workgroup takes 16 compact rows; LANES lanes share a row, lane l merging tiles l, l + LANES, ...,
+// and their results meet in LDS in lane order (fixed order: the bits repeat from run to run).  What
 // bounds it is latency - the partials of 1056 rows and 594 tiles are 5 MB - so every lane reads all
-// of its partials into registers at once (up to LM_CMB_KEEP tiles, V = 196608; tiles beyond them are
-// read twice) and the maximum and the sums are taken from there.  16 lanes to a row, each walking 37
-// tiles twice, took 48 us on that batch.
-constexpr int LM_CMB_ROWS = 16, LM_CMB_LANES = 64, LM_CMB_KEEP = 12;
-template <bool AUX>
+// of its partials into registers at once (LM_CMB_KEEP each; tiles beyond them are read twice) and the
+// maximum and the sums are taken from there.  16 lanes where they hold all tiles (V <= 49152), 64
+// for more: 16 lanes walking 594 tiles twice took 48 us on that batch, 64 lanes take 8; 64 lanes on the
+// 11 tiles of V = 2711 made a whole 29 us call 1 us longer.
+constexpr int LM_CMB_ROWS = 16, LM_CMB_KEEP = 12;
+inline int lm_combine_lanes(int tiles_n) { return tiles_n <= 16 * LM_CMB_KEEP ? 16 : 64; }
+template <bool AUX, int LM_CMB_LANES>
 __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowParams p, LmRows w)
 {
     __shared__ float sh_m[LM_CMB_LANES][LM_CMB_ROWS + 1], sh_s[LM_CMB_LANES][LM_CMB_ROWS + 1];
@@ -1340,10 +1342,12 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             if (e != hipSuccess) return GRPO_ERR_HIP;
 
             const dim3 cmb_grid((unsigned)((Mc + LM_CMB_ROWS - 1) / LM_CMB_ROWS));
+            const bool few = lm_combine_lanes(L.tiles_n) == 16;
+            const dim3 cmb_block((unsigned)(LM_CMB_ROWS * lm_combine_lanes(L.tiles_n)));
             if (aux)
-                hipLaunchKernelGGL(lm_combine<true>, cmb_grid, dim3(LM_CMB_ROWS * LM_CMB_LANES), 0, st, p, w);
+                hipLaunchKernelGGL((few ? lm_combine<true, 16> : lm_combine<true, 64>), cmb_grid, cmb_block, 0, st, p, w);
             else
-                hipLaunchKernelGGL(lm_combine<false>, cmb_grid, dim3(LM_CMB_ROWS * LM_CMB_LANES), 0, st, p, w);
+                hipLaunchKernelGGL((few ? lm_combine<false, 16> : lm_combine<false, 64>), cmb_grid, cmb_block, 0, st, p, w);
             if (!bwd) continue;
 
             hipLaunchKernelGGL(lm_select_grad_rows, dim3(1), dim3(1024), 0, st, w);
