@@ -147,7 +147,7 @@ __device__ __forceinline__ void lm_tile_of(int L, int tiles_m, int tiles_n, int 
 struct LmSplit {
     int full, rest, s2;
 };
-__host__ __device__ inline LmSplit lm_plan_split(int tiles, int k_tiles, int max_items, int n_cu)
+__device__ __forceinline__ LmSplit lm_plan_split(int tiles, int k_tiles, int max_items, int n_cu)
 {
     LmSplit sp;
     sp.rest = max_items > 0 ? tiles % n_cu : 0;
@@ -168,32 +168,15 @@ __host__ __device__ inline LmSplit lm_plan_split(int tiles, int k_tiles, int max
     return sp;
 }
 
-// Workgroups that cover every plan a product of at most tiles_m tile rows can get (the device knows
-// how many there really are): whole tiles and parts, each kind rounded up to the 8 XCDs.  The plans
-// repeat with the tile count modulo n_cu while the whole tiles only grow, so the last n_cu row
-// counts hold the largest.  A workgroup without work is not free - it takes all 160 KB of a CU's
-// LDS, so only one at a time gets in, about 5 us each: launched for the most parts any plan could
-// have (32 for each of n_cu tiles, 8192 workgroups) they cost 0.15 to 0.2 ms a product whatever its
-// size (dL/dH of 612 x 50304 x 768: 236 us, 92 us with this bound).
-inline long long lm_split_grid(int tiles_m, int tiles_n, int k_tiles, int max_items, int n_cu)
-{
-    long long most = 8;
-    for (int t = tiles_m > n_cu ? tiles_m - n_cu + 1 : 1; t <= tiles_m; ++t) {
-        const LmSplit sp = lm_plan_split(t * tiles_n, k_tiles, max_items, n_cu);
-        const long long g = ((long long)(sp.full + 7) / 8 + (sp.rest * sp.s2 + 7) / 8) * 8;
-        if (g > most) most = g;
-    }
-    return most;
-}
-
-// Workgroup -> tile (and part).  Each XCD takes a contiguous run of the whole tiles, then a
+// Work item -> tile (and part).  Each XCD takes a contiguous run of the whole tiles, then a
 // contiguous run of the parts, so that both kinds of work are spread evenly over the XCDs; the
 // parts are ordered part by part (the same K range of neighbouring tiles shares operand panels).
+// idx: position in the XCD's list of lm_items_per_xcd items; false: no work at that position.
 // rest_index: which of the cut tiles this is, -1 for a whole tile.
-__device__ __forceinline__ bool lm_map_tile(int tiles_m, int tiles_n, const LmSplit &sp, int group_m, int &tm, int &tn,
-                                            int &part, int &rest_index)
+__device__ __forceinline__ int lm_items_per_xcd(const LmSplit &sp) { return (sp.full + 7) / 8 + (sp.rest * sp.s2 + 7) / 8; }
+__device__ __forceinline__ bool lm_map_tile(int xcd, int idx, int tiles_m, int tiles_n, const LmSplit &sp, int group_m,
+                                            int &tm, int &tn, int &part, int &rest_index)
 {
-    const int xcd = (int)(blockIdx.x & 7), idx = (int)(blockIdx.x >> 3);
     const int per_xcd = (sp.full + 7) / 8;
     int L;
     part = 0;
@@ -257,59 +240,74 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     }
     const int K = p.K_dev ? min((*p.K_dev + LM_BK - 1) / LM_BK * LM_BK, p.K) : p.K;
     if (EPI == LM_EPI_F32 && p.accumulate && K == 0) return;  // nothing to add (an empty chunk)
-    int tm, tn, part = 0, parts = 1, rest_index = -1;
-    {
-        const int tiles_m = (M + LM_BM - 1) / LM_BM;
-        const LmSplit sp = lm_plan_split(tiles_m * p.tiles_n, K / LM_BK, EPI == LM_EPI_BF16 ? p.split_items : 0,
-                                         p.n_cu > 0 ? p.n_cu : 256);
-        if (!lm_map_tile(tiles_m, p.tiles_n, sp, p.group_m, tm, tn, part, rest_index))
-            return;  // whole workgroup alike, before any barrier
-        if (rest_index >= 0) parts = sp.s2;
-    }
+    const int tiles_m = (M + LM_BM - 1) / LM_BM;
+    const LmSplit sp = lm_plan_split(tiles_m * p.tiles_n, K / LM_BK, EPI == LM_EPI_BF16 ? p.split_items : 0, p.n_cu);
+    // The workgroups stay: the grid has one for each CU (all of its LDS), workgroup b takes the items b / 8,
+    // b / 8 + grid / 8, ... of XCD b % 8's list - the order in which one workgroup per item would be
+    // dispatched - and prepares the next item while it stores this one (below).
+    const int xcd = (int)(blockIdx.x & 7), per_xcd = (int)(gridDim.x >> 3), n_items = lm_items_per_xcd(sp);
+    int idx = (int)(blockIdx.x >> 3);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // in a scalar register: LDS targets are uniform
     const int wm = wave / LM_WN, wn = wave % LM_WN;  // this wavefront's 128 x 64 part of the tile
-    const int row0 = tm * LM_BM, col0 = tn * LM_BN;
 
-    // Byte offsets of this lane's four 16-byte loads per operand tile, relative to the
+    // The current item: its tile, its part of the contraction (K steps [kt0, kt0 + KT)) and the addresses of its
+    // loads.  Byte offsets of this lane's four 16-byte loads per operand tile, relative to the
     // tile's first row at k = 0.  Load i of a wavefront fills LDS chunks [i*512 + wave*64,
     // +64) of the tile; chunk c sits in tile row c / 8 at physical position c % 8 and holds
     // logical chunk (c % 8) ^ ((row >> 1) & 7).  Rows past the end of the matrix re-read the
     // last row (their results are never stored).
+    int row0 = 0, col0 = 0, part = 0, parts = 1, rest_index = -1, kt0 = 0, KT = 0;
     unsigned a_off[LM_LPT], b_off[LM_LPT];
-#pragma unroll
-    for (int i = 0; i < LM_LPT; ++i) {
-        const int c = i * LM_THREADS + tid;
-        const int r = c / LM_CPR, pc = c % LM_CPR;
-        const int lc = pc ^ ((r >> 1) & (LM_CPR - 1));
-        const int ra = min(row0 + r, M - 1) - row0;
-        const int rb = min(col0 + r, p.N - 1) - col0;
-        // K-major operand: the tile is [64 k rows][256 m]; chunk c is k row c / 32 at position c % 32 and holds
-        // logical chunk (c % 32) ^ lm_km_swizzle(k row); chunks past the end of the operand's k row re-read
-        // its last chunk (they belong to rows or columns of C that are never stored)
-        const int kk = c >> 5, lck = (c & 31) ^ lm_km_swizzle(kk);
-        if constexpr (AKM) {
-            const int ch = min((row0 >> 3) + lck, (p.a_cols >> 3) - 1) - (row0 >> 3);
-            a_off[i] = (unsigned)((long long)kk * p.lda * 2 + ch * 16);
-        } else {
-            a_off[i] = (unsigned)(((long long)ra * p.lda + lc * 8) * 2);
-        }
-        if constexpr (BKM) {
-            const int ch = min((col0 >> 3) + lck, (p.b_cols >> 3) - 1) - (col0 >> 3);
-            b_off[i] = (unsigned)((long long)kk * p.ldb * 2 + ch * 16);
-        } else {
-            b_off[i] = (unsigned)(((long long)rb * p.ldb + lc * 8) * 2);
-        }
-    }
-    // this workgroup's part of the contraction: K steps [kt0, kt0 + KT)
-    const int kt0 = (int)((long long)(K / LM_BK) * part / parts);
-    const int KT = (int)((long long)(K / LM_BK) * (part + 1) / parts) - kt0;
-    const char *a_tile = AKM ? (const char *)p.A + ((long long)kt0 * LM_BK * p.lda + row0) * 2
-                             : (const char *)p.A + ((long long)(chunk_base + row0) * p.lda + (long long)kt0 * LM_BK) * 2;
-    const char *b_tile = BKM ? (const char *)p.B + ((long long)kt0 * LM_BK * p.ldb + col0) * 2
-                             : (const char *)p.B + ((long long)col0 * p.ldb + (long long)kt0 * LM_BK) * 2;
+    const char *a_tile = nullptr, *b_tile = nullptr;
     const long long a_kstep = (long long)LM_BK * p.lda * 2, b_kstep = (long long)LM_BK * p.ldb * 2;  // K-major only
+    // takes this workgroup's next item, from position idx on; false: none is left
+    auto next_item = [&]() __attribute__((always_inline)) -> bool {
+        int tm, tn;
+        for (;; idx += per_xcd) {
+            if (idx >= n_items) return false;  // whole workgroup alike
+            if (lm_map_tile(xcd, idx, tiles_m, p.tiles_n, sp, p.group_m, tm, tn, part, rest_index)) break;
+        }
+        idx += per_xcd;
+        parts = rest_index >= 0 ? sp.s2 : 1;
+        row0 = tm * LM_BM;
+        col0 = tn * LM_BN;
+        int t = tid;  // opaque: what follows from it is computed again for each item, not kept in registers
+        asm volatile("" : "+v"(t));
+#pragma unroll
+        for (int i = 0; i < LM_LPT; ++i) {
+            const int c = i * LM_THREADS + t;
+            const int r = c / LM_CPR, pc = c % LM_CPR;
+            const int lc = pc ^ ((r >> 1) & (LM_CPR - 1));
+            const int ra = min(row0 + r, M - 1) - row0;
+            const int rb = min(col0 + r, p.N - 1) - col0;
+            // K-major operand: the tile is [64 k rows][256 m]; chunk c is k row c / 32 at position c % 32 and holds
+            // logical chunk (c % 32) ^ lm_km_swizzle(k row); chunks past the end of the operand's k row re-read
+            // its last chunk (they belong to rows or columns of C that are never stored)
+            const int kk = c >> 5, lck = (c & 31) ^ lm_km_swizzle(kk);
+            if constexpr (AKM) {
+                const int ch = min((row0 >> 3) + lck, (p.a_cols >> 3) - 1) - (row0 >> 3);
+                a_off[i] = (unsigned)((long long)kk * p.lda * 2 + ch * 16);
+            } else {
+                a_off[i] = (unsigned)(((long long)ra * p.lda + lc * 8) * 2);
+            }
+            if constexpr (BKM) {
+                const int ch = min((col0 >> 3) + lck, (p.b_cols >> 3) - 1) - (col0 >> 3);
+                b_off[i] = (unsigned)((long long)kk * p.ldb * 2 + ch * 16);
+            } else {
+                b_off[i] = (unsigned)(((long long)rb * p.ldb + lc * 8) * 2);
+            }
+        }
+        kt0 = (int)((long long)(K / LM_BK) * part / parts);
+        KT = (int)((long long)(K / LM_BK) * (part + 1) / parts) - kt0;
+        a_tile = AKM ? (const char *)p.A + ((long long)kt0 * LM_BK * p.lda + row0) * 2
+                     : (const char *)p.A + ((long long)(chunk_base + row0) * p.lda + (long long)kt0 * LM_BK) * 2;
+        b_tile = BKM ? (const char *)p.B + ((long long)kt0 * LM_BK * p.ldb + col0) * 2
+                     : (const char *)p.B + ((long long)col0 * p.ldb + (long long)kt0 * LM_BK) * 2;
+        return true;
+    };
+    if (!next_item()) return;  // before any barrier
 
     // LDS is a ring of five 32 KB slots that operand tiles pass through in the order
     // A(0), B(0), A(1), B(1), ...: entry q = 2 kt + (0 for A, 1 for B) lives in slot q % 5.
@@ -323,8 +321,6 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     // vector register, the K position a scalar one, the LDS address goes through M0 - no
     // vector arithmetic per load.  The range check of the buffer is left wide open (rows are
     // clamped above and K steps below, so every address is inside the operand).
-    const __amdgpu_buffer_rsrc_t a_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)a_tile, 0, -1, 0x00020000);
-    const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)b_tile, 0, -1, 0x00020000);
     // A K-major operand moves by whole k rows from step to step, further than a 32-bit offset reaches:
     // its descriptor is made again for every step (scalar arithmetic).
     auto issue_half = [&](int q, bool b_operand, int half) {
@@ -345,9 +341,11 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             return;
         }
         const int k0 = kt * (LM_BK * 2);
+        const __amdgpu_buffer_rsrc_t rsrc =
+            __builtin_amdgcn_make_buffer_rsrc((void *)(b_operand ? b_tile : a_tile), 0, -1, 0x00020000);
 #pragma unroll
         for (int i = half * (LM_LPT / 2); i < (half + 1) * (LM_LPT / 2); ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_operand ? b_rsrc : a_rsrc,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc,
                                                      (__attribute__((address_space(3))) void *)(sd + i * (LM_THREADS * 16)),
                                                      16, (int)(b_operand ? b_off[i] : a_off[i]), k0, 0, 0);
     };
@@ -396,12 +394,6 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     static_assert(4 * (LM_BM * 2) == 2048, "the second read's offset is written into the assembly");
 
     f32x16 acc[LM_FA][LM_FB];
-#pragma unroll
-    for (int i = 0; i < LM_FA; ++i)
-#pragma unroll
-        for (int j = 0; j < LM_FB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     // Fragments are double buffered in registers (F[0], F[1]) and read one k-step ahead of
     // the products that use them.  One barrier per tile, before its last k-step: by then
@@ -451,61 +443,38 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
         __builtin_amdgcn_sched_group_barrier(0x008, LM_FA * LM_FB - LM_LPT, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
+    auto interleave_reads = [&]() {  // a k-step that issues no loads
+        __builtin_amdgcn_sched_group_barrier(0x100, (AKM ? 2 : 1) * LM_FA + (BKM ? 2 : 1) * LM_FB, 0);
+        __builtin_amdgcn_sched_group_barrier(0x008, LM_FA * LM_FB, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     static_assert(LM_BM == 256 && LM_BN == 256, "K-major tiles: 32 chunks per k row");
     static_assert(LM_BK / 16 == 4 && LM_SLOTS == 5 && LM_LPT == 4 && LM_FA * LM_FB >= LM_LPT,
                   "the pipeline and its wait counts are written for 4 k-steps, 5 slots, 4 loads per operand tile");
 
-    // Memory loads return in order, so "at most n outstanding" means that everything older
-    // than the n youngest loads is in LDS.  The wait, the wait for the own LDS reads and the
-    // workgroup barrier are one asm statement so that nothing is scheduled in between.
-    if (KT > 0) {
-    issue_half(0, false, 0);
-    issue_half(0, false, 1);
-    issue_half(1, true, 0);
-    issue_half(1, true, 1);
-    issue_half(2, false, 0);
-    issue_half(2, false, 1);
-    issue_half(3, true, 0);
-    asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // A(0), B(0) are there
-    read_frags(F[0], 0, 0);
-    for (int kt = 0; kt < KT; ++kt) {
-        lds_landed();
-        read_frags(F[1], kt, 1);
-        products(F[0]);
-        issue_half(2 * kt + 3, true, 1);   // rest of B(kt + 1)
-        interleave();
-        lds_landed();
-        read_frags(F[0], kt, 2);
-        products(F[1]);
-        issue_half(2 * kt + 4, false, 0);  // A(kt + 2)
-        interleave();
-        lds_landed();
-        read_frags(F[1], kt, 3);
-        products(F[0]);
-        issue_half(2 * kt + 4, false, 1);
-        interleave();
-        // outstanding, oldest first: ..., B(kt + 1), A(kt + 2): 4 left = tile kt + 1 landed
-        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        lds_landed();
-        read_frags(F[0], kt + 1, 0);
-        products(F[1]);
-        issue_half(2 * kt + 5, true, 0);   // B(kt + 2) into the slot A(kt) just left
-        interleave();
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }  // KT > 0
-
+    // Stores one item's result from the accumulators (see the softmax epilogue for LM_EPI_LSE).
+    auto store_item = [&](const int row0, const int col0, const int part, const int parts, const int rest_index)
+        __attribute__((always_inline)) {
     // Accumulator layout of a 32 x 32 block: lane l holds column l % 32; register v holds
     // row 8 (v / 4) + 4 (l / 32) + v % 4.
-    const int cl = lane & 31, g = lane >> 5;
+    int ln = lane;  // opaque, as above
+    asm volatile("" : "+v"(ln));
+    const int cl = ln & 31, g = ln >> 5;
     const int wrow = wm * (LM_FA * 32), wcol = wn * (LM_FB * 32);
     // Where a wavefront's part lies inside the matrix whole - every part but those of the last tile row:
     // N is a multiple of 64 here, so a part's 64 columns are all inside or all outside - its stores need no
     // checks: a scalar address per row and one 32-bit offset per lane.  With a row and a column test, a 64-bit
-    // address and a branch for each of 128 stores the epilogue was bound by its 2200 instructions a wavefront
-    // (FIGURES).
+    // address and a branch for each of 128 stores an epilogue was 2200 instructions a wavefront (dL/dH of
+    // 450 x 12000 x 1152, all of it parts: 44 us, now 30).
+    // The next item's loads are in flight meanwhile: they have landed when no more operations are outstanding
+    // than the stores issued since (the counter ends at 63).
+    auto loads_landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    auto loads_landed_behind_64_stores = [&]() { asm volatile("s_waitcnt vmcnt(63)" ::: "memory"); };
     if constexpr (EPI == LM_EPI_F32) {
-        if (col0 + wcol >= p.N) return;
+        if (col0 + wcol >= p.N) {
+            loads_landed();
+            return;
+        }
         const bool whole = row0 + wrow + LM_FA * 32 <= M && col0 + wcol + LM_FB * 32 <= p.N && p.ldc < (1ll << 28);
         if (whole) {
             char *cw = (char *)p.C + ((long long)(row0 + wrow) * p.ldc + col0 + wcol) * 4;
@@ -532,7 +501,10 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 for (int v = 0; v < 16; ++v)
 #pragma unroll
                     for (int j = 0; j < LM_FB; ++j)
-                        *(float *)(cw + (i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 128 + voff) = old[v][j] + acc[i][j][v];
+                        __builtin_nontemporal_store(
+                            old[v][j] + acc[i][j][v],
+                            (float *)(cw + (i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 128 + voff));
+                if (i == 1) loads_landed_behind_64_stores();
             }
             return;
         }
@@ -550,6 +522,7 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                     *at = p.accumulate ? *at + acc[i][j][v] : acc[i][j][v];
                 }
             }
+        loads_landed();
         return;
     }
     if constexpr (EPI == LM_EPI_BF16) {
@@ -558,12 +531,14 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             char *bw = (char *)(p.split_ws + (((long long)rest_index * parts + part) << 16) + wrow * LM_BN + wcol);
             const unsigned voff = (unsigned)((4 * g * LM_BN + cl) * 4);
 #pragma unroll
-            for (int i = 0; i < LM_FA; ++i)
+            for (int i = 0; i < LM_FA; ++i) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
 #pragma unroll
                     for (int j = 0; j < LM_FB; ++j)
                         *(float *)(bw + ((i * 32 + 8 * (v >> 2) + (v & 3)) * LM_BN + j * 32) * 4 + voff) = acc[i][j][v];
+                if (i == 1) loads_landed_behind_64_stores();
+            }
             return;
         }
 #pragma unroll
@@ -579,6 +554,7 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                     if (col < p.N) ((__bf16 *)p.C)[orow * p.ldc + col] = (__bf16)acc[i][j][v];
                 }
             }
+        loads_landed();
         return;
     }
 
@@ -708,10 +684,110 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                     if constexpr (AUX) ws = fmaf(f, fmaf(d, sw, red_w[w * LM_BM + tid]), ws);
                 }
             }
-            p.part_m[(long long)tn * p.part_stride + row] = m;
-            p.part_s[(long long)tn * p.part_stride + row] = s;
-            if constexpr (AUX) p.part_w[(long long)tn * p.part_stride + row] = ws;
+            p.part_m[(long long)(col0 / LM_BN) * p.part_stride + row] = m;
+            p.part_s[(long long)(col0 / LM_BN) * p.part_stride + row] = s;
+            if constexpr (AUX) p.part_w[(long long)(col0 / LM_BN) * p.part_stride + row] = ws;
         }
+    }
+    };
+
+    // Memory operations retire in order, so "at most n outstanding" means that everything older
+    // than the n youngest is done.  The wait, the wait for the own LDS reads and the
+    // workgroup barrier are one asm statement so that nothing is scheduled in between.
+    //
+    // All five slots are filled before an item's first k-step: A(0), B(0), A(1), B(1), A(2).  For the items
+    // after the first that happens in front of the stores of the item before (except behind the softmax
+    // epilogue, which needs the LDS itself): the loads' latency passes under the stores, and the stores drain
+    // under the first two steps - step 0 issues and waits for nothing, step 1 waits for A(2) and for B(2), which
+    // is the first load behind the stores.
+    auto prologue = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < LM_SLOTS; ++q) {
+            issue_half(q, q & 1, 0);
+            issue_half(q, q & 1, 1);
+        }
+        asm volatile("" ::: "memory");  // what follows stays behind these loads: the waits count on it
+    };
+    if (KT > 0) prologue();
+    bool fresh = true;  // the loads of the five slots are the youngest operations, and none has been waited for
+
+    for (;;) {
+#pragma unroll
+    for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+        for (int j = 0; j < LM_FB; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    if (KT > 0) {
+        // every wavefront waits for its own loads (all five slots have landed unless they are fresh)
+        if (fresh) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");  // A(0), B(0)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        read_frags(F[0], 0, 0);
+        {   // step 0
+            lds_landed();
+            read_frags(F[1], 0, 1);
+            products(F[0]);
+            interleave_reads();
+            lds_landed();
+            read_frags(F[0], 0, 2);
+            products(F[1]);
+            interleave_reads();
+            lds_landed();
+            read_frags(F[1], 0, 3);
+            products(F[0]);
+            interleave_reads();
+            if (fresh) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // A(1), B(1)
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // A(0), B(0) are read
+            lds_landed();
+            read_frags(F[0], 1, 0);
+            products(F[1]);
+            issue_half(5, true, 0);  // B(2) into the slot A(0) just left
+            interleave();
+        }
+        for (int kt = 1; kt < KT; ++kt) {
+            lds_landed();
+            read_frags(F[1], kt, 1);
+            products(F[0]);
+            issue_half(2 * kt + 3, true, 1);   // rest of B(kt + 1)
+            interleave();
+            lds_landed();
+            read_frags(F[0], kt, 2);
+            products(F[1]);
+            issue_half(2 * kt + 4, false, 0);  // A(kt + 2)
+            interleave();
+            lds_landed();
+            read_frags(F[1], kt, 3);
+            products(F[0]);
+            issue_half(2 * kt + 4, false, 1);
+            interleave();
+            // outstanding, oldest first: ..., B(kt + 1), A(kt + 2): 4 left = tile kt + 1 landed
+            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            lds_landed();
+            read_frags(F[0], kt + 1, 0);
+            products(F[1]);
+            issue_half(2 * kt + 5, true, 0);   // B(kt + 2) into the slot A(kt) just left
+            interleave();
+        }
+        // the last steps' loads (of the last tile again) and everybody's reads of the slots are done
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }  // KT > 0
+
+    const int row0_c = row0, col0_c = col0, part_c = part, parts_c = parts, rest_c = rest_index;  // the item being stored
+    bool more = false;
+    fresh = EPI == LM_EPI_LSE;
+    if constexpr (EPI != LM_EPI_LSE) {
+        more = next_item();
+        if (more && KT > 0) prologue();
+    }
+    store_item(row0_c, col0_c, part_c, parts_c, rest_c);
+    if constexpr (EPI == LM_EPI_LSE) {
+        more = next_item();
+        if (more) {
+            __syncthreads();  // the staging area is free
+            if (KT > 0) prologue();
+        }
+    }
+    if (!more) return;
     }
 }
 
@@ -1086,10 +1162,10 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
     }
     p.tiles_n = (p.N + LM_BN - 1) / LM_BN;
     if (p.group_m <= 0) p.group_m = LM_GROUP_M;
-    const int tiles_m = (p.M + LM_BM - 1) / LM_BM;
-    const long long grid = EPI == LM_EPI_BF16 && p.split_items > 0
-                               ? lm_split_grid(tiles_m, p.tiles_n, p.K / LM_BK, p.split_items, p.n_cu > 0 ? p.n_cu : 256)
-                               : ((long long)tiles_m * p.tiles_n + 7) / 8 * 8;
+    // One workgroup for each CU, on whole XCDs; fewer when there cannot be as many tiles.
+    p.n_cu = cu_count();
+    const long long most = EPI == LM_EPI_BF16 && p.split_items > 0 ? p.n_cu : (long long)((p.M + LM_BM - 1) / LM_BM) * p.tiles_n;
+    const long long grid = std::max<long long>(8, std::min<long long>(p.n_cu / 8, (most + 7) / 8) * 8);
     hipLaunchKernelGGL((lm_gemm_nt<EPI, STORE_Z, AUX, AKM, BKM>), dim3((unsigned)grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
     return hipGetLastError();
 }
@@ -1386,7 +1462,6 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             const size_t z_blocks = (size_t)cap * (size_t)L.ldz * 4 / ((size_t)LM_BM * LM_BN * 4);
             gh.split_items = (int)(z_blocks < 0x7fffffffu ? z_blocks : 0x7fffffffu);
             gh.split_ws = (float *)(ws + L.Z);
-            gh.n_cu = n_cu;
             e = lm_launch_gemm<LM_EPI_BF16, false, false, false, true>(gh, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
             if (gh.split_items > 0)
