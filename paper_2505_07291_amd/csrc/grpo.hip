@@ -937,6 +937,11 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
 #pragma unroll
     for (int i = 0; i < NV; ++i) buf[i] = neg_inf_vec<DT>();
     float zy = 0.f, tz = -INFINITY;
+    // The streamed remainder of the next row, up to 128 KB of it, is brought into L2 with the row's other
+    // loads, one lane to a 128-byte line; its two reads, each a few loads at a time behind everything that is
+    // in flight, then come from there (2048 x 152064 fp32 step, 67 KB of remainder a row: 397 -> 378 us).
+    constexpr int REM_PF = REM ? 2 : 1;
+    unsigned pf[REM_PF] = {};
 
     // The lane's number and byte offset as the slot loops use them.  In the instantiations with
     // LDS-resident slots they are made opaque at every use: otherwise the compiler keeps the
@@ -997,6 +1002,13 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     auto fetch_rest = [&](const char *zrow, long long y) {
         if (ragged && tid < tail) tz = load_elem<DT>(zrow, (long long)nvec_full * EPV + tid);
         zy = load_elem<DT>(zrow, y);
+        if constexpr (REM) {
+#pragma unroll
+            for (int i = 0; i < REM_PF; ++i) {
+                const unsigned off = (unsigned)(NV + NL) * SLAB + (unsigned)(i * BLOCK + tid) * 128u;
+                pf[i] = off < (unsigned)nvec_full * 16u ? *(const unsigned *)(zrow + off) : 0u;
+            }
+        }
     };
 
     long long y = 0, y_next = 0;
@@ -1046,17 +1058,19 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             }
         }
         if (ragged) mx = fmaxf(mx, tz);
-        // the part of the row that is not resident: online statistics, first read
+        // the part of the row that is not resident: online statistics, first read (kept in the caches)
         const char *zrow_cur = (const char *)p.logits + row * p.row_stride * BYTES;
         float rem_m = -INFINITY, rem_s = 0.f, rem_w = 0.f;
         if constexpr (REM) {
+#pragma unroll
+            for (int i = 0; i < REM_PF; ++i) asm volatile("" ::"v"(pf[i]));  // landed with the row; its value is not needed
             for (int base = (NV + NL) * BLOCK; base < nvec_full; base += RU * BLOCK) {
                 u32x4 z[RU];
 #pragma unroll
                 for (int u = 0; u < RU; ++u) {
                     const int v = base + u * BLOCK + tid;
                     z[u] = neg_inf_vec<DT>();
-                    if (v < nvec_full) z[u] = ld16(zrow_cur + (size_t)v * 16);
+                    if (v < nvec_full) z[u] = *(const u32x4 *)(zrow_cur + (size_t)v * 16);
                 }
 #pragma unroll
                 for (int u = 0; u < RU; ++u) {
