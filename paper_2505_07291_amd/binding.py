@@ -107,13 +107,18 @@ def grpo_row_kernel_plan(dtype: int, vocab: int) -> dict:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+def _raw_stream(stream, device_index=None):
+    """The hipStream_t of `stream`, or of the current stream (of the given or the current device).  The current
+    one is asked for as a number: making torch's Stream object around it takes 2.6 us, a third of what a
+    small call spends on the host."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device_index is None else device_index)
+
+
 
 
 def _check(t, dtype, n, name, device):
@@ -163,7 +168,7 @@ def grpo_group_advantages(rewards, group_size=None, group_offsets=None, eps_std=
     rc = lib().grpo_group_advantages(_ptr(rewards), R, _ptr(group_offsets), n_groups, gs,
                                      float(eps_std), int(ddof), _ptr(adv_out),
                                      _ptr(rollout_of_token), n_tok, _ptr(adv_tok_out),
-                                     _stream(stream))
+                                     _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_group_advantages")
     return adv_out, adv_tok_out
@@ -176,9 +181,8 @@ def _queue_workspace(device, stream):
     """The small workspace grpo_logprobs_fwd's row queue lives in, one per device and stream, made
     on first use and kept: calls on one stream run one after the other, so they can share it, and
     the call does not allocate again (calls on different streams may overlap and must not)."""
-    if stream is None:
-        stream = torch.cuda.current_stream(device)
-    key = (device.index if device.index is not None else torch.cuda.current_device(), stream.cuda_stream)
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    key = (index, _raw_stream(stream, index))
     ws = _queue_workspaces.get(key)
     if ws is None:
         ws = torch.empty(grpo_workspace_bytes(0), dtype=torch.uint8, device=device)
@@ -203,7 +207,7 @@ def grpo_logprobs_fwd(logits, tokens, mask=None, temperature=1.0, vocab=None, lo
         workspace = _queue_workspace(dev, stream)
     rc = lib().grpo_logprobs_fwd(_ptr(logits), dt, n, v, stride, _ptr(tokens), _ptr(mask),
                                  float(temperature), _ptr(logprobs_out), _ptr(workspace),
-                                 0 if workspace is None else workspace.numel(), _stream(stream))
+                                 0 if workspace is None else workspace.numel(), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_logprobs_fwd")
     return logprobs_out
@@ -246,7 +250,7 @@ def grpo_loss_fwd_bwd(logits, tokens, old_logprobs, advantages, mask=None, eps_l
                                  float(delta), float(temperature), float(denom), float(grad_scale),
                                  _ptr(loss_out), _ptr(logprobs_out), _ptr(counts_out),
                                  _ptr(grad_logits), _ptr(workspace), workspace.numel(),
-                                 _stream(stream))
+                                 _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_loss_fwd_bwd")
     return loss_out, logprobs_out, counts_out, grad_logits
@@ -282,7 +286,7 @@ def grpo_loss_fwd_bwd_noalloc(logits, tokens, old_logprobs, advantages, mask, ep
                                          _ptr(advantages), _ptr(mask), float(eps_low), float(eps_high),
                                          float(delta), float(temperature), float(denom), float(grad_scale),
                                          _ptr(loss_out), _ptr(logprobs_out), _ptr(counts_out),
-                                         _ptr(grad_logits), _ptr(error_out), _stream(stream))
+                                         _ptr(grad_logits), _ptr(error_out), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_loss_fwd_bwd_noalloc")
 
@@ -331,7 +335,7 @@ def grpo_loss_aux_fwd_bwd(logits, tokens, old_logprobs, ref_logprobs, advantages
         float(delta), float(temperature), float(kl_coef), float(entropy_coef), float(denom),
         float(grad_scale),
         _ptr(loss_out), _ptr(logprobs_out), _ptr(entropy_out), _ptr(counts_out), _ptr(grad_logits),
-        _ptr(workspace), workspace.numel(), _stream(stream))
+        _ptr(workspace), workspace.numel(), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_loss_aux_fwd_bwd")
     return loss_out, logprobs_out, entropy_out, counts_out, grad_logits
@@ -347,7 +351,7 @@ def grpo_total_rewards(task_rewards, lengths, target_lengths, alpha, rewards_out
     if rewards_out is None:
         rewards_out = torch.empty(R, dtype=torch.float32, device=dev)
     rc = lib().grpo_total_rewards(_ptr(task_rewards), _ptr(lengths), _ptr(target_lengths), R,
-                                  float(alpha), _ptr(rewards_out), _stream(stream))
+                                  float(alpha), _ptr(rewards_out), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_total_rewards")
     return rewards_out
@@ -371,7 +375,7 @@ def grpo_filter_groups(rewards, group_size=None, group_offsets=None, stream=None
     # groups of one size own every rollout; with offsets some may belong to none and keep their 0
     rk = (torch.empty if group_offsets is None else torch.zeros)(R, dtype=torch.uint8, device=dev)
     rc = lib().grpo_filter_groups(_ptr(rewards), R, _ptr(group_offsets), n_groups, gs, _ptr(keep),
-                                  _ptr(kept), _ptr(n_kept), _ptr(rk), _stream(stream))
+                                  _ptr(kept), _ptr(n_kept), _ptr(rk), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_filter_groups")
     return keep, kept, n_kept, rk
@@ -389,7 +393,7 @@ def grpo_packed_layout(cu_seqlens, n_tokens, sample_level, weights_out=None, rol
         rollout_of_token_out = torch.empty(n_tokens, dtype=torch.int32, device=dev)
     rc = lib().grpo_packed_layout(_ptr(cu_seqlens), cu_seqlens.shape[0] - 1, int(n_tokens),
                                   1 if sample_level else 0, _ptr(weights_out),
-                                  _ptr(rollout_of_token_out), _stream(stream))
+                                  _ptr(rollout_of_token_out), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_packed_layout")
     return weights_out, rollout_of_token_out
@@ -397,7 +401,7 @@ def grpo_packed_layout(cu_seqlens, n_tokens, sample_level, weights_out=None, rol
 
 def grpo_workspace_error(workspace, stream=None) -> int:
     flag = ctypes.c_int32(0)
-    rc = lib().grpo_workspace_error(_ptr(workspace), ctypes.byref(flag), _stream(stream))
+    rc = lib().grpo_workspace_error(_ptr(workspace), ctypes.byref(flag), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_workspace_error")
     return int(flag.value)
@@ -442,7 +446,7 @@ def grpo_lmhead_logprobs_fwd(hidden, weight, tokens, mask=None, temperature=1.0,
         workspace = torch.empty(grpo_lmhead_workspace_bytes(n, v, d, False), dtype=torch.uint8, device=dev)
     rc = lib().grpo_lmhead_logprobs_fwd(_ptr(hidden), hs, _ptr(weight), ws, n, v, d, _ptr(tokens),
                                         _ptr(mask), float(temperature), _ptr(logprobs_out),
-                                        _ptr(workspace), workspace.numel(), _stream(stream))
+                                        _ptr(workspace), workspace.numel(), _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_lmhead_logprobs_fwd")
     return logprobs_out
@@ -488,7 +492,7 @@ def grpo_lmhead_loss_fwd_bwd(hidden, weight, tokens, old_logprobs, advantages, m
         _ptr(mask), float(eps_low), float(eps_high), float(delta), float(temperature), float(denom),
         float(grad_scale), _ptr(loss_out), _ptr(logprobs_out), _ptr(counts_out), _ptr(grad_hidden), ghs,
         _ptr(grad_weight), gws, 1 if accumulate_grad_weight else 0, _ptr(workspace), workspace.numel(),
-        _stream(stream))
+        _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_lmhead_loss_fwd_bwd")
     return loss_out, logprobs_out, counts_out, grad_hidden, grad_weight
@@ -543,7 +547,7 @@ def grpo_lmhead_loss_aux_fwd_bwd(hidden, weight, tokens, old_logprobs, ref_logpr
         float(temperature), float(kl_coef), float(entropy_coef), float(denom), float(grad_scale),
         _ptr(loss_out), _ptr(logprobs_out), _ptr(entropy_out), _ptr(counts_out), _ptr(grad_hidden), ghs,
         _ptr(grad_weight), gws, 1 if accumulate_grad_weight else 0, _ptr(workspace), workspace.numel(),
-        _stream(stream))
+        _raw_stream(stream))
     if rc != GRPO_OK:
         raise GrpoError(rc, "grpo_lmhead_loss_aux_fwd_bwd")
     return loss_out, logprobs_out, entropy_out, counts_out, grad_hidden, grad_weight
