@@ -877,6 +877,98 @@ __global__ void __launch_bounds__(1024) lm_select_rows(RowParams p, LmRows w)
     if (threadIdx.x == 0) *w.n_live = total;
 }
 
+// The same for up to LM_TAKE_MAX tokens, with everything else that happens per row before the first
+// product: the hidden states of the rows that take part are copied side by side, and with the backward
+// dL/dH is zeroed (rows without gradient keep that) and the header set as grpo_prepare sets it.  A
+// workgroup takes 16 rows and counts the rows ahead of its own itself, 9 bytes a row from the caches: more
+// reading than one workgroup walking through the batch, but no step waits for another (724 rows: four
+// launches of 12 us together, now one of 6; 4096 rows of 5120 values: 53 us before).  Beyond the limit the repeated counting, which
+// grows with the square of the batch, would cost more than the walk.
+constexpr int LM_TAKE_ROWS = 16, LM_TAKE_THREADS = 512;
+constexpr long long LM_TAKE_MAX = 32768;
+__global__ void __launch_bounds__(LM_TAKE_THREADS) lm_take_rows(RowParams p, LmRows w, const __bf16 *hidden, long long ldh,
+                                                                int d, __bf16 *out, unsigned short *grad_hidden,
+                                                                long long ldgh, double denom, WsHeader *hdr)
+{
+    __shared__ int lds_live[LM_TAKE_THREADS / 64], lds_mask[LM_TAKE_THREADS / 64], lds_pos[LM_TAKE_ROWS];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const long long r0 = (long long)blockIdx.x * LM_TAKE_ROWS;
+    // bit 0: takes part; bit 1: counts towards M (a bad token id does, see grpo_loss_fwd_bwd)
+    auto state_of = [&](long long r) -> int {
+        const bool on = (!p.mask || p.mask[r] != 0) && (!p.token_w || p.token_w[r] != 0.f);
+        if (!on) return 0;
+        const long long y = p.tokens[r];
+        return y >= 0 && y < p.vocab ? 3 : 2;
+    };
+    int live_before = 0, mask_before = 0;
+#pragma unroll 4
+    for (long long r = tid; r < r0; r += LM_TAKE_THREADS) {
+        const int st = state_of(r);
+        live_before += st & 1;
+        mask_before += st >> 1;
+    }
+    live_before = wave_sum(live_before);
+    mask_before = wave_sum(mask_before);
+    if (lane == 0) {
+        lds_live[wv] = live_before;
+        lds_mask[wv] = mask_before;
+    }
+    const long long r = r0 + lane;
+    const int st = (wv == 0 && lane < LM_TAKE_ROWS && r < p.n_tokens) ? state_of(r) : 0;
+    __syncthreads();
+    int before = 0, mask_all = 0;
+#pragma unroll
+    for (int i = 0; i < LM_TAKE_THREADS / 64; ++i) {
+        before += lds_live[i];
+        mask_all += lds_mask[i];
+    }
+    if (wv == 0) {
+        const unsigned long long live = __ballot(st & 1), masked = __ballot(st >> 1);
+        const int pos = before + __popcll(live & ((1ull << lane) - 1ull));
+        if (lane < LM_TAKE_ROWS) lds_pos[lane] = (st & 1) ? pos : -1;
+        if (st & 1) {
+            w.rows[pos] = (int)r;
+            w.tokens32[pos] = (int)p.tokens[r];
+        } else if (lane < LM_TAKE_ROWS && r < p.n_tokens) {
+            write_row_outputs(p, r, (st == 2 && !p.bwd) ? NAN : 0.f, 0.f, 0);
+            write_row_aux(p, r, 0.f, 0.f);
+        }
+        if (lane == 0 && blockIdx.x == gridDim.x - 1) {
+            const int n_live = before + __popcll(live);
+            *w.n_live = n_live;
+            if (hdr) {
+                const long long M = mask_all + __popcll(masked);
+                const double D = denom > 0.0 ? denom : (double)M;
+                hdr->D = D;
+                hdr->inv_D = D > 0.0 ? 1.0 / D : 0.0;
+                hdr->M = M;
+                hdr->error = M != n_live ? 1 : 0;  // some unmasked row has a bad token id
+                hdr->fin_ticket = 0u;
+            }
+        }
+    }
+    __syncthreads();
+    const int rows_here = (int)(p.n_tokens - r0 < LM_TAKE_ROWS ? p.n_tokens - r0 : LM_TAKE_ROWS);
+    for (int i = wv; i < rows_here; i += LM_TAKE_THREADS / 64) {  // a wavefront to a row
+        const int pos = __builtin_amdgcn_readfirstlane(lds_pos[i]);
+        if (pos >= 0) {
+            const u32x4 *src = (const u32x4 *)(hidden + (r0 + i) * ldh);
+            u32x4 *dst = (u32x4 *)(out + (long long)pos * d);
+#pragma unroll 4
+            for (int c = lane; c < d / 8; c += 64) dst[c] = src[c];
+        }
+        if (grad_hidden) {
+            unsigned short *row = grad_hidden + (r0 + i) * ldgh;
+            const u32x4 z = {0u, 0u, 0u, 0u};
+            if ((((unsigned long long)grad_hidden | (unsigned long long)(ldgh * 2)) & 15u) == 0) {  // d is a multiple of 64
+                for (int c = lane; c < d / 8; c += 64) *(u32x4 *)(row + c * 8) = z;
+            } else {
+                for (int c = lane; c < d; c += 64) row[c] = 0;
+            }
+        }
+    }
+}
+
 // Compact rows of the current chunk with a gradient -> rows2[] (compact row), orig2[] (original
 // row), *n_grad.
 __global__ void __launch_bounds__(1024) lm_select_grad_rows(LmRows w)
@@ -1006,11 +1098,57 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
 // (two 16-byte reads, one 16-byte write); a workgroup 16 rows of them.  Padding is written as zeros: the
 // columns V .. ldg (dL/dH runs over whole K steps of the vocabulary) and the rows n_grad .. the next
 // multiple of 64 (dL/dW runs over whole K steps of rows).
+// out[c][r] = in[rowmap ? rowmap[r] : r][c] for r < R (R = *R_dev when given), c < C; the
+// columns R .. ldo of out are zero-filled.  64 x 64 tiles through LDS, four consecutive
+// elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
+// 8-byte aligned (the operands of this path: d_model is a multiple of 64, rows 16-byte aligned).
+__device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *in, long long ldi, int R, const int *rowmap,
+                                                  int C, __bf16 *out, long long ldo)
+{
+    __shared__ unsigned short tile[64][66];
+    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;  // 16 lanes x 4 elements across, 16 down
+    const unsigned short *src = (const unsigned short *)in;
+    unsigned short *dst = (unsigned short *)out;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int rl = ty + 16 * i, r = r0 + rl, c = c0 + tx * 4;
+        unsigned lo = 0, hi = 0;
+        if (r < R && c < C) {
+            const unsigned *q = (const unsigned *)(src + (long long)(rowmap ? rowmap[r] : r) * ldi + c);
+            lo = q[0];
+            hi = q[1];
+        }
+        tile[rl][tx * 4 + 0] = (unsigned short)lo;
+        tile[rl][tx * 4 + 1] = (unsigned short)(lo >> 16);
+        tile[rl][tx * 4 + 2] = (unsigned short)hi;
+        tile[rl][tx * 4 + 3] = (unsigned short)(hi >> 16);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int cl2 = ty + 16 * i, c = c0 + cl2, r = r0 + tx * 4;  // a row of the output, four of its columns
+        if (c < C && r < ldo) {
+            unsigned *q = (unsigned *)(dst + (long long)c * ldo + r);
+            q[0] = (unsigned)tile[tx * 4][cl2] | ((unsigned)tile[tx * 4 + 1][cl2] << 16);
+            q[1] = (unsigned)tile[tx * 4 + 2][cl2] | ((unsigned)tile[tx * 4 + 3][cl2] << 16);
+        }
+    }
+}
+
 constexpr int LM_GL_COLS = 512, LM_GL_ROWS = 16;
 template <bool AUX>
 __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long ldz, int V, LmRows w,
-                                                      float k, __bf16 *G, long long ldg, int col_groups)
+                                                      float k, __bf16 *G, long long ldg, int col_groups, unsigned gl_blocks,
+                                                      const __bf16 *hidden, long long ldh, int d, __bf16 *Ht, long long ldht)
 {
+    if (blockIdx.x >= gl_blocks) {  // H^T of the chunk's gradient rows, [d][ldht]: independent of G, in the same launch
+        const int t = (int)(blockIdx.x - gl_blocks), across = (int)(ldht / 64);
+        const int n = *w.n_grad;
+        // columns past the rows that exist are read as zeros up to the next whole K step, and not at all beyond it
+        if (t % across * 64 < (n + 63) / 64 * 64)
+            lm_transpose_tile(t % across * 64, t / across * 64, hidden, ldh, n, w.orig2, d, Ht, ldht);
+        return;
+    }
     const int n2 = *w.n_grad, n2_pad = (n2 + 63) / 64 * 64;
     const int r0 = (int)(blockIdx.x / (unsigned)col_groups) * LM_GL_ROWS;
     if (r0 >= n2_pad) return;  // LM_GL_ROWS divides 64: a workgroup's rows are all inside or all outside
@@ -1060,46 +1198,6 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
         for (int e = 0; e < 4; ++e)
             out[e] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){gv[2 * e], gv[2 * e + 1]}, bf16x2));
         *(u32x4 *)(G + (long long)r * ldg + c) = out;
-    }
-}
-
-// out[c][r] = in[rowmap ? rowmap[r] : r][c] for r < R (R = *R_dev when given), c < C; the
-// columns R .. ldo of out are zero-filled.  64 x 64 tiles through LDS, four consecutive
-// elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
-// 8-byte aligned (the operands of this path: d_model is a multiple of 64, rows 16-byte aligned).
-__global__ void __launch_bounds__(256) lm_transpose(const __bf16 *in, long long ldi, int R, const int *R_dev,
-                                                    const int *rowmap, int C, __bf16 *out, long long ldo)
-{
-    __shared__ unsigned short tile[64][66];
-    if (R_dev) R = min(R, *R_dev);
-    // x walks the rows of `in` (the vocabulary for W: the y extent of a grid ends at 65535)
-    const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;  // 16 lanes x 4 elements across, 16 down
-    const unsigned short *src = (const unsigned short *)in;
-    unsigned short *dst = (unsigned short *)out;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int rl = ty + 16 * i, r = r0 + rl, c = c0 + tx * 4;
-        unsigned lo = 0, hi = 0;
-        if (r < R && c < C) {
-            const unsigned *q = (const unsigned *)(src + (long long)(rowmap ? rowmap[r] : r) * ldi + c);
-            lo = q[0];
-            hi = q[1];
-        }
-        tile[rl][tx * 4 + 0] = (unsigned short)lo;
-        tile[rl][tx * 4 + 1] = (unsigned short)(lo >> 16);
-        tile[rl][tx * 4 + 2] = (unsigned short)hi;
-        tile[rl][tx * 4 + 3] = (unsigned short)(hi >> 16);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int cl2 = ty + 16 * i, c = c0 + cl2, r = r0 + tx * 4;  // a row of the output, four of its columns
-        if (c < C && r < ldo) {
-            unsigned *q = (unsigned *)(dst + (long long)c * ldo + r);
-            q[0] = (unsigned)tile[tx * 4][cl2] | ((unsigned)tile[tx * 4 + 1][cl2] << 16);
-            q[1] = (unsigned)tile[tx * 4 + 2][cl2] | ((unsigned)tile[tx * 4 + 3][cl2] << 16);
-        }
     }
 }
 
@@ -1313,7 +1411,8 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
     unsigned char *flags_ws = (unsigned char *)(ws + kHeaderBytes + 3 * col);
     FinPartial *partials = (FinPartial *)(ws + kHeaderBytes + 3 * col + align_up((size_t)n_tokens, 256));
 
-    if (bwd)
+    const bool take = n_tokens > 0 && n_tokens <= LM_TAKE_MAX;
+    if (bwd && !take)
         hipLaunchKernelGGL(grpo_prepare, dim3(1), dim3(1024), 0, st, mask, aux ? token_weights : (const float *)nullptr,
                            (long long)n_tokens, denom, hdr, (int *)nullptr);
     if (n_tokens > 0) {
@@ -1375,19 +1474,25 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             p.ent_coef = entropy_coef;
         }
 
-        // rows that take part, and their hidden states side by side
+        // rows that take part, and their hidden states side by side; dL/dH zeroed (fill kernels rather than
+        // memsets, so that the call can be captured into a graph)
         __bf16 *Hc = (__bf16 *)(ws + L.Hc);
-        hipLaunchKernelGGL(lm_select_rows, dim3(1), dim3(1024), 0, st, p, w);
-        hipLaunchKernelGGL(lm_gather_rows, dim3((unsigned)(M < 8192 ? M : 8192)), dim3(256), 0, st,
-                           (const __bf16 *)hidden, (long long)hidden_stride, (const int *)w.rows,
-                           (const int *)w.n_live, D, Hc, (long long)d_model);
         __bf16 *G = nullptr, *Ht = nullptr;
         const int n_cu = cu_count();
-        if (bwd) {
-            G = (__bf16 *)(ws + L.G), Ht = (__bf16 *)(ws + L.Ht);
-            // rows without gradient keep the zeros written here
-            hipLaunchKernelGGL(lm_zero<unsigned short>, dim3(2048), dim3(256), 0, st, (unsigned short *)grad_hidden,
-                               (long long)n_tokens, (long long)d_model, (long long)grad_hidden_stride);
+        if (bwd) G = (__bf16 *)(ws + L.G), Ht = (__bf16 *)(ws + L.Ht);
+        if (take) {
+            hipLaunchKernelGGL(lm_take_rows, dim3((unsigned)((M + LM_TAKE_ROWS - 1) / LM_TAKE_ROWS)), dim3(LM_TAKE_THREADS), 0, st,
+                               p, w, (const __bf16 *)hidden, (long long)hidden_stride, D, Hc,
+                               bwd ? (unsigned short *)grad_hidden : (unsigned short *)nullptr, (long long)grad_hidden_stride,
+                               denom, bwd ? hdr : (WsHeader *)nullptr);
+        } else {
+            hipLaunchKernelGGL(lm_select_rows, dim3(1), dim3(1024), 0, st, p, w);
+            hipLaunchKernelGGL(lm_gather_rows, dim3((unsigned)(M < 8192 ? M : 8192)), dim3(256), 0, st,
+                               (const __bf16 *)hidden, (long long)hidden_stride, (const int *)w.rows,
+                               (const int *)w.n_live, D, Hc, (long long)d_model);
+            if (bwd)
+                hipLaunchKernelGGL(lm_zero<unsigned short>, dim3(2048), dim3(256), 0, st, (unsigned short *)grad_hidden,
+                                   (long long)n_tokens, (long long)d_model, (long long)grad_hidden_stride);
         }
 
         for (int c = 0; c < n_chunks; ++c) {
@@ -1429,17 +1534,11 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             hipLaunchKernelGGL(lm_select_grad_rows, dim3(1), dim3(1024), 0, st, w);
             const int gl_cols = (int)((L.ldg + LM_GL_COLS - 1) / LM_GL_COLS);
             // rows up to the next multiple of 64: the padding rows are written too (G has cap >= 256 rows)
-            const dim3 gl_grid((unsigned)((long long)gl_cols * ((Mc + 63) / 64 * (64 / LM_GL_ROWS))));
-            if (aux)
-                hipLaunchKernelGGL(lm_grad_logits<true>, gl_grid, dim3(256), 0, st, (const float *)(ws + L.Z), L.ldz,
-                                   V, w, k, G, L.ldg, gl_cols);
-            else
-                hipLaunchKernelGGL(lm_grad_logits<false>, gl_grid, dim3(256), 0, st, (const float *)(ws + L.Z), L.ldz,
-                                   V, w, k, G, L.ldg, gl_cols);
-            // H^T of the chunk's gradient rows [d][ldgt]
-            hipLaunchKernelGGL(lm_transpose, dim3((unsigned)(L.ldgt / 64), (unsigned)((D + 63) / 64)), dim3(256), 0,
-                               st, (const __bf16 *)hidden, (long long)hidden_stride, M, (const int *)w.n_grad,
-                               (const int *)w.orig2, D, Ht, L.ldgt);
+            const unsigned gl_blocks = (unsigned)((long long)gl_cols * ((Mc + 63) / 64 * (64 / LM_GL_ROWS)));
+            const dim3 gl_grid(gl_blocks + (unsigned)((L.ldgt / 64) * ((D + 63) / 64)));  // then the tiles of H^T
+            hipLaunchKernelGGL((aux ? lm_grad_logits<true> : lm_grad_logits<false>), gl_grid, dim3(256), 0, st,
+                               (const float *)(ws + L.Z), L.ldz, V, w, k, G, L.ldg, gl_cols, gl_blocks,
+                               (const __bf16 *)hidden, (long long)hidden_stride, D, Ht, L.ldgt);
 
             GemmParams gh = {};  // dL/dH [gradient rows][d] = G . W, scattered to the original rows; W is read as it
                                  // lies, [vocab][d]: K-major, its rows past the vocabulary read as zeros

@@ -4,6 +4,8 @@ comparison are those of the other shapes (run_shape_case)."""
 import numpy as np
 import pytest
 
+import paper_2505_07291_amd.workloads as wl
+from test_gpu_lmhead_parity import run_case
 from test_gpu_parity import run_shape_case
 
 pytestmark = pytest.mark.gpu
@@ -36,3 +38,19 @@ def test_narrow_rows_strided_and_queued(rows):
 def test_ragged_rows_around_the_resident_widths(dtype, epv, vectors):
     vocab = vectors * epv + 1
     run_shape_case(dtype, vocab, (vectors + 1) * epv, 300, grad_rows=sampled(300, vectors))
+
+
+# the head's rows are taken by one kernel up to 32768 tokens, by the walk and the gather beyond; groups
+# of 16 rows, the last one whole, of one row, and short of one
+@pytest.mark.parametrize("prompts,seq", [(1, 1), (2, 33), (8, 256), (8, 257)])
+def test_head_rows_taken_by_either_path(prompts, seq):
+    cfg = wl.CONFIGS["qwen_short"].scaled(n_prompts=prompts, seq_len=seq, vocab=40, group_size=16)
+    run_case(cfg, 64, label="N=%d" % cfg.n_tokens)
+
+
+# partials per row merged by 16 lanes (one, and all of their 192 tiles) and by 64 (one tile more, and more
+# tiles than their registers hold)
+@pytest.mark.parametrize("vocab", [256, 192 * 256, 192 * 256 + 1, 768 * 256 + 300])
+def test_head_partials_of_few_and_many_tiles(vocab):
+    cfg = wl.CONFIGS["qwen_short"].scaled(n_prompts=1, seq_len=5, vocab=vocab, group_size=4)
+    run_case(cfg, 64, label="V=%d" % vocab)
