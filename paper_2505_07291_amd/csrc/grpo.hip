@@ -610,10 +610,12 @@ __device__ __forceinline__ float exp_sum_vec_aux(u32x4 &z, float k, float mx, fl
 }
 
 // Gradient of one vector with the entropy term fused in: g_j = p_j (q2 + bq a'_j),
-// a'_j = (z_j - max) k - log2 s = log2 p_j.  Returns the packed vector.
+// a'_j = (z_j - max) k - log2 s = log2 p_j.  Returns the packed vector; the sampled token's element is
+// put in by the caller (put_elem), in one slot of one lane: selected at every element it cost one instruction in
+// ten of the gradient pass (8192 x 128256 packed step 630 -> 618 us).  Word by word as above (two and four
+// words between the fences, where the registers hold them: 630 and 641 us).
 template <grpo_dtype DT>
-__device__ __forceinline__ u32x4 grad_vec_aux(u32x4 &z, float k, float mx, float log2s, float q2,
-                                              float bq, bool has_y, int ey, float gy)
+__device__ __forceinline__ u32x4 grad_vec_aux(u32x4 &z, float k, float mx, float log2s, float q2, float bq)
 {
     constexpr int EPW = Elem<DT>::EPV / 4;
     u32x4 out;
@@ -627,11 +629,6 @@ __device__ __forceinline__ u32x4 grad_vec_aux(u32x4 &z, float k, float mx, float
             const float a = fmaxf(fmaf(f[e] - mx, k, -log2s), kExpFloor);
             g[e] = __builtin_amdgcn_exp2f(a) * fmaf(bq, a, q2);
         }
-        if (has_y) {
-#pragma unroll
-            for (int e = 0; e < EPW; ++e)
-                if (d * EPW + e == ey) g[e] = gy;
-        }
         if constexpr (DT == GRPO_BF16) {
             f32x2 pr = {g[0], g[1]};
             out[d] = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
@@ -641,6 +638,25 @@ __device__ __forceinline__ u32x4 grad_vec_aux(u32x4 &z, float k, float mx, float
         VECTOR_FENCE();
     }
     return out;
+}
+
+// Element e of a packed vector becomes x (rounded as the others are).
+template <grpo_dtype DT>
+__device__ __forceinline__ void put_elem(u32x4 &v, int e, float x)
+{
+    asm volatile("" : "+v"(x));  // keeps this behind a branch: it is for one lane of one slot
+    if constexpr (DT == GRPO_BF16) {
+        f32x2 pr = {x, x};
+        const unsigned xx = __builtin_bit_cast(unsigned, __builtin_convertvector(pr, bf16x2));
+        const unsigned keep = (e & 1) ? 0x0000ffffu : 0xffff0000u;
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            if (d == (e >> 1)) v[d] = (v[d] & keep) | (xx & ~keep);
+    } else {
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+            if (d == e) v[d] = as_u32(x);
+    }
 }
 
 // Gradient of one vector: g_j = -(c/T) p_j with p_j = exp2(z_j k - shift), and at
@@ -1169,7 +1185,8 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                             const int v = base + u * BLOCK + tid;
                             u32x4 packed;
                             if constexpr (AUX) {
-                                packed = grad_vec_aux<DT>(z[u], p.k, sc.mx, sc.log2s, sc.q2, sc.bq, v == vy, ey, gy);
+                                packed = grad_vec_aux<DT>(z[u], p.k, sc.mx, sc.log2s, sc.q2, sc.bq);
+                                if (v == vy) put_elem<DT>(packed, ey, gy);
                             } else {
                                 float g[EPV];
                                 grad_vec<DT>(z[u], p.k, sc.shift, q, v == vy, ey, gy, g);
@@ -1187,7 +1204,8 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                     forget(buf[i]);
                     u32x4 packed;
                     if constexpr (AUX) {
-                        packed = grad_vec_aux<DT>(buf[i], p.k, sc.mx, sc.log2s, sc.q2, sc.bq, v == vy, ey, gy);
+                        packed = grad_vec_aux<DT>(buf[i], p.k, sc.mx, sc.log2s, sc.q2, sc.bq);
+                        if (i == vy / BLOCK && v == vy) put_elem<DT>(packed, ey, gy);
                     } else {
                         float g[EPV];
                         grad_vec<DT>(buf[i], p.k, sc.shift, q, v == vy, ey, gy, g);
@@ -1208,7 +1226,8 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                     u32x4 z = lds_slot(j, -1, 0);
                     u32x4 packed;
                     if constexpr (AUX) {
-                        packed = grad_vec_aux<DT>(z, p.k, sc.mx, sc.log2s, sc.q2, sc.bq, v == vy, ey, gy);
+                        packed = grad_vec_aux<DT>(z, p.k, sc.mx, sc.log2s, sc.q2, sc.bq);
+                        if (NV + j == vy / BLOCK && v == vy) put_elem<DT>(packed, ey, gy);
                     } else {
                         float g[EPV];
                         grad_vec<DT>(z, p.k, sc.shift, q, v == vy, ey, gy, g);
@@ -1422,7 +1441,8 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
             const float gy = (sc.c * p.inv_T) * (sc.s_excl / sc.s) + (AUX ? sc.gy_ent : 0.f);
             auto grad_of = [&](u32x4 &z, bool has_y, int e) __attribute__((always_inline)) {
                 if constexpr (AUX) {
-                    z = grad_vec_aux<DT>(z, p.k, sc.mx, sc.log2s, sc.q2, sc.bq, has_y, e, gy);
+                    z = grad_vec_aux<DT>(z, p.k, sc.mx, sc.log2s, sc.q2, sc.bq);
+                    if (has_y) put_elem<DT>(z, e, gy);
                 } else {
                     float g[EPV];
                     grad_vec<DT>(z, p.k, sc.shift, q, has_y, e, gy, g);
