@@ -2084,8 +2084,10 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
     // row for each workgroup there is nothing to balance; narrow rows, which are queued several at a
     // time, leave workgroups without any until there are several chunks for each, and a workgroup
     // that finds the queue empty has asked all its counters in turn.  512 fp32 rows of 1024 entries
-    // (64 chunks of 8, 512 workgroups): 25 us through the queue, 5 us strided.
-    if (p.n_tokens <= grid || (p.queue_chunk > 1 && p.n_tokens <= 4 * grid)) p.queued = 0;
+    // (64 chunks of 8, 512 workgroups): 25 us through the queue, 5 us strided; a step on 16000 bf16 rows
+    // of 4000 (eight rounds) 84 us and 78.  With more rounds narrow rows still gain (32000 such rows 77 and 70)
+    // but those near 32 KB lose (10000 fp32 rows of 7001, ten rounds: 118 and 129).
+    if (p.n_tokens <= grid || (p.queue_chunk > 1 && p.n_tokens <= 8 * grid)) p.queued = 0;
     if (grid > p.n_tokens) grid = p.n_tokens;
     // dynamic LDS: the waiting gradient slots, or the LDS-resident part of the row
     constexpr unsigned lds_bytes = (unsigned)(NL + row_stash_slots(BLOCK, NV, NL)) * BLOCK * 16u;

@@ -26,8 +26,8 @@ def test_streamed_rows_around_whole_batches(dtype, epv, vectors):
     run_shape_case(dtype, vocab, vocab + 1, 600, grad_rows=sampled(600, vectors))
 
 
-# narrow rows: at most one row for each workgroup, up to four, and more (through the queue)
-@pytest.mark.parametrize("rows", [1, 7, 2048, 2049, 8192, 8193])
+# narrow rows: at most one row for each workgroup, up to eight, and more (through the queue)
+@pytest.mark.parametrize("rows", [1, 7, 2048, 2049, 8192, 8193, 16384, 16385])
 def test_narrow_rows_strided_and_queued(rows):
     run_shape_case("f32", 1024, 1024, rows, grad_rows=sampled(rows, rows))
 
