@@ -24,8 +24,8 @@
 // that are needed (lm_chunk_range, computed on the device from the live count), so no
 // chunk is a small remainder.
 //
-// Kernel shape (gfx950): 512 lanes = 8 wavefronts per workgroup (two per SIMD), one
-// 256 x 256 tile of C per workgroup, K in steps of 64.  Each wavefront owns a 128 x 64 part
+// Kernel shape (gfx950): 512 lanes = 8 wavefronts per workgroup (two per SIMD), one workgroup
+// for each CU that walks through 256 x 256 tiles of C, K in steps of 64.  Each wavefront owns a 128 x 64 part
 // as 4 x 2 blocks of v_mfma_f32_32x32x16_bf16 (128 accumulator registers per lane).  Eight
 // wavefronts rather than four because one wavefront sustains only about one 16-byte-per-lane
 // load every 170 cycles and one ds_read_b128 every 58 (measured, whatever is in flight):
@@ -35,8 +35,12 @@
 // CU.  Inside a tile row the eight 16-byte chunks are stored at chunk ^ ((row >> 1) & 7),
 // applied on the global-address side, so that 16 consecutive rows of one logical chunk (a
 // quarter of a ds_read_b128 fragment read) fall on 16 different groups of four banks.
-// After the last K step the same LDS serves the epilogue: the accumulators are turned round
-// through it so that the per-row softmax partials are plain loops, one row per lane.
+// After the last K step the same LDS serves the softmax epilogue: the accumulators are turned round
+// through it so that the per-row partials are plain loops, one row per lane; the other epilogues store
+// from the accumulators while the next tile's first operand tiles are loaded.
+// What bounds it: LDS (its reads and the tiles' arrival take as many cycles as the products: 48 KB of
+// fragments and 16 KB of tiles per 16 values of k against 512 matrix cycles) and the clock the chip
+// holds (a K step takes 1.53 us on random data, 1.24 us on zeros, 0.85 at the peak rate).
 
 #include <algorithm>
 
@@ -1098,8 +1102,8 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
 // (two 16-byte reads, one 16-byte write); a workgroup 16 rows of them.  Padding is written as zeros: the
 // columns V .. ldg (dL/dH runs over whole K steps of the vocabulary) and the rows n_grad .. the next
 // multiple of 64 (dL/dW runs over whole K steps of rows).
-// out[c][r] = in[rowmap ? rowmap[r] : r][c] for r < R (R = *R_dev when given), c < C; the
-// columns R .. ldo of out are zero-filled.  64 x 64 tiles through LDS, four consecutive
+// One 64 x 64 tile of out[c][r] = in[rowmap[r]][c], r < R, c < C, at (r0, c0); the
+// columns R .. of out are zero-filled.  Through LDS, four consecutive
 // elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
 // 8-byte aligned (the operands of this path: d_model is a multiple of 64, rows 16-byte aligned).
 __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *in, long long ldi, int R, const int *rowmap,
@@ -1114,7 +1118,7 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
         const int rl = ty + 16 * i, r = r0 + rl, c = c0 + tx * 4;
         unsigned lo = 0, hi = 0;
         if (r < R && c < C) {
-            const unsigned *q = (const unsigned *)(src + (long long)(rowmap ? rowmap[r] : r) * ldi + c);
+            const unsigned *q = (const unsigned *)(src + (long long)rowmap[r] * ldi + c);
             lo = q[0];
             hi = q[1];
         }
