@@ -372,8 +372,10 @@ def grpo_filter_groups(rewards, group_size=None, group_offsets=None, stream=None
     keep = torch.empty(n_groups, dtype=torch.uint8, device=dev)
     kept = torch.empty(n_groups, dtype=torch.int32, device=dev)
     n_kept = torch.empty(1, dtype=torch.int32, device=dev)
-    # groups of one size own every rollout; with offsets some may belong to none and keep their 0
-    rk = (torch.empty if group_offsets is None else torch.zeros)(R, dtype=torch.uint8, device=dev)
+    # groups of one size own every rollout (the library refuses sizes that leave some over) unless there is
+    # no group at all; with offsets some rollouts may belong to none: such a rollout keeps its 0
+    owned = group_offsets is None and n_groups > 0
+    rk = (torch.empty if owned else torch.zeros)(R, dtype=torch.uint8, device=dev)
     rc = lib().grpo_filter_groups(_ptr(rewards), R, _ptr(group_offsets), n_groups, gs, _ptr(keep),
                                   _ptr(kept), _ptr(n_kept), _ptr(rk), _raw_stream(stream))
     if rc != GRPO_OK:

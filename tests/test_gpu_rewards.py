@@ -64,3 +64,16 @@ def test_reward_chain_feeds_the_advantages():
     assert int(keep[0]) == 0 and int(n_kept) == n - 1
     a = adv.cpu().numpy().reshape(n, G)
     assert not a[0].any() and np.all(np.any(a[1:] != 0, axis=1))
+
+
+@pytest.mark.parametrize("R,size", [(3, 4), (1, 16), (5, 0)])
+def test_filter_without_a_whole_group_flags_nobody(R, size):
+    """Fewer rewards than a group takes, or no group size: there is no group, and no rollout is flagged as
+    kept, whatever the memory of the flags held before."""
+    dirt = [torch.full((512,), 255, dtype=torch.uint8, device=DEV) for _ in range(4096)]
+    torch.cuda.synchronize()
+    del dirt                                                  # the allocator hands these blocks out again
+    keep, kept, n_kept, rk = grpo.grpo_filter_groups(torch.rand(R, device=DEV), group_size=size)
+    torch.cuda.synchronize()
+    assert keep.numel() == 0 and kept.numel() == 0 and int(n_kept) == 0
+    assert rk.tolist() == [0] * R
