@@ -123,7 +123,7 @@ grpo_status grpo_row_kernel_plan(grpo_dtype dtype, int64_t vocab, grpo_row_plan 
  *                   rollouts and n_rollouts must equal n_groups * group_size.
  *  eps_std >= 0, ddof in {0, 1}.
  *  adv_out          [n_rollouts] f32, device, written (rollouts no group owns are
- *                   left untouched).
+ *                   left untouched; may be rewards itself).
  *  rollout_of_token [n_tokens] i32, device, read, or NULL: rollout index of every
  *                   token row.  With it, adv_tok_out[t] = adv_out[rollout_of_token[t]]
  *                   (NaN if the index is outside [0, n_rollouts)).

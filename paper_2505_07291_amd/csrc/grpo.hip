@@ -1845,7 +1845,8 @@ __global__ void __launch_bounds__(256) grpo_adv_to_tokens(const float *adv, long
 // (16 lanes to a group of up to 16 rollouts, 64 to a larger one; the sums run over the lanes in the
 // same order as above) and looks its tokens up in LDS; the first one also writes adv_out.  Two launches
 // of 2 to 5 us each became one of the same length.  Up to 1024 rollouts and four rounds of groups: beyond
-// them the repeated work costs more than the launch.
+// them the repeated work costs more than the launch.  Neither output may overlap the rewards: a workgroup may
+// still be reading them when another one writes (in place, the two launches above are taken).
 constexpr int kAdvRollouts = 1024, kAdvTokens = 4096;
 __global__ void __launch_bounds__(1024) grpo_adv_fused(const float *rewards, int n_rollouts, int n_groups, int group_size,
                                                        double eps_std, int ddof, float *adv_out,
@@ -2415,6 +2416,12 @@ size_t grpo_workspace_bytes(int64_t n_tokens)
     return loss_workspace_bytes(n_tokens);
 }
 
+// Do [a, a + na) and [b, b + nb) share a byte?
+static bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 grpo_status grpo_group_advantages(const float *rewards, int64_t n_rollouts,
                                   const int32_t *group_offsets, int64_t n_groups,
                                   int64_t group_size, float eps_std, int ddof, float *adv_out,
@@ -2431,7 +2438,9 @@ grpo_status grpo_group_advantages(const float *rewards, int64_t n_rollouts,
     const bool any_work = (n_groups > 0 && n_rollouts > 0) || (rollout_of_token && n_tokens > 0);
     if (!any_work) return GRPO_OK;
     if (!group_offsets && n_groups > 0 && n_rollouts > 0 && rollout_of_token && n_tokens > 0 &&
-        n_rollouts <= kAdvRollouts && n_groups <= (group_size <= 16 ? 4 * 64 : 4 * 16)) {
+        n_rollouts <= kAdvRollouts && n_groups <= (group_size <= 16 ? 4 * 64 : 4 * 16) &&
+        !overlap(rewards, (size_t)n_rollouts * 4, adv_out, (size_t)n_rollouts * 4) &&
+        !overlap(rewards, (size_t)n_rollouts * 4, adv_tok_out, (size_t)n_tokens * 4)) {
         hipLaunchKernelGGL(grpo_adv_fused, dim3((unsigned)((n_tokens + kAdvTokens - 1) / kAdvTokens)), dim3(1024), 0, st,
                            rewards, (int)n_rollouts, (int)n_groups, (int)group_size, (double)eps_std, ddof, adv_out,
                            rollout_of_token, (long long)n_tokens, adv_tok_out);

@@ -527,6 +527,28 @@ def test_group_advantages(ddof):
     assert bool(torch.isnan(t2[0])) and not bool(torch.isnan(t2[1:]).any())
 
 
+@pytest.mark.parametrize("G,n_groups", [(16, 64), (4, 256), (64, 16), (1000, 1)])
+def test_group_advantages_in_place(G, n_groups):
+    """The advantages written over the rewards, and the advantages per token over a buffer that holds them: the
+    same bits as into buffers of their own, with many more tokens than one workgroup takes."""
+    g = torch.Generator().manual_seed(G)
+    R = G * n_groups
+    rewards = torch.rand(R, generator=g).to(DEV)
+    rot = torch.randint(0, R, (1 << 18,), generator=g, dtype=torch.int32).to(DEV)
+    adv, adv_tok = grpo.grpo_group_advantages(rewards, group_size=G, rollout_of_token=rot)
+    for _ in range(10):
+        r2 = rewards.clone()
+        adv2, tok2 = grpo.grpo_group_advantages(r2, group_size=G, rollout_of_token=rot, adv_out=r2)
+        buf = torch.cat([torch.zeros(rot.numel() - R, device=DEV), rewards])
+        adv3, tok3 = grpo.grpo_group_advantages(buf[-R:], group_size=G, rollout_of_token=rot, adv_tok_out=buf)
+        torch.cuda.synchronize()
+        assert adv2.data_ptr() == r2.data_ptr() and torch.equal(adv2, adv) and torch.equal(tok2, adv_tok)
+        assert tok3.data_ptr() == buf.data_ptr() and torch.equal(adv3, adv) and torch.equal(tok3, adv_tok)
+    ref = orc.group_advantages(rewards.cpu().numpy(), group_size=G, eps_std=f32(1e-6))
+    assert np.max(np.abs(adv.cpu().numpy() - ref)) <= 2e-6 * max(1.0, np.max(np.abs(ref)))
+    assert torch.equal(adv_tok, adv[rot.long()])
+
+
 FULL = ["qwen_short", "qwen_medium", "long_reasoning", "numerics_stress"]
 
 
