@@ -323,9 +323,10 @@ __device__ __forceinline__ float block_sum(float v, float *lds)
     return r;
 }
 
-// Exponents (log2 units) are kept above this floor before they are multiplied by their
+// Exponents (log2 units) are kept above this floor where they are multiplied by their
 // probability: an element at -inf has probability 0 and must contribute 0 to
-// sum p log p, not 0 * inf = NaN.  2^-1e30 is 0 all the same.
+// sum p log p, not 0 * inf = NaN.  The probability itself is taken from the exponent as it is:
+// the floor (fmaxf) would turn a NaN into a probability of 0 and hide it.
 constexpr float kExpFloor = -1.0e30f;
 
 // Two sums behind one barrier.
@@ -594,10 +595,11 @@ __device__ __forceinline__ float exp_sum_vec_aux(u32x4 &z, float k, float mx, fl
         for (int e = 0; e < EPW; ++e) {
             // (z - max) k rather than fma(z, k, -max k): exactly 0 at the maximum, which the
             // entropy of a near-one-hot row needs (its sum e a is all cancellation otherwise)
-            const float a = fmaxf((f[e] - mx) * k, kExpFloor);
+            // (only the factor of the weighted sum is floored: fmaxf drops a NaN, which must reach the sum)
+            const float a = (f[e] - mx) * k;
             const float ex = __builtin_amdgcn_exp2f(a);
             part += ex;
-            partw = fmaf(ex, a, partw);
+            partw = fmaf(ex, fmaxf(a, kExpFloor), partw);
         }
         // the running sums must exist here: left alone, the additions drift to the end
         // of the row pass and every product waits for them in a register of its own
@@ -770,11 +772,11 @@ __device__ __forceinline__ void online_vec(const u32x4 &z, bool has_y, int ey, f
     float part = 0.f, partw = 0.f;
 #pragma unroll
     for (int e = 0; e < EPV; ++e) {
-        const float a = AUX ? fmaxf((f[e] - m) * k, kExpFloor) : fmaf(f[e], k, -mk_t);
+        const float a = AUX ? (f[e] - m) * k : fmaf(f[e], k, -mk_t);
         float ex = __builtin_amdgcn_exp2f(a);
         if (has_y && e == ey) ex = 0.f;
         part += ex;
-        if constexpr (AUX) partw = fmaf(ex, a, partw);
+        if constexpr (AUX) partw = fmaf(ex, fmaxf(a, kExpFloor), partw);
     }
     if (m > -INFINITY) {  // all -inf so far: exponents would be NaN
         s += part;
@@ -1130,11 +1132,11 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             VECTOR_FENCE();
         }
         if (ragged) {
-            const float a = AUX ? fmaxf((tz - mx) * p.k, kExpFloor) : fmaf(tz, p.k, -mk);
+            const float a = AUX ? (tz - mx) * p.k : fmaf(tz, p.k, -mk);
             const float ex = __builtin_amdgcn_exp2f(a);
             if (tid < tail) {  // (the other lanes' -inf is no number against a maximum of -inf)
                 acc += ex;
-                if constexpr (AUX) accw = fmaf(ex, a, accw);
+                if constexpr (AUX) accw = fmaf(ex, fmaxf(a, kExpFloor), accw);
             }
         }
         if constexpr (REM) {
@@ -1295,10 +1297,10 @@ __device__ __forceinline__ void online_batch(u32x4 (&z)[U], float k, float &m, f
             unpack_word<DT>(z[u][d], f);
 #pragma unroll
             for (int e = 0; e < EPW; ++e) {
-                const float a = AUX ? fmaxf((f[e] - ref) * k, kExpFloor) : fmaf(f[e], k, -mk_t);
+                const float a = AUX ? (f[e] - ref) * k : fmaf(f[e], k, -mk_t);
                 const float ex = __builtin_amdgcn_exp2f(a);
                 part += ex;
-                if constexpr (AUX) partw = fmaf(ex, a, partw);
+                if constexpr (AUX) partw = fmaf(ex, fmaxf(a, kExpFloor), partw);
             }
         }
         s += part;

@@ -368,3 +368,41 @@ def test_packed_batch_with_sample_level_weights(sample_level):
     denom = float(len(lens)) if sample_level else 0.0
     out = run_aux_case(batch, old, ref, adv_tok, 0.02, 0.01, denom=denom, token_weights=w, label="packed")
     assert int(out["counts"][0]) == int(lens.sum())
+
+
+# one width of every kind of row: registers in several widths, ragged ends beside them, last slots in LDS,
+# a streamed remainder, and streamed rows with and without a ragged end
+@pytest.mark.parametrize("dtype,V", [("bf16", 4096), ("bf16", 5003), ("bf16", 50304), ("bf16", 81925), ("bf16", 107001),
+                                     ("bf16", 152064), ("bf16", 262144), ("bf16", 300000), ("bf16", 200003),
+                                     ("bf16", 600000), ("f32", 1000), ("f32", 50257), ("f32", 100003), ("f32", 152064)])
+def test_aux_nan_and_inf_poison_their_row(dtype, V):
+    """A NaN or +inf logit at any position poisons its row's log-prob, entropy and whole gradient and the
+    four loss scalars, and no other row: even and odd positions (the halves of a 32-bit word in bf16), both ends
+    of the row, the ragged end, and the sampled token."""
+    N = 8
+    g = torch.Generator().manual_seed(V)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    pitch = (V + 7) // 8 * 8
+    store = torch.zeros((N, pitch), dtype=dt)
+    store[:, :V] = (torch.randn((N, V), generator=g) * 2).to(dt)
+    store = store.to(DEV)
+    tokens = torch.randint(0, V - 200, (N,), generator=g).to(DEV)
+    old, ref = torch.full((N,), -8.0, device=DEV), torch.full((N,), -8.5, device=DEV)
+    adv = torch.randn(N, generator=g).to(DEV)
+    adv[5] = 0.0                                               # the poison needs no advantage to spread
+    say("\n[case] aux NaN dtype=%s V=%d" % (dtype, V))
+    inf, nan = float("inf"), float("nan")
+    for pos, val in ((0, nan), (3, nan), (V // 2, nan), (V // 2 + 1, inf), (V - 100, nan), (V - 99, nan), (V - 1, nan),
+                     (V - 1, inf), (int(tokens[5]), nan), (int(tokens[5]), inf)):
+        z = store.clone()
+        z[5, pos] = val
+        loss, lp, ent, counts, grad = grpo.grpo_loss_aux_fwd_bwd(
+            z[:, :V], tokens, old, ref, adv, None, kl_coef=0.01, entropy_coef=0.01)
+        torch.cuda.synchronize()
+        what = "%s at %d" % (val, pos)
+        bad = [False] * 5 + [True] + [False] * 2
+        assert torch.isnan(lp).tolist() == bad, what
+        assert torch.isnan(ent).tolist() == bad, what
+        assert bool(torch.isnan(loss).all()), what
+        gn = torch.isnan(grad.float())
+        assert bool(gn[5].all()) and int(gn.sum()) == V, what
