@@ -748,7 +748,9 @@ __device__ __forceinline__ void order_after(unsigned &off, X &x)
 
 // One vector of an online softmax pass: running maximum m (in logit units), sum s of the
 // exponentials relative to it and, for the entropy, w = sum e a with a the exponent in log2
-// units.  The sampled token's element (has_y, ey) takes part in the maximum only.
+// units.  The sampled token's element (has_y, ey) takes part in the maximum only.  As long as a lane
+// has seen no maximum (all -inf, or NaN, which the maximum skips) its exponents are taken relative
+// to 0: -inf adds nothing, NaN poisons s.
 template <grpo_dtype DT, bool AUX>
 __device__ __forceinline__ void online_vec(const u32x4 &z, bool has_y, int ey, float k, float &m, float &s,
                                            float &w)
@@ -762,26 +764,24 @@ __device__ __forceinline__ void online_vec(const u32x4 &z, bool has_y, int ey, f
     vm = max3_f32(vm, f[EPV - 1], f[EPV - 1]);  // EPV is even: the last element is still to come
     if (vm > m) {
         // new reference: every exponent so far moves by dlt, every term by 2^dlt
-        const float dlt = (m - vm) * k;  // -inf the first time: s and w are 0 and stay 0
+        const float dlt = (m - vm) * k;  // -inf the first time: s and w are 0 (s: or NaN) and stay so
         const float sc_ = __builtin_amdgcn_exp2f(dlt);
         if constexpr (AUX) w = (s > 0.f) ? sc_ * fmaf(dlt, s, w) : 0.f;
         s *= sc_;
         m = vm;
     }
-    const float mk_t = m * k;
+    const float ref = m > -INFINITY ? m : 0.f, mk_t = ref * k;
     float part = 0.f, partw = 0.f;
 #pragma unroll
     for (int e = 0; e < EPV; ++e) {
-        const float a = AUX ? (f[e] - m) * k : fmaf(f[e], k, -mk_t);
+        const float a = AUX ? (f[e] - ref) * k : fmaf(f[e], k, -mk_t);
         float ex = __builtin_amdgcn_exp2f(a);
         if (has_y && e == ey) ex = 0.f;
         part += ex;
         if constexpr (AUX) partw = fmaf(ex, fmaxf(a, kExpFloor), partw);
     }
-    if (m > -INFINITY) {  // all -inf so far: exponents would be NaN
-        s += part;
-        w += partw;
-    }
+    s += part;
+    if constexpr (AUX) w += partw;
 }
 
 // The online partials (m, s, w) of one lane moved to the row's reference maximum mx.
@@ -1269,8 +1269,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
 
 // One batch of vectors joined into a lane's online statistics: running maximum m (in logit units),
 // sum s of the exponentials relative to it, and for the entropy w = sum e a.  One comparison with
-// the running maximum for the whole batch.  As long as a lane has seen no maximum (all -inf, or
-// NaN, which the maximum skips) its exponents are taken relative to 0: -inf adds nothing, NaN poisons s.
+// the running maximum for the whole batch; a lane without a maximum as in online_vec.
 template <grpo_dtype DT, bool AUX, int U>
 __device__ __forceinline__ void online_batch(u32x4 (&z)[U], float k, float &m, float &s, float &w)
 {

@@ -449,6 +449,39 @@ def test_edge_cases(V):
     check_against_oracle(batch, old4, lp_orc, adv.cpu().numpy(), label="-inf entries")
 
 
+@pytest.mark.parametrize("aux", [False, True], ids=["plain", "aux"])
+@pytest.mark.parametrize("dtype,V", [("bf16", 152064), ("bf16", 262144), ("bf16", 300000), ("bf16", 200003), ("bf16", 600000),
+                                     ("f32", 152064)])
+def test_nan_among_masked_vocabulary_entries(dtype, V, aux):
+    """A NaN whose neighbours are all -inf still poisons its row: a lane that has seen no number yet has no
+    maximum to take exponents against.  The NaN stands at several places of a masked stretch that covers the
+    second half of the row (the part beyond registers and LDS, where there is one, begins in it)."""
+    N = 4
+    g = torch.Generator().manual_seed(V + 1)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    store = torch.zeros((N, (V + 7) // 8 * 8), dtype=dt)
+    store[:, :V] = (torch.randn((N, V), generator=g) * 2).to(dt)
+    store[:, V // 2:V] = float("-inf")
+    store[:, V - 20:V] = 1.0                                   # numbers again behind the masked entries
+    store = store.to(DEV)
+    tokens = torch.randint(0, V // 2, (N,), generator=g).to(DEV)
+    old, adv = torch.full((N,), -8.0, device=DEV), torch.randn(N, generator=g).to(DEV)
+    say("\n[case] NaN among masked entries dtype=%s V=%d aux=%s" % (dtype, V, aux))
+    for pos in [V // 2 + (V // 2 - 40) * i // 12 for i in range(13)] + [V - 21]:
+        z = store.clone()
+        z[2, pos] = float("nan")
+        if aux:
+            loss, lp, _, _, grad = grpo.grpo_loss_aux_fwd_bwd(z[:, :V], tokens, old, None, adv, None, entropy_coef=0.01)
+        else:
+            loss, lp, _, grad = grpo.grpo_loss_fwd_bwd(z[:, :V], tokens, old, adv, None)
+            assert torch.isnan(grpo.grpo_logprobs_fwd(z[:, :V], tokens)).tolist() == [False, False, True, False], pos
+        torch.cuda.synchronize()
+        assert torch.isnan(lp).tolist() == [False, False, True, False], pos
+        assert bool(torch.isnan(loss[0])), pos
+        gn = torch.isnan(grad.float())
+        assert bool(gn[2].all()) and int(gn.sum()) == V, pos
+
+
 @pytest.mark.parametrize("vocab,rows", [(24, 300000), (1000, 100000)])
 def test_many_narrow_rows(vocab, rows):
     """Row counts far above the grid with rows of a few bytes: the row queue hands them out in
