@@ -679,13 +679,14 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             float s = 0.f, ws = 0.f;
 #pragma unroll
             for (int w = 0; w < LM_WN; ++w) {
-                const float mw = red_m[w * LM_BM + tid];
+                const float mw = red_m[w * LM_BM + tid], sw = red_s[w * LM_BM + tid];
                 if (mw != -INFINITY) {
                     const float d = (mw - m) * p.k;  // <= 0; exactly 0 for the part that holds the maximum
                     const float f = __builtin_amdgcn_exp2f(d);
-                    const float sw = red_s[w * LM_BM + tid];
                     s = fmaf(sw, f, s);
                     if constexpr (AUX) ws = fmaf(f, fmaf(d, sw, red_w[w * LM_BM + tid]), ws);
+                } else {
+                    s += sw;  // a part without a number: 0, or NaN, which the maximum has skipped
                 }
             }
             p.part_m[(long long)(col0 / LM_BN) * p.part_stride + row] = m;
@@ -1046,8 +1047,9 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
     const float mk = mx * p.k;
     float s = 0.f, ws = 0.f;
     auto add = [&](float mt, float st, float wt) __attribute__((always_inline)) {
-        if (mt == -INFINITY) return;
-        if constexpr (AUX) {
+        if (mt == -INFINITY) {
+            s += st;  // no tile, or one without a number: 0, or NaN, which the maximum has skipped
+        } else if constexpr (AUX) {
             const float d = (mt - mx) * p.k;
             const float f = __builtin_amdgcn_exp2f(d);
             s = fmaf(st, f, s);

@@ -246,3 +246,24 @@ def test_full_size_qwen_short():
     assert abs(inner_W - inner_H) <= U * scale
     col = dW.double().sum(dim=0).abs().max().item()
     assert col <= U * dW.double().abs().sum(dim=0).max().item()
+
+
+@pytest.mark.parametrize("first,last", [(100, 101), (192, 256), (256, 320), (320, 321)])
+def test_nan_in_the_weights_reaches_every_row(first, last):
+    """A vocabulary entry whose weight row is NaN has a NaN logit in every row: log-probs, loss and gradients are
+    NaN, also where a whole 64-column part of a tile, or all that a part has inside the matrix, is NaN (the last
+    of 321 entries is alone in its part) and no number is left to be its maximum."""
+    V, d, n = 321, 64, 70
+    g = torch.Generator().manual_seed(first)
+    w = (torch.randn((V, d), generator=g) * 0.3).to(torch.bfloat16)
+    w[first:last] = float("nan")
+    w, h = w.to(DEV), torch.randn((n, d), generator=g).to(torch.bfloat16).to(DEV)
+    tok = torch.randint(0, 90, (n,), generator=g).to(DEV)
+    old, adv = torch.full((n,), -6.0, device=DEV), torch.randn(n, generator=g).to(DEV)
+    assert bool(torch.isnan(grpo.grpo_lmhead_logprobs_fwd(h, w, tok)).all())
+    loss, lp, _, dH, _ = grpo.grpo_lmhead_loss_fwd_bwd(h, w, tok, old, adv)
+    aux = grpo.grpo_lmhead_loss_aux_fwd_bwd(h, w, tok, old, old, adv, kl_coef=0.01, entropy_coef=0.01)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(lp).all()) and bool(torch.isnan(loss).all()) and bool(torch.isnan(dH.float()).all())
+    assert bool(torch.isnan(aux[1]).all()) and bool(torch.isnan(aux[2]).all()) and bool(torch.isnan(aux[0]).all())
+    assert bool(torch.isnan(aux[4].float()).all())
