@@ -1523,26 +1523,52 @@ __device__ __forceinline__ int count_live(const unsigned char *mask, const float
     return cnt;
 }
 
+// The rows of each segment of 4096 that take part, for batches too long for every workgroup of
+// grpo_prepare to count them all itself.
+__global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned char *mask, const float *token_w, long long n,
+                                                        int *live_of)
+{
+    __shared__ int lds[16];
+    const long long r0 = (long long)blockIdx.x * kOrderRows, r1 = r0 + kOrderRows < n ? r0 + kOrderRows : n;
+    const int cnt = wave_sum(count_live(mask, token_w, r0, r1));
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = cnt;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int total = 0;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) total += lds[i];
+        live_of[blockIdx.x] = total;
+    }
+}
+
 // Counts the unmasked rows, fixes the denominator and resets the queue before any row is processed;
 // with `order`, also writes the order in which the row kernels hand out the rows of a batch with
 // masked rows: first the rows that take part (mask 1 and weight not 0), then the masked ones, which
 // only need zeros.  Handed out in index order, masked rows between live ones cost more than their
 // bytes: the same rows with the masked ones at the end ran 5 to 8 % faster at V = 152064 (the zero fill
 // of a masked row and the read-compute-write cycle of a live row share the memory system badly).
-// One workgroup per 4096 rows: an ordered compaction inside the workgroup, behind the rows it counts
+// One workgroup per 4096 rows: an ordered compaction inside the workgroup, behind the rows counted
 // before its own.  Every workgroup counts the whole mask itself, at 16 bytes a lane: for the 16 KB of
 // 16384 rows that is one step, against a launch of its own for the counting (2 to 5 us) and two
-// atomics on the way.  order[0 .. M) are the live rows in increasing order, order[M .. n) the masked
-// ones (written from the end).
+// atomics on the way.  That work grows with the square of the batch: in longer batches (prepare_counts_itself)
+// grpo_count_rows has counted each segment (live_of) and only those numbers are added up here.
+// order[0 .. M) are the live rows in increasing order, order[M .. n) the masked ones (written from the end).
 __global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask, const float *token_w, long long n,
-                                                     double denom, WsHeader *hdr, int *order)
+                                                     double denom, WsHeader *hdr, int *order, const int *live_of)
 {
     __shared__ long long lds_before[16], lds_rest[16];
     __shared__ int wave_l[16], wave_m[16];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const long long seg0 = (long long)blockIdx.x * kOrderRows < n ? (long long)blockIdx.x * kOrderRows : n;
-    const int cb = wave_sum(count_live(mask, token_w, 0, seg0));
-    const int cr = wave_sum(count_live(mask, token_w, seg0, n));
+    int cb = 0, cr = 0;
+    if (live_of) {
+        for (unsigned i = tid; i < gridDim.x; i += 1024) (i < blockIdx.x ? cb : cr) += live_of[i];
+    } else {
+        cb = count_live(mask, token_w, 0, seg0);
+        cr = count_live(mask, token_w, seg0, n);
+    }
+    cb = wave_sum(cb);
+    cr = wave_sum(cr);
     if (lane == 0) {
         lds_before[wv] = cb;
         lds_rest[wv] = cr;
@@ -2238,6 +2264,11 @@ constexpr size_t loss_workspace_bytes(long long n)
     return kHeaderBytes + 4 * (((size_t)n * 4 + 255) / 256 * 256) + ((size_t)n + 255) / 256 * 256 + fin_partials_bytes(n);
 }
 constexpr long long kOrderMinRowBytes = 32768;  // narrower rows are handed out several at a time, in index order
+// Up to how many rows every workgroup of grpo_prepare counts all of them itself.  Counting them first takes 9.5 us
+// for both launches up to 524288 rows and 13 for 2097152; counted by every workgroup, a mask of 131072 rows
+// takes 7.3 us, of 262144 10.3, of 2097152 51 and of 4194304 194; weights, read one by one, of 16384 rows 8.5,
+// of 32768 13.7 and of 4194304 3300 (mask and weights 5200).
+constexpr bool prepare_counts_itself(long long n, bool weights) { return n <= (weights ? 16384 : 131072); }
 
 grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens, int64_t vocab,
                       int64_t row_stride, const int64_t *tokens, const float *old_logprobs,
@@ -2278,8 +2309,15 @@ grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens,
     if (!((mask || (aux && token_weights)) && n_tokens <= 0x7fffffffll && n_tokens > cu_count() &&
           vocab * (dtype == GRPO_BF16 ? 2 : 4) >= kOrderMinRowBytes))
         order = nullptr;
-    hipLaunchKernelGGL(grpo_prepare, dim3(order ? (unsigned)((n_tokens + kOrderRows - 1) / kOrderRows) : 1u), dim3(1024), 0,
-                       st, mask, aux ? token_weights : (const float *)nullptr, (long long)n_tokens, denom, hdr, order);
+    const float *weights = aux ? token_weights : nullptr;
+    const dim3 segments(order ? (unsigned)((n_tokens + kOrderRows - 1) / kOrderRows) : 1u);
+    int *live_of = nullptr;
+    if (order && !prepare_counts_itself(n_tokens, weights)) {
+        live_of = (int *)partials;  // 64 bytes for each 4096 rows, free until grpo_finalize
+        hipLaunchKernelGGL(grpo_count_rows, segments, dim3(1024), 0, st, mask, weights, (long long)n_tokens, live_of);
+    }
+    hipLaunchKernelGGL(grpo_prepare, segments, dim3(1024), 0, st, mask, weights, (long long)n_tokens, denom, hdr, order,
+                       (const int *)live_of);
     if (n_tokens > 0) {
         RowParams p = {};
         p.logits = logits;

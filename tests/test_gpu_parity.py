@@ -510,6 +510,50 @@ def test_mask_at_any_alignment_and_length():
             assert int(counts[0]) == int((raw[offset:offset + N] != 0).sum()), (N, offset)
 
 
+@pytest.mark.parametrize("rows,weighted", [(16384, True), (16385, True), (20481, True), (131072, False), (131073, False)])
+def test_row_counts_of_long_batches(rows, weighted):
+    """The live rows are counted by every workgroup itself or by a launch in front of them, by the batch's length:
+    the batch's counters, per-row bits and zeros are those of the same rows in micro-batches that are far below
+    either limit.  Whole segments of 4096 rows masked or live, a mask that starts off a 16-byte boundary."""
+    V = 16384                                                  # rows of 32 KB are handed out live ones first
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    logits = torch.empty((rows, V), dtype=torch.bfloat16, device=DEV)
+    for a in range(0, rows, 8192):
+        logits[a:a + 8192] = torch.randn((min(8192, rows - a), V), generator=g, device=DEV)
+    tokens = torch.randint(0, V, (rows,), generator=g, device=DEV)
+    old, adv = torch.full((rows,), -10.0, device=DEV), torch.randn(rows, generator=g, device=DEV)
+    mask = torch.randint(0, 3, (rows + 3,), generator=g, device=DEV).to(torch.uint8)[3:]
+    mask[4096:8192] = 0
+    mask[8192:12288] = 7
+    weights = None
+    if weighted:
+        weights = torch.rand(rows, generator=g, device=DEV)
+        weights[::5] = 0.0
+
+    def call(b, e, denom):
+        w = None if weights is None else weights[b:e]
+        if weighted:
+            loss, lp, _, counts, grad = grpo.grpo_loss_aux_fwd_bwd(
+                logits[b:e], tokens[b:e], old[b:e], None, adv[b:e], mask[b:e], entropy_coef=0.01, denom=denom, token_weights=w)
+            return loss[0], lp, counts, grad
+        return grpo.grpo_loss_fwd_bwd(logits[b:e], tokens[b:e], old[b:e], adv[b:e], mask[b:e], denom=denom)
+
+    M = int(((mask != 0) & (weights != 0)).sum()) if weighted else int((mask != 0).sum())
+    loss, lp, counts, grad = call(0, rows, 0.0)
+    torch.cuda.synchronize()
+    assert int(counts[0]) == M
+    loss_sum, counts_sum = 0.0, torch.zeros_like(counts)
+    for b in range(0, rows, 8000):
+        e = min(rows, b + 8000)
+        l_i, lp_i, c_i, g_i = call(b, e, float(M))
+        torch.cuda.synchronize()
+        assert torch.equal(lp_i, lp[b:e]) and torch.equal(g_i, grad[b:e]), (b, e)
+        loss_sum += float(l_i)
+        counts_sum += c_i
+    assert torch.equal(counts_sum, counts)
+    assert abs(loss_sum - float(loss)) <= 1e-6 * abs(float(loss)) + 1e-9
+
+
 def test_maximum_vocabulary():
     """The widest row the library accepts, 2^28 entries (512 MB in bf16): three rows, one of them
     masked; log-probs, loss and counters of all, the gradient of one row element by element."""
