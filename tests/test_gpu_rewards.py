@@ -66,6 +66,22 @@ def test_reward_chain_feeds_the_advantages():
     assert not a[0].any() and np.all(np.any(a[1:] != 0, axis=1))
 
 
+# one lane to a group up to 1024 groups of up to 64 and 16384 rollouts, a wavefront to a group beyond: both
+# sides of each limit, and of the 64 groups of a wavefront
+@pytest.mark.parametrize("G,n", [(16, 1024), (16, 1025), (64, 256), (64, 257), (64, 1024), (65, 252), (17, 963), (17, 964),
+                                 (1, 1024), (7, 63), (7, 64), (7, 65), (2, 961)])
+def test_filter_groups_around_its_limits(G, n):
+    g = torch.Generator().manual_seed(G * 10000 + n)
+    R = (torch.rand(G * n, generator=g) < 0.2 / G ** 0.5).float()
+    if G > 1:
+        R[-1] = float("nan")                                  # differs from the others, whatever they are
+    keep, kept, n_kept, rk = grpo.grpo_filter_groups(R.to(DEV), group_size=G)
+    torch.cuda.synchronize()
+    rkeep, rkept, rn, rrk = orc.filter_groups(R.numpy(), group_size=G)
+    assert np.array_equal(keep.cpu().numpy(), rkeep) and int(n_kept) == rn
+    assert np.array_equal(kept.cpu().numpy(), rkept) and np.array_equal(rk.cpu().numpy(), rrk)
+
+
 @pytest.mark.parametrize("R,size", [(3, 4), (1, 16), (5, 0)])
 def test_filter_without_a_whole_group_flags_nobody(R, size):
     """Fewer rewards than a group takes, or no group size: there is no group, and no rollout is flagged as
