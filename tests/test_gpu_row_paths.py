@@ -3,7 +3,9 @@
 comparison are those of the other shapes (run_shape_case)."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2505_07291_amd as grpo
 import paper_2505_07291_amd.workloads as wl
 from test_gpu_lmhead_parity import run_case
 from test_gpu_parity import run_shape_case
@@ -54,3 +56,20 @@ def test_head_rows_taken_by_either_path(prompts, seq):
 def test_head_partials_of_few_and_many_tiles(vocab):
     cfg = wl.CONFIGS["qwen_short"].scaled(n_prompts=1, seq_len=5, vocab=vocab, group_size=4)
     run_case(cfg, 64, label="V=%d" % vocab)
+
+
+# rows strided over the grid, several rounds of it, where workgroups share a CU and where each has one to
+# itself: every row is taken once, whatever workgroup takes it
+@pytest.mark.parametrize("dtype,vocab,rows", [("f32", 1000, 9000), ("bf16", 8192, 5000), ("bf16", 50304, 1300),
+                                              ("bf16", 100352, 1030), ("f32", 50257, 700)])
+def test_strided_rows_equal_queued_rows(dtype, vocab, rows):
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    pitch = (vocab + 7) // 8 * 8
+    logits = torch.randn((rows, pitch), generator=g, device="cuda").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    tokens = torch.randint(0, vocab, (rows,), generator=g, device="cuda")
+    mask = (torch.rand(rows, generator=g, device="cuda") < 0.6).to(torch.uint8)
+    out = torch.full((rows,), 3.0, device="cuda")
+    grpo.grpo_logprobs_fwd(logits[:, :vocab], tokens, mask, logprobs_out=out, use_queue=False)
+    want = grpo.grpo_logprobs_fwd(logits[:, :vocab], tokens, mask)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want) and bool((out[mask == 0] == 0).all()) and bool((out[mask != 0] < 0).all())
