@@ -566,6 +566,10 @@ __device__ __forceinline__ float exp_sum_vec(const u32x4 &z, float k, float mk)
 // spills the row to scratch memory.  Emits no instruction.
 __device__ __forceinline__ void forget(u32x4 &v) { asm volatile("" : "+v"(v)); }
 
+// Inside a branch on a uniform condition: keeps it a branch.  The compiler would otherwise compute the few
+// cheap instructions of either side for every row and select.  Emits no instruction.
+__device__ __forceinline__ void keep_branch(float &x) { asm volatile("" : "+v"(x)); }
+
 // One 32-bit word of a resident vector -> its elements (2 bf16 or 1 f32).
 template <grpo_dtype DT>
 __device__ __forceinline__ void unpack_word(unsigned w, float (&f)[Elem<DT>::EPV / 4])
@@ -898,7 +902,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     // response (log-probs of 3000 bf16 rows of 262144, responses of up to 256: 257 us, turned 206).  Not turned
     // are batches of any length, i.e. without a workspace, where several workgroups share a CU: those with
     // live rows take over what the others leave, and turning only costs (65536 fp32 rows of 1024, responses of
-    // up to 1024: 90 us turned, 77 not; 16000 bf16 rows of 4000 42 and 36).
+    // up to 1024: 90 us turned, 75 not; 16000 bf16 rows of 4000 42 and 35).
     const bool queued = p.queued != 0;
     const unsigned turn_step = row_blocks_per_cu(BLOCK, NV) == 1 || p.hdr ? gridDim.x / 8 * 5 : 0;
     long long strided_base = 0;
@@ -1059,7 +1063,10 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             for (int i = 0; i < NV; ++i)
                 if (i == vy / BLOCK) set_neg_inf<DT>(buf[i], ey);
         }
-        if (ragged && vy == nvec_full && tid == ey) tz = -INFINITY;
+        if (ragged) {
+            keep_branch(tz);
+            if (vy == nvec_full && tid == ey) tz = -INFINITY;
+        }
 
         // reference maximum over j != y, then joined with z_y
         float mx = -INFINITY;
@@ -1079,7 +1086,10 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                 VECTOR_FENCE();
             }
         }
-        if (ragged) mx = fmaxf(mx, tz);
+        if (ragged) {
+            keep_branch(tz);
+            mx = fmaxf(mx, tz);
+        }
         // the part of the row that is not resident: online statistics, first read (kept in the caches)
         const char *zrow_cur = (const char *)p.logits + row * p.row_stride * BYTES;
         float rem_m = -INFINITY, rem_s = 0.f, rem_w = 0.f;
@@ -1136,6 +1146,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             VECTOR_FENCE();
         }
         if (ragged) {
+            keep_branch(tz);
             const float a = AUX ? (tz - mx) * p.k : fmaf(tz, p.k, -mk);
             const float ex = __builtin_amdgcn_exp2f(a);
             if (tid < tail) {  // (the other lanes' -inf is no number against a maximum of -inf)
@@ -1245,6 +1256,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                     VECTOR_FENCE();
                 }
                 if (ragged && tid < tail) {
+                    keep_branch(tz);
                     float g;
                     if constexpr (AUX) {
                         const float a = fmaxf(fmaf(tz - sc.mx, p.k, -sc.log2s), kExpFloor);
