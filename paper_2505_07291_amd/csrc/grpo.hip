@@ -2095,8 +2095,10 @@ __global__ void __launch_bounds__(256) grpo_packed_rows(const long long *cu, lon
                 long long b = cu[lo - 1], e = cu[lo];
                 b = b < 0 ? 0 : (b > n_tokens ? n_tokens : b);
                 e = e < b ? b : (e > n_tokens ? n_tokens : e);
-                r = (int)(lo - 1);
-                w = sample_level ? (float)(1.0 / (double)(e - b)) : 1.f;
+                if (t >= b && t < e) {  // always, unless cu decreases: such a row is nobody's rather than of weight 1 / 0
+                    r = (int)(lo - 1);
+                    w = sample_level ? (float)(1.0 / (double)(e - b)) : 1.f;
+                }
             }
             if (weights) weights[t] = w;
             if (rollout_of_token) rollout_of_token[t] = r;

@@ -93,3 +93,18 @@ def test_filter_without_a_whole_group_flags_nobody(R, size):
     torch.cuda.synchronize()
     assert keep.numel() == 0 and kept.numel() == 0 and int(n_kept) == 0
     assert rk.tolist() == [0] * R
+
+
+def test_packed_layout_with_decreasing_offsets():
+    """Offsets that decrease or leave the batch: no weight is infinite, a row either has the weight of a rollout
+    whose range it is in or none, and rows away from the fault are what they would be without it."""
+    cu = torch.tensor([0, 10, 5, 20, 20, 900, 40, 1000, 5000], dtype=torch.int64)
+    n = 1024
+    w, rot = grpo.grpo_packed_layout(cu.to(DEV), n, True)
+    torch.cuda.synchronize()
+    w, rot, c = w.cpu().numpy(), rot.cpu().numpy(), cu.numpy().clip(0, n)
+    assert np.isfinite(w).all() and np.array_equal(w == 0, rot == -1)
+    t = np.flatnonzero(rot >= 0)
+    b, e = c[rot[t]], c[rot[t] + 1]
+    assert np.all((b <= t) & (t < e)) and np.array_equal(w[t], (1.0 / (e - b)).astype(np.float32))
+    assert np.all(rot[:5] == 0) and np.all(rot[10:20] == 2) and np.all(rot[20:40] == 4) and np.all(rot[1000:] == 7)
