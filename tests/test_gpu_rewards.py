@@ -108,3 +108,54 @@ def test_packed_layout_with_decreasing_offsets():
     b, e = c[rot[t]], c[rot[t] + 1]
     assert np.all((b <= t) & (t < e)) and np.array_equal(w[t], (1.0 / (e - b)).astype(np.float32))
     assert np.all(rot[:5] == 0) and np.all(rot[10:20] == 2) and np.all(rot[20:40] == 4) and np.all(rot[1000:] == 7)
+
+
+# a wavefront looks 64 of the R + 1 offsets up at once (65: a second round, 4097: a third), for 256 rows; a
+# workgroup has four wavefronts, and the grid 4096 workgroups
+@pytest.mark.parametrize("R", [1, 62, 63, 64, 4095, 4096, 9000])
+def test_packed_layout_search(R):
+    g = torch.Generator().manual_seed(R)
+    for n in (1, 255, 256, 257, 1024, 1025, 4099, 70001):
+        lead, trail = (n // 10, n // 7) if n > 255 else (0, 0)  # rows before and after the rollouts are nobody's
+        cu = torch.randint(lead, n - trail + 1, (R + 1,), generator=g).sort().values
+        cu[0] = lead                                          # (R above n: most rollouts are empty)
+        for sample_level in (True, False):
+            w, rot = grpo.grpo_packed_layout(cu.to(DEV), n, sample_level)
+            torch.cuda.synchronize()
+            w_ref, rot_ref = orc.packed_layout(cu.numpy(), n, sample_level)
+            assert np.array_equal(rot.cpu().numpy(), rot_ref), (R, n)
+            assert np.array_equal(w.cpu().numpy(), w_ref), (R, n)
+
+
+def test_packed_layout_of_more_rows_than_the_grid_takes_at_once():
+    n, R = 4096 * 1024 + 300, 3000
+    cu = torch.randint(0, n + 1, (R + 1,), generator=torch.Generator().manual_seed(5)).sort().values
+    w, rot = grpo.grpo_packed_layout(cu.to(DEV), n, True)
+    torch.cuda.synchronize()
+    w_ref, rot_ref = orc.packed_layout(cu.numpy(), n, True)
+    assert np.array_equal(rot.cpu().numpy(), rot_ref) and np.array_equal(w.cpu().numpy(), w_ref)
+
+
+# advantages and their tokens in one launch: 16 lanes to a group of up to 16 rollouts (64 groups at once, up to
+# four rounds), 64 to a larger one (16 at once); at most 1024 rollouts; 4096 tokens to a workgroup.  Both sides of
+# each limit.
+@pytest.mark.parametrize("G,n_groups", [(16, 1), (16, 63), (16, 64), (1, 256), (1, 257), (4, 255), (4, 256), (4, 257), (15, 65),
+                                        (17, 1), (17, 16), (17, 17), (17, 60), (64, 16), (64, 17), (100, 10), (1000, 1),
+                                        (1024, 1), (1025, 1)])
+@pytest.mark.parametrize("ddof", [0, 1])
+def test_advantages_of_equal_groups_with_tokens(G, n_groups, ddof):
+    g = torch.Generator().manual_seed(1000 * G + n_groups)
+    R = G * n_groups
+    rewards = (torch.randint(0, 5, (R,), generator=g).float() * 0.25)
+    rewards[-G:] = 0.5                                        # a group without signal
+    ref = orc.group_advantages(rewards.numpy(), group_size=G, eps_std=float(np.float32(1e-6)), ddof=ddof)
+    for n in (1, 1024, 4095, 4096, 4097, 20000):
+        rot = torch.randint(0, R, (n,), generator=g, dtype=torch.int32)
+        bad = torch.rand(n, generator=g) < 0.05
+        rot[bad] = torch.tensor([-1, R, 10 ** 9, -10 ** 9], dtype=torch.int32)[torch.randint(0, 4, (int(bad.sum()),), generator=g)]
+        adv, adv_tok = grpo.grpo_group_advantages(rewards.to(DEV), group_size=G, ddof=ddof, rollout_of_token=rot.to(DEV))
+        torch.cuda.synchronize()
+        a, t = adv.cpu().numpy(), adv_tok.cpu().numpy()
+        assert np.max(np.abs(a - ref)) <= 2e-6 * max(1.0, np.max(np.abs(ref))) and not a[-G:].any()
+        assert np.isnan(t[bad.numpy()]).all()
+        assert np.array_equal(t[~bad.numpy()], a[rot[~bad].numpy()])

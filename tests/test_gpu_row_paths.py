@@ -7,6 +7,7 @@ import torch
 
 import paper_2505_07291_amd as grpo
 import paper_2505_07291_amd.workloads as wl
+from test_gpu_aux_parity import run_aux_shape_case
 from test_gpu_lmhead_parity import run_case
 from test_gpu_parity import run_shape_case
 
@@ -73,3 +74,20 @@ def test_strided_rows_equal_queued_rows(dtype, vocab, rows):
     want = grpo.grpo_logprobs_fwd(logits[:, :vocab], tokens, mask)
     torch.cuda.synchronize()
     assert torch.equal(out, want) and bool((out[mask == 0] == 0).all()) and bool((out[mask != 0] < 0).all())
+
+
+# the same widths with the auxiliary terms, which have code of their own at every stage of a row; per-token
+# weights in every other case; each workgroup takes rows in turn
+@pytest.mark.parametrize("dtype,epv", [("bf16", 8), ("f32", 4)])
+@pytest.mark.parametrize("vectors", [10240, 26 * 512 - 1, 26 * 512, 32 * 512 - 1, 32 * 512])
+def test_aux_ragged_rows_around_the_resident_widths(dtype, epv, vectors):
+    run_aux_shape_case(dtype, vectors * epv + epv - 1, (vectors + 1) * epv, 400, weights=vectors % 2 == 0)
+
+
+# streamed rows: an even and an odd number of batches, whole and with a vector more; more rows than
+# workgroups, so that a row's gradient pass loads the next row
+@pytest.mark.parametrize("dtype,epv,vectors", [("bf16", 8, 10 * 2048), ("bf16", 8, 9 * 2048 - 1), ("f32", 4, 10 * 2048 + 1),
+                                               ("f32", 4, 11 * 2048)])
+def test_aux_streamed_rows_around_whole_batches(dtype, epv, vectors):
+    vocab = vectors * epv + 1
+    run_aux_shape_case(dtype, vocab, (vectors + 1) * epv, 700, weights=vectors % 2 == 0)
