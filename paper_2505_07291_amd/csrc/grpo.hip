@@ -1334,12 +1334,12 @@ __device__ __forceinline__ void online_batch(u32x4 (&z)[U], float k, float &m, f
 // per CU.  The gradient pass walks the batches backwards: the last two are still in the buffers and
 // are not read again, the ones before them are the most recent in the caches, and the buffers it
 // frees last take the first two batches of the next row.  The loads are ordinary ones: 512 rows of
-// 300 KB in flight fit the memory-side cache, non-temporal reads pass it by (380 us instead of 321,
-// 530 instead of 461 on the two batches below).  Loads stand in front of the stores of the same step.
+// 300 KB in flight fit the memory-side cache, non-temporal reads pass it by (312 us instead of 270,
+// 519 instead of 466 on the two batches below).  Loads stand in front of the stores of the same step.
 // Rows come from the queue, live ones first, like the resident kernel's.
-// Whole step, against one vector in flight per lane and rows strided over the grid (which gave
-// some workgroups the live head of every response and others its masked tail): 4096 x 50257 fp32
-// 410 -> 321 us, 4096 x 152069 bf16 529 -> 461 us.  Batches of five and six: 318 and 355, 470 and 497.
+// Whole step in turn on one card, against one vector in flight per lane and rows strided over the grid (which
+// gave some workgroups the live head of every response and others its masked tail): 2048 x 100003 fp32
+// 317 -> 270 us, 4096 x 152069 bf16 550 -> 466 us.  Batches of five and six: 270 and 286, 473 and 486.
 // ---------------------------------------------------------------------------
 constexpr int kStreamBlock = 512, kStreamPerCu = 2, kStreamBatch = 4;
 template <grpo_dtype DT, bool AUX>
@@ -1682,7 +1682,9 @@ struct FinPartial {
 };
 static_assert(sizeof(FinPartial) == 64, "one partial per 64 bytes");
 static_assert(kFinSegment < 65536, "counters of a segment fit 16 bits");
-constexpr size_t fin_partials_bytes(long long n)  // sized for segments of 4096 rows
+// One partial per 4096 rows, more than the segments need: what a workspace must hold is part of the interface and
+// stays; grpo_count_rows leaves a count per 4096 rows in the same place.
+constexpr size_t fin_partials_bytes(long long n)
 {
     return (((size_t)((n + 4095) / 4096) * sizeof(FinPartial)) + 255) / 256 * 256;
 }
@@ -2132,10 +2134,10 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
     // Batches of so few rows that the queue costs more than the balance it gives: with at most one
     // row for each workgroup there is nothing to balance; narrow rows, which are queued several at a
     // time, leave workgroups without any until there are several chunks for each, and a workgroup
-    // that finds the queue empty has asked all its counters in turn.  512 fp32 rows of 1024 entries
-    // (64 chunks of 8, 512 workgroups): 25 us through the queue, 5 us strided; a step on 16000 bf16 rows
-    // of 4000 (eight rounds) 84 us and 78.  With more rounds narrow rows still gain (32000 such rows 77 and 70)
-    // but those near 32 KB lose (10000 fp32 rows of 7001, ten rounds: 118 and 129).
+    // that finds the queue empty has asked all its counters in turn.  A step on 512 fp32 rows of 1024
+    // entries (64 chunks of 8, 512 workgroups): 29 us through the queue, 19 strided; on 16000 bf16 rows
+    // of 4000 (eight rounds) 77 and 73.  With more rounds the narrowest rows still gain (40000 bf16 rows of 1000
+    // 126 and 114) but wider ones lose (32000 of 4000 126 and 140, 10000 fp32 rows of 7001, ten rounds, 107 and 113).
     if (p.n_tokens <= grid || (p.queue_chunk > 1 && p.n_tokens <= 8 * grid)) p.queued = 0;
     if (grid > p.n_tokens) grid = p.n_tokens;
     // dynamic LDS: the waiting gradient slots, or the LDS-resident part of the row
@@ -2187,8 +2189,8 @@ constexpr int kRowStreaming = -1;  // the plan's id for grpo_rows_streamed
 // phases of different rows then overlap inside a CU and the per-row bookkeeping
 // (queue, three barriers, scalar arithmetic) is hidden.  Only rows too wide for that
 // use one workgroup per CU: 512 lanes with twice the registers, the spare ones holding
-// gradient vectors back behind the next row's loads (1024 lanes with up to 10 slots where
-// the ragged-tail slot is needed, which those are built without).
+// gradient vectors back behind the next row's loads (ragged rows of up to 10 slots of 1024 lanes
+// take those).
 int plan_rows(long long nvec, bool ragged)
 {
     if (nvec <= 256 * 1) return 0;
@@ -2205,7 +2207,10 @@ int plan_rows(long long nvec, bool ragged)
     if (nvec <= 1024 * 10) return 7;
     // 512 lanes with twice the registers, in several widths: the arithmetic of a pass runs over
     // every slot of the instantiation, used or not.  Ragged rows as well up to 32 slots (step on
-    // 4096 x 50257 fp32: 290 us, streamed 326); wider ones are streamed.
+    // 4096 x 50257 fp32: 290 us, streamed 326); wider ones are streamed.  With one workgroup to a CU against
+    // two, the log-probs pass alone loses there on the few row counts that just begin another round (512 rows of
+    // 50257 fp32 19 us, streamed 16; 257 of 107003 bf16 18 and 16; from 1000 rows on it gains a quarter and
+    // more); one plan serves both calls, so that they give the same bits.
     if (nvec <= 512 * 26) return ragged ? 16 : 8;
     if (nvec <= 512 * 32) return ragged ? 17 : 9;
     if (ragged) return kRowStreaming;

@@ -206,31 +206,6 @@ __device__ __forceinline__ bool lm_map_tile(int xcd, int idx, int tiles_m, int t
 // wavefront), 64 bytes of each, and with the swizzle those land on different banks.
 __device__ __forceinline__ int lm_km_swizzle(int k) { return (4 * (k & 3)) ^ (2 * ((k >> 3) & 1)); }
 
-template <int CTRL>
-__device__ __forceinline__ float lm_dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf,
-                                                                   0xf, true));
-}
-// Reductions over the 32 lanes that hold one row of a 32 x 32 accumulator block: quad
-// swaps, mirror inside 8, mirror inside 16 (all DPP), then the other 16 lanes.
-__device__ __forceinline__ float lm_row32_max(float v)
-{
-    v = fmaxf(v, lm_dpp<0xB1>(v));
-    v = fmaxf(v, lm_dpp<0x4E>(v));
-    v = fmaxf(v, lm_dpp<0x141>(v));
-    v = fmaxf(v, lm_dpp<0x140>(v));
-    return fmaxf(v, __shfl_xor(v, 16, 64));
-}
-__device__ __forceinline__ float lm_row32_sum(float v)
-{
-    v += lm_dpp<0xB1>(v);
-    v += lm_dpp<0x4E>(v);
-    v += lm_dpp<0x141>(v);
-    v += lm_dpp<0x140>(v);
-    return v + __shfl_xor(v, 16, 64);
-}
-
 template <int EPI, bool STORE_Z, bool AUX = false, bool AKM = false, bool BKM = false>
 __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
 {
@@ -1099,11 +1074,6 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
     }
 }
 
-// G = dL/dz in bf16 for the chunk's gradient rows, row-major [n_grad][ldg], from the fp32 logits:
-// g_j = -q p_j, g_y = q (1 - p_y).  A wavefront takes 512 consecutive entries of a row, eight per lane
-// (two 16-byte reads, one 16-byte write); a workgroup 16 rows of them.  Padding is written as zeros: the
-// columns V .. ldg (dL/dH runs over whole K steps of the vocabulary) and the rows n_grad .. the next
-// multiple of 64 (dL/dW runs over whole K steps of rows).
 // One 64 x 64 tile of out[c][r] = in[rowmap[r]][c], r < R, c < C, at (r0, c0); the
 // columns R .. of out are zero-filled.  Through LDS, four consecutive
 // elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
@@ -1141,6 +1111,11 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
     }
 }
 
+// G = dL/dz in bf16 for the chunk's gradient rows, row-major [n_grad][ldg], from the fp32 logits:
+// g_j = -q p_j, g_y = q (1 - p_y).  A wavefront takes 512 consecutive entries of a row, eight per lane
+// (two 16-byte reads, one 16-byte write); a workgroup 16 rows of them.  Padding is written as zeros: the
+// columns V .. ldg (dL/dH runs over whole K steps of the vocabulary) and the rows n_grad .. the next
+// multiple of 64 (dL/dW runs over whole K steps of rows).
 constexpr int LM_GL_COLS = 512, LM_GL_ROWS = 16;
 template <bool AUX>
 __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long ldz, int V, LmRows w,
