@@ -902,9 +902,10 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     // response (log-probs of 3000 bf16 rows of 262144, responses of up to 256: 257 us, turned 206).  Not turned
     // are batches of any length, i.e. without a workspace, where several workgroups share a CU: those with
     // live rows take over what the others leave, and turning only costs (65536 fp32 rows of 1024, responses of
-    // up to 1024: 90 us turned, 75 not; 16000 bf16 rows of 4000 42 and 35).
+    // up to 1024: 92 us turned, 73 not; 16384 bf16 rows of 4000 37 and 32).
     const bool queued = p.queued != 0;
-    const unsigned turn_step = row_blocks_per_cu(BLOCK, NV) == 1 || p.hdr ? gridDim.x / 8 * 5 : 0;
+    constexpr bool ALONE = row_blocks_per_cu(BLOCK, NV) == 1;
+    const unsigned turn_step = p.hdr ? gridDim.x / 8 * 5 : 0;
     long long strided_base = 0;
     unsigned turn = blockIdx.x, grabs = 0;
     // very narrow rows are also handed out several at a time
@@ -918,7 +919,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         if (!queued) {
             const long long r = strided_base + turn;
             strided_base += gridDim.x;
-            turn += turn_step;
+            turn += ALONE ? gridDim.x / 8 * 5 : turn_step;
             if (turn >= gridDim.x) turn -= gridDim.x;
             return r;  // only the last round has positions past the batch: they end the workgroup's work
         }
