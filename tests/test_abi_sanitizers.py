@@ -2,7 +2,7 @@
 everything tests/test_abi_cpu.py drives) under AddressSanitizer and UndefinedBehaviorSanitizer.
 
 The library's translation unit is compiled for the host only (seconds instead of the minutes the
-94 device kernels take) with -fsanitize=address,undefined on the host pass, linked against an
+device kernels take) with -fsanitize=address,undefined on the host pass, linked against an
 empty stand-in for the device image, and test_abi_cpu.py is run against that build in a child
 process with the sanitizer runtime preloaded.  Nothing here launches a kernel, on any machine:
 those tests stop at validation.  Any out-of-bounds access, overflow or invalid enum load in the
