@@ -1,0 +1,189 @@
+// How the products of the language-model head are divided: rows into chunks, a product into tiles, parts and
+// work items.  Plain integer arithmetic on sizes, the same on the host and on the device (lmhead.hpp uses it
+// in its kernels; a host compiler takes it alone).
+#pragma once
+
+#include <cmath>
+
+#ifndef __HIP__
+#define __host__
+#define __device__
+#endif
+
+namespace {
+
+constexpr int LM_BM = 256, LM_BN = 256, LM_BK = 64;  // tile of C, K step
+constexpr int LM_GROUP_M = 8;                        // tile rows that share a sweep along N
+constexpr int LM_SPLIT_MAX = 32;                     // parts the contraction of one tile of dL/dH may be cut into
+
+// Which of n_live rows chunk number `chunk` covers when no chunk may hold more than cap rows
+// (cap a multiple of 256): the fewest chunks that can hold them, each of the same size rounded
+// up to whole 256-row tiles.  Chunks beyond those are empty (count 0).
+__host__ __device__ inline void lm_chunk_range(int n_live, int cap, int chunk, int &base, int &count)
+{
+    const int needed = (n_live + cap - 1) / cap;
+    if (chunk >= needed) {
+        base = n_live;
+        count = 0;
+        return;
+    }
+    const int per = ((n_live + needed - 1) / needed + 255) / 256 * 256;  // <= cap
+    base = chunk * per;  // < n_live: (needed - 1) cap < n_live and per <= cap
+    count = n_live - base < per ? n_live - base : per;
+}
+
+// Workgroup -> tile.  The hardware deals consecutive workgroups to the 8 XCDs in turn;
+// each XCD has its own L2.  Workgroups of one XCD are given a contiguous run of the
+// tile order below, and that order walks LM_GROUP_M tile rows down before it moves one
+// tile column on, so the tiles in flight on an XCD at any moment share a few A and B
+// panels and most operand traffic is served by that XCD's L2.  The number of tile rows
+// comes from the device-side row count, so that the live tiles are spread over all XCDs
+// whatever part of the launched grid they are.
+__host__ __device__ inline void lm_tile_of(int L, int tiles_m, int tiles_n, int &tm, int &tn)
+{
+    const int group_tiles = LM_GROUP_M * tiles_n;
+    const int grp = L / group_tiles;
+    const int in_grp = L - grp * group_tiles;
+    const int left = tiles_m - grp * LM_GROUP_M, rows_here = left < LM_GROUP_M ? left : LM_GROUP_M;
+    tm = grp * LM_GROUP_M + in_grp % rows_here;
+    tn = in_grp / rows_here;
+}
+
+// The work of one product.  A tile row of C whose live rows do not reach past its first 128 (the last one, as often
+// as not) is "thin": the lower four wavefronts, which share their SIMDs with the upper four, skip its products, and it
+// takes about 0.55 of a whole tile's time.  Whole tiles come first, in the order of lm_tile_of, thin ones behind
+// them, so that the workgroups that got one whole tile less than the others take the first of them.
+//
+// Whole tiles that do not fill a round of the CUs (780 tiles on 256 CUs: three rounds and twelve tiles) would run that
+// round on a few CUs, each for a whole tile's time.  Two ways out, for the `rest` tiles behind the last whole round:
+//  - where the contraction may be split (dL/dH), each is cut into s2 parts along it, so that the last round is s2 times
+//    shorter and spread over all CUs, and thin tiles into t2 = half as many, so that all parts take the same time.
+//    s2 minimises the rounds of parts, counted in tile times, with a small charge per part for the fp32 partial
+//    results and their sum.  Every workgroup, and lm_split_reduce, computes the same plan from the same numbers.
+//  - else each is cut into its upper and lower 128 rows, two thin tiles, if all thin tiles then fit one round.
+struct LmPlan {
+    int rows_w, has_thin;  // whole tile rows; 1 if a thin one follows
+    int full;              // whole tiles computed as they are
+    int rest, s2;          // whole tiles cut into s2 parts each along the contraction
+    int halves;            // whole tiles cut into two thin ones
+    int thin, t2;          // tiles of the thin tile row, and the parts each is cut into
+};
+// what cutting `over` whole and `thin` thin tiles into S and (S + 1) / 2 parts each costs, in tile times (S = 1: not cut)
+__host__ __device__ inline float lm_split_cost(int S, int over, int thin, int max_items, int n_cu)
+{
+    const int items = over * S + thin * ((S + 1) / 2);
+    if (S > 1 && items > max_items) return INFINITY;
+    return (float)((items + n_cu - 1) / n_cu) / (float)S + (S > 1 ? 0.002f * (float)S : 0.f);
+}
+__host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool split, int max_items, int n_cu)
+{
+    LmPlan pl;
+    const int tail = M % LM_BM;
+    pl.has_thin = tail > 0 && tail <= LM_BM / 2 ? 1 : 0;
+    pl.rows_w = M / LM_BM + (tail > LM_BM / 2 ? 1 : 0);
+    pl.thin = pl.has_thin * tiles_n;
+    pl.full = pl.rows_w * tiles_n;
+    pl.rest = pl.halves = 0;
+    pl.s2 = pl.t2 = 1;
+    const int over = pl.full % n_cu;
+    if (!split) {
+        if (over > 0 && 2 * over + pl.thin <= n_cu) {
+            pl.halves = over;
+            pl.full -= over;
+        }
+        return pl;
+    }
+    if (over + pl.thin == 0) return pl;
+    // up to LM_SPLIT_MAX parts of 8 K steps or more; a whole tile has twice the parts of a thin one
+    const int most = over > 0 ? LM_SPLIT_MAX : 2 * LM_SPLIT_MAX, long_enough = over > 0 ? k_tiles / 8 : k_tiles / 4;
+    const int lim = most < long_enough ? most : long_enough;
+    int s_best = 1;
+    float best = lm_split_cost(1, over, pl.thin, max_items, n_cu);
+#ifdef __HIP_DEVICE_COMPILE__
+    // a lane to a candidate (64 of them one after the other are 5 us)
+    static_assert(2 * LM_SPLIT_MAX == 64, "one candidate for each lane");
+    const int S = (int)(threadIdx.x & 63) + 1;
+    float c = S <= lim || S == 1 ? lm_split_cost(S, over, pl.thin, max_items, n_cu) : INFINITY;
+    s_best = S;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float c2 = __shfl_xor(c, o, 64);
+        const int s2 = __shfl_xor(s_best, o, 64);
+        if (c2 < c || (c2 == c && s2 < s_best)) c = c2, s_best = s2;
+    }
+    s_best = __builtin_amdgcn_readfirstlane(s_best);
+    (void)best;
+#else
+    for (int S = 2; S <= lim; ++S) {
+        const float c = lm_split_cost(S, over, pl.thin, max_items, n_cu);
+        if (c < best) {
+            best = c;
+            s_best = S;
+        }
+    }
+#endif
+    if (s_best == 1) return pl;
+    pl.rest = over;
+    pl.full -= over;
+    pl.s2 = s_best;
+    pl.t2 = (s_best + 1) / 2;
+    return pl;
+}
+
+// Work item -> tile, part and height.  Each XCD takes a contiguous run of each list - whole tiles, parts or halves
+// of the rest, thin tiles - so that all kinds of work are spread evenly over the XCDs; parts are ordered part by
+// part (the same K range of neighbouring tiles shares operand panels).
+// idx: position in the XCD's lists, below lm_items_per_xcd; false: no work at that position.
+struct LmItem {
+    int row0, tn;     // first row, tile column
+    int height;       // 256, or 128 for a thin item
+    int part, parts;  // which part of the contraction
+    int block;        // parts > 1: index of its fp32 block
+};
+__host__ __device__ inline int lm_items_per_xcd(const LmPlan &pl)
+{
+    return (pl.full + 7) / 8 + (pl.rest * pl.s2 + 2 * pl.halves + 7) / 8 + (pl.thin * pl.t2 + 7) / 8;
+}
+__host__ __device__ inline bool lm_map_item(int xcd, int idx, int tiles_n, const LmPlan &pl, LmItem &it)
+{
+    const int n1 = (pl.full + 7) / 8, mid = pl.rest * pl.s2 + 2 * pl.halves, n2 = (mid + 7) / 8;
+    it.part = 0;
+    it.parts = 1;
+    it.block = -1;
+    it.height = LM_BM;
+    int L, half = 0;
+    if (idx < n1) {
+        L = xcd * n1 + idx;
+        if (L >= pl.full) return false;
+    } else if (idx < n1 + n2) {
+        const int j = xcd * n2 + (idx - n1);
+        if (j >= mid) return false;
+        if (pl.halves > 0) {  // the two halves of a tile side by side: they share the B panel
+            L = pl.full + (j >> 1);
+            half = j & 1;
+            it.height = LM_BM / 2;
+        } else {
+            it.part = j / pl.rest;
+            it.parts = pl.s2;
+            L = pl.full + (j - it.part * pl.rest);
+            it.block = (j - it.part * pl.rest) * pl.s2 + it.part;
+        }
+    } else {
+        const int items = pl.thin * pl.t2, n3 = (items + 7) / 8;
+        const int j = xcd * n3 + (idx - n1 - n2);
+        if (idx - n1 - n2 >= n3 || j >= items) return false;
+        it.part = j / pl.thin;
+        it.parts = pl.t2;
+        it.tn = j - it.part * pl.thin;
+        it.row0 = pl.rows_w * LM_BM;
+        it.height = LM_BM / 2;
+        it.block = pl.rest * pl.s2 + it.tn * pl.t2 + it.part;
+        return true;
+    }
+    int tm;
+    lm_tile_of(L, pl.rows_w, tiles_n, tm, it.tn);
+    it.row0 = tm * LM_BM + half * (LM_BM / 2);
+    return true;
+}
+
+}  // namespace

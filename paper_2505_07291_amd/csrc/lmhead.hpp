@@ -26,45 +26,41 @@
 //
 // Kernel shape (gfx950): 512 lanes = 8 wavefronts per workgroup (two per SIMD), one workgroup
 // for each CU that walks through 256 x 256 tiles of C, K in steps of 64.  Each wavefront owns a 128 x 64 part
-// as 4 x 2 blocks of v_mfma_f32_32x32x16_bf16 (128 accumulator registers per lane).  Eight
+// as 8 x 4 blocks of v_mfma_f32_16x16x32_bf16 (128 accumulator registers per lane).  Eight
 // wavefronts rather than four because one wavefront sustains only about one 16-byte-per-lane
 // load every 170 cycles and one ds_read_b128 every 58 (measured, whatever is in flight):
 // at four wavefronts the tile's operand loads take longer than its products.  Operand
 // tiles go from global memory straight into LDS (buffer_load_dwordx4 ... lds, no register
 // staging, no vector address arithmetic) through a ring of five 32 KB slots, all 160 KB of a
-// CU.  Inside a tile row the eight 16-byte chunks are stored at chunk ^ ((row >> 1) & 7),
-// applied on the global-address side, so that 16 consecutive rows of one logical chunk (a
+// CU, that runs on from one tile of C to the next.  Inside a tile row the eight 16-byte chunks are stored at
+// chunk ^ ((row >> 1) & 7), applied on the global-address side, so that 16 consecutive rows of one logical chunk (a
 // quarter of a ds_read_b128 fragment read) fall on 16 different groups of four banks.
-// After the last K step the same LDS serves the softmax epilogue: the accumulators are turned round
-// through it so that the per-row partials are plain loops, one row per lane; the other epilogues store
-// from the accumulators while the next tile's first operand tiles are loaded.
-// What bounds it: the matrix cores and the clock the chip holds under them.  By counters of the products of 10066
-// rows with [152064, 5120] they are busy 0.76 of the cycles in the log-probs call (0.67 with the fp32 copy of the
-// logits, 0.69 in dL/dH, 0.77 in dL/dW) at 1.5 to 1.7 GHz; LDS serves the wavefronts 0.26 to 0.31 of the
-// cycles, without bank conflicts, and a wavefront waits for it 0.04 to 0.06 of its time.  A K step takes 1.53 us
-// on random data, 1.24 us on zeros, 0.85 at the peak rate.
+// What bounds it is power: the chip lowers its clock until the products of random data fit.  In registers alone,
+// 16 x 16 x 32 products of normally distributed values reach 2040 TFLOP/s and 32 x 32 x 16 ones 1810 (both 2460 on
+// zeros): half of the accumulator traffic per product.  Fragments from LDS bring that to 1670, operand tiles
+// from the L2 caches to about 1500, from memory to 1400.  With the products in this form, their loads issued at the
+// beginning of a half step and wavefronts in the middle of their products preferred over others (2 % of a product each),
+// the products of 2560 rows with [152064, 5120] went from 3.09 / 2.69 / 2.71 ms (logits with their fp32 copy,
+// dL/dH, dL/dW) to 2.80 / 2.33 / 2.52.  Because power bounds it, a wait costs little by itself: workgroups that
+// start out of step, so that the bursts of stores between tiles meet another's products, gain nothing at 40 K steps or more.
 
 #include <algorithm>
+
+#include "lm_plan.hpp"
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int LM_BM = 256, LM_BN = 256, LM_BK = 64;
 constexpr int LM_THREADS = 512;                      // 8 wavefronts, two per SIMD
 constexpr int LM_WM = 2, LM_WN = 4;                  // wavefront grid over the tile
-constexpr int LM_FA = 4, LM_FB = 2;                  // 32 x 32 blocks per wavefront: 128 x 64
+constexpr int LM_FA = 8, LM_FB = 4;                  // 16 x 16 blocks per wavefront: 128 x 64
 constexpr int LM_CPR = LM_BK / 8;                    // 16-byte chunks per tile row: 8
 constexpr int LM_TILE_BYTES = LM_BM * LM_BK * 2;     // one operand tile: 32 KB
 constexpr int LM_SLOTS = 5;                          // operand tiles resident in LDS: all 160 KB
 constexpr int LM_LPT = LM_BM * LM_CPR / LM_THREADS;  // 16-byte loads per lane and operand tile: 4
 constexpr int LM_LDS_BYTES = LM_SLOTS * LM_TILE_BYTES;
-constexpr int LM_GROUP_M = 8;                        // tile rows that share a sweep along N
-constexpr int LM_GM_BWD = 4;                         // the same for the two gradient products: their A panels (of G)
-                                                     // come from HBM, and a lower group re-reads them less often
-constexpr int LM_SPLIT_MAX = 32;                     // parts the contraction of one tile of dL/dH may be cut into
 
 enum { LM_EPI_LSE = 0, LM_EPI_BF16 = 1, LM_EPI_F32 = 2 };
 
@@ -80,7 +76,6 @@ struct GemmParams {
     const int *K_dev;    // optional: length of the contraction actually present, rounded up to LM_BK
                          // in the kernel (the padding must hold zeros); 0 gives a zero result
     int tiles_n;
-    int group_m;         // tile rows that share a sweep along N (0: LM_GROUP_M)
     // LM_EPI_BF16 / LM_EPI_F32
     void *C;
     long long ldc;
@@ -99,114 +94,44 @@ struct GemmParams {
     float *part_w;           // with the auxiliary terms: sum of exp2(a) a, a = (z - max) k, over the same columns
     long long part_stride;
     float *zy;               // [M]: the accumulator at the sampled token's column
-    float *Z;                // optional fp32 copy of the logits, [M][ldz]
+    float *Z;                // optional fp32 copy of the logits: lm_z_part
     long long ldz;
     // K-major operands (AKM / BKM: stored [K][M] resp. [K][N], contiguous along M resp. N, lda / ldb between
     // k rows): how many elements of a k row exist (a multiple of 8; chunks past them re-read the last one)
     int a_cols, b_cols;
-    // K-major B: how many k rows exist when that is fewer than K (0: all of them).  The rows past them read
+    // K-major B: how many k rows exist (K or fewer).  The rows past them read
     // as zeros: the buffer descriptor of the last K step ends with the last row that exists, and a load
     // past a descriptor's end puts zeros into LDS (measured on gfx950).
     int b_rows;
 };
-
-// Which of n_live rows chunk number `chunk` covers when no chunk may hold more than cap rows
-// (cap a multiple of 256): the fewest chunks that can hold them, each of the same size rounded
-// up to whole 256-row tiles.  Chunks beyond those are empty (count 0).
-__host__ __device__ inline void lm_chunk_range(int n_live, int cap, int chunk, int &base, int &count)
-{
-    const int needed = (n_live + cap - 1) / cap;
-    if (chunk >= needed) {
-        base = n_live;
-        count = 0;
-        return;
-    }
-    const int per = ((n_live + needed - 1) / needed + 255) / 256 * 256;  // <= cap
-    base = chunk * per;  // < n_live: (needed - 1) cap < n_live and per <= cap
-    count = n_live - base < per ? n_live - base : per;
-}
-
-// Workgroup -> tile.  The hardware deals consecutive workgroups to the 8 XCDs in turn;
-// each XCD has its own L2.  Workgroups of one XCD are given a contiguous run of the
-// tile order below, and that order walks LM_GROUP_M tile rows down before it moves one
-// tile column on, so the tiles in flight on an XCD at any moment share a few A and B
-// panels and most operand traffic is served by that XCD's L2.  The number of tile rows
-// comes from the device-side row count, so that the live tiles are spread over all XCDs
-// whatever part of the launched grid they are.
-__device__ __forceinline__ void lm_tile_of(int L, int tiles_m, int tiles_n, int group_m, int &tm, int &tn)
-{
-    const int group_tiles = group_m * tiles_n;
-    const int grp = L / group_tiles;
-    const int in_grp = L - grp * group_tiles;
-    const int rows_here = min(group_m, tiles_m - grp * group_m);
-    tm = grp * group_m + in_grp % rows_here;
-    tn = in_grp / rows_here;
-}
-
-// A product whose tiles do not fill whole rounds of the CUs (780 tiles on 256 CUs: three rounds
-// and twelve tiles) would run its last round on a few CUs, each for a whole tile's time.  The
-// first `full` tiles of the order above (whole rounds) are therefore computed as they are, and
-// each of the `rest` that remain is cut into s2 parts along the contraction, so that the last
-// round is s2 times shorter and spread over all CUs: s2 minimises the rounds of parts, counted in
-// tile times, with a small charge per part for the fp32 partial results and their sum.  Every
-// workgroup, and lm_split_reduce, computes the same plan from the same numbers.
-struct LmSplit {
-    int full, rest, s2;
-};
-__device__ __forceinline__ LmSplit lm_plan_split(int tiles, int k_tiles, int max_items, int n_cu)
-{
-    LmSplit sp;
-    sp.rest = max_items > 0 ? tiles % n_cu : 0;
-    sp.full = tiles - sp.rest;
-    sp.s2 = 1;
-    if (sp.rest == 0) return sp;
-    int lim = LM_SPLIT_MAX;
-    if (k_tiles / 8 < lim) lim = k_tiles / 8;
-    if (max_items / sp.rest < lim) lim = max_items / sp.rest;
-    float best = 1.f;
-    for (int S = 2; S <= lim; ++S) {
-        const float cost = (float)((sp.rest * S + n_cu - 1) / n_cu) / (float)S + 0.002f * (float)S;
-        if (cost < best) {
-            best = cost;
-            sp.s2 = S;
-        }
-    }
-    return sp;
-}
-
-// Work item -> tile (and part).  Each XCD takes a contiguous run of the whole tiles, then a
-// contiguous run of the parts, so that both kinds of work are spread evenly over the XCDs; the
-// parts are ordered part by part (the same K range of neighbouring tiles shares operand panels).
-// idx: position in the XCD's list of lm_items_per_xcd items; false: no work at that position.
-// rest_index: which of the cut tiles this is, -1 for a whole tile.
-__device__ __forceinline__ int lm_items_per_xcd(const LmSplit &sp) { return (sp.full + 7) / 8 + (sp.rest * sp.s2 + 7) / 8; }
-__device__ __forceinline__ bool lm_map_tile(int xcd, int idx, int tiles_m, int tiles_n, const LmSplit &sp, int group_m,
-                                            int &tm, int &tn, int &part, int &rest_index)
-{
-    const int per_xcd = (sp.full + 7) / 8;
-    int L;
-    part = 0;
-    rest_index = -1;
-    if (idx < per_xcd) {
-        L = xcd * per_xcd + idx;
-        if (L >= sp.full) return false;
-    } else {
-        const int items = sp.rest * sp.s2, items_per_xcd = (items + 7) / 8;
-        const int j = xcd * items_per_xcd + (idx - per_xcd);
-        if (idx - per_xcd >= items_per_xcd || j >= items) return false;
-        part = j / sp.rest;
-        rest_index = j - part * sp.rest;
-        L = sp.full + rest_index;
-    }
-    lm_tile_of(L, tiles_m, tiles_n, group_m, tm, tn);
-    return true;
-}
 
 // A K-major operand tile in LDS is [64 k][256 m] bf16, 512 bytes per k row.  The 16-byte chunk at
 // position pc of row k holds logical chunk pc ^ lm_km_swizzle(k) (applied on the global-address side):
 // a transposing fragment read touches rows k .. k + 3 (and k + 8 .. k + 11 in the other half of the
 // wavefront), 64 bytes of each, and with the swizzle those land on different banks.
 __device__ __forceinline__ int lm_km_swizzle(int k) { return (4 * (k & 3)) ^ (2 * ((k >> 3) & 1)); }
+
+// Which column of the tile lies in row r of B's operand tile in LDS.  For fp32 results the 64 columns of a wavefront
+// are dealt so that a lane, which holds column lane % 16 of every block of 16 columns, has four neighbouring ones:
+// its 16-byte stores and those of its neighbours make whole lines.
+template <int EPI>
+__device__ __forceinline__ int lm_column_of(int r)
+{
+    return EPI == LM_EPI_F32 ? (r & ~63) | ((r & 15) << 2) | ((r >> 4) & 3) : r;
+}
+
+// Where entry (row, col) of the fp32 logits of a chunk lies in Z (in floats, a multiple of 4; col a multiple of 4).  Z is kept
+// the way the accumulators are: for each part of 128 rows x 64 columns, 8 x 4 blocks of 16 x 16, in a block 16 bytes per
+// lane, lane = row % 16 + 16 (col % 16 / 4).  A wavefront stores 1 KB at a time, whole; written by rows, every lane's
+// 16 bytes went to another line: 7 us of a CU's time for a tile, now 2.  The space is rows (a multiple of 128) x ldz.
+__device__ __forceinline__ long long lm_z_part(int row, int col, long long ldz)
+{
+    return ((long long)(row >> 7) * (ldz >> 6) + (col >> 6)) * (128 * 64);
+}
+__device__ __forceinline__ int lm_z_in_part(int row, int col)
+{
+    return ((((row >> 4) & 7) * 4 + ((col >> 4) & 3)) * 64 + (row & 15) + 16 * ((col >> 2) & 3)) * 4;
+}
 
 template <int EPI, bool STORE_Z, bool AUX = false, bool AKM = false, bool BKM = false>
 __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
@@ -221,39 +146,66 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     }
     const int K = p.K_dev ? min((*p.K_dev + LM_BK - 1) / LM_BK * LM_BK, p.K) : p.K;
     if (EPI == LM_EPI_F32 && p.accumulate && K == 0) return;  // nothing to add (an empty chunk)
-    const int tiles_m = (M + LM_BM - 1) / LM_BM;
-    const LmSplit sp = lm_plan_split(tiles_m * p.tiles_n, K / LM_BK, EPI == LM_EPI_BF16 ? p.split_items : 0, p.n_cu);
+    const LmPlan pl = lm_plan(M, p.tiles_n, K / LM_BK, EPI == LM_EPI_BF16 && p.split_items > 0, p.split_items, p.n_cu);
     // The workgroups stay: the grid has one for each CU (all of its LDS), workgroup b takes the items b / 8,
     // b / 8 + grid / 8, ... of XCD b % 8's list - the order in which one workgroup per item would be
-    // dispatched - and prepares the next item while it stores this one (below).
-    const int xcd = (int)(blockIdx.x & 7), per_xcd = (int)(gridDim.x >> 3), n_items = lm_items_per_xcd(sp);
+    // dispatched - and its loads run ahead into the next item (below).
+    const int xcd = (int)(blockIdx.x & 7), per_xcd = (int)(gridDim.x >> 3), n_items = lm_items_per_xcd(pl);
     int idx = (int)(blockIdx.x >> 3);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // in a scalar register: LDS targets are uniform
     const int wm = wave / LM_WN, wn = wave % LM_WN;  // this wavefront's 128 x 64 part of the tile
 
-    // The current item: its tile, its part of the contraction (K steps [kt0, kt0 + KT)) and the addresses of its
+    // The item being loaded: its tile, its part of the contraction (K steps [kt0, kt0 + KT)) and the addresses of its
     // loads.  Byte offsets of this lane's four 16-byte loads per operand tile, relative to the
     // tile's first row at k = 0.  Load i of a wavefront fills LDS chunks [i*512 + wave*64,
     // +64) of the tile; chunk c sits in tile row c / 8 at physical position c % 8 and holds
-    // logical chunk (c % 8) ^ ((row >> 1) & 7).  Rows past the end of the matrix re-read the
-    // last row (their results are never stored).
-    int row0 = 0, col0 = 0, part = 0, parts = 1, rest_index = -1, kt0 = 0, KT = 0;
+    // logical chunk (c % 8) ^ ((row >> 1) & 7).  Rows past the item's last re-read that
+    // row (their results are never stored).
+    LmItem item;
+    int L = 0, L_end = 0, tm = 0, group_row0 = 0, group_rows = 1, step_m = 0, step_n = 0;  // its place among the whole tiles
+    int kt0 = 0, KT = 0;
     unsigned a_off[LM_LPT], b_off[LM_LPT];
     const char *a_tile = nullptr, *b_tile = nullptr;
     const long long a_kstep = (long long)LM_BK * p.lda * 2, b_kstep = (long long)LM_BK * p.ldb * 2;  // K-major only
     // takes this workgroup's next item, from position idx on; false: none is left
     auto next_item = [&]() __attribute__((always_inline)) -> bool {
-        int tm, tn;
-        for (;; idx += per_xcd) {
-            if (idx >= n_items) return false;  // whole workgroup alike
-            if (lm_map_tile(xcd, idx, tiles_m, p.tiles_n, sp, p.group_m, tm, tn, part, rest_index)) break;
+        if (L + per_xcd < L_end) {  // the next whole tile of the same group of tile rows: per_xcd further on, no division
+            L += per_xcd;
+            tm += step_m;
+            item.tn += step_n;
+            if (tm >= group_rows) {
+                tm -= group_rows;
+                ++item.tn;
+            }
+            item.row0 = (group_row0 + tm) * LM_BM;
+        } else {
+            LmItem it;
+            for (;; idx += per_xcd) {
+                if (idx >= n_items) {  // whole workgroup alike
+                    KT = 0;  // the loads that still follow find no step and touch no memory
+                    return false;
+                }
+                if (lm_map_item(xcd, idx, p.tiles_n, pl, it)) break;
+            }
+            item = it;
+            const int n1 = (pl.full + 7) / 8;
+            L_end = 0;
+            if (idx < n1) {
+                const int group_tiles = LM_GROUP_M * p.tiles_n;
+                L = xcd * n1 + idx;
+                group_row0 = L / group_tiles * LM_GROUP_M;
+                group_rows = min(LM_GROUP_M, pl.rows_w - group_row0);
+                L_end = min(min(pl.full, (xcd + 1) * n1), (L / group_tiles + 1) * group_tiles);
+                tm = it.row0 / LM_BM - group_row0;
+                step_n = per_xcd / group_rows;
+                step_m = per_xcd - step_n * group_rows;
+            }
         }
         idx += per_xcd;
-        parts = rest_index >= 0 ? sp.s2 : 1;
-        row0 = tm * LM_BM;
-        col0 = tn * LM_BN;
+        const LmItem &it = item;
+        const int row0 = it.row0, col0 = it.tn * LM_BN, row_end = min(M, row0 + it.height);
         int t = tid;  // opaque: what follows from it is computed again for each item, not kept in registers
         asm volatile("" : "+v"(t));
 #pragma unroll
@@ -261,14 +213,14 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             const int c = i * LM_THREADS + t;
             const int r = c / LM_CPR, pc = c % LM_CPR;
             const int lc = pc ^ ((r >> 1) & (LM_CPR - 1));
-            const int ra = min(row0 + r, M - 1) - row0;
-            const int rb = min(col0 + r, p.N - 1) - col0;
+            const int ra = min(row0 + r, row_end - 1) - row0;
+            const int rb = min(col0 + lm_column_of<EPI>(r), p.N - 1) - col0;
             // K-major operand: the tile is [64 k rows][256 m]; chunk c is k row c / 32 at position c % 32 and holds
-            // logical chunk (c % 32) ^ lm_km_swizzle(k row); chunks past the end of the operand's k row re-read
-            // its last chunk (they belong to rows or columns of C that are never stored)
+            // logical chunk (c % 32) ^ lm_km_swizzle(k row); chunks past the item's last row or the end of the
+            // operand's k row re-read the last chunk (they belong to rows or columns of C that are never stored)
             const int kk = c >> 5, lck = (c & 31) ^ lm_km_swizzle(kk);
             if constexpr (AKM) {
-                const int ch = min((row0 >> 3) + lck, (p.a_cols >> 3) - 1) - (row0 >> 3);
+                const int ch = min((row0 >> 3) + lck, (min(row_end + 7, p.a_cols) >> 3) - 1) - (row0 >> 3);
                 a_off[i] = (unsigned)((long long)kk * p.lda * 2 + ch * 16);
             } else {
                 a_off[i] = (unsigned)(((long long)ra * p.lda + lc * 8) * 2);
@@ -280,8 +232,9 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 b_off[i] = (unsigned)(((long long)rb * p.ldb + lc * 8) * 2);
             }
         }
-        kt0 = (int)((long long)(K / LM_BK) * part / parts);
-        KT = (int)((long long)(K / LM_BK) * (part + 1) / parts) - kt0;
+        // K / LM_BK < 2^17 where there are parts (at most 64): see lm_bwd_vocab_ok
+        kt0 = it.parts > 1 ? (int)((unsigned)(K / LM_BK) * (unsigned)it.part / (unsigned)it.parts) : 0;
+        KT = (it.parts > 1 ? (int)((unsigned)(K / LM_BK) * (unsigned)(it.part + 1) / (unsigned)it.parts) : K / LM_BK) - kt0;
         a_tile = AKM ? (const char *)p.A + ((long long)kt0 * LM_BK * p.lda + row0) * 2
                      : (const char *)p.A + ((long long)(chunk_base + row0) * p.lda + (long long)kt0 * LM_BK) * 2;
         b_tile = BKM ? (const char *)p.B + ((long long)kt0 * LM_BK * p.ldb + col0) * 2
@@ -291,81 +244,69 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     if (!next_item()) return;  // before any barrier
 
     // LDS is a ring of five 32 KB slots that operand tiles pass through in the order
-    // A(0), B(0), A(1), B(1), ...: entry q = 2 kt + (0 for A, 1 for B) lives in slot q % 5.
-    // Two slots hold the tile being multiplied, the other three the next loads, which are
-    // issued two at a time between the products.  Past the last tile the last one is loaded
-    // again, into a slot nobody reads any more: every iteration then issues the same number
-    // of loads and "landed" is a fixed vmcnt value.
-    auto slot_of = [&](int q) { return lm_smem + (q % LM_SLOTS) * LM_TILE_BYTES; };
+    // A(0), B(0), A(1), B(1), ..., from item to item without a break: behind the last K step of one item come the
+    // first ones of the next.  Two slots hold the step being multiplied, two the next step, and the fifth
+    // takes A of the step after that; its B goes where the current A was.  An item takes two steps at least
+    // (steps that its contraction does not have read zeros), so that the loads never run further ahead than
+    // the next item.  `slot` is where A of the current step lies.
+    int slot = 0;
+    auto slot_at = [&](int ahead) __attribute__((always_inline)) -> int {  // slot + ahead, ahead < 5
+        int q = slot + ahead;
+        if (q >= LM_SLOTS) q -= LM_SLOTS;
+        return q * LM_TILE_BYTES;
+    };
     // The loads are buffer loads with LDS as their target: the tile's first row at this
-    // workgroup's first K step is the buffer's base, the lane's offset inside the tile a
+    // item's first K step is the buffer's base, the lane's offset inside the tile a
     // vector register, the K position a scalar one, the LDS address goes through M0 - no
     // vector arithmetic per load.  The range check of the buffer is left wide open (rows are
-    // clamped above and K steps below, so every address is inside the operand).
+    // clamped above, so every address of a step that exists is inside the operand), shut for a step that does not
+    // exist, and ends with the last row there is in a ragged last step of a K-major B.
     // A K-major operand moves by whole k rows from step to step, further than a 32-bit offset reaches:
     // its descriptor is made again for every step (scalar arithmetic).
-    auto issue_half = [&](int q, bool b_operand, int half) {
-        const int kt = min(q >> 1, KT - 1);
-        char *sd = slot_of(q) + wave * 1024;
-        if (b_operand ? BKM : AKM) {
-            const char *base = b_operand ? b_tile + kt * b_kstep : a_tile + kt * a_kstep;
-            unsigned bytes = 0xffffffffu;  // range check wide open, except for a ragged last step of B
-            const int k0 = (kt0 + kt) * LM_BK;
-            if (b_operand && p.b_rows > 0 && k0 + LM_BK > p.b_rows)
-                bytes = (unsigned)((long long)(p.b_rows - k0 - 1) * p.ldb * 2 + (long long)(p.b_cols - col0) * 2);
-            const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)bytes, 0x00020000);
-#pragma unroll
-            for (int i = half * (LM_LPT / 2); i < (half + 1) * (LM_LPT / 2); ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc,
-                                                         (__attribute__((address_space(3))) void *)(sd + i * (LM_THREADS * 16)),
-                                                         16, (int)(b_operand ? b_off[i] : a_off[i]), 0, 0, 0);
-            return;
+    struct Source {
+        const char *base;
+        unsigned bytes;
+        int k0;
+    };
+    auto source_of = [&](bool b_operand, int kt) __attribute__((always_inline)) -> Source {
+        unsigned bytes = kt < KT ? 0xfffffff0u : 0u;  // (as -1 the select would become a vector instruction)
+        if (b_operand && BKM) {
+            const int left = kt < KT ? p.b_rows - (kt0 + kt) * LM_BK : 0;  // rows of B from this step on
+            const unsigned edge = left > 0 ? (unsigned)(left - 1) * (unsigned)(p.ldb * 2) + (unsigned)(p.b_cols - item.tn * LM_BN) * 2u : 0u;
+            bytes = left >= LM_BK ? 0xfffffff0u : edge;
         }
-        const int k0 = kt * (LM_BK * 2);
-        const __amdgpu_buffer_rsrc_t rsrc =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(b_operand ? b_tile : a_tile), 0, -1, 0x00020000);
-#pragma unroll
-        for (int i = half * (LM_LPT / 2); i < (half + 1) * (LM_LPT / 2); ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc,
-                                                     (__attribute__((address_space(3))) void *)(sd + i * (LM_THREADS * 16)),
-                                                     16, (int)(b_operand ? b_off[i] : a_off[i]), k0, 0, 0);
+        const bool km = b_operand ? BKM : AKM;
+        const char *base = (b_operand ? b_tile : a_tile) + (km ? kt * (b_operand ? b_kstep : a_kstep) : 0);
+        return {base, bytes, km ? 0 : kt * (LM_BK * 2)};
+    };
+    auto issue_load = [&](const Source &src, bool b_operand, int at, int i) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)src.base, 0, (int)src.bytes, 0x00020000);
+        const int k0 = src.k0;  // (given as a member, the compiler's host pass drops the kernel)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            rsrc, (__attribute__((address_space(3))) void *)(lm_smem + at + wave * 1024 + i * (LM_THREADS * 16)), 16,
+            (int)(b_operand ? b_off[i] : a_off[i]), k0, 0, 0);
     };
 
-    // Fragment addresses: lane (r = lane % 32, half = lane / 32) reads, for k-step ks, the
-    // logical chunk 2 ks + half of tile row (block row) + r.
-    const int fr = lane & 31, fh = lane >> 5;
-    unsigned frag_off[LM_BK / 16];
-#pragma unroll
-    for (int ks = 0; ks < LM_BK / 16; ++ks)
-        frag_off[ks] = (unsigned)((fr * LM_CPR + ((2 * ks + fh) ^ ((fr >> 1) & (LM_CPR - 1)))) * 16);
-    const unsigned a_wave = (unsigned)(wm * (LM_FA * 32) * LM_BK * 2);
-    const unsigned b_wave = (unsigned)(wn * (LM_FB * 32) * LM_BK * 2);
+    // Fragment addresses.  Lane (r = lane % 16, g = lane / 16) holds, for the 16 x 16 x 32 product, the 8 consecutive
+    // k from 8 g on of row r of a 16-row block: logical chunk 4 ks + g of that tile row, for half ks of the step.
+    const int fr = lane & 15, fg = lane >> 4;
+    const unsigned frag0 = (unsigned)((fr * LM_CPR + (fg ^ ((fr >> 1) & (LM_CPR - 1)))) * 16);  // half 1: ^ 64
     // K-major tiles are read with the transposing 64-bit LDS read: lane i of a group of 16 lanes gives the
     // address of 4 consecutive m at k row i / 4 (piece i % 4 of 16 m) and receives the 4 k values of m = i.
-    // Two such reads (k rows +0..3 and +4..7) make the 8 consecutive k of m = lane % 32 that a lane holds
-    // for the 32 x 32 x 16 product: lanes 0-15 and 16-31 cover m 0-15 and 16-31, lanes 32-63 the k rows + 8.
-    unsigned akm_off[LM_FA], bkm_off[LM_FB];
+    // Two such reads (k rows +0..3 and +4..7) make a lane's 8 consecutive k; group g of 16 lanes has the k rows from
+    // 8 g on.  Block i is 32 i bytes further on inside a k row: bits that the swizzle of the chunks only flips.
+    unsigned akm0, bkm0;
     {
-        const int kh = lane >> 5, mg = (lane >> 4) & 1, i16 = lane & 15;
-        const int kkl = 8 * kh + (i16 >> 2), sw = lm_km_swizzle(kkl);
-#pragma unroll
-        for (int i = 0; i < LM_FA; ++i) {
-            const int ml = wm * (LM_FA * 32) + i * 32 + 16 * mg + 4 * (i16 & 3);
-            akm_off[i] = (unsigned)(kkl * (LM_BM * 2) + (((ml >> 3) ^ sw) * 16) + (ml & 7) * 2);
-        }
-#pragma unroll
-        for (int j = 0; j < LM_FB; ++j) {
-            const int nl = wn * (LM_FB * 32) + j * 32 + 16 * mg + 4 * (i16 & 3);
-            bkm_off[j] = (unsigned)(kkl * (LM_BN * 2) + (((nl >> 3) ^ sw) * 16) + (nl & 7) * 2);
-        }
+        const int kkl = 8 * fg + (fr >> 2), sw = lm_km_swizzle(kkl);
+        akm0 = (unsigned)(kkl * (LM_BM * 2) + (((wm * (LM_FA * 2) + ((fr & 3) >> 1)) ^ sw) * 16) + (fr & 1) * 8);
+        bkm0 = (unsigned)(kkl * (LM_BN * 2) + (((wn * (LM_FB * 2) + ((fr & 3) >> 1)) ^ sw) * 16) + (fr & 1) * 8);
     }
     // Written as assembly: the compiler holds the builtin form of this read back behind every outstanding
-    // load to LDS (s_waitcnt vmcnt(0) in front of each k-step's reads), which the pipeline below exists to
-    // avoid.  The results arrive asynchronously; every use sits behind the explicit lgkmcnt(0) of lds_landed().
-    auto tr_frag = [&](const char *s) {
+    // load to LDS (s_waitcnt vmcnt(0) in front of each half's reads), which the pipeline below exists to
+    // avoid.  The results arrive asynchronously; every use sits behind an explicit lgkmcnt(0).
+    auto tr_frag = [&](unsigned at) __attribute__((always_inline)) {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         s16x4 lo, hi;
-        const unsigned at = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char *)s;
         asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:2048"
                      : "=&v"(lo), "=&v"(hi)
                      : "v"(at)
@@ -373,414 +314,386 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
     static_assert(4 * (LM_BM * 2) == 2048, "the second read's offset is written into the assembly");
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const char *)lm_smem;
 
-    f32x16 acc[LM_FA][LM_FB];
+    f32x4 acc[LM_FA][LM_FB];
 
-    // Fragments are double buffered in registers (F[0], F[1]) and read one k-step ahead of
-    // the products that use them.  One barrier per tile, before its last k-step: by then
-    // every wavefront holds that k-step's fragments in registers, so the tile's two slots
-    // are free, and everybody's loads of the next tile have landed.
-    bf16x8 F[2][LM_FA + LM_FB];
-    auto read_frags = [&](bf16x8 (&f)[LM_FA + LM_FB], int kt, int ks) {
-        const char *sa = slot_of(2 * kt), *sb = slot_of(2 * kt + 1);
-#pragma unroll
-        for (int i = 0; i < LM_FA; ++i) {
-            if constexpr (AKM)
-                f[i] = tr_frag(sa + akm_off[i] + ks * (16 * LM_BM * 2));
-            else
-                f[i] = *(const bf16x8 *)(sa + a_wave + i * (32 * LM_BK * 2) + frag_off[ks]);
-        }
-#pragma unroll
-        for (int j = 0; j < LM_FB; ++j) {
+    // Fragments are double buffered in registers (F[0], F[1]) and read one half step ahead of the products that use
+    // them: B's, then A's.  One barrier per step, in its middle: by then every wavefront holds the second half's
+    // fragments in registers, so the step's two slots are free, and everybody's loads of the next step have landed.
+    bf16x8 F[2][LM_FB + LM_FA];
+    auto read_frag = [&](int f, int at_a, int at_b, int ks) __attribute__((always_inline)) -> bf16x8 {
+        if (f < LM_FB) {
             if constexpr (BKM)
-                f[LM_FA + j] = tr_frag(sb + bkm_off[j] + ks * (16 * LM_BN * 2));
+                return tr_frag((lds0 + at_b + ks * (32 * LM_BN * 2) + bkm0) ^ (f * 32));
             else
-                f[LM_FA + j] = *(const bf16x8 *)(sb + b_wave + j * (32 * LM_BK * 2) + frag_off[ks]);
+                return *(const bf16x8 *)(lm_smem + at_b + wn * (LM_FB * 16 * LM_BK * 2) + (frag0 ^ (ks * 64)) + f * (16 * LM_BK * 2));
         }
+        if constexpr (AKM)
+            return tr_frag((lds0 + at_a + ks * (32 * LM_BM * 2) + akm0) ^ ((f - LM_FB) * 32));
+        else
+            return *(const bf16x8 *)(lm_smem + at_a + wm * (LM_FA * 16 * LM_BK * 2) + (frag0 ^ (ks * 64)) +
+                                     (f - LM_FB) * (16 * LM_BK * 2));
     };
-    auto products = [&](const bf16x8 (&f)[LM_FA + LM_FB]) {
-#pragma unroll
-        for (int i = 0; i < LM_FA; ++i)
-#pragma unroll
-            for (int j = 0; j < LM_FB; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[i], f[LM_FA + j], acc[i][j], 0, 0, 0);
-    };
-    // One k-step: wait for the fragments read during the previous k-step (they had all of its
-    // products' time to arrive), issue the six reads of the next k-step's fragments, then the
-    // eight products with the two global -> LDS loads behind the second and the fourth.  The
-    // wait is written out so that it sits in front of the new reads: left to itself the
-    // compiler puts one wait for everything between the reads and the first product.
-    auto lds_landed = [&]() {
+    auto lds_landed = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0) and nothing else
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto interleave = [&]() {
-        __builtin_amdgcn_sched_group_barrier(0x100, (AKM ? 2 : 1) * LM_FA + (BKM ? 2 : 1) * LM_FB, 0);
+    // One half step: the products of the fragments in `f`, the reads of the next half's into `nf` and the loads of one
+    // operand tile dealt out between them.  A block row of A goes through the columns of B to and fro, so that
+    // consecutive products share an operand.  Which operand comes first says what a lane holds of a 16 x 16 block of C:
+    // A: column lane % 16, rows 4 (lane / 16) + v (fp32 results); B: row lane % 16, columns 4 (lane / 16) + v (the others).
+    auto half_step = [&](const bf16x8 (&f)[LM_FB + LM_FA], bf16x8 (&nf)[LM_FB + LM_FA], int next_a, int next_b, int next_ks,
+                         bool b_operand, int load_at, int load_kt) __attribute__((always_inline)) {
+        const Source src = source_of(b_operand, load_kt);
 #pragma unroll
-        for (int i = 0; i < LM_LPT / 2; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        for (int i = 0; i < LM_FA; ++i) {
+            if (2 * i < LM_FB + LM_FA) {
+                nf[2 * i] = read_frag(2 * i, next_a, next_b, next_ks);
+                nf[2 * i + 1] = read_frag(2 * i + 1, next_a, next_b, next_ks);
+            }
+            if (i < LM_LPT) issue_load(src, b_operand, load_at, i);
+#pragma unroll
+            for (int jj = 0; jj < LM_FB; ++jj) {
+                if (jj == 0) __builtin_amdgcn_s_setprio(1);
+                if (jj == LM_FB - 1) __builtin_amdgcn_s_setprio(0);
+                const int j = i % 2 ? LM_FB - 1 - jj : jj;
+                if constexpr (EPI == LM_EPI_F32)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[LM_FB + i], f[j], acc[i][j], 0, 0, 0);
+                else
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[j], f[LM_FB + i], acc[i][j], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, LM_FA * LM_FB - LM_LPT, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto interleave_reads = [&]() {  // a k-step that issues no loads
-        __builtin_amdgcn_sched_group_barrier(0x100, (AKM ? 2 : 1) * LM_FA + (BKM ? 2 : 1) * LM_FB, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, LM_FA * LM_FB, 0);
-        __builtin_amdgcn_sched_barrier(0);
     };
     static_assert(LM_BM == 256 && LM_BN == 256, "K-major tiles: 32 chunks per k row");
-    static_assert(LM_BK / 16 == 4 && LM_SLOTS == 5 && LM_LPT == 4 && LM_FA * LM_FB >= LM_LPT,
-                  "the pipeline and its wait counts are written for 4 k-steps, 5 slots, 4 loads per operand tile");
-
-    // Stores one item's result from the accumulators (see the softmax epilogue for LM_EPI_LSE).
-    auto store_item = [&](const int row0, const int col0, const int part, const int parts, const int rest_index)
-        __attribute__((always_inline)) {
-    // Accumulator layout of a 32 x 32 block: lane l holds column l % 32; register v holds
-    // row 8 (v / 4) + 4 (l / 32) + v % 4.
-    int ln = lane;  // opaque, as above
-    asm volatile("" : "+v"(ln));
-    const int cl = ln & 31, g = ln >> 5;
-    const int wrow = wm * (LM_FA * 32), wcol = wn * (LM_FB * 32);
-    // Where a wavefront's part lies inside the matrix whole - every part but those of the last tile row:
-    // N is a multiple of 64 here, so a part's 64 columns are all inside or all outside - its stores need no
-    // checks: a scalar address per row and one 32-bit offset per lane.  With a row and a column test, a 64-bit
-    // address and a branch for each of 128 stores an epilogue was 2200 instructions a wavefront (dL/dH of
-    // 450 x 12000 x 1152, all of it parts: 44 us, now 30).
-    // The next item's loads are in flight meanwhile: they have landed when no more operations are outstanding
-    // than the stores issued since (the counter ends at 63).
-    auto loads_landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
-    auto loads_landed_behind_64_stores = [&]() { asm volatile("s_waitcnt vmcnt(63)" ::: "memory"); };
-    if constexpr (EPI == LM_EPI_F32) {
-        if (col0 + wcol >= p.N) {
-            loads_landed();
-            return;
-        }
-        const bool whole = row0 + wrow + LM_FA * 32 <= M && col0 + wcol + LM_FB * 32 <= p.N && p.ldc < (1ll << 28);
-        if (whole) {
-            char *cw = (char *)p.C + ((long long)(row0 + wrow) * p.ldc + col0 + wcol) * 4;
-            const unsigned voff = (unsigned)((4 * g * p.ldc + cl) * 4);
-            const long long pitch = p.ldc * 4;
-#pragma unroll
-            for (int i = 0; i < LM_FA; ++i) {
-                float old[16][LM_FB];
-                if (p.accumulate) {
-                    // C += result: all loads of a block row first, then the sums and stores (a dependent load in
-                    // front of every store made this epilogue take 2 ms longer than the plain store)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-#pragma unroll
-                        for (int j = 0; j < LM_FB; ++j)
-                            old[v][j] = *(const float *)(cw + (i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 128 + voff);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v)
-#pragma unroll
-                        for (int j = 0; j < LM_FB; ++j) old[v][j] = -0.f;  // x + -0 is x, whatever x
-                }
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-#pragma unroll
-                    for (int j = 0; j < LM_FB; ++j)
-                        __builtin_nontemporal_store(
-                            old[v][j] + acc[i][j][v],
-                            (float *)(cw + (i * 32 + 8 * (v >> 2) + (v & 3)) * pitch + j * 128 + voff));
-                if (i == 1) loads_landed_behind_64_stores();
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < LM_FA; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + wrow + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                if (row >= M) continue;
-#pragma unroll
-                for (int j = 0; j < LM_FB; ++j) {
-                    const int col = col0 + wcol + j * 32 + cl;
-                    if (col >= p.N) continue;
-                    float *at = (float *)p.C + (long long)row * p.ldc + col;
-                    *at = p.accumulate ? *at + acc[i][j][v] : acc[i][j][v];
-                }
-            }
-        loads_landed();
-        return;
-    }
-    if constexpr (EPI == LM_EPI_BF16) {
-        if (parts > 1) {
-            // the partial block is dense and read only where rows and columns exist: stored whole
-            char *bw = (char *)(p.split_ws + (((long long)rest_index * parts + part) << 16) + wrow * LM_BN + wcol);
-            const unsigned voff = (unsigned)((4 * g * LM_BN + cl) * 4);
-#pragma unroll
-            for (int i = 0; i < LM_FA; ++i) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v)
-#pragma unroll
-                    for (int j = 0; j < LM_FB; ++j)
-                        *(float *)(bw + ((i * 32 + 8 * (v >> 2) + (v & 3)) * LM_BN + j * 32) * 4 + voff) = acc[i][j][v];
-                if (i == 1) loads_landed_behind_64_stores();
-            }
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < LM_FA; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + wrow + i * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                if (row >= M) continue;
-                const long long orow = p.c_rows ? p.c_rows[row] : row;
-#pragma unroll
-                for (int j = 0; j < LM_FB; ++j) {
-                    const int col = col0 + wcol + j * 32 + cl;
-                    if (col < p.N) ((__bf16 *)p.C)[orow * p.ldc + col] = (__bf16)acc[i][j][v];
-                }
-            }
-        loads_landed();
-        return;
-    }
-
-    // Softmax partials of this tile: for every row the maximum of z k over the tile's
-    // columns and the sum of exp2(z k - max), the sampled token's column left out of both
-    // (its accumulator goes to zy instead) so that 1 - p_y keeps its precision later.
-    //
-    // An accumulator block spreads a row over 32 lanes; reducing it there costs ten cross-lane
-    // steps per row.  Instead every wavefront turns its part of the tile round through LDS
-    // (free now), 64 rows at a time: written as accumulators, read back one whole row per
-    // lane, so that maximum and sum are plain loops with every lane busy, and the fp32 copy of
-    // the logits leaves in 16-byte pieces.  Rows are LM_EPI_PITCH floats apart: 16-byte aligned,
-    // and neither the row-per-lane reads nor the 16-lanes-per-row reads collide on banks.
-    constexpr int LM_EPI_PITCH = 68;
-    constexpr int LM_EPI_WAVE_BYTES = 64 * LM_EPI_PITCH * 4;
-    static_assert(8 * LM_EPI_WAVE_BYTES + (3 * LM_WN * LM_BM + LM_BM) * 4 <= LM_LDS_BYTES, "epilogue staging fits LDS");
-    static_assert(LM_FA == 4 && LM_FB == 2 && LM_WM * LM_WN == 8, "the staging below is written for 128 x 64 parts");
-    __syncthreads();  // the operand slots are free now
-    float *stage = (float *)(lm_smem + wave * LM_EPI_WAVE_BYTES);
-    float *red_m = (float *)(lm_smem + 8 * LM_EPI_WAVE_BYTES);  // [LM_WN][256]
-    float *red_s = red_m + LM_WN * LM_BM;
-    float *red_w = red_s + LM_WN * LM_BM;
-    int *ycol_s = (int *)(red_w + LM_WN * LM_BM);
-    if (tid < LM_BM) {
-        // column of the sampled token inside this tile, -1 when it is elsewhere
-        const int r = row0 + tid;
-        int yc = -1;
-        if (r < M) {
-            const int y = p.tokens32[chunk_base + r];
-            if (y >= col0 && y < col0 + LM_BN && y < p.N) yc = y - col0;
-        }
-        ycol_s[tid] = yc;
-    }
-    __syncthreads();
-    const int ncols = min(64, p.N - col0 - wcol);  // columns of this wavefront's part inside the matrix
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        // accumulators of block rows 2h, 2h + 1 -> stage[64][pitch]
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-#pragma unroll
-                for (int j = 0; j < LM_FB; ++j)
-                    stage[(ii * 32 + 8 * (v >> 2) + 4 * g + (v & 3)) * LM_EPI_PITCH + j * 32 + cl] = acc[2 * h + ii][j][v];
-        // LDS serves a wavefront's accesses in order: what follows sees these writes
-        const int rbase = wrow + h * 64;  // first of the 64 rows inside the tile
-        if (STORE_Z && col0 + wcol < p.ldz) {
-            // 16 lanes per row, four rows per instruction; the columns between N and the row
-            // pitch of Z receive the products with the clamped operand rows: never read
-            const int rr = lane >> 4, c4 = (lane & 15) * 4;
-            char *zw = (char *)(p.Z + (long long)(row0 + rbase) * p.ldz + col0 + wcol);  // ldz < 2^23: see lm_bwd_vocab_ok
-            const unsigned voff = (unsigned)((rr * p.ldz + c4) * 4);
-            if (row0 + rbase + 64 <= M) {
-#pragma unroll
-                for (int it = 0; it < 16; ++it)
-                    *(f32x4 *)(zw + it * 4 * (p.ldz * 4) + voff) =
-                        *(const f32x4 *)(stage + (it * 4 + rr) * LM_EPI_PITCH + c4);
-            } else {
-#pragma unroll
-                for (int it = 0; it < 16; ++it)
-                    if (row0 + rbase + it * 4 + rr < M)
-                        *(f32x4 *)(zw + it * 4 * (p.ldz * 4) + voff) =
-                            *(const f32x4 *)(stage + (it * 4 + rr) * LM_EPI_PITCH + c4);
-            }
-        }
-        // lane = row: take the sampled token's logit out, blank what lies outside the matrix
-        float *myrow = stage + lane * LM_EPI_PITCH;
-        const int yc = ycol_s[rbase + lane] - wcol;
-        if (yc >= 0 && yc < 64) {
-            p.zy[chunk_base + row0 + rbase + lane] = myrow[yc];
-            myrow[yc] = -INFINITY;
-        }
-        if (ncols < 64)
-            for (int c = max(ncols, 0); c < 64; ++c) myrow[c] = -INFINITY;
-        f32x4 zv[16];
-#pragma unroll
-        for (int c = 0; c < 16; ++c) zv[c] = *(const f32x4 *)(myrow + 4 * c);
-        float mz = -INFINITY;
-#pragma unroll
-        for (int c = 0; c < 16; ++c) mz = fmaxf(fmaxf(fmaxf(mz, zv[c][0]), fmaxf(zv[c][1], zv[c][2])), zv[c][3]);
-        float s0 = 0.f, s1 = 0.f;
-        if constexpr (AUX) {
-            // exponents (z - max) k, exactly 0 at the maximum: the entropy gradient of a near-one-hot
-            // row depends on it (see row_scalars_aux); elements at -inf contribute 0, not 0 * inf
-            const float refz = mz == -INFINITY ? 0.f : mz;
-            float w0 = 0.f, w1 = 0.f;
-#pragma unroll
-            for (int c = 0; c < 16; ++c)
-#pragma unroll
-                for (int e = 0; e < 4; e += 2) {
-                    const float a0 = (zv[c][e] - refz) * p.k, a1 = (zv[c][e + 1] - refz) * p.k;
-                    const float e0 = __builtin_amdgcn_exp2f(a0), e1 = __builtin_amdgcn_exp2f(a1);
-                    s0 += e0;
-                    s1 += e1;
-                    w0 = fmaf(e0, fmaxf(a0, kExpFloor), w0);
-                    w1 = fmaf(e1, fmaxf(a1, kExpFloor), w1);
-                }
-            red_w[wn * LM_BM + rbase + lane] = w0 + w1;
-        } else {
-            const float ref = mz == -INFINITY ? 0.f : mz * p.k;  // 0 for a row with nothing to sum
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                s0 += __builtin_amdgcn_exp2f(fmaf(zv[c][0], p.k, -ref)) + __builtin_amdgcn_exp2f(fmaf(zv[c][1], p.k, -ref));
-                s1 += __builtin_amdgcn_exp2f(fmaf(zv[c][2], p.k, -ref)) + __builtin_amdgcn_exp2f(fmaf(zv[c][3], p.k, -ref));
-            }
-        }
-        red_m[wn * LM_BM + rbase + lane] = mz;  // in units of z
-        red_s[wn * LM_BM + rbase + lane] = s0 + s1;
-    }
-    __syncthreads();
-    if (tid < LM_BM) {
-        const int row = row0 + tid;
-        if (row < M) {
-            float m = -INFINITY;
-#pragma unroll
-            for (int w = 0; w < LM_WN; ++w) m = fmaxf(m, red_m[w * LM_BM + tid]);
-            float s = 0.f, ws = 0.f;
-#pragma unroll
-            for (int w = 0; w < LM_WN; ++w) {
-                const float mw = red_m[w * LM_BM + tid], sw = red_s[w * LM_BM + tid];
-                if (mw != -INFINITY) {
-                    const float d = (mw - m) * p.k;  // <= 0; exactly 0 for the part that holds the maximum
-                    const float f = __builtin_amdgcn_exp2f(d);
-                    s = fmaf(sw, f, s);
-                    if constexpr (AUX) ws = fmaf(f, fmaf(d, sw, red_w[w * LM_BM + tid]), ws);
-                } else {
-                    s += sw;  // a part without a number: 0, or NaN, which the maximum has skipped
-                }
-            }
-            p.part_m[(long long)(col0 / LM_BN) * p.part_stride + row] = m;
-            p.part_s[(long long)(col0 / LM_BN) * p.part_stride + row] = s;
-            if constexpr (AUX) p.part_w[(long long)(col0 / LM_BN) * p.part_stride + row] = ws;
-        }
-    }
-    };
+    static_assert(LM_BK == 64 && LM_SLOTS == 5 && LM_LPT == 4 && LM_FA == 8 && LM_FB == 4,
+                  "the pipeline and its wait counts are written for two halves, 5 slots, 4 loads per operand tile");
 
     // Memory operations retire in order, so "at most n outstanding" means that everything older
     // than the n youngest is done.  The wait, the wait for the own LDS reads and the
     // workgroup barrier are one asm statement so that nothing is scheduled in between.
-    //
-    // All five slots are filled before an item's first k-step: A(0), B(0), A(1), B(1), A(2).  For the items
-    // after the first that happens in front of the stores of the item before (except behind the softmax
-    // epilogue, which needs the LDS itself): the loads' latency passes under the stores, and the stores drain
-    // under the first two steps - step 0 issues and waits for nothing, step 1 waits for A(2) and for B(2), which
-    // is the first load behind the stores.
-    auto prologue = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < LM_SLOTS; ++q) {
-            issue_half(q, q & 1, 0);
-            issue_half(q, q & 1, 1);
-        }
-        asm volatile("" ::: "memory");  // what follows stays behind these loads: the waits count on it
-    };
-    if (KT > 0) prologue();
-    bool fresh = true;  // the loads of the five slots are the youngest operations, and none has been waited for
+    for (int q = 0; q < 4; ++q) {
+        const Source src = source_of(q & 1, q >> 1);
+#pragma unroll
+        for (int i = 0; i < LM_LPT; ++i) issue_load(src, q & 1, q * LM_TILE_BYTES, i);
+    }
+    asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");  // A(0), B(0)
+#pragma unroll
+    for (int f = 0; f < LM_FB + LM_FA; ++f) F[0][f] = read_frag(f, slot_at(0), slot_at(1), 0);
+    lds_landed();
+    bool landed = false;  // the next step's loads are known to have landed without a wait
+    int load_kt = 2;      // K step of the item being loaded that is loaded next
 
     for (;;) {
-#pragma unroll
-    for (int i = 0; i < LM_FA; ++i)
-#pragma unroll
-        for (int j = 0; j < LM_FB; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    if (KT > 0) {
-        // every wavefront waits for its own loads (all five slots have landed unless they are fresh)
-        if (fresh) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");  // A(0), B(0)
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        read_frags(F[0], 0, 0);
-        {   // step 0
-            lds_landed();
-            read_frags(F[1], 0, 1);
-            products(F[0]);
-            interleave_reads();
-            lds_landed();
-            read_frags(F[0], 0, 2);
-            products(F[1]);
-            interleave_reads();
-            lds_landed();
-            read_frags(F[1], 0, 3);
-            products(F[0]);
-            interleave_reads();
-            if (fresh) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");  // A(1), B(1)
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // A(0), B(0) are read
-            lds_landed();
-            read_frags(F[0], 1, 0);
-            products(F[1]);
-            issue_half(5, true, 0);  // B(2) into the slot A(0) just left
-            interleave();
+        // the item being multiplied
+        const int row0 = item.row0, col0 = item.tn * LM_BN, part = item.part, parts = item.parts, block = item.block;
+        const int rows_here = min(item.height, M - row0);
+        const int steps = max(KT, 2);
+        const bool active = wm * (LM_FA * 16) < rows_here;  // else this wavefront's part has no row that exists
+        const int wrow = wm * (LM_FA * 16), wcol = wn * (LM_FB * 16);
+        int tok0 = 0, tok1 = 0;  // sampled tokens of rows `lane` and 64 + `lane` of the wavefront's part
+        if constexpr (EPI == LM_EPI_LSE) {
+            tok0 = p.tokens32[chunk_base + min(row0 + wrow + lane, M - 1)];
+            tok1 = p.tokens32[chunk_base + min(row0 + wrow + 64 + lane, M - 1)];
         }
-        for (int kt = 1; kt < KT; ++kt) {
+#pragma unroll
+        for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+            for (int j = 0; j < LM_FB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bool more = false;
+        auto landed_barrier = [&]() __attribute__((always_inline)) {
+            // outstanding, oldest first: ..., A and B of the next step, A of the one after: 4 left = the next step landed
+            if (landed)
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            landed = false;
+        };
+        if (active) {
+            for (int kt = 0; kt < steps; ++kt) {
+                if (kt == steps - 2) {  // from here on the loads are the next item's
+                    more = next_item();
+                    load_kt = 0;
+                }
+                half_step(F[0], F[1], slot_at(0), slot_at(1), 1, false, slot_at(4), load_kt);
+                landed_barrier();
+                lds_landed();  // (for the compiler, which does not look into the statement above)
+                half_step(F[1], F[0], slot_at(2), slot_at(3), 0, true, slot_at(0), load_kt);
+                lds_landed();
+                ++load_kt;
+                slot += 2;
+                if (slot >= LM_SLOTS) slot -= LM_SLOTS;
+            }
+        } else {
+            for (int kt = 0; kt < steps; ++kt) {
+                if (kt == steps - 2) {
+                    more = next_item();
+                    load_kt = 0;
+                }
+                const Source a_src = source_of(false, load_kt), b_src = source_of(true, load_kt);
+#pragma unroll
+                for (int i = 0; i < LM_LPT; ++i) issue_load(a_src, false, slot_at(4), i);
+                landed_barrier();
+#pragma unroll
+                for (int i = 0; i < LM_LPT; ++i) issue_load(b_src, true, slot_at(0), i);
+                ++load_kt;
+                slot += 2;
+                if (slot >= LM_SLOTS) slot -= LM_SLOTS;
+            }
+#pragma unroll
+            for (int f = 0; f < LM_FB + LM_FA; ++f) F[0][f] = read_frag(f, slot_at(0), slot_at(1), 0);
             lds_landed();
-            read_frags(F[1], kt, 1);
-            products(F[0]);
-            issue_half(2 * kt + 3, true, 1);   // rest of B(kt + 1)
-            interleave();
-            lds_landed();
-            read_frags(F[0], kt, 2);
-            products(F[1]);
-            issue_half(2 * kt + 4, false, 0);  // A(kt + 2)
-            interleave();
-            lds_landed();
-            read_frags(F[1], kt, 3);
-            products(F[0]);
-            issue_half(2 * kt + 4, false, 1);
-            interleave();
-            // outstanding, oldest first: ..., B(kt + 1), A(kt + 2): 4 left = tile kt + 1 landed
-            asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            lds_landed();
-            read_frags(F[0], kt + 1, 0);
-            products(F[1]);
-            issue_half(2 * kt + 5, true, 0);   // B(kt + 2) into the slot A(kt) just left
-            interleave();
         }
-        // the last steps' loads (of the last tile again) and everybody's reads of the slots are done
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    }  // KT > 0
 
-    const int row0_c = row0, col0_c = col0, part_c = part, parts_c = parts, rest_c = rest_index;  // the item being stored
-    bool more = false;
-    fresh = EPI == LM_EPI_LSE;
-    if constexpr (EPI != LM_EPI_LSE) {
-        more = next_item();
-        if (more && KT > 0) prologue();
-    }
-    store_item(row0_c, col0_c, part_c, parts_c, rest_c);
-    if constexpr (EPI == LM_EPI_LSE) {
-        more = next_item();
-        if (more) {
-            __syncthreads();  // the staging area is free
-            if (KT > 0) prologue();
+        // The result is stored while the next item's first two steps are on their way: they have landed when no more
+        // operations are outstanding than the stores issued since.
+        auto loads_landed = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+        auto loads_landed_behind_stores = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(32)" ::: "memory"); };
+        landed = true;
+        int ln = lane;  // opaque, as above
+        asm volatile("" : "+v"(ln));
+        const int n = ln & 15, g = ln >> 4;  // this lane's place in a block, see half_step
+        // the wavefront's part as the accumulators lie, 1 KB a store
+        auto store_blocks = [&](float *base) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+                for (int j = 0; j < LM_FB; ++j) *(f32x4 *)(base + ((i * LM_FB + j) * 64 + ln) * 4) = acc[i][j];
+        };
+
+        if constexpr (EPI == LM_EPI_F32) {
+            if (!active || col0 + wcol >= p.N) {  // N is a multiple of 64: a part's columns are all inside or all outside
+                loads_landed();
+            } else {
+                // this lane's columns 4 n .. 4 n + 3 (see lm_column_of), rows 16 i + 4 g + v
+                float *cw = (float *)p.C + (long long)(row0 + wrow) * p.ldc + col0 + wcol;
+                const int rows = min(rows_here - wrow, LM_FA * 16);
+                const unsigned voff = (unsigned)((4 * g * p.ldc + 4 * n) * 4);
+                if ((((unsigned long long)p.C | (unsigned long long)(p.ldc * 4)) & 15u) != 0 || p.ldc >= (1ll << 26)) {
+                    // C itself not in whole 16-byte pieces: element by element
+#pragma unroll
+                    for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int r = i * 16 + 4 * g + v;
+                            if (r >= rows) continue;
+                            float *at = cw + (long long)r * p.ldc + 4 * n;
+#pragma unroll
+                            for (int j = 0; j < LM_FB; ++j) at[j] = p.accumulate ? at[j] + acc[i][j][v] : acc[i][j][v];
+                        }
+                    loads_landed();
+                } else if (p.accumulate) {
+                    // C += result: all loads of two block rows first, then the sums and stores (a dependent load in
+                    // front of every store made this epilogue take 2 ms longer than the plain store)
+#pragma unroll
+                    for (int i = 0; i < LM_FA; i += 2) {
+                        f32x4 old[8];
+                        char *at = (char *)(cw + (long long)i * 16 * p.ldc);
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            old[q] = (i + q / 4) * 16 + 4 * g + q % 4 < rows
+                                         ? *(const f32x4 *)(at + ((q / 4) * 16 + q % 4) * (p.ldc * 4) + voff)
+                                         : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+#pragma unroll
+                            for (int j = 0; j < LM_FB; ++j) old[q][j] += acc[i + q / 4][j][q % 4];
+                            if ((i + q / 4) * 16 + 4 * g + q % 4 < rows)
+                                __builtin_nontemporal_store(old[q], (f32x4 *)(at + ((q / 4) * 16 + q % 4) * (p.ldc * 4) + voff));
+                        }
+                    }
+                    loads_landed();
+                } else {
+#pragma unroll
+                    for (int i = 0; i < LM_FA; ++i)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            if (rows < LM_FA * 16 && i * 16 + 4 * g + v >= rows) continue;
+                            __builtin_nontemporal_store(f32x4{acc[i][0][v], acc[i][1][v], acc[i][2][v], acc[i][3][v]},
+                                                        (f32x4 *)((char *)cw + (i * 16 + v) * (p.ldc * 4) + voff));
+                        }
+                    if (rows == LM_FA * 16)
+                        loads_landed_behind_stores();  // 32 of them
+                    else
+                        loads_landed();
+                }
+            }
         }
+        if constexpr (EPI == LM_EPI_BF16) {
+            if (!active || col0 + wcol >= p.N) {
+                loads_landed();
+            } else if (parts > 1) {
+                // read only where rows and columns exist: stored whole
+                store_blocks(p.split_ws + ((long long)block << 16) + wave * (LM_FA * LM_FB * 256));
+                loads_landed_behind_stores();
+            } else {
+                const bool quads = (((unsigned long long)p.C | (unsigned long long)(p.ldc * 2)) & 7u) == 0;
+#pragma unroll
+                for (int i = 0; i < LM_FA; ++i) {
+                    const int r = wrow + i * 16 + n;
+                    if (r >= rows_here) continue;
+                    const long long orow = p.c_rows ? p.c_rows[row0 + r] : row0 + r;
+                    __bf16 *at = (__bf16 *)p.C + orow * p.ldc + col0 + wcol + 4 * g;
+#pragma unroll
+                    for (int j = 0; j < LM_FB; ++j) {
+                        const bf16x2 lo = __builtin_convertvector((f32x2){acc[i][j][0], acc[i][j][1]}, bf16x2);
+                        const bf16x2 hi = __builtin_convertvector((f32x2){acc[i][j][2], acc[i][j][3]}, bf16x2);
+                        if (quads) {
+                            *(u32x2 *)(at + j * 16) = u32x2{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
+                        } else {
+                            at[j * 16] = lo[0];
+                            at[j * 16 + 1] = lo[1];
+                            at[j * 16 + 2] = hi[0];
+                            at[j * 16 + 3] = hi[1];
+                        }
+                    }
+                }
+                loads_landed();
+            }
+        }
+        if constexpr (EPI == LM_EPI_LSE) {
+            // Softmax partials of this tile: for every row the maximum of z over the tile's
+            // columns and the sum of exp2((z - max) k), the sampled token's column left out of both
+            // (its accumulator goes to zy instead) so that 1 - p_y keeps its precision later.
+            //
+            // A lane holds 16 of a row's 64 columns in this wavefront's part, the four lanes n, n + 16, n + 32, n + 48 the
+            // whole of them: two exchanges finish a row, and no accumulator passes through LDS.  Only the partials of
+            // the four wavefronts that share a row meet there, in the one slot of the ring that is free between two items.
+            float *red_m = (float *)(lm_smem + slot_at(4));  // [LM_WN][256]
+            float *red_s = red_m + LM_WN * LM_BM;
+            float *red_w = red_s + LM_WN * LM_BM;
+            static_assert(3 * LM_WN * LM_BM * 4 <= LM_TILE_BYTES, "the partials fit the free slot");
+            if (active) {
+                const int ncols = max(0, min(LM_FB * 16, p.N - col0 - wcol));  // columns of this part inside the matrix
+                // the columns of the sampled tokens inside this part: mostly nowhere
+                const unsigned y0 = (unsigned)(tok0 - col0 - wcol), y1 = (unsigned)(tok1 - col0 - wcol);
+                const bool y_here = __any(y0 < (unsigned)ncols || y1 < (unsigned)ncols);
+                auto both = [](float a, auto op) __attribute__((always_inline)) {  // op over lanes n, n + 16, n + 32, n + 48
+                    // (the bits go through scalars: of an element of a vector, __builtin_bit_cast takes the first one)
+                    auto q = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, a),
+                                                              false, false);
+                    unsigned u0 = q[0], u1 = q[1];
+                    a = op(__builtin_bit_cast(float, u0), __builtin_bit_cast(float, u1));
+                    q = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, a), false,
+                                                         false);
+                    u0 = q[0], u1 = q[1];
+                    return op(__builtin_bit_cast(float, u0), __builtin_bit_cast(float, u1));
+                };
+                auto add = [](float a, float b) __attribute__((always_inline)) { return a + b; };
+                auto larger = [](float a, float b) __attribute__((always_inline)) { return fmaxf(a, b); };
+                float out_m[2] = {0.f, 0.f}, out_s[2] = {0.f, 0.f}, out_w[2] = {0.f, 0.f};
+#pragma unroll
+                for (int i = 0; i < LM_FA; ++i) {
+                    float z[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) z[e] = acc[i][e >> 2][e & 3];
+                    if (y_here) {
+                        const int yc = (int)__shfl(i < 4 ? y0 : y1, 16 * (i & 3) + n, 64);
+                        // the sampled token's place among this lane's 16 columns
+                        const int at = (unsigned)yc < (unsigned)ncols && ((yc >> 2) & 3) == g ? 4 * (yc >> 4) + (yc & 3) : -1;
+                        if (__any(at >= 0)) {
+                            const int r = row0 + wrow + i * 16 + n;
+                            float zy = 0.f;
+#pragma unroll
+                            for (int e = 0; e < 16; ++e) {
+                                zy = e == at ? z[e] : zy;
+                                z[e] = e == at ? -INFINITY : z[e];
+                            }
+                            if (at >= 0 && r < M) p.zy[chunk_base + r] = zy;
+                        }
+                    }
+                    if (ncols < LM_FB * 16) {
+#pragma unroll
+                        for (int e = 0; e < 16; ++e)
+                            if (16 * (e >> 2) + (e & 3) >= ncols - 4 * g) z[e] = -INFINITY;
+                    }
+                    float mz = fmaxf(z[0], z[1]);
+#pragma unroll
+                    for (int e = 2; e < 16; e += 2) mz = fmaxf(fmaxf(mz, z[e]), z[e + 1]);
+                    mz = both(mz, larger);
+                    float s0 = 0.f, s1 = 0.f, w0 = 0.f, w1 = 0.f;
+                    if constexpr (AUX) {
+                        // exponents (z - max) k, exactly 0 at the maximum: the entropy gradient of a near-one-hot
+                        // row depends on it (see row_scalars_aux); elements at -inf contribute 0, not 0 * inf
+                        const float refz = mz == -INFINITY ? 0.f : mz;
+#pragma unroll
+                        for (int e = 0; e < 16; e += 2) {
+                            const float a0 = (z[e] - refz) * p.k, a1 = (z[e + 1] - refz) * p.k;
+                            const float e0 = __builtin_amdgcn_exp2f(a0), e1 = __builtin_amdgcn_exp2f(a1);
+                            s0 += e0;
+                            s1 += e1;
+                            w0 = fmaf(e0, fmaxf(a0, kExpFloor), w0);
+                            w1 = fmaf(e1, fmaxf(a1, kExpFloor), w1);
+                        }
+                        w0 = both(w0 + w1, add);
+                    } else {
+                        const float ref = mz == -INFINITY ? 0.f : mz * p.k;  // 0 for a row with nothing to sum
+#pragma unroll
+                        for (int e = 0; e < 16; e += 2) {
+                            s0 += __builtin_amdgcn_exp2f(fmaf(z[e], p.k, -ref));
+                            s1 += __builtin_amdgcn_exp2f(fmaf(z[e + 1], p.k, -ref));
+                        }
+                    }
+                    s0 = both(s0 + s1, add);
+                    if (g == (i & 3)) {  // lane 16 g + n keeps rows `lane` and 64 + `lane` of the part
+                        out_m[i >> 2] = mz;  // in units of z
+                        out_s[i >> 2] = s0;
+                        out_w[i >> 2] = w0;
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    red_m[wn * LM_BM + wrow + q * 64 + ln] = out_m[q];
+                    red_s[wn * LM_BM + wrow + q * 64 + ln] = out_s[q];
+                    if constexpr (AUX) red_w[wn * LM_BM + wrow + q * 64 + ln] = out_w[q];
+                }
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (tid < rows_here) {  // at most 256
+                const int row = row0 + tid;
+                float m = -INFINITY;
+#pragma unroll
+                for (int w = 0; w < LM_WN; ++w) m = fmaxf(m, red_m[w * LM_BM + tid]);
+                float s = 0.f, ws = 0.f;
+#pragma unroll
+                for (int w = 0; w < LM_WN; ++w) {
+                    const float mw = red_m[w * LM_BM + tid], sw = red_s[w * LM_BM + tid];
+                    if (mw != -INFINITY) {
+                        const float d = (mw - m) * p.k;  // <= 0; exactly 0 for the part that holds the maximum
+                        const float f = __builtin_amdgcn_exp2f(d);
+                        s = fmaf(sw, f, s);
+                        if constexpr (AUX) ws = fmaf(f, fmaf(d, sw, red_w[w * LM_BM + tid]), ws);
+                    } else {
+                        s += sw;  // a part without a number: 0, or NaN, which the maximum has skipped
+                    }
+                }
+                p.part_m[(long long)(col0 / LM_BN) * p.part_stride + row] = m;
+                p.part_s[(long long)(col0 / LM_BN) * p.part_stride + row] = s;
+                if constexpr (AUX) p.part_w[(long long)(col0 / LM_BN) * p.part_stride + row] = ws;
+            }
+            // the slot is free again for the next item's loads when every wavefront has read its partials
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            loads_landed();
+            // the fp32 copy of the logits, rows past the last one and the columns between N and the row pitch of Z with the
+            // products of the clamped operand rows: never read
+            if (STORE_Z && active && col0 + wcol < p.ldz)  // ldz < 2^23: see lm_bwd_vocab_ok
+                store_blocks(p.Z + lm_z_part(row0 + wrow, col0 + wcol, p.ldz));
+        }
+        if (!more) break;
     }
-    if (!more) return;
-    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the loads behind the last item write zeros to LDS until they are done
 }
 
 // Per-row arrays the fused path keeps between its kernels.  Rows that take part (mask 1,
 // token id inside the vocabulary) are compacted: "compact row i" is original row rows[i],
 // i < *n_live.  Of those, the ones with a gradient (c != 0) are compacted once more for
-// the backward: "gradient row j" is compact row rows2[j], original row orig2[j], j < *n_grad.
+// the backward: row i of the chunk is gradient row pos2[i] (-1: none), gradient row j is original row orig2[j], j < *n_grad.
 // The masked tail of every rollout and the clipped tokens then cost no matrix work at all.
 struct LmRows {
     int *rows, *tokens32, *n_live;   // [n], [n] (by compact row), [1]
-    int *rows2, *orig2, *n_grad;     // [n], [n], [1]
+    int *pos2, *orig2, *n_grad;      // [cap] (by row inside the chunk), [cap], [1]
     float *zy;     // by compact row: logit of the sampled token (fp32 accumulator)
     float *shift;  // max k + log2(sum): p_j = exp2(z_j k - shift)
     float *q;      // c / T
@@ -951,16 +864,20 @@ __global__ void __launch_bounds__(LM_TAKE_THREADS) lm_take_rows(RowParams p, LmR
     }
 }
 
-// Compact rows of the current chunk with a gradient -> rows2[] (compact row), orig2[] (original
-// row), *n_grad.
+// Compact rows of the current chunk with a gradient -> pos2[] (by row of the chunk: its place among them, or -1),
+// orig2[] (original row), *n_grad.
 __global__ void __launch_bounds__(1024) lm_select_grad_rows(LmRows w)
 {
     int base, count;
     lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, base, count);
     const int total = lm_ordered_select(
-        count, [&](long long j) { return w.q[base + j] != 0.f || (w.bq && w.bq[base + j] != 0.f); },
+        count,
+        [&](long long j) {
+            w.pos2[j] = -1;
+            return w.q[base + j] != 0.f || (w.bq && w.bq[base + j] != 0.f);
+        },
         [&](int pos, long long j) {
-            w.rows2[pos] = base + (int)j;
+            w.pos2[j] = pos;
             w.orig2[pos] = w.rows[base + j];
         });
     if (threadIdx.x == 0) *w.n_grad = total;
@@ -1081,9 +998,8 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
 // elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
 // 8-byte aligned (the operands of this path: d_model is a multiple of 64, rows 16-byte aligned).
 __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *in, long long ldi, int R, const int *rowmap,
-                                                  int C, __bf16 *out, long long ldo)
+                                                  int C, __bf16 *out, long long ldo, unsigned short (*tile)[66])
 {
-    __shared__ unsigned short tile[64][66];
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;  // 16 lanes x 4 elements across, 16 down
     const unsigned short *src = (const unsigned short *)in;
     unsigned short *dst = (unsigned short *)out;
@@ -1114,8 +1030,9 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
 }
 
 // G = dL/dz in bf16 for the chunk's gradient rows, row-major [n_grad][ldg], from the fp32 logits:
-// g_j = -q p_j, g_y = q (1 - p_y).  A wavefront takes 512 consecutive entries of a row, eight per lane
-// (two 16-byte reads, one 16-byte write); a workgroup 16 rows of them.  Padding is written as zeros: the
+// g_j = -q p_j, g_y = q (1 - p_y).  A wavefront takes 16 rows of Z x 128 entries.  A lane reads 16 bytes, four entries of row
+// lane % 16 (the rows' own values are read once), as Z lies: 1 KB a wavefront; the rows are turned round through
+// LDS and leave 256 bytes at a time, each to its place among the gradient rows.  Padding is written as zeros: the
 // columns V .. ldg (dL/dH runs over whole K steps of the vocabulary) and the rows n_grad .. the next
 // multiple of 64 (dL/dW runs over whole K steps of rows).
 constexpr int LM_GL_COLS = 512, LM_GL_ROWS = 16;
@@ -1124,93 +1041,132 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
                                                       float k, __bf16 *G, long long ldg, int col_groups, unsigned gl_blocks,
                                                       const __bf16 *hidden, long long ldh, int d, __bf16 *Ht, long long ldht)
 {
+    constexpr int WAVE_COLS = LM_GL_COLS / 4, PITCH = WAVE_COLS * 2 + 16;  // bytes: 16-byte aligned rows, 4 banks apart
+    __shared__ __attribute__((aligned(16))) char turn_all[4 * LM_GL_ROWS * PITCH];
+    static_assert(sizeof(turn_all) >= 64 * 66 * 2, "the tile that is turned round for H^T fits");
     if (blockIdx.x >= gl_blocks) {  // H^T of the chunk's gradient rows, [d][ldht]: independent of G, in the same launch
         const int t = (int)(blockIdx.x - gl_blocks), across = (int)(ldht / 64);
         const int n = *w.n_grad;
         // columns past the rows that exist are read as zeros up to the next whole K step, and not at all beyond it
         if (t % across * 64 < (n + 63) / 64 * 64)
-            lm_transpose_tile(t % across * 64, t / across * 64, hidden, ldh, n, w.orig2, d, Ht, ldht);
+            lm_transpose_tile(t % across * 64, t / across * 64, hidden, ldh, n, w.orig2, d, Ht, ldht,
+                              (unsigned short(*)[66])turn_all);
         return;
     }
     const int n2 = *w.n_grad, n2_pad = (n2 + 63) / 64 * 64;
     const int r0 = (int)(blockIdx.x / (unsigned)col_groups) * LM_GL_ROWS;
-    if (r0 >= n2_pad) return;  // LM_GL_ROWS divides 64: a workgroup's rows are all inside or all outside
     int zbase, zcount;  // Z holds the current chunk's rows only
     lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, zbase, zcount);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int c = (int)(blockIdx.x % (unsigned)col_groups) * LM_GL_COLS + lane * 8;
-    if (c >= ldg) return;  // ldg is a multiple of 64: whole groups of eight
+    if (r0 >= zcount && r0 >= n2_pad) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+    const int c0 = (int)(blockIdx.x % (unsigned)col_groups) * LM_GL_COLS + wv * WAVE_COLS;  // this wavefront's columns
+    char *turn = turn_all + wv * (LM_GL_ROWS * PITCH);
+    const int ci = zbase + r0 + n;  // this lane's compact row
+    // all of this lane's logits at once, whether the row has a gradient or not (Z is there up to whole parts); V <= ldz,
+    // which is a multiple of 64
+    f32x4 z[WAVE_COLS / 16];
+#pragma unroll
+    for (int it = 0; it < WAVE_COLS / 16; ++it) {
+        const int c = c0 + it * 16 + 4 * g;
+        z[it] = r0 < zcount && c < ldz ? *(const f32x4 *)(Z + lm_z_part(r0, c, ldz) + lm_z_in_part(r0 + n, c)) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int pos = r0 + n < zcount ? w.pos2[r0 + n] : -1;
+    float q = 0.f, sh = 0.f, mxr = 0.f, l2s = 0.f, q2 = 0.f, bq = 0.f, gy = 0.f;
+    int y = -1;
+    if (r0 + n < zcount) {  // (of a row without a gradient nothing is stored)
+        if constexpr (AUX) {
+            mxr = w.mx[ci], l2s = w.log2s[ci], q2 = w.q2[ci], bq = w.bq[ci];
+        } else {
+            q = w.q[ci], sh = w.shift[ci];
+        }
+        gy = w.gy[ci];
+        y = w.tokens32[ci];
+    }
+    const int yc = y - c0 - 4 * g, ncols = V - c0 - 4 * g;  // the sampled token and the end of the row, from this lane's first column
+    const bool whole = c0 + WAVE_COLS <= V;
+#pragma unroll
+    for (int it = 0; it < WAVE_COLS / 16; ++it) {
+        float gv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (AUX) {
+                // g_j = p_j (q2 + bq log2 p_j): policy, KL and entropy parts in one (see grad_vec_aux)
+                const float a = fmaxf(fmaf(z[it][e] - mxr, k, -l2s), kExpFloor);
+                gv[e] = __builtin_amdgcn_exp2f(a) * fmaf(bq, a, q2);
+            } else {
+                gv[e] = -q * __builtin_amdgcn_exp2f(fmaf(z[it][e], k, -sh));
+            }
+            gv[e] = it * 16 + e == yc ? gy : gv[e];
+        }
+        if (!whole) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) gv[e] = it * 16 + e >= ncols ? 0.f : gv[e];
+        }
+        const bf16x2 lo = __builtin_convertvector((f32x2){gv[0], gv[1]}, bf16x2);
+        const bf16x2 hi = __builtin_convertvector((f32x2){gv[2], gv[3]}, bf16x2);
+        *(u32x2 *)(turn + n * PITCH + (it * 16 + 4 * g) * 2) = u32x2{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
+    }
+    // LDS serves a wavefront's accesses in order: no barrier.  16 lanes to a row, four rows a store
+    const int c = c0 + n * 8;
 #pragma unroll
     for (int i = 0; i < LM_GL_ROWS / 4; ++i) {
-        const int r = r0 + wv + 4 * i;
-        float gv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (r < n2 && c < V) {
-            const int ci = w.rows2[r];
-            float q = 0.f, sh = 0.f, mxr = 0.f, l2s = 0.f, q2 = 0.f, bq = 0.f;
-            if constexpr (AUX) {
-                mxr = w.mx[ci], l2s = w.log2s[ci], q2 = w.q2[ci], bq = w.bq[ci];
-            } else {
-                q = w.q[ci], sh = w.shift[ci];
-            }
-            const int y = w.tokens32[ci];
-            const float *zrow = Z + (long long)(ci - zbase) * ldz + c;
-            float z[8];
-            if (c + 7 < V) {
-                const f32x4 z0 = *(const f32x4 *)zrow, z1 = *(const f32x4 *)(zrow + 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) z[e] = z0[e], z[4 + e] = z1[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) z[e] = c + e < V ? zrow[e] : -INFINITY;
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if constexpr (AUX) {
-                    // g_j = p_j (q2 + bq log2 p_j): policy, KL and entropy parts in one (see grad_vec_aux)
-                    const float a = fmaxf(fmaf(z[e] - mxr, k, -l2s), kExpFloor);
-                    gv[e] = __builtin_amdgcn_exp2f(a) * fmaf(bq, a, q2);
-                } else {
-                    gv[e] = -q * __builtin_amdgcn_exp2f(fmaf(z[e], k, -sh));
-                }
-                if (c + e == y) gv[e] = w.gy[ci];
-                if (c + e >= V) gv[e] = 0.f;
-            }
+        const int r = 4 * i + g;
+        const u32x4 out = *(const u32x4 *)(turn + r * PITCH + n * 16);
+        const int to = __shfl(pos, r, 64);  // lane r < 16 holds row r's
+        if (c < ldg) {                      // ldg is a multiple of 64: whole groups of eight
+            if (to >= 0) *(u32x4 *)(G + (long long)to * ldg + c) = out;
+            if (r0 + r >= n2 && r0 + r < n2_pad) *(u32x4 *)(G + (long long)(r0 + r) * ldg + c) = u32x4{0u, 0u, 0u, 0u};
         }
-        u32x4 out;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            out[e] = __builtin_bit_cast(unsigned, __builtin_convertvector((f32x2){gv[2 * e], gv[2 * e + 1]}, bf16x2));
-        *(u32x4 *)(G + (long long)r * ldg + c) = out;
     }
 }
 
 // Sum of the parts of the tiles lm_gemm_nt has cut: C[c_rows[r]][:] = bf16(sum over s of the
 // tile's partial blocks) for the rows present, parts in order.  Does nothing when no tile was cut.
 __global__ void __launch_bounds__(256) lm_split_reduce(const float *ws, const int *M_dev, int M, int N, int tiles_n,
-                                                       int k_tiles, int max_items, int n_cu, int group_m,
+                                                       int k_tiles, int max_items, int n_cu,
                                                        const int *c_rows, __bf16 *C, long long ldc)
 {
     const int rows = M_dev ? min(*M_dev, M) : M;
-    const int tiles_m = (rows + LM_BM - 1) / LM_BM;
-    const LmSplit sp = lm_plan_split(tiles_m * tiles_n, k_tiles, max_items, n_cu);
-    if (sp.s2 == 1) return;
-    constexpr int quads = LM_BN / 4;
-    const long long total = (long long)sp.rest * LM_BM * quads;
+    const LmPlan pl = lm_plan(rows, tiles_n, k_tiles, true, max_items, n_cu);
+    if (pl.s2 == 1) return;
+    // 16 bytes a lane, as lm_gemm_nt's wavefronts have stored them; whole tiles first, then thin ones (wavefronts 0 .. 3)
+    constexpr int quads = LM_BM * LM_BN / 4;
+    const long long rest = (long long)pl.rest * quads, total = rest + (long long)pl.thin * (quads / 2);
     for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long long)gridDim.x * 256) {
-        const int t = (int)(e / (LM_BM * quads)), in_tile = (int)(e % (LM_BM * quads));
-        const int r = in_tile / quads, c = in_tile % quads * 4;
-        int tm, tn;
-        lm_tile_of(sp.full + t, tiles_m, tiles_n, group_m, tm, tn);
-        const int row = tm * LM_BM + r, col = tn * LM_BN + c;
-        if (row >= rows || col >= N) continue;  // N is a multiple of LM_BK: a quad is inside or outside
-        const float *src = ws + (((long long)t * sp.s2) << 16) + r * LM_BN + c;
+        int row, col, parts, q;
+        const float *src;
+        if (e < rest) {
+            const int t = (int)(e / quads);
+            q = (int)(e % quads);
+            int tm, tn;
+            lm_tile_of(pl.full + t, pl.rows_w, tiles_n, tm, tn);
+            row = tm * LM_BM, col = tn * LM_BN, parts = pl.s2;
+            src = ws + (((long long)t * pl.s2) << 16) + q * 4;
+        } else {
+            const long long e2 = e - rest;
+            const int t = (int)(e2 / (quads / 2));
+            q = (int)(e2 % (quads / 2));
+            row = pl.rows_w * LM_BM, col = t * LM_BN, parts = pl.t2;
+            src = ws + (((long long)pl.rest * pl.s2 + (long long)t * pl.t2) << 16) + q * 4;
+        }
+        const int wave = q / (LM_FA * LM_FB * 64), lane = q & 63;
+        row += wave / LM_WN * (LM_FA * 16) + (q / (LM_FB * 64)) % LM_FA * 16 + (lane & 15);
+        col += wave % LM_WN * (LM_FB * 16) + (q / 64) % LM_FB * 16 + 4 * (lane >> 4);
+        if (row >= rows || col >= N || parts == 1) continue;  // N is a multiple of LM_BK: a quad is inside or outside
         f32x4 a = *(const f32x4 *)src;
-        for (int s = 1; s < sp.s2; ++s) a += *(const f32x4 *)(src + ((long long)s << 16));
+#pragma unroll 8
+        for (int s = 1; s < parts; ++s) a += *(const f32x4 *)(src + ((long long)s << 16));
         const bf16x2 lo = __builtin_convertvector((f32x2){a[0], a[1]}, bf16x2);
         const bf16x2 hi = __builtin_convertvector((f32x2){a[2], a[3]}, bf16x2);
-        unsigned *dst = (unsigned *)(C + (long long)(c_rows ? c_rows[row] : row) * ldc + col);
-        dst[0] = __builtin_bit_cast(unsigned, lo);
-        dst[1] = __builtin_bit_cast(unsigned, hi);
+        __bf16 *dst = C + (long long)(c_rows ? c_rows[row] : row) * ldc + col;
+        if ((((unsigned long long)C | (unsigned long long)(ldc * 2)) & 7u) == 0) {
+            *(u32x2 *)dst = u32x2{__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi)};
+        } else {
+            dst[0] = lo[0];
+            dst[1] = lo[1];
+            dst[2] = hi[0];
+            dst[3] = hi[1];
+        }
     }
 }
 
@@ -1242,17 +1198,16 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
         attr_done[dev].store(true);
     }
     p.tiles_n = (p.N + LM_BN - 1) / LM_BN;
-    if (p.group_m <= 0) p.group_m = LM_GROUP_M;
     // One workgroup for each CU, on whole XCDs; fewer when there cannot be as many tiles.
     p.n_cu = cu_count();
-    const long long most = EPI == LM_EPI_BF16 && p.split_items > 0 ? p.n_cu : (long long)((p.M + LM_BM - 1) / LM_BM) * p.tiles_n;
+    const long long most = EPI == LM_EPI_BF16 && p.split_items > 0 ? p.n_cu : 2 * (long long)((p.M + LM_BM - 1) / LM_BM) * p.tiles_n;
     const long long grid = std::max<long long>(8, std::min<long long>(p.n_cu / 8, (most + 7) / 8) * 8);
     hipLaunchKernelGGL((lm_gemm_nt<EPI, STORE_Z, AUX, AKM, BKM>), dim3((unsigned)grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
     return hipGetLastError();
 }
 
 struct LmLayout {
-    size_t rows, tokens32, rows2, orig2, counts, zy, shift, q, gy, mx, log2s, q2, bq, part_m, part_s, part_w, Hc, Z, G, Ht,
+    size_t rows, tokens32, pos2, orig2, counts, zy, shift, q, gy, mx, log2s, q2, bq, part_m, part_s, part_w, Hc, Z, G, Ht,
         total;
     long long ldz, ldg, ldgt;  // vocab and chunk rows rounded up to whole K steps
     int tiles_n;
@@ -1290,7 +1245,7 @@ LmLayout lm_layout(int64_t n, int64_t V, int64_t d, bool bwd, int64_t cap)
     L.part_s = take((size_t)L.tiles_n * cap * 4);
     L.Hc = take((size_t)n * d * 2);
     if (bwd) {
-        L.rows2 = take((size_t)cap * 4);
+        L.pos2 = take((size_t)cap * 4);
         L.orig2 = take((size_t)cap * 4);
         L.shift = take((size_t)n * 4);
         L.q = take((size_t)n * 4);
@@ -1421,7 +1376,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             w.bq = (float *)(ws + L.bq);
         }
         if (bwd) {
-            w.rows2 = (int *)(ws + L.rows2);
+            w.pos2 = (int *)(ws + L.pos2);
             w.orig2 = (int *)(ws + L.orig2);
             w.shift = (float *)(ws + L.shift);
             w.q = (float *)(ws + L.q);
@@ -1538,7 +1493,6 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             gh.C = grad_hidden;
             gh.ldc = grad_hidden_stride;
             gh.c_rows = w.orig2;
-            gh.group_m = LM_GM_BWD;
             // The fp32 logits are no longer needed: their space takes the partial results (blocks of
             // 256 x 256 fp32) of the tiles whose contraction over the vocabulary is cut into parts.
             const size_t z_blocks = (size_t)cap * (size_t)L.ldz * 4 / ((size_t)LM_BM * LM_BN * 4);
@@ -1549,7 +1503,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             if (gh.split_items > 0)
                 hipLaunchKernelGGL(lm_split_reduce, dim3(2048), dim3(256), 0, st, (const float *)gh.split_ws,
                                    (const int *)w.n_grad, Mc, D, (D + LM_BN - 1) / LM_BN, (int)(L.ldg / LM_BK),
-                                   gh.split_items, n_cu, LM_GM_BWD, (const int *)w.orig2, (__bf16 *)grad_hidden,
+                                   gh.split_items, n_cu, (const int *)w.orig2, (__bf16 *)grad_hidden,
                                    (long long)grad_hidden_stride);
 
             GemmParams gw = {};  // dL/dW [V][d] (+)= G^T . H over the chunk's gradient rows; G is read as it lies,
@@ -1566,7 +1520,6 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             gw.C = grad_weight;
             gw.ldc = grad_weight_stride;
             gw.accumulate = (accumulate_grad_weight || c > 0) ? 1 : 0;  // the first chunk starts the sum
-            gw.group_m = LM_GM_BWD;
             e = lm_launch_gemm<LM_EPI_F32, false, false, true, false>(gw, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
         }

@@ -1,0 +1,49 @@
+"""Sizes at which the head's products change how they divide their work: rows around 128 and 256 (whole, thin and
+halved tiles), vocabularies around the 64 columns of a wavefront's part and the 256 of a tile, one and two K steps,
+contractions that are cut and that are not.  Against the fp64 oracle, element by element (run_case)."""
+import pytest
+import torch
+
+import paper_2505_07291_amd as grpo
+import paper_2505_07291_amd.workloads as wl
+from test_gpu_lmhead_parity import DEV, run_case
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [
+    # rows, vocab, d_model
+    (2, 60, 64), (2, 64, 128), (126, 65, 64), (128, 128, 192), (130, 250, 64), (254, 256, 128), (256, 257, 64),
+    (258, 320, 64), (384, 321, 128), (386, 900, 64), (640, 1000, 64),
+    (130, 5000, 64),    # dL/dH: thin tiles and whole ones, both cut along the vocabulary
+    (256, 9000, 576),   # dL/dW: 108 tiles, halved; dL/dH: three tiles in many parts
+    (258, 20000, 64),   # 79 whole tiles, halved, and 79 thin ones
+    (514, 20000, 64),   # 158 whole tiles: not halved
+]
+
+
+@pytest.mark.parametrize("rows,vocab,d", SIZES)
+def test_every_element_around_tile_edges(rows, vocab, d):
+    cfg = wl.CONFIGS["numerics_stress"].scaled(n_prompts=1, seq_len=rows // 2, vocab=vocab, group_size=2)
+    run_case(cfg, d, label="%dx%dx%d" % (rows, vocab, d), products="library" if rows * vocab * d > 10 ** 8 else "loops")
+
+
+# results whose rows do not lie on 16 (dL/dW) or 8 bytes (dL/dH) are stored element by element: the same bits
+@pytest.mark.parametrize("rows,vocab,d", [(130, 300, 128), (300, 700, 64)])
+def test_results_at_odd_pitches_and_offsets(rows, vocab, d):
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    h = torch.randn(rows, d, generator=g, device=DEV).bfloat16()
+    w = (torch.randn(vocab, d, generator=g, device=DEV) * 0.2).bfloat16()
+    tokens = torch.randint(0, vocab, (rows,), generator=g, device=DEV)
+    adv = torch.randn(rows, generator=g, device=DEV)
+    old = grpo.grpo_lmhead_logprobs_fwd(h, w, tokens) + 0.1 * torch.randn(rows, generator=g, device=DEV)
+    call = lambda **kw: grpo.grpo_lmhead_loss_fwd_bwd(h, w, tokens, old, adv, **kw)  # noqa: E731
+    *_, gh, gw = call()
+    odd_h = torch.full((rows, d + 1), 7.0, dtype=torch.bfloat16, device=DEV)
+    odd_w = torch.full((vocab, d + 3), 7.0, device=DEV)
+    call(grad_hidden=odd_h[:, 1:], grad_weight=odd_w[:, 1:d + 1])
+    assert torch.equal(odd_h[:, 1:], gh) and torch.equal(odd_w[:, 1:d + 1], gw)
+    assert (odd_h[:, 0] == 7).all() and (odd_w[:, 0] == 7).all() and (odd_w[:, d + 1:] == 7).all()
+    twice = gw.clone()
+    call(grad_weight=twice, accumulate_grad_weight=True)
+    call(grad_weight=odd_w[:, 1:d + 1], accumulate_grad_weight=True)
+    assert torch.equal(twice, gw + gw) and torch.equal(odd_w[:, 1:d + 1], twice)
