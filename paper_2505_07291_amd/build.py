@@ -10,6 +10,7 @@ _ROOT = os.path.dirname(_PKG)
 SOURCES = [os.path.join(_PKG, "csrc", "grpo.hip")]
 INCLUDE = os.path.join(_ROOT, "include")
 LIB_PATH = os.path.join(_PKG, "libgrpo.so")
+FASTCALL_PATH = os.path.join(_PKG, "_fastcall.so")
 
 # -packed-fp32-ops is switched off on purpose: packed fp32 forms generated from plain
 # float code have produced wrong results on the test machines.
@@ -37,6 +38,27 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
+def build_fastcall(verbose: bool = False) -> str:
+    """Compiles the binding's native part (host code against torch's headers) and returns its path."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = FASTCALL_PATH + ".tmp.%d" % os.getpid()
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM"]
+    for path in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                 sysconfig.get_paths()["include"], "/opt/rocm/include"):
+        cmd += ["-isystem", path]
+    cmd += ["-I", INCLUDE, "-o", tmp, os.path.join(_PKG, "csrc", "fastcall.cpp"), "-L" + os.path.join(root, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
+    os.replace(tmp, FASTCALL_PATH)
+    return FASTCALL_PATH
+
+
 def is_stale() -> bool:
     if not os.path.exists(LIB_PATH):
         return True
@@ -47,3 +69,4 @@ def is_stale() -> bool:
 
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_fastcall(verbose=True))
