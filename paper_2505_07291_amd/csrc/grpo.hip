@@ -84,6 +84,9 @@ struct RowParams {
     float *KL_ws, *H_ws;  // per-row KL estimate and entropy
     float *entropy_out;   // optional copy of the per-row entropy for the caller
     float kl_coef, ent_coef;
+    // small batches of narrow rows: the row kernel counts the rows that take part itself (kCountRows)
+    int count_here;
+    double denom;  // the caller's denominator, or <= 0: that count
 };
 
 template <grpo_dtype DT>
@@ -409,8 +412,9 @@ __device__ __forceinline__ void surrogate(const RowParams &p, float r, float A, 
     if (r < p.lo || r > p.hi) fl |= kFlagOutOfBand;
 }
 
+// inv_D: 1 / D as the header holds it, or a workgroup's own (not looked at without the gradient)
 __device__ __forceinline__ RowScalars row_scalars(const RowParams &p, long long row, float zy,
-                                                  float mk, float s_excl)
+                                                  float mk, float s_excl, const float *inv_D = nullptr)
 {
     RowScalars o = {};
     const float ay = fmaf(zy, p.k, -mk);
@@ -427,7 +431,7 @@ __device__ __forceinline__ RowScalars row_scalars(const RowParams &p, long long 
 
     float dJ;
     surrogate(p, hw_exp(o.logp - p.old_lp[row]), p.adv[row], o.J, dJ, o.flags);
-    o.c = -(p.grad_scale * dJ) * (float)p.hdr->inv_D;
+    o.c = -(p.grad_scale * dJ) * (inv_D ? *inv_D : (float)p.hdr->inv_D);
     return o;
 }
 
@@ -441,7 +445,7 @@ __device__ __forceinline__ RowScalars row_scalars(const RowParams &p, long long 
 // the entropy part needs no difference of nearly equal numbers even when p_max -> 1.
 __device__ __forceinline__ RowScalars row_scalars_aux(const RowParams &p, long long row, float zy,
                                                       float mx, float s_excl, float w_excl,
-                                                      float &kl_out, float &H_out)
+                                                      float &kl_out, float &H_out, const float *inv_D = nullptr)
 {
     RowScalars o = {};
     const float ay = (zy - mx) * p.k;
@@ -478,7 +482,7 @@ __device__ __forceinline__ RowScalars row_scalars_aux(const RowParams &p, long l
         kl = fabsf(d) < 0.1f ? series : em1 - d;
     }
     // omega_t / D: the weight of this row in all three sums
-    const float wD = (p.token_w ? p.token_w[row] : 1.f) * (float)p.hdr->inv_D;
+    const float wD = (p.token_w ? p.token_w[row] : 1.f) * (inv_D ? *inv_D : (float)p.hdr->inv_D);
     o.c = (p.grad_scale * (-dJ + p.kl_coef * dkl)) * wD;
     o.b = (p.grad_scale * p.ent_coef) * wD;
     o.bq = o.b * p.inv_T * kLn2;
@@ -701,7 +705,8 @@ __device__ __forceinline__ void write_row_aux(const RowParams &p, long long row,
 
 // Decides whether a row takes part; handles the rows that do not (masked, or with a
 // token id outside the vocabulary).  Returns true when the row must be processed.
-template <grpo_dtype DT, int BLOCK>
+// COUNT: the header's error word is not the rows' business (see grpo_rows_cached).
+template <grpo_dtype DT, int BLOCK, bool COUNT = false>
 __device__ __forceinline__ bool row_is_live(const RowParams &p, long long row, int nvec_full,
                                             int tail, long long &y)
 {
@@ -721,7 +726,7 @@ __device__ __forceinline__ bool row_is_live(const RowParams &p, long long row, i
         // log-probs-only mode has no error word: a bad token id shows up as NaN
         write_row_outputs(p, row, (bad && !p.bwd) ? NAN : 0.f, 0.f, 0);
         write_row_aux(p, row, 0.f, 0.f);
-        if (bad && p.bwd) atomicOr(&p.hdr->error, 1);
+        if (!COUNT && bad && p.bwd) atomicOr(&p.hdr->error, 1);
     }
     if (p.bwd)
         zero_row<DT, BLOCK>((char *)p.grad + row * p.row_stride * Elem<DT>::BYTES, nvec_full, tail,
@@ -854,8 +859,12 @@ constexpr int row_stash_slots(int block, int nv, int nl = 0)
 // REM: the row may be wider still; what lies beyond slot NV + NL is streamed from memory, once
 // for an online (max, sum) pass that is merged into the resident part's statistics and once
 // more for the gradient: 2 reads + 1 write for that remainder only.
+// COUNT: a small batch of narrow rows.  Every workgroup counts the rows that take part (up to four bytes a
+// lane, on their way while the first row is looked up), and the first one writes the header, error word
+// included, for grpo_finalize: no grpo_prepare in front, which is one of four launches of a step on 512 fp32 rows
+// of 1024 (figures at kCountRows).
 // ---------------------------------------------------------------------------
-template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false>
+template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false>
 // 4 wavefronts per SIMD and 128 registers each; the widest instantiations 2 and 256
 __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowParams p)
 {
@@ -883,8 +892,19 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     __shared__ float lds_sum[BLOCK / 64];
     __shared__ float lds_sumw[BLOCK / 64];
     __shared__ long long lds_row[2];
+    __shared__ int lds_count[COUNT ? BLOCK / 64 : 1], lds_bad[COUNT ? BLOCK / 64 : 1];
+    __shared__ float lds_inv_D;
     const int tid = threadIdx.x;
     const unsigned toff = (unsigned)tid * 16u;
+    int rows_on = 0, rows_bad = 0;  // COUNT: this lane's share of the rows that take part, and of those with a bad token id
+    if constexpr (COUNT) {
+#pragma unroll 4
+        for (int i = tid; i < (int)p.n_tokens; i += BLOCK) {
+            const bool on = (!p.mask || p.mask[i] != 0) && (!p.token_w || p.token_w[i] != 0.f);
+            rows_on += on ? 1 : 0;
+            if (blockIdx.x == 0 && on && (p.tokens[i] < 0 || p.tokens[i] >= p.vocab)) rows_bad = 1;
+        }
+    }
     const int nvec_full = (int)(p.vocab / EPV);
     const int tail = (int)(p.vocab % EPV);
     // The ragged last vector (vocab not a multiple of EPV): lane i < tail holds its entry i, one
@@ -954,7 +974,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             long long r = grab();
             if (r >= p.n_tokens) return p.n_tokens;
             if (p.order) r = uniform((long long)p.order[r]);  // position in the hand-out order -> row
-            if (row_is_live<DT, BLOCK>(p, r, nvec_full, tail, y)) return r;
+            if (row_is_live<DT, BLOCK, COUNT>(p, r, nvec_full, tail, y)) return r;
         }
     };
 
@@ -1044,6 +1064,30 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         const char *zrow = (const char *)p.logits + row * p.row_stride * BYTES;
         fetch_all(zrow);
         fetch_rest(zrow, y);
+    }
+    if constexpr (COUNT) {
+        rows_on = wave_sum(rows_on);
+        rows_bad = __any(rows_bad) ? 1 : 0;
+        if ((tid & 63) == 0) {
+            lds_count[tid >> 6] = rows_on;
+            lds_bad[tid >> 6] = rows_bad;
+        }
+        lds_barrier();
+        if (tid == 0) {
+            long long M = 0;
+            int bad = 0;
+#pragma unroll
+            for (int w = 0; w < BLOCK / 64; ++w) M += lds_count[w], bad |= lds_bad[w];
+            const double D = p.denom > 0.0 ? p.denom : (double)M, inv_D = D > 0.0 ? 1.0 / D : 0.0;
+            lds_inv_D = (float)inv_D;  // read behind the barriers of a row's reductions
+            if (blockIdx.x == 0) {
+                p.hdr->D = D;
+                p.hdr->inv_D = inv_D;
+                p.hdr->M = M;
+                p.hdr->error = bad;
+                p.hdr->fin_ticket = 0u;
+            }
+        }
     }
 
     while (row < p.n_tokens) {
@@ -1167,11 +1211,11 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         if constexpr (AUX) {
             block_sum2<BLOCK>(acc, accw, lds_sum, lds_sumw);
             float kl, H;
-            sc = row_scalars_aux(p, row, zy_row, mx, acc, accw, kl, H);
+            sc = row_scalars_aux(p, row, zy_row, mx, acc, accw, kl, H, COUNT ? &lds_inv_D : nullptr);
             if (tid == 0) write_row_aux(p, row, kl, H);
         } else {
             const float s_excl = block_sum<BLOCK>(acc, lds_sum);
-            sc = row_scalars(p, row, zy_row, mk, s_excl);
+            sc = row_scalars(p, row, zy_row, mk, s_excl, COUNT ? &lds_inv_D : nullptr);
         }
         if (tid == 0) write_row_outputs(p, row, sc.logp, sc.J, sc.flags);
 
@@ -2127,7 +2171,7 @@ int cu_count()
     return n;
 }
 
-template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false>
+template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false>
 void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
 {
     RowParams p = p_in;
@@ -2147,12 +2191,12 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
         static std::atomic<bool> attr_done[64];  // setting the attribute twice is harmless
         int dev = 0;
         if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !attr_done[dev].load()) {
-            if (hipFuncSetAttribute((const void *)grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM>,
+            if (hipFuncSetAttribute((const void *)grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) == hipSuccess)
                 attr_done[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM>), dim3((unsigned)grid), dim3(BLOCK),
+    hipLaunchKernelGGL((grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT>), dim3((unsigned)grid), dim3(BLOCK),
                        lds_bytes, st, p);
 }
 
@@ -2238,6 +2282,14 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
     }
     p.queued = p.hdr != nullptr;
     const long long nvec = (p.vocab + Elem<DT>::EPV - 1) / Elem<DT>::EPV;
+    if (p.count_here) {
+        p.queued = 0;
+        if (nvec <= 256 * 1)
+            launch_cached<DT, 256, 1, AUX, true, 0, -1, false, true>(p, 8, st);
+        else
+            launch_cached<DT, 256, 4, AUX, true, 0, -1, false, true>(p, 8, st);
+        return;
+    }
     switch (plan_rows(nvec, p.vocab % Elem<DT>::EPV != 0)) {
 #define GRPO_ROW_CASE(ID, BLOCK, NV, TAIL, NL, RSTP, RSTA, REM, PERCU)                              \
     case ID:                                                                                       \
@@ -2291,6 +2343,12 @@ constexpr size_t loss_workspace_bytes(long long n)
     return kHeaderBytes + 4 * (((size_t)n * 4 + 255) / 256 * 256) + ((size_t)n + 255) / 256 * 256 + fin_partials_bytes(n);
 }
 constexpr long long kOrderMinRowBytes = 32768;  // narrower rows are handed out several at a time, in index order
+// Up to how many rows, of at most how many vectors, the row kernel counts the rows itself and grpo_prepare is not
+// launched.  Every workgroup then reads the whole mask, and the weights.  Step with and without grpo_prepare: 512 rows of
+// 1000 fp32 21.4 and 18.1 us, 1024 rows of 8000 bf16 21.0 and 18.6, with weights and auxiliary terms 28.4 and 27.0
+// (4000 bf16); 1500 rows 23.1 and 22.1, 30.2 and 30.3; 2048 rows 27.0 and 27.6, 34.2 and 36.0.  Wider rows take
+// long enough, and from more rows than CUs on they want grpo_prepare's order.
+constexpr long long kCountRows = 1024, kCountVectors = 1024;
 // Up to how many rows every workgroup of grpo_prepare counts all of them itself.  Counting them first takes 9.5 us
 // for both launches up to 524288 rows and 13 for 2097152; counted by every workgroup, a mask of 131072 rows
 // takes 7.3 us, of 262144 10.3, of 2097152 51 and of 4194304 194; weights, read one by one, of 16384 rows 8.5,
@@ -2343,10 +2401,15 @@ grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens,
         live_of = (int *)partials;  // 64 bytes for each 4096 rows, free until grpo_finalize
         hipLaunchKernelGGL(grpo_count_rows, segments, dim3(1024), 0, st, mask, weights, (long long)n_tokens, live_of);
     }
-    hipLaunchKernelGGL(grpo_prepare, segments, dim3(1024), 0, st, mask, weights, (long long)n_tokens, denom, hdr, order,
-                       (const int *)live_of);
+    const long long epv = dtype == GRPO_BF16 ? 8 : 4;
+    const bool count_here = n_tokens > 0 && n_tokens <= kCountRows && (vocab + epv - 1) / epv <= kCountVectors;
+    if (!count_here)
+        hipLaunchKernelGGL(grpo_prepare, segments, dim3(1024), 0, st, mask, weights, (long long)n_tokens, denom, hdr, order,
+                           (const int *)live_of);
     if (n_tokens > 0) {
         RowParams p = {};
+        p.count_here = count_here ? 1 : 0;
+        p.denom = denom;
         p.logits = logits;
         p.grad = grad_logits;
         p.tokens = (const long long *)tokens;

@@ -91,3 +91,37 @@ def test_aux_ragged_rows_around_the_resident_widths(dtype, epv, vectors):
 def test_aux_streamed_rows_around_whole_batches(dtype, epv, vectors):
     vocab = vectors * epv + 1
     run_aux_shape_case(dtype, vocab, (vectors + 1) * epv, 700, weights=vectors % 2 == 0)
+
+
+# up to 1024 rows of up to 1024 vectors the row kernel counts the rows itself and writes the header; with one row
+# more, masked, grpo_prepare does: the same bits, counters and error word, with and without a bad token id
+@pytest.mark.parametrize("aux", [False, True])
+@pytest.mark.parametrize("dtype,vocab", [(torch.bfloat16, 1000), (torch.bfloat16, 8191), (torch.float32, 4096), (torch.float32, 4100)])
+@pytest.mark.parametrize("rows,bad", [(1024, None), (1024, 1023), (1024, 5), (3, 1)])
+def test_rows_counted_by_the_row_kernel(aux, dtype, vocab, rows, bad):
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    pitch = (vocab + 7) // 8 * 8
+    logits = (torch.randn(rows + 1, pitch, generator=g, device="cuda") * 3).to(dtype)[:, :vocab]
+    tokens = torch.randint(0, vocab, (rows + 1,), generator=g, device="cuda")
+    old, adv, ref = (torch.randn(rows + 1, generator=g, device="cuda") for _ in range(3))
+    mask = (torch.rand(rows + 1, generator=g, device="cuda") < 0.7).to(torch.uint8)
+    weights = torch.rand(rows + 1, generator=g, device="cuda") * (torch.rand(rows + 1, generator=g, device="cuda") < 0.9)
+    mask[rows] = 0
+    if bad is not None:
+        tokens[bad], mask[bad], weights[bad] = vocab, 1, 0.5
+    for denom in (0.0, 777.0):
+        got = []
+        for n in (rows, rows + 1):
+            ws = torch.full((grpo.grpo_workspace_bytes(n),), 255, dtype=torch.uint8, device="cuda")
+            grad = torch.full((n, pitch), 7.0, dtype=dtype, device="cuda")[:, :vocab]
+            kw = dict(denom=denom, grad_logits=grad, workspace=ws)
+            if aux:
+                out = grpo.grpo_loss_aux_fwd_bwd(logits[:n], tokens[:n], old[:n], ref[:n], adv[:n], mask[:n], kl_coef=0.1,
+                                                 entropy_coef=0.01, token_weights=weights[:n], **kw)
+            else:
+                out = grpo.grpo_loss_fwd_bwd(logits[:n], tokens[:n], old[:n], adv[:n], mask[:n], **kw)
+            error = grpo.grpo_workspace_error(ws)
+            assert error == (0 if bad is None else 1)
+            got.append([t[:rows] if t.dim() > 0 and t.shape[0] == n else t for t in out])
+        for a, b in zip(*got):
+            assert torch.equal(a, b)
