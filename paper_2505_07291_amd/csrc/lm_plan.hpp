@@ -14,7 +14,7 @@ namespace {
 
 constexpr int LM_BM = 256, LM_BN = 256, LM_BK = 64;  // tile of C, K step
 constexpr int LM_GROUP_M = 8;                        // tile rows that share a sweep along N
-constexpr int LM_SPLIT_MAX = 32;                     // parts the contraction of one tile of dL/dH may be cut into
+constexpr int LM_SPLIT_MAX = 64;                     // parts the contraction of one tile of dL/dH may be cut into
 
 // Which of n_live rows chunk number `chunk` covers when no chunk may hold more than cap rows
 // (cap a multiple of 256): the fewest chunks that can hold them, each of the same size rounded
@@ -52,14 +52,15 @@ __host__ __device__ inline void lm_tile_of(int L, int tiles_m, int tiles_n, int 
 // The work of one product.  A tile row of C whose live rows do not reach past its first 128 (the last one, as often
 // as not) is "thin": the lower four wavefronts, which share their SIMDs with the upper four, skip its products, and it
 // takes about 0.55 of a whole tile's time.  Whole tiles come first, in the order of lm_tile_of, thin ones behind
-// them, so that the workgroups that got one whole tile less than the others take the first of them.
+// them, so that the workgroups that got one whole tile less than the others take the first of them - two each,
+// as far as there are more than these workgroups (640 rows of a vocabulary of 50304: 394 whole tiles and 197 thin ones, at
+// most 2 and none or 1 and 2 for a workgroup, not 2 and 1: a call with 768 values a row 312 and 302 us).
 //
 // Whole tiles that do not fill a round of the CUs (780 tiles on 256 CUs: three rounds and twelve tiles) would run that
 // round on a few CUs, each for a whole tile's time.  Two ways out, for the `rest` tiles behind the last whole round:
 //  - where the contraction may be split (dL/dH), each is cut into s2 parts along it, so that the last round is s2 times
 //    shorter and spread over all CUs, and thin tiles into t2 = half as many, so that all parts take the same time.
-//    s2 minimises the rounds of parts, counted in tile times, with a small charge per part for the fp32 partial
-//    results and their sum.  Every workgroup, and lm_split_reduce, computes the same plan from the same numbers.
+//    The number of parts minimises lm_split_cost.  Every workgroup, and lm_split_reduce, computes the same plan from the same numbers.
 //  - else each is cut into its upper and lower 128 rows, two thin tiles, if all thin tiles then fit one round.
 struct LmPlan {
     int rows_w, has_thin;  // whole tile rows; 1 if a thin one follows
@@ -67,13 +68,18 @@ struct LmPlan {
     int rest, s2;          // whole tiles cut into s2 parts each along the contraction
     int halves;            // whole tiles cut into two thin ones
     int thin, t2;          // tiles of the thin tile row, and the parts each is cut into
+    int pairs;             // of each XCD's list of thin tiles: how many places at its beginning hold two
 };
-// what cutting `over` whole and `thin` thin tiles into S and (S + 1) / 2 parts each costs, in tile times (S = 1: not cut)
-__host__ __device__ inline float lm_split_cost(int S, int over, int thin, int max_items, int n_cu)
+// The time, in us, of `over` whole and `thin` thin tiles of k_tiles K steps with S parts to a whole one and T to a thin one (1 and
+// 1: not cut).  A K step is 1.2 us in a whole tile, 0.7 in a thin one; a part 6 us more; its 256 KB of fp32 results
+// (128 KB of a thin tile) are written and read again at 6 TB/s.
+__host__ __device__ inline float lm_split_cost(int S, int T, int over, int thin, int k_tiles, int max_items, int n_cu)
 {
-    const int items = over * S + thin * ((S + 1) / 2);
+    const int items = over * S + thin * T;
     if (S > 1 && items > max_items) return INFINITY;
-    return (float)((items + n_cu - 1) / n_cu) / (float)S + (S > 1 ? 0.002f * (float)S : 0.f);
+    const int per_xcd = n_cu >= 8 ? n_cu / 8 : 1, longest = (over * S + 7) / 8 + (thin * T + 7) / 8;  // see lm_map_item
+    const float one = over > 0 ? 1.2f * (float)k_tiles / (float)S : 0.7f * (float)k_tiles / (float)T;
+    return (float)((longest + per_xcd - 1) / per_xcd) * (one + 6.f) + (S > 1 ? 0.04f * (float)(2 * over * S + thin * T) : 0.f);
 }
 __host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool split, int max_items, int n_cu)
 {
@@ -85,25 +91,29 @@ __host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool 
     pl.full = pl.rows_w * tiles_n;
     pl.rest = pl.halves = 0;
     pl.s2 = pl.t2 = 1;
+    pl.pairs = 0;
     const int over = pl.full % n_cu;
     if (!split) {
         if (over > 0 && 2 * over + pl.thin <= n_cu) {
             pl.halves = over;
             pl.full -= over;
+        } else if (n_cu >= 8) {
+            const int per_xcd = n_cu / 8, left = ((pl.full + 7) / 8) % per_xcd, free = left > 0 ? per_xcd - left : 0;
+            const int more = (pl.thin + 7) / 8 - free;
+            pl.pairs = more <= 0 ? 0 : more < free ? more : free;
         }
         return pl;
     }
     if (over + pl.thin == 0) return pl;
-    // up to LM_SPLIT_MAX parts of 8 K steps or more; a whole tile has twice the parts of a thin one
-    const int most = over > 0 ? LM_SPLIT_MAX : 2 * LM_SPLIT_MAX, long_enough = over > 0 ? k_tiles / 8 : k_tiles / 4;
-    const int lim = most < long_enough ? most : long_enough;
+    // Up to LM_SPLIT_MAX parts of 8 K steps or more.  A whole tile has twice the parts of a thin one; the
+    // candidates are numbers of parts of a whole tile, or of a thin one where there are no others.
+    const int lim = k_tiles / 8 < LM_SPLIT_MAX ? k_tiles / 8 : LM_SPLIT_MAX;
     int s_best = 1;
-    float best = lm_split_cost(1, over, pl.thin, max_items, n_cu);
 #ifdef __HIP_DEVICE_COMPILE__
     // a lane to a candidate (64 of them one after the other are 5 us)
-    static_assert(2 * LM_SPLIT_MAX == 64, "one candidate for each lane");
-    const int S = (int)(threadIdx.x & 63) + 1;
-    float c = S <= lim || S == 1 ? lm_split_cost(S, over, pl.thin, max_items, n_cu) : INFINITY;
+    static_assert(LM_SPLIT_MAX == 64, "one candidate for each lane");
+    const int S = (int)(threadIdx.x & 63) + 1, T = over > 0 ? (S + 1) / 2 : S;
+    float c = S <= lim || S == 1 ? lm_split_cost(S, T, over, pl.thin, k_tiles, max_items, n_cu) : INFINITY;
     s_best = S;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -112,10 +122,10 @@ __host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool 
         if (c2 < c || (c2 == c && s2 < s_best)) c = c2, s_best = s2;
     }
     s_best = __builtin_amdgcn_readfirstlane(s_best);
-    (void)best;
 #else
+    float best = lm_split_cost(1, 1, over, pl.thin, k_tiles, max_items, n_cu);
     for (int S = 2; S <= lim; ++S) {
-        const float c = lm_split_cost(S, over, pl.thin, max_items, n_cu);
+        const float c = lm_split_cost(S, over > 0 ? (S + 1) / 2 : S, over, pl.thin, k_tiles, max_items, n_cu);
         if (c < best) {
             best = c;
             s_best = S;
@@ -126,7 +136,7 @@ __host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool 
     pl.rest = over;
     pl.full -= over;
     pl.s2 = s_best;
-    pl.t2 = (s_best + 1) / 2;
+    pl.t2 = over > 0 ? (s_best + 1) / 2 : s_best;
     return pl;
 }
 
@@ -139,10 +149,11 @@ struct LmItem {
     int height;       // 256, or 128 for a thin item
     int part, parts;  // which part of the contraction
     int block;        // parts > 1: index of its fp32 block
+    int pair;         // 1: the same place holds the thin tile of the next column too
 };
 __host__ __device__ inline int lm_items_per_xcd(const LmPlan &pl)
 {
-    return (pl.full + 7) / 8 + (pl.rest * pl.s2 + 2 * pl.halves + 7) / 8 + (pl.thin * pl.t2 + 7) / 8;
+    return (pl.full + 7) / 8 + (pl.rest * pl.s2 + 2 * pl.halves + 7) / 8 + (pl.thin * pl.t2 + 7) / 8 - pl.pairs;
 }
 __host__ __device__ inline bool lm_map_item(int xcd, int idx, int tiles_n, const LmPlan &pl, LmItem &it)
 {
@@ -150,6 +161,7 @@ __host__ __device__ inline bool lm_map_item(int xcd, int idx, int tiles_n, const
     it.part = 0;
     it.parts = 1;
     it.block = -1;
+    it.pair = 0;
     it.height = LM_BM;
     int L, half = 0;
     if (idx < n1) {
@@ -170,8 +182,9 @@ __host__ __device__ inline bool lm_map_item(int xcd, int idx, int tiles_n, const
         }
     } else {
         const int items = pl.thin * pl.t2, n3 = (items + 7) / 8;
-        const int j = xcd * n3 + (idx - n1 - n2);
-        if (idx - n1 - n2 >= n3 || j >= items) return false;
+        const int place = idx - n1 - n2, in_run = place + (place < pl.pairs ? place : pl.pairs), j = xcd * n3 + in_run;
+        if (in_run >= n3 || j >= items) return false;
+        it.pair = place < pl.pairs && in_run + 1 < n3 && j + 1 < items ? 1 : 0;
         it.part = j / pl.thin;
         it.parts = pl.t2;
         it.tn = j - it.part * pl.thin;

@@ -45,6 +45,7 @@
 // start out of step, so that the bursts of stores between tiles meet another's products, gain nothing at 40 K steps or more.
 
 #include <algorithm>
+#include <type_traits>
 
 #include "lm_plan.hpp"
 
@@ -63,6 +64,7 @@ constexpr int LM_LPT = LM_BM * LM_CPR / LM_THREADS;  // 16-byte loads per lane a
 constexpr int LM_LDS_BYTES = LM_SLOTS * LM_TILE_BYTES;
 
 enum { LM_EPI_LSE = 0, LM_EPI_BF16 = 1, LM_EPI_F32 = 2 };
+enum { LM_Z_NONE = 0, LM_Z_KEPT = 1, LM_Z_LARGE = 2 };  // the fp32 copy of the logits: none, stored, stored past the caches
 
 struct GemmParams {
     const __bf16 *A;
@@ -133,7 +135,7 @@ __device__ __forceinline__ int lm_z_in_part(int row, int col)
     return ((((row >> 4) & 7) * 4 + ((col >> 4) & 3)) * 64 + (row & 15) + 16 * ((col >> 2) & 3)) * 4;
 }
 
-template <int EPI, bool STORE_Z, bool AUX = false, bool AKM = false, bool BKM = false>
+template <int EPI, int Z, bool AUX = false, bool AKM = false, bool BKM = false>
 __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
 {
     extern __shared__ __attribute__((aligned(1024))) char lm_smem[];
@@ -163,7 +165,7 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     // +64) of the tile; chunk c sits in tile row c / 8 at physical position c % 8 and holds
     // logical chunk (c % 8) ^ ((row >> 1) & 7).  Rows past the item's last re-read that
     // row (their results are never stored).
-    LmItem item;
+    LmItem item = {};
     int L = 0, L_end = 0, tm = 0, group_row0 = 0, group_rows = 1, step_m = 0, step_n = 0;  // its place among the whole tiles
     int kt0 = 0, KT = 0;
     unsigned a_off[LM_LPT], b_off[LM_LPT];
@@ -180,6 +182,10 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 ++item.tn;
             }
             item.row0 = (group_row0 + tm) * LM_BM;
+            idx += per_xcd;
+        } else if (item.pair) {
+            item.pair = 0;
+            ++item.tn;
         } else {
             LmItem it;
             for (;; idx += per_xcd) {
@@ -202,8 +208,8 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 step_n = per_xcd / group_rows;
                 step_m = per_xcd - step_n * group_rows;
             }
+            idx += per_xcd;
         }
-        idx += per_xcd;
         const LmItem &it = item;
         const int row0 = it.row0, col0 = it.tn * LM_BN, row_end = min(M, row0 + it.height);
         int t = tid;  // opaque: what follows from it is computed again for each item, not kept in registers
@@ -456,11 +462,17 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
         asm volatile("" : "+v"(ln));
         const int n = ln & 15, g = ln >> 4;  // this lane's place in a block, see half_step
         // the wavefront's part as the accumulators lie, 1 KB a store
-        auto store_blocks = [&](float *base) __attribute__((always_inline)) {
+        auto store_blocks = [&](float *base, auto nontemporal) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = 0; i < LM_FA; ++i)
 #pragma unroll
-                for (int j = 0; j < LM_FB; ++j) *(f32x4 *)(base + ((i * LM_FB + j) * 64 + ln) * 4) = acc[i][j];
+                for (int j = 0; j < LM_FB; ++j) {
+                    f32x4 *at = (f32x4 *)(base + ((i * LM_FB + j) * 64 + ln) * 4);
+                    if constexpr (decltype(nontemporal)::value)
+                        __builtin_nontemporal_store(acc[i][j], at);
+                    else
+                        *at = acc[i][j];
+                }
         };
 
         if constexpr (EPI == LM_EPI_F32) {
@@ -526,7 +538,7 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 loads_landed();
             } else if (parts > 1) {
                 // read only where rows and columns exist: stored whole
-                store_blocks(p.split_ws + ((long long)block << 16) + wave * (LM_FA * LM_FB * 256));
+                store_blocks(p.split_ws + ((long long)block << 16) + wave * (LM_FA * LM_FB * 256), std::false_type{});
                 loads_landed_behind_stores();
             } else {
                 const bool quads = (((unsigned long long)p.C | (unsigned long long)(p.ldc * 2)) & 7u) == 0;
@@ -678,8 +690,10 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             loads_landed();
             // the fp32 copy of the logits, rows past the last one and the columns between N and the row pitch of Z with the
             // products of the clamped operand rows: never read
-            if (STORE_Z && active && col0 + wcol < p.ldz)  // ldz < 2^23: see lm_bwd_vocab_ok
-                store_blocks(p.Z + lm_z_part(row0 + wrow, col0 + wcol, p.ldz));
+            if (Z != LM_Z_NONE && active && col0 + wcol < p.ldz) {  // ldz < 2^23: see lm_bwd_vocab_ok
+                float *at = p.Z + lm_z_part(row0 + wrow, col0 + wcol, p.ldz);
+                store_blocks(at, std::bool_constant<Z == LM_Z_LARGE>{});
+            }
         }
         if (!more) break;
     }
@@ -1063,12 +1077,15 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
     char *turn = turn_all + wv * (LM_GL_ROWS * PITCH);
     const int ci = zbase + r0 + n;  // this lane's compact row
     // all of this lane's logits at once, whether the row has a gradient or not (Z is there up to whole parts); V <= ldz,
-    // which is a multiple of 64
+    // which is a multiple of 64.  They are read once: what the caches hold longer is G, which both products read
+    // (non-temporal or not: 1024 x 50304 x 768 278 and 289 us a call, 3000 rows of it 759 and 785)
     f32x4 z[WAVE_COLS / 16];
 #pragma unroll
     for (int it = 0; it < WAVE_COLS / 16; ++it) {
         const int c = c0 + it * 16 + 4 * g;
-        z[it] = r0 < zcount && c < ldz ? *(const f32x4 *)(Z + lm_z_part(r0, c, ldz) + lm_z_in_part(r0 + n, c)) : f32x4{0.f, 0.f, 0.f, 0.f};
+        z[it] = r0 < zcount && c < ldz
+                    ? __builtin_nontemporal_load((const f32x4 *)(Z + lm_z_part(r0, c, ldz) + lm_z_in_part(r0 + n, c)))
+                    : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const int pos = r0 + n < zcount ? w.pos2[r0 + n] : -1;
     float q = 0.f, sh = 0.f, mxr = 0.f, l2s = 0.f, q2 = 0.f, bq = 0.f, gy = 0.f;
@@ -1184,7 +1201,7 @@ __global__ void __launch_bounds__(256) lm_zero(T *out, long long rows, long long
 // Host side
 // ---------------------------------------------------------------------------
 
-template <int EPI, bool STORE_Z, bool AUX = false, bool AKM = false, bool BKM = false>
+template <int EPI, int Z, bool AUX = false, bool AKM = false, bool BKM = false>
 hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
 {
     static std::atomic<bool> attr_done[64];      // setting the attribute twice is harmless
@@ -1192,7 +1209,7 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64 && !attr_done[dev].load()) {
-        e = hipFuncSetAttribute((const void *)lm_gemm_nt<EPI, STORE_Z, AUX, AKM, BKM>,
+        e = hipFuncSetAttribute((const void *)lm_gemm_nt<EPI, Z, AUX, AKM, BKM>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LM_LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done[dev].store(true);
@@ -1202,7 +1219,7 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
     p.n_cu = cu_count();
     const long long most = EPI == LM_EPI_BF16 && p.split_items > 0 ? p.n_cu : 2 * (long long)((p.M + LM_BM - 1) / LM_BM) * p.tiles_n;
     const long long grid = std::max<long long>(8, std::min<long long>(p.n_cu / 8, (most + 7) / 8) * 8);
-    hipLaunchKernelGGL((lm_gemm_nt<EPI, STORE_Z, AUX, AKM, BKM>), dim3((unsigned)grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
+    hipLaunchKernelGGL((lm_gemm_nt<EPI, Z, AUX, AKM, BKM>), dim3((unsigned)grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
     return hipGetLastError();
 }
 
@@ -1455,9 +1472,16 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             g.zy = w.zy;
             g.Z = bwd ? (float *)(ws + L.Z) : nullptr;
             g.ldz = L.ldz;
-            hipError_t e = aux   ? lm_launch_gemm<LM_EPI_LSE, true, true>(g, st)
-                           : bwd ? lm_launch_gemm<LM_EPI_LSE, true>(g, st)
-                                 : lm_launch_gemm<LM_EPI_LSE, false>(g, st);
+            // Logits beyond what the 256 MB memory-side cache holds until lm_grad_logits reads them pass it by (as far as the
+            // host knows their number): call on 6000 x 50304 x 512 tokens, five eighths of them live, 1029 us kept and
+            // 1003 past it, 3000 x 50304 x 768 with auxiliary terms 759 and 744; on 1000 x 30000 x 512 153 and 157, on
+            // 2000 x 20000 x 1024 264 and 268.
+            const bool large = (long long)Mc * L.ldz > (256ll << 20) / 4;
+            hipError_t e = aux   ? large ? lm_launch_gemm<LM_EPI_LSE, LM_Z_LARGE, true>(g, st)
+                                         : lm_launch_gemm<LM_EPI_LSE, LM_Z_KEPT, true>(g, st)
+                           : !bwd ? lm_launch_gemm<LM_EPI_LSE, LM_Z_NONE>(g, st)
+                           : large ? lm_launch_gemm<LM_EPI_LSE, LM_Z_LARGE>(g, st)
+                                   : lm_launch_gemm<LM_EPI_LSE, LM_Z_KEPT>(g, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
 
             const dim3 cmb_grid((unsigned)((Mc + LM_CMB_ROWS - 1) / LM_CMB_ROWS));
@@ -1498,7 +1522,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             const size_t z_blocks = (size_t)cap * (size_t)L.ldz * 4 / ((size_t)LM_BM * LM_BN * 4);
             gh.split_items = (int)(z_blocks < 0x7fffffffu ? z_blocks : 0x7fffffffu);
             gh.split_ws = (float *)(ws + L.Z);
-            e = lm_launch_gemm<LM_EPI_BF16, false, false, false, true>(gh, st);
+            e = lm_launch_gemm<LM_EPI_BF16, LM_Z_NONE, false, false, true>(gh, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
             if (gh.split_items > 0)
                 hipLaunchKernelGGL(lm_split_reduce, dim3(2048), dim3(256), 0, st, (const float *)gh.split_ws,
@@ -1520,7 +1544,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             gw.C = grad_weight;
             gw.ldc = grad_weight_stride;
             gw.accumulate = (accumulate_grad_weight || c > 0) ? 1 : 0;  // the first chunk starts the sum
-            e = lm_launch_gemm<LM_EPI_F32, false, false, true, false>(gw, st);
+            e = lm_launch_gemm<LM_EPI_F32, LM_Z_NONE, false, true, false>(gw, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
         }
     } else if (bwd && !accumulate_grad_weight && vocab > 0) {

@@ -97,7 +97,7 @@ def test_aux_streamed_rows_around_whole_batches(dtype, epv, vectors):
 # more, masked, grpo_prepare does: the same bits, counters and error word, with and without a bad token id
 @pytest.mark.parametrize("aux", [False, True])
 @pytest.mark.parametrize("dtype,vocab", [(torch.bfloat16, 1000), (torch.bfloat16, 8191), (torch.float32, 4096), (torch.float32, 4100)])
-@pytest.mark.parametrize("rows,bad", [(1024, None), (1024, 1023), (1024, 5), (3, 1)])
+@pytest.mark.parametrize("rows,bad", [(1024, None), (1024, 1023), (1024, 5)])
 def test_rows_counted_by_the_row_kernel(aux, dtype, vocab, rows, bad):
     g = torch.Generator(device="cuda").manual_seed(vocab)
     pitch = (vocab + 7) // 8 * 8

@@ -34,6 +34,7 @@ int main()
                     for (int idx = b / 8; idx < items; idx += per_xcd) {
                         LmItem i;
                         if (!lm_map_item(b % 8, idx, tn, pl, i)) continue;
+                        for (int two = i.pair; two >= 0; --two, ++i.tn) {
                         if (i.tn < 0 || i.tn >= tn || i.row0 < 0 || i.row0 >= M || i.row0 % 128)
                             return fail("outside", M, tn, kt, split, cu);
                         const int k0 = (int)((unsigned)kt * (unsigned)i.part / (unsigned)i.parts);
@@ -41,6 +42,7 @@ int main()
                         if (i.parts > 1 && k1 - k0 < 2) return fail("short part", M, tn, kt, split, cu);
                         for (int r = i.row0; r < std::min(M, i.row0 + i.height); r += 128) cov[(size_t)(r / 128) * tn + i.tn] += k1 - k0;
                         if (i.parts > 1) blocks.push_back(i.block);
+                        }
                     }
                 for (int c : cov)
                     if (c != kt) return fail("coverage", M, tn, kt, split, cu);
