@@ -5,8 +5,8 @@ current HIP stream; every step of the computation runs in the library's kernels.
 There is no fallback: if the shared library cannot be loaded the call raises.
 
 The small entry points take an ordinary call (outputs and stream not given, plain tensors and numbers) through
-_fastcall (csrc/fastcall.cpp), which does the same in native code: a step on 512 x 1024 logits takes FAST_TINY us of
-the host's time instead of 28, the shaping of a small rollout step FAST_REW instead of 35.  It declines every call that is
+_fastcall (csrc/fastcall.cpp), which does the same in native code: the two calls of a step on 512 x 1024 logits took
+28.8 us and take 19.5, the four of the shaping of a small rollout step 36.3 and 25.2.  It declines every call that is
 not ordinary, and the Python below it, which checks and converts everything, takes it.
 """
 from __future__ import annotations

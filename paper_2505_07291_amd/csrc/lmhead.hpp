@@ -38,11 +38,12 @@
 // What bounds it is power: the chip lowers its clock until the products of random data fit.  In registers alone,
 // 16 x 16 x 32 products of normally distributed values reach 2040 TFLOP/s and 32 x 32 x 16 ones 1810 (both 2460 on
 // zeros): half of the accumulator traffic per product.  Fragments from LDS bring that to 1670, operand tiles
-// from the L2 caches to about 1500, from memory to 1400.  With the products in this form, their loads issued at the
-// beginning of a half step and wavefronts in the middle of their products preferred over others (2 % of a product each),
-// the products of 2560 rows with [152064, 5120] went from 3.09 / 2.69 / 2.71 ms (logits with their fp32 copy,
-// dL/dH, dL/dW) to 2.80 / 2.33 / 2.52.  Because power bounds it, a wait costs little by itself: workgroups that
-// start out of step, so that the bursts of stores between tiles meet another's products, gain nothing at 40 K steps or more.
+// from the L2 caches to about 1500, from memory to 1400 (2048 rows, 65536 x 4096: 634, 777 and 826 us).  With the
+// products in this form, their loads issued at the beginning of a half step and wavefronts in the middle of their products
+// preferred over others (1.3 and 2.3 % of a call), the three products of about 2560 live rows with [152064, 5120]
+// went from 3.11 / 2.72 / 2.72 ms (logits with their fp32 copy, dL/dH, dL/dW) to 2.75 / 2.36 / 2.66.  Because power
+// bounds it, a wait costs little by itself: with workgroups started out of step, so that the bursts of stores between
+// tiles meet others' products, that call took 2 % longer.
 
 #include <algorithm>
 #include <type_traits>
@@ -83,7 +84,7 @@ struct GemmParams {
     long long ldc;
     const int *c_rows;   // LM_EPI_BF16, optional: row i of the result goes to row c_rows[i] of C
     // LM_EPI_BF16, optional split of the contraction (split_items > 0): the tiles that do not fill
-    // a whole round of the CUs are cut into parts along K (lm_plan_split, from the live tile count);
+    // a whole round of the CUs are cut into parts along K (lm_plan, from the live row count);
     // part s of the t-th such tile goes as a 256 x 256 fp32 block to split_ws[t * parts + s] and
     // lm_split_reduce finishes.  split_items: how many such blocks split_ws holds.
     int split_items, n_cu;
