@@ -38,24 +38,29 @@ def build_library(verbose: bool = False) -> str:
     return LIB_PATH
 
 
-def build_fastcall(verbose: bool = False) -> str:
-    """Compiles the binding's native part (host code against torch's headers) and returns its path."""
+def compile_fastcall(source: str, out: str, verbose: bool = False) -> None:
+    """Compiles host code against torch's headers into a Python extension."""
     import sysconfig
     import torch
     root = os.path.dirname(torch.__file__)
-    tmp = FASTCALL_PATH + ".tmp.%d" % os.getpid()
+    tmp = out + ".tmp.%d" % os.getpid()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM"]
     for path in (os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
                  sysconfig.get_paths()["include"], "/opt/rocm/include"):
         cmd += ["-isystem", path]
-    cmd += ["-I", INCLUDE, "-o", tmp, os.path.join(_PKG, "csrc", "fastcall.cpp"), "-L" + os.path.join(root, "lib"),
+    cmd += ["-I", INCLUDE, "-o", tmp, source, "-L" + os.path.join(root, "lib"),
             "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("g++ failed:\n" + res.stdout + res.stderr)
-    os.replace(tmp, FASTCALL_PATH)
+    os.replace(tmp, out)
+
+
+def build_fastcall(verbose: bool = False) -> str:
+    """Compiles the binding's native part and returns its path."""
+    compile_fastcall(os.path.join(_PKG, "csrc", "fastcall.cpp"), FASTCALL_PATH, verbose)
     return FASTCALL_PATH
 
 

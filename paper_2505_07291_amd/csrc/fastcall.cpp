@@ -113,15 +113,18 @@ T *as(const at::Tensor &t)
 }
 void *current_stream() { return (void *)c10::hip::getCurrentHIPStream(c10::hip::current_device()).stream(); }
 
-// The call itself without the interpreter's lock, as ctypes makes it.
-template <typename F>
-grpo_status unlocked(F call)
+// The call itself without the interpreter's lock, as ctypes makes it.  Its arguments are values by then: what may
+// throw (data_ptr() of a tensor whose memory is gone) is evaluated with the lock held, and the lock is taken again
+// however the block is left.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <typename... T>
+grpo_status call(grpo_status (*f)(T...), std::common_type_t<T>... args)
 {
-    grpo_status rc;
-    Py_BEGIN_ALLOW_THREADS;
-    rc = call();
-    Py_END_ALLOW_THREADS;
-    return rc;
+    Unlocked no_lock;
+    return f(args...);
 }
 // (None for a tensor that is not defined, the object itself for one of the caller's)
 PyObject *tuple_of(std::initializer_list<at::Tensor> made, PyObject *last = nullptr)
@@ -193,10 +196,8 @@ PyObject *total_rewards(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     ORDINARY(len && target);
     at::Tensor out = make(n, at::kFloat, dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_total_rewards(as<const float>(task), as<const int32_t>(len), as<const int32_t>(target), n, (float)alpha,
-                               as<float>(out), st);
-    });
+    const grpo_status rc = call(f_total_rewards, as<const float>(task), as<const int32_t>(len), as<const int32_t>(target),
+                                n, (float)alpha, as<float>(out), st);
     return rc == GRPO_OK ? THPVariable_Wrap(out) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -215,10 +216,8 @@ PyObject *filter_groups(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     at::Tensor keep = make(groups, at::kByte, dev), kept = make(groups, at::kInt, dev), n_kept = make(1, at::kInt, dev),
                rollouts = make(n, at::kByte, dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_filter_groups(as<const float>(rewards), n, nullptr, groups, size, as<uint8_t>(keep), as<int32_t>(kept),
-                               as<int32_t>(n_kept), as<uint8_t>(rollouts), st);
-    });
+    const grpo_status rc = call(f_filter_groups, as<const float>(rewards), n, nullptr, groups, size, as<uint8_t>(keep),
+                                as<int32_t>(kept), as<int32_t>(n_kept), as<uint8_t>(rollouts), st);
     return rc == GRPO_OK ? tuple_of({keep, kept, n_kept, rollouts}) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -234,10 +233,8 @@ PyObject *packed_layout(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     const c10::Device dev = cu->device();
     at::Tensor weights = make(n, at::kFloat, dev), rollout = make(n, at::kInt, dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_packed_layout(as<const int64_t>(cu), cu->size(0) - 1, n, a[2] == Py_True ? 1 : 0, as<float>(weights),
-                               as<int32_t>(rollout), st);
-    });
+    const grpo_status rc = call(f_packed_layout, as<const int64_t>(cu), cu->size(0) - 1, n, a[2] == Py_True ? 1 : 0,
+                                as<float>(weights), as<int32_t>(rollout), st);
     return rc == GRPO_OK ? tuple_of({weights, rollout}) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -258,10 +255,9 @@ PyObject *group_advantages(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     at::Tensor adv = make(n, at::kFloat, dev), adv_tok;
     if (rollout) adv_tok = make(tokens, at::kFloat, dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_group_advantages(as<const float>(rewards), n, nullptr, n / size, size, (float)eps, (int)ddof, as<float>(adv),
-                                  as<const int32_t>(rollout), tokens, rollout ? as<float>(adv_tok) : nullptr, st);
-    });
+    const grpo_status rc = call(f_group_advantages, as<const float>(rewards), n, nullptr, n / size, size, (float)eps,
+                                (int)ddof, as<float>(adv), as<const int32_t>(rollout), tokens, rollout ?
+                                as<float>(adv_tok) : nullptr, st);
     return rc == GRPO_OK ? tuple_of({adv, adv_tok}) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -277,10 +273,8 @@ PyObject *logprobs_fwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     ORDINARY(tokens && ws && row_or_none(a[2], at::kByte, l.n, &l.dev, &mask));
     at::Tensor lp = make(l.n, at::kFloat, l.dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_logprobs_fwd(ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens), as<const uint8_t>(mask),
-                              (float)temperature, as<float>(lp), ptr(ws), (size_t)ws->numel(), st);
-    });
+    const grpo_status rc = call(f_logprobs_fwd, ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens),
+                                as<const uint8_t>(mask), (float)temperature, as<float>(lp), ptr(ws), (size_t)ws->numel(), st);
     return rc == GRPO_OK ? THPVariable_Wrap(lp) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -301,12 +295,10 @@ PyObject *loss_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     at::Tensor loss = make(1, at::kFloat, l.dev), lp = make(l.n, at::kFloat, l.dev), counts = make(5, at::kLong, l.dev);
     const at::Tensor ws = given ? *given : make((int64_t)f_workspace_bytes(l.n), at::kByte, l.dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_loss_fwd_bwd(ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens), as<const float>(old),
-                              as<const float>(adv), as<const uint8_t>(mask), (float)f[0], (float)f[1], (float)f[2], (float)f[3],
-                              f[4], (float)f[5], as<float>(loss), as<float>(lp), as<int64_t>(counts), ptr(grad), ptr(ws),
-                              (size_t)ws.numel(), st);
-    });
+    const grpo_status rc = call(f_loss_fwd_bwd, ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens),
+                                as<const float>(old), as<const float>(adv), as<const uint8_t>(mask), (float)f[0], (float)f[1],
+                                (float)f[2], (float)f[3], f[4], (float)f[5], as<float>(loss), as<float>(lp),
+                                as<int64_t>(counts), ptr(grad), ptr(ws), (size_t)ws.numel(), st);
     return rc == GRPO_OK ? tuple_of({loss, lp, counts}, a[11]) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
@@ -330,14 +322,12 @@ PyObject *loss_aux_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     if (a[17] == Py_True) entropy = make(l.n, at::kFloat, l.dev);
     const at::Tensor ws = given ? *given : make((int64_t)f_workspace_bytes(l.n), at::kByte, l.dev);
     void *st = current_stream();
-    const grpo_status rc = unlocked([&] {
-        return f_loss_aux_fwd_bwd(ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens), as<const float>(old),
-                                  as<const float>(ref), as<const float>(adv), as<const uint8_t>(mask),
-                                  as<const float>(weights), (float)f[0], (float)f[1], (float)f[2], (float)f[3], (float)f[4],
-                                  (float)f[5], f[6], (float)f[7], as<float>(loss), as<float>(lp),
-                                  entropy.defined() ? as<float>(entropy) : nullptr, as<int64_t>(counts), ptr(grad), ptr(ws),
-                                  (size_t)ws.numel(), st);
-    });
+    const grpo_status rc = call(f_loss_aux_fwd_bwd, ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens),
+                                as<const float>(old), as<const float>(ref), as<const float>(adv), as<const uint8_t>(mask),
+                                as<const float>(weights), (float)f[0], (float)f[1], (float)f[2], (float)f[3], (float)f[4],
+                                (float)f[5], f[6], (float)f[7], as<float>(loss), as<float>(lp), entropy.defined() ?
+                                as<float>(entropy) : nullptr, as<int64_t>(counts), ptr(grad), ptr(ws), (size_t)ws.numel(),
+                                st);
     return rc == GRPO_OK ? tuple_of({loss, lp, entropy, counts}, a[15]) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
