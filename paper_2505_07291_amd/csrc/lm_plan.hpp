@@ -199,4 +199,15 @@ __host__ __device__ inline bool lm_map_item(int xcd, int idx, int tiles_n, const
     return true;
 }
 
+// Workgroups launched for each XCD: one for each of its CUs, or as many as its lists can have places if those are
+// fewer (others would return at once).  M: the most rows there can be.  A tile is at most two items, and two of an
+// XCD's three lists may be rounded up: bounded by the number of items alone, one workgroup had to take two places
+// one after the other while others had none (log-probs of 511 rows x 511 x 1024: 44 us, 33 with a place each).
+inline int lm_workgroups_per_xcd(int M, int tiles_n, bool split, int n_cu)
+{
+    const int cus = n_cu >= 8 ? n_cu / 8 : 1;
+    const long long places = (2 * (long long)((M + (long long)LM_BM - 1) / LM_BM) * tiles_n + 14) / 8;
+    return split || places > cus ? cus : places > 1 ? (int)places : 1;
+}
+
 }  // namespace

@@ -1216,11 +1216,9 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
         attr_done[dev].store(true);
     }
     p.tiles_n = (p.N + LM_BN - 1) / LM_BN;
-    // One workgroup for each CU, on whole XCDs; fewer when there cannot be as many tiles.
     p.n_cu = cu_count();
-    const long long most = EPI == LM_EPI_BF16 && p.split_items > 0 ? p.n_cu : 2 * (long long)((p.M + LM_BM - 1) / LM_BM) * p.tiles_n;
-    const long long grid = std::max<long long>(8, std::min<long long>(p.n_cu / 8, (most + 7) / 8) * 8);
-    hipLaunchKernelGGL((lm_gemm_nt<EPI, Z, AUX, AKM, BKM>), dim3((unsigned)grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
+    const unsigned grid = 8u * (unsigned)lm_workgroups_per_xcd(p.M, p.tiles_n, EPI == LM_EPI_BF16 && p.split_items > 0, p.n_cu);
+    hipLaunchKernelGGL((lm_gemm_nt<EPI, Z, AUX, AKM, BKM>), dim3(grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
     return hipGetLastError();
 }
 

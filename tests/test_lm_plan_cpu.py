@@ -1,6 +1,7 @@
 """The division of the head's products into work items (csrc/lm_plan.hpp), taken by the host compiler alone: over
 sizes, whole and cut contractions and numbers of CUs, every 128 rows x 256 columns of the result get every K step
-exactly once, no item leaves the matrix, and no two parts share a block of partial results."""
+exactly once, no item leaves the matrix, no two parts share a block of partial results, and a launch of fewer
+workgroups than CUs has one for every place."""
 import os
 import subprocess
 
@@ -22,6 +23,9 @@ int main()
 {
     long plans = 0;
     srand(7);
+    // 320 live rows of 511, two columns of tiles: four halves and two thin tiles
+    if (lm_items_per_xcd(lm_plan(320, 2, 16, false, 0, 256)) > lm_workgroups_per_xcd(511, 2, false, 256))
+        return fail("two places for one of few workgroups", 320, 2, 16, 0, 256);
     for (int cu : {64, 256, 304})
         for (int split = 0; split < 2; ++split)
             for (int it = 0; it < 5000; ++it) {
@@ -29,7 +33,10 @@ int main()
                 const int kt = 1 + rand() % (rand() % 2 ? 30 : 2400), blocks_max = rand() % 4 ? 20000 : rand() % 400;
                 const LmPlan pl = lm_plan(M, tn, kt, split, blocks_max, cu);
                 std::vector<int> cov((size_t)((M + 127) / 128) * tn, 0), blocks;
-                const int per_xcd = cu / 8, items = lm_items_per_xcd(pl);
+                const int most = M + rand() % 600;  // what the host knows about the rows
+                const int per_xcd = lm_workgroups_per_xcd(most, tn, split, cu), items = lm_items_per_xcd(pl);
+                if (per_xcd < 1 || per_xcd > cu / 8) return fail("workgroups", M, tn, kt, split, cu);
+                if (per_xcd < cu / 8 && items > per_xcd) return fail("two places for one of few workgroups", M, tn, kt, split, cu);
                 for (int b = 0; b < per_xcd * 8; ++b)
                     for (int idx = b / 8; idx < items; idx += per_xcd) {
                         LmItem i;
