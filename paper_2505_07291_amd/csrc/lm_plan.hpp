@@ -3,7 +3,7 @@
 // in its kernels; a host compiler takes it alone).
 #pragma once
 
-#include <cmath>
+#include <climits>
 
 #ifndef __HIP__
 #define __host__
@@ -60,7 +60,9 @@ __host__ __device__ inline void lm_tile_of(int L, int tiles_m, int tiles_n, int 
 // round on a few CUs, each for a whole tile's time.  Two ways out, for the `rest` tiles behind the last whole round:
 //  - where the contraction may be split (dL/dH), each is cut into s2 parts along it, so that the last round is s2 times
 //    shorter and spread over all CUs, and thin tiles into t2 = half as many, so that all parts take the same time.
-//    The number of parts minimises lm_split_cost.  Every workgroup, and lm_split_reduce, computes the same plan from the same numbers.
+//    The number of parts minimises lm_split_cost.  Every workgroup of the product, and lm_split_reduce, which reads the
+//    blocks that the parts have written, computes the plan anew from the same numbers: in whole numbers, so that all of
+//    them, and the host, come to the same one whatever a compiler makes of each place.
 //  - else each is cut into its upper and lower 128 rows, two thin tiles, if all thin tiles then fit one round.
 struct LmPlan {
     int rows_w, has_thin;  // whole tile rows; 1 if a thin one follows
@@ -70,16 +72,30 @@ struct LmPlan {
     int thin, t2;          // tiles of the thin tile row, and the parts each is cut into
     int pairs;             // of each XCD's list of thin tiles: how many places at its beginning hold two
 };
-// The time, in us, of `over` whole and `thin` thin tiles of k_tiles K steps with S parts to a whole one and T to a thin one (1 and
-// 1: not cut).  A K step is 1.2 us in a whole tile, 0.7 in a thin one; a part 6 us more; its 256 KB of fp32 results
-// (128 KB of a thin tile) are written and read again at 6 TB/s.
-__host__ __device__ inline float lm_split_cost(int S, int T, int over, int thin, int k_tiles, int max_items, int n_cu)
+// What `over` whole and `thin` thin tiles of k_tiles K steps cost with S parts to a whole one and T to a thin one (1 and 1: not
+// cut), to compare numbers of parts by: about nanoseconds with operands in the L2 caches and the chip at its full clock.  A K
+// step is 1200 in a whole tile, 700 in a thin one; a part 6000 more; its 256 KB of fp32 results (128 KB of a thin tile),
+// written and read again, 40 each 128 KB.
+__host__ __device__ inline long long lm_split_cost(int S, int T, int over, int thin, int k_tiles, int max_items, int n_cu)
 {
     const int items = over * S + thin * T;
-    if (S > 1 && items > max_items) return INFINITY;
+    if (S > 1 && items > max_items) return LLONG_MAX;
     const int per_xcd = n_cu >= 8 ? n_cu / 8 : 1, longest = (over * S + 7) / 8 + (thin * T + 7) / 8;  // see lm_map_item
-    const float one = over > 0 ? 1.2f * (float)k_tiles / (float)S : 0.7f * (float)k_tiles / (float)T;
-    return (float)((longest + per_xcd - 1) / per_xcd) * (one + 6.f) + (S > 1 ? 0.04f * (float)(2 * over * S + thin * T) : 0.f);
+    // (k_tiles <= 2^17: see lm_bwd_vocab_ok)
+    const unsigned one = over > 0 ? 1200u * (unsigned)k_tiles / (unsigned)S : 700u * (unsigned)k_tiles / (unsigned)T;
+    return (long long)((longest + per_xcd - 1) / per_xcd) * (one + 6000u) + (S > 1 ? 40ll * (2 * over * S + thin * T) : 0);
+}
+// The candidates are S = 1 .. LM_SPLIT_MAX parts of 8 K steps or more to a whole tile and half as many to a thin one, which then
+// take the same time; where there are only thin tiles, S is theirs.
+__host__ __device__ inline int lm_split_thin_parts(int S, int over) { return over > 0 ? (S + 1) / 2 : S; }
+__host__ __device__ inline long long lm_split_candidate(int S, int over, int thin, int k_tiles, int max_items, int n_cu)
+{
+    if (S > 1 && S > k_tiles / 8) return LLONG_MAX;
+    return lm_split_cost(S, lm_split_thin_parts(S, over), over, thin, k_tiles, max_items, n_cu);
+}
+__host__ __device__ inline bool lm_split_better(long long cost, int S, long long than_cost, int than_S)
+{
+    return cost < than_cost || (cost == than_cost && S < than_S);
 }
 __host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool split, int max_items, int n_cu)
 {
@@ -105,38 +121,31 @@ __host__ __device__ inline LmPlan lm_plan(int M, int tiles_n, int k_tiles, bool 
         return pl;
     }
     if (over + pl.thin == 0) return pl;
-    // Up to LM_SPLIT_MAX parts of 8 K steps or more.  A whole tile has twice the parts of a thin one; the
-    // candidates are numbers of parts of a whole tile, or of a thin one where there are no others.
-    const int lim = k_tiles / 8 < LM_SPLIT_MAX ? k_tiles / 8 : LM_SPLIT_MAX;
     int s_best = 1;
 #ifdef __HIP_DEVICE_COMPILE__
     // a lane to a candidate (64 of them one after the other are 5 us)
     static_assert(LM_SPLIT_MAX == 64, "one candidate for each lane");
-    const int S = (int)(threadIdx.x & 63) + 1, T = over > 0 ? (S + 1) / 2 : S;
-    float c = S <= lim || S == 1 ? lm_split_cost(S, T, over, pl.thin, k_tiles, max_items, n_cu) : INFINITY;
-    s_best = S;
+    s_best = (int)(threadIdx.x & 63) + 1;
+    long long c = lm_split_candidate(s_best, over, pl.thin, k_tiles, max_items, n_cu);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const float c2 = __shfl_xor(c, o, 64);
+        const long long c2 = __shfl_xor(c, o, 64);
         const int s2 = __shfl_xor(s_best, o, 64);
-        if (c2 < c || (c2 == c && s2 < s_best)) c = c2, s_best = s2;
+        if (lm_split_better(c2, s2, c, s_best)) c = c2, s_best = s2;
     }
     s_best = __builtin_amdgcn_readfirstlane(s_best);
 #else
-    float best = lm_split_cost(1, 1, over, pl.thin, k_tiles, max_items, n_cu);
-    for (int S = 2; S <= lim; ++S) {
-        const float c = lm_split_cost(S, over > 0 ? (S + 1) / 2 : S, over, pl.thin, k_tiles, max_items, n_cu);
-        if (c < best) {
-            best = c;
-            s_best = S;
-        }
+    long long best = lm_split_candidate(1, over, pl.thin, k_tiles, max_items, n_cu);
+    for (int S = 2; S <= LM_SPLIT_MAX; ++S) {
+        const long long c = lm_split_candidate(S, over, pl.thin, k_tiles, max_items, n_cu);
+        if (lm_split_better(c, S, best, s_best)) best = c, s_best = S;
     }
 #endif
     if (s_best == 1) return pl;
     pl.rest = over;
     pl.full -= over;
     pl.s2 = s_best;
-    pl.t2 = over > 0 ? (s_best + 1) / 2 : s_best;
+    pl.t2 = lm_split_thin_parts(s_best, over);
     return pl;
 }
 

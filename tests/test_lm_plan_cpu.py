@@ -1,7 +1,7 @@
 """The division of the head's products into work items (csrc/lm_plan.hpp), taken by the host compiler alone: over
 sizes, whole and cut contractions and numbers of CUs, every 128 rows x 256 columns of the result get every K step
-exactly once, no item leaves the matrix, no two parts share a block of partial results, and a launch of fewer
-workgroups than CUs has one for every place."""
+exactly once, no item leaves the matrix, no two parts share a block of partial results, a launch of fewer
+workgroups than CUs has one for every place, and the lanes of a wavefront agree with the host on the number of parts."""
 import os
 import subprocess
 
@@ -12,8 +12,28 @@ HARNESS = r"""
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 #include <vector>
 #include "lm_plan.hpp"
+// two kernels derive one plan: in whole numbers, whatever a compiler makes of the expression in each
+static_assert(std::is_integral<decltype(lm_split_cost(1, 1, 1, 1, 1, 1, 256))>::value, "whole numbers");
+// the choice of a wavefront: a lane to a candidate, exchanges with lane ^ 1, ^ 2, ... ^ 32
+static int wavefront_choice(int lane, int over, int thin, int kt, int blocks, int cu)
+{
+    long long c[64], d[64];
+    int s[64], t[64];
+    for (int l = 0; l < 64; ++l) c[l] = lm_split_candidate(s[l] = l + 1, over, thin, kt, blocks, cu);
+    for (int o = 1; o < 64; o <<= 1) {
+        for (int l = 0; l < 64; ++l) {
+            const bool other = lm_split_better(c[l ^ o], s[l ^ o], c[l], s[l]);
+            d[l] = other ? c[l ^ o] : c[l];
+            t[l] = other ? s[l ^ o] : s[l];
+        }
+        std::copy(d, d + 64, c);
+        std::copy(t, t + 64, s);
+    }
+    return s[lane];
+}
 static int fail(const char *what, int M, int tn, int kt, int split, int cu)
 {
     printf("%s: M %d tiles_n %d k_tiles %d split %d cu %d\n", what, M, tn, kt, split, cu);
@@ -32,6 +52,11 @@ int main()
                 const int M = it < 700 ? it + 1 : 1 + rand() % 9000, tn = 1 + rand() % (rand() % 2 ? 40 : 600);
                 const int kt = 1 + rand() % (rand() % 2 ? 30 : 2400), blocks_max = rand() % 4 ? 20000 : rand() % 400;
                 const LmPlan pl = lm_plan(M, tn, kt, split, blocks_max, cu);
+                if (const int over = pl.rows_w * tn % cu; split && over + pl.thin > 0) {
+                    for (int lane : {0, 17, 63})
+                        if (wavefront_choice(lane, over, pl.thin, kt, blocks_max, cu) != pl.s2)
+                            return fail("a lane chooses otherwise", M, tn, kt, split, cu);
+                }
                 std::vector<int> cov((size_t)((M + 127) / 128) * tn, 0), blocks;
                 const int most = M + rand() % 600;  // what the host knows about the rows
                 const int per_xcd = lm_workgroups_per_xcd(most, tn, split, cu), items = lm_items_per_xcd(pl);
