@@ -4,10 +4,10 @@ Argument marshalling only: tensors become raw device pointers, sizes and the
 current HIP stream; every step of the computation runs in the library's kernels.
 There is no fallback: if the shared library cannot be loaded the call raises.
 
-The small entry points take an ordinary call (outputs and stream not given, plain tensors and numbers) through
-_fastcall (csrc/fastcall.cpp), which does the same in native code: the two calls of a step on 512 x 1024 logits took
-28.8 us and take 19.5, the four of the shaping of a small rollout step 36.3 and 25.2.  It declines every call that is
-not ordinary, and the Python below it, which checks and converts everything, takes it.
+The small entry points take an ordinary call (plain tensors and numbers; no stream given, and no output but the
+gradient's tensor) through _fastcall (csrc/fastcall.cpp), which does the same in native code: the two calls of a step
+on 512 x 1024 logits took 28.8 us and take 19.5, the four of the shaping of a small rollout step 36.3 and 25.2.  It
+declines every call that is not ordinary, and the Python below it, which checks and converts everything, takes it.
 """
 from __future__ import annotations
 
@@ -262,9 +262,9 @@ def grpo_loss_fwd_bwd(logits, tokens, old_logprobs, advantages, mask=None, eps_l
     Returns (loss [1] f32, logprobs [n] f32, counts [5] i64, grad_logits), all on the device and
     valid once the stream has run.  ``inplace=True`` writes the gradient over the logits.
     """
-    if vocab is None and not inplace and loss_out is None and logprobs_out is None and counts_out is None and stream is None:
+    if vocab is None and loss_out is None and logprobs_out is None and counts_out is None and stream is None:
         out = _fast.loss_fwd_bwd(logits, tokens, old_logprobs, advantages, mask, eps_low, eps_high, delta, temperature, denom,
-                                 grad_scale, grad_logits, workspace)
+                                 grad_scale, logits if inplace else grad_logits, workspace)
         if out is not None:
             return _fast_result(out, "grpo_loss_fwd_bwd")
     dt, n, v, stride = _logits_args(logits, vocab)
@@ -346,11 +346,11 @@ def grpo_loss_aux_fwd_bwd(logits, tokens, old_logprobs, ref_logprobs, advantages
 
     Returns (loss [4] f32: total, policy, mean kl, mean entropy; logprobs [n]; entropy [n] or
     None; counts [5] i64; grad_logits)."""
-    if vocab is None and not inplace and loss_out is None and logprobs_out is None and entropy_out is None and \
+    if vocab is None and loss_out is None and logprobs_out is None and entropy_out is None and \
             counts_out is None and stream is None:
         out = _fast.loss_aux_fwd_bwd(logits, tokens, old_logprobs, ref_logprobs, advantages, mask, token_weights, eps_low,
-                                     eps_high, delta, temperature, kl_coef, entropy_coef, denom, grad_scale, grad_logits,
-                                     workspace, want_entropy)
+                                     eps_high, delta, temperature, kl_coef, entropy_coef, denom, grad_scale,
+                                     logits if inplace else grad_logits, workspace, want_entropy)
         if out is not None:
             return _fast_result(out, "grpo_loss_aux_fwd_bwd")
     dt, n, v, stride = _logits_args(logits, vocab)

@@ -3,10 +3,11 @@
 // (four calls, four launches, 13 us on the GPU) two thirds were attribute lookups, nine torch.empty and ctypes
 // conversions in Python.
 //
-// A function returns None when a call is not an ordinary one - another tensor class, dtype, device or layout, an
-// output or stream of the caller's, a number that is not a plain int or float, a mode or transform that wants to see
-// the allocations - and binding.py then takes its general path, which checks everything and raises what there is
-// to raise; an int is a grpo_status other than GRPO_OK.  Nothing is kept between calls but the library's addresses.
+// A function returns None when a call is not an ordinary one - another tensor class, dtype, device or layout, a
+// number that is not a plain int or float, a mode or transform that wants to see the allocations - and binding.py then
+// takes its general path, which checks everything and raises what there is to raise (it does not ask at all where a
+// stream, or an output other than the gradient, is given); an int is a grpo_status other than GRPO_OK.  Nothing is kept
+// between calls but the library's addresses.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -126,8 +127,8 @@ grpo_status call(grpo_status (*f)(T...), std::common_type_t<T>... args)
     Unlocked no_lock;
     return f(args...);
 }
-// (None for a tensor that is not defined, the object itself for one of the caller's)
-PyObject *tuple_of(std::initializer_list<at::Tensor> made, PyObject *last = nullptr)
+// (None for a tensor that is not defined.)  last: an object of the caller's, or None, and then made_last's.
+PyObject *tuple_of(std::initializer_list<at::Tensor> made, PyObject *last = nullptr, const at::Tensor &made_last = {})
 {
     PyObject *out = PyTuple_New((Py_ssize_t)made.size() + (last ? 1 : 0));
     if (!out) return nullptr;
@@ -141,7 +142,14 @@ PyObject *tuple_of(std::initializer_list<at::Tensor> made, PyObject *last = null
         PyTuple_SET_ITEM(out, i++, o);
     }
     if (last) {
-        Py_INCREF(last);
+        if (last == Py_None)
+            last = THPVariable_Wrap(made_last);
+        else
+            Py_INCREF(last);
+        if (!last) {
+            Py_DECREF(out);
+            return nullptr;
+        }
         PyTuple_SET_ITEM(out, i, last);
     }
     return out;
@@ -169,14 +177,19 @@ bool logits_of(PyObject *o, Logits *l)
     l->stride = l->n > 1 ? l->t->stride(0) : std::max<int64_t>(l->t->stride(0), l->v);
     return true;
 }
-// the caller's gradient tensor: of the logits' type, shape and strides
-const at::Tensor *grad_of(PyObject *o, const Logits &l)
+// Where the gradient goes: the caller's tensor, of the logits' type, shape and strides (it may be the logits), or, for
+// None, a new one of that kind, made by grad_made when the other arguments have been looked at.
+bool grad_ok(PyObject *o, const Logits &l)
 {
+    if (o == Py_None) return true;
     const at::Tensor *g = plain(o);
-    if (!g || g->scalar_type() != l.t->scalar_type() || g->device() != l.dev || g->sizes() != l.t->sizes() ||
-        g->strides() != l.t->strides())
-        return nullptr;
-    return g;
+    return g && g->scalar_type() == l.t->scalar_type() && g->device() == l.dev && g->sizes() == l.t->sizes() &&
+           g->strides() == l.t->strides();
+}
+at::Tensor grad_made(PyObject *o, const Logits &l)
+{
+    if (o != Py_None) return THPVariable_Unpack(o);
+    return at::empty_strided(l.t->sizes(), l.t->strides(), at::TensorOptions().dtype(l.t->scalar_type()).device(l.dev));
 }
 
 #define ORDINARY(cond) \
@@ -280,7 +293,7 @@ PyObject *logprobs_fwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
 }
 
 // loss_fwd_bwd(logits, tokens, old_logprobs, advantages, mask or None, eps_low, eps_high, delta, temperature, denom,
-//              grad_scale, grad_logits, workspace or None)
+//              grad_scale, grad_logits or None, workspace or None)
 PyObject *loss_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
 {
     HANDLE_TH_ERRORS
@@ -289,23 +302,23 @@ PyObject *loss_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     ORDINARY(n_args == 13 && plain_mode() && logits_of(a[0], &l));
     for (int i = 0; i < 6; ++i) ORDINARY(number(a[5 + i], &f[i]));
     const at::Tensor *tokens = row(a[1], at::kLong, l.n, &l.dev), *old = row(a[2], at::kFloat, l.n, &l.dev),
-                     *adv = row(a[3], at::kFloat, l.n, &l.dev), *grad = grad_of(a[11], l), *mask, *given;
-    ORDINARY(tokens && old && adv && grad && row_or_none(a[4], at::kByte, l.n, &l.dev, &mask) &&
+                     *adv = row(a[3], at::kFloat, l.n, &l.dev), *mask, *given;
+    ORDINARY(tokens && old && adv && grad_ok(a[11], l) && row_or_none(a[4], at::kByte, l.n, &l.dev, &mask) &&
              row_or_none(a[12], at::kByte, -1, &l.dev, &given));
     at::Tensor loss = make(1, at::kFloat, l.dev), lp = make(l.n, at::kFloat, l.dev), counts = make(5, at::kLong, l.dev);
-    const at::Tensor ws = given ? *given : make((int64_t)f_workspace_bytes(l.n), at::kByte, l.dev);
+    const at::Tensor grad = grad_made(a[11], l), ws = given ? *given : make((int64_t)f_workspace_bytes(l.n), at::kByte, l.dev);
     void *st = current_stream();
     const grpo_status rc = call(f_loss_fwd_bwd, ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens),
                                 as<const float>(old), as<const float>(adv), as<const uint8_t>(mask), (float)f[0], (float)f[1],
                                 (float)f[2], (float)f[3], f[4], (float)f[5], as<float>(loss), as<float>(lp),
                                 as<int64_t>(counts), ptr(grad), ptr(ws), (size_t)ws.numel(), st);
-    return rc == GRPO_OK ? tuple_of({loss, lp, counts}, a[11]) : PyLong_FromLong(rc);
+    return rc == GRPO_OK ? tuple_of({loss, lp, counts}, a[11], grad) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
 
 // loss_aux_fwd_bwd(logits, tokens, old_logprobs, ref_logprobs or None, advantages, mask or None, token_weights or None,
-//                  eps_low, eps_high, delta, temperature, kl_coef, entropy_coef, denom, grad_scale, grad_logits,
-//                  workspace or None, want_entropy)
+//                  eps_low, eps_high, delta, temperature, kl_coef, entropy_coef, denom, grad_scale,
+//                  grad_logits or None, workspace or None, want_entropy)
 PyObject *loss_aux_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
 {
     HANDLE_TH_ERRORS
@@ -314,13 +327,13 @@ PyObject *loss_aux_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
     ORDINARY(n_args == 18 && plain_mode() && PyBool_Check(a[17]) && logits_of(a[0], &l));
     for (int i = 0; i < 8; ++i) ORDINARY(number(a[7 + i], &f[i]));
     const at::Tensor *tokens = row(a[1], at::kLong, l.n, &l.dev), *old = row(a[2], at::kFloat, l.n, &l.dev),
-                     *adv = row(a[4], at::kFloat, l.n, &l.dev), *grad = grad_of(a[15], l), *ref, *mask, *weights, *given;
-    ORDINARY(tokens && old && adv && grad && row_or_none(a[3], at::kFloat, l.n, &l.dev, &ref) &&
+                     *adv = row(a[4], at::kFloat, l.n, &l.dev), *ref, *mask, *weights, *given;
+    ORDINARY(tokens && old && adv && grad_ok(a[15], l) && row_or_none(a[3], at::kFloat, l.n, &l.dev, &ref) &&
              row_or_none(a[5], at::kByte, l.n, &l.dev, &mask) && row_or_none(a[6], at::kFloat, l.n, &l.dev, &weights) &&
              row_or_none(a[16], at::kByte, -1, &l.dev, &given));
     at::Tensor loss = make(4, at::kFloat, l.dev), lp = make(l.n, at::kFloat, l.dev), counts = make(5, at::kLong, l.dev), entropy;
     if (a[17] == Py_True) entropy = make(l.n, at::kFloat, l.dev);
-    const at::Tensor ws = given ? *given : make((int64_t)f_workspace_bytes(l.n), at::kByte, l.dev);
+    const at::Tensor grad = grad_made(a[15], l), ws = given ? *given : make((int64_t)f_workspace_bytes(l.n), at::kByte, l.dev);
     void *st = current_stream();
     const grpo_status rc = call(f_loss_aux_fwd_bwd, ptr(l.t), l.dtype, l.n, l.v, l.stride, as<const int64_t>(tokens),
                                 as<const float>(old), as<const float>(ref), as<const float>(adv), as<const uint8_t>(mask),
@@ -328,7 +341,7 @@ PyObject *loss_aux_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n_args)
                                 (float)f[5], f[6], (float)f[7], as<float>(loss), as<float>(lp), entropy.defined() ?
                                 as<float>(entropy) : nullptr, as<int64_t>(counts), ptr(grad), ptr(ws), (size_t)ws.numel(),
                                 st);
-    return rc == GRPO_OK ? tuple_of({loss, lp, entropy, counts}, a[15]) : PyLong_FromLong(rc);
+    return rc == GRPO_OK ? tuple_of({loss, lp, entropy, counts}, a[15], grad) : PyLong_FromLong(rc);
     END_HANDLE_TH_ERRORS
 }
 

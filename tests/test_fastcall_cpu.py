@@ -107,3 +107,39 @@ t.start(), t.join()
 assert len(calls) == 2
 print("done")
 """)
+
+
+def test_loss_calls_without_a_gradient_tensor_and_in_place(run):
+    """The default form of the two loss calls makes the gradient itself, like the logits; in place it is the logits."""
+    run("""
+from paper_2505_07291_amd import binding
+binding._fast = fast
+pitched = torch.randn(n, v + 8)[:, :v]
+for logits in (z, pitched, pitched[:1], torch.randn(1, 4, v)[0, :1]):
+    m = logits.shape[0]
+    args = (tok[:m], old[:m])
+    for aux in (False, True):
+        def call(**kw):
+            calls.clear()
+            if aux:
+                out = grpo.grpo_loss_aux_fwd_bwd(logits, *args, None, adv[:m], kl_coef=0.0, **kw)
+            else:
+                out = grpo.grpo_loss_fwd_bwd(logits, *args, adv[:m], **kw)
+            assert [c[0] for c in calls] == ["grpo_loss_aux_fwd_bwd" if aux else "grpo_loss_fwd_bwd"]
+            return out[-1], calls[0]
+        at = 23 if aux else 18  # grad_logits among the library's arguments
+        grad, sent = call()
+        assert grad.shape == logits.shape and grad.stride() == logits.stride() and grad.dtype == logits.dtype
+        assert sent[1 + at] == grad.data_ptr() != logits.data_ptr()
+        grad, sent = call(workspace=ws)
+        assert sent[1 + at] == grad.data_ptr() and sent[2 + at] == ws.data_ptr()
+        grad, sent = call(inplace=True)
+        assert grad is logits and sent[1 + at] == logits.data_ptr()
+        given = torch.empty_strided(logits.shape, logits.stride())
+        grad, sent = call(grad_logits=given)
+        assert grad is given and sent[1 + at] == given.data_ptr()
+        grad, sent = call(grad_logits=given, inplace=True)
+        assert grad is logits and sent[1 + at] == logits.data_ptr()
+assert fast.loss_fwd_bwd(z, tok, old, adv, None, 0.2, 0.2, 4.0, 1.0, 0.0, 1.0, z.double(), ws) is None
+print("done")
+""")

@@ -35,6 +35,13 @@ CALLS = {
     "grpo_logprobs_fwd": lambda s, **kw: grpo.grpo_logprobs_fwd(s["logits"], s["tokens"], s["mask"], 0.7, **kw),
     "grpo_loss_fwd_bwd": lambda s, **kw: grpo.grpo_loss_fwd_bwd(
         s["logits"], s["tokens"], s["old"], s["adv"], s["mask"], grad_logits=s["grad"], **kw),
+    "grpo_loss_fwd_bwd default": lambda s, **kw: grpo.grpo_loss_fwd_bwd(s["logits"], s["tokens"], s["old"], s["adv"], s["mask"], **kw),
+    "grpo_loss_fwd_bwd in place": lambda s, **kw: grpo.grpo_loss_fwd_bwd(
+        s["logits"].clone(), s["tokens"], s["old"], s["adv"], inplace=True, **kw),
+    "grpo_loss_aux_fwd_bwd default": lambda s, **kw: grpo.grpo_loss_aux_fwd_bwd(
+        s["logits"][:, :511], s["tokens"] // 2, s["old"], None, s["adv"], s["mask"], want_entropy=False, **kw),
+    "grpo_loss_aux_fwd_bwd in place": lambda s, **kw: grpo.grpo_loss_aux_fwd_bwd(
+        s["logits"].clone(), s["tokens"], s["old"], s["ref"], s["adv"], s["mask"], kl_coef=0.1, inplace=True, **kw),
     "grpo_loss_aux_fwd_bwd": lambda s, **kw: grpo.grpo_loss_aux_fwd_bwd(
         s["logits"], s["tokens"], s["old"], s["ref"], s["adv"], None, 0.1, 0.3, 5, 1, 0.001, 1e-4, 17, grad_logits=s["grad"], **kw),
 }
