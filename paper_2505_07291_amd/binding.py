@@ -15,6 +15,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import warnings
 
 import torch  # imported first so that the HIP runtime torch ships is the one in the process
 
@@ -27,17 +28,35 @@ COUNT_NAMES = ("tokens", "clip_high", "clip_low", "delta", "out_of_band")
 _lib = None
 
 
+class _NoFastcall:
+    """In _fastcall's place before lib() has loaded it, or where it cannot be loaded: declines every call."""
+
+    def __getattr__(self, name):
+        return self._decline
+
+    @staticmethod
+    def _decline(*args):
+        return None
+
+
+_fast = _NoFastcall()
+
+
 def _load_fastcall():
-    """The binding's native part; builds it only if absent."""
-    if not os.path.exists(_build.FASTCALL_PATH):
-        _build.build_fastcall()
-    loader = importlib.machinery.ExtensionFileLoader("_fastcall", _build.FASTCALL_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fastcall", loader))
-    loader.exec_module(module)
-    return module
-
-
-_fast = _load_fastcall()  # its functions decline until lib() has given them the library's addresses
+    """The binding's native part, built if there is none for these sources and this torch; None, with a warning, where it
+    cannot be had (no compiler or headers): the general path can do every call."""
+    try:
+        path = _build.fastcall_path()
+        if not os.path.exists(path):
+            _build.build_fastcall()
+        loader = importlib.machinery.ExtensionFileLoader("_fastcall", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_fastcall", loader))
+        loader.exec_module(module)
+        return module
+    except (ImportError, OSError, RuntimeError) as e:
+        warnings.warn("libgrpo's small calls take the general Python path, which is slower: the binding's native part cannot "
+                      "be loaded (%s)" % e, RuntimeWarning, stacklevel=3)
+        return None
 
 
 class GrpoError(RuntimeError):
@@ -47,8 +66,8 @@ class GrpoError(RuntimeError):
 
 
 def lib():
-    """The loaded C library with argument types declared.  Builds it only if absent."""
-    global _lib
+    """The loaded C library with argument types declared, and with it the binding's native part.  Builds them only if absent."""
+    global _lib, _fast
     if _lib is None:
         path = _build.LIB_PATH
         if not os.path.exists(path):
@@ -97,10 +116,13 @@ def lib():
         L.grpo_lmhead_loss_aux_fwd_bwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, vp, vp, vp, vp,
                                                    f32, f32, f32, f32, f32, f32, f64, f32, vp, vp, vp, vp,
                                                    vp, i64, vp, i64, i32, vp, sz, vp]
-        _fast.bind(*[ctypes.cast(f, vp).value for f in (
-            L.grpo_workspace_bytes, L.grpo_group_advantages, L.grpo_logprobs_fwd, L.grpo_loss_fwd_bwd,
-            L.grpo_loss_aux_fwd_bwd, L.grpo_total_rewards, L.grpo_filter_groups, L.grpo_packed_layout)])
         _lib = L
+        fast = _load_fastcall()
+        if fast is not None:
+            fast.bind(*[ctypes.cast(f, vp).value for f in (
+                L.grpo_workspace_bytes, L.grpo_group_advantages, L.grpo_logprobs_fwd, L.grpo_loss_fwd_bwd,
+                L.grpo_loss_aux_fwd_bwd, L.grpo_total_rewards, L.grpo_filter_groups, L.grpo_packed_layout)])
+            _fast = fast
     return _lib
 
 

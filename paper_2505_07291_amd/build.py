@@ -1,6 +1,8 @@
-"""Builds libgrpo.so (the C-ABI library with the gfx950 HIP kernels) in-tree."""
+"""Builds libgrpo.so (the C-ABI library with the gfx950 HIP kernels) and the binding's native part in-tree."""
 from __future__ import annotations
 
+import glob
+import hashlib
 import os
 import shutil
 import subprocess
@@ -10,7 +12,7 @@ _ROOT = os.path.dirname(_PKG)
 SOURCES = [os.path.join(_PKG, "csrc", "grpo.hip")]
 INCLUDE = os.path.join(_ROOT, "include")
 LIB_PATH = os.path.join(_PKG, "libgrpo.so")
-FASTCALL_PATH = os.path.join(_PKG, "_fastcall.so")
+FASTCALL_SOURCE = os.path.join(_PKG, "csrc", "fastcall.cpp")
 
 # -packed-fp32-ops is switched off on purpose: packed fp32 forms generated from plain
 # float code have produced wrong results on the test machines.
@@ -58,14 +60,34 @@ def compile_fastcall(source: str, out: str, verbose: bool = False) -> None:
     os.replace(tmp, out)
 
 
+def fastcall_path() -> str:
+    """Where the binding's native part lies.  The library's argument types, the order of its own arguments and torch's C++
+    interface are compiled into it, so its name says which sources, which torch and which Python it was built for:
+    one that was left over from others has another name and is never loaded."""
+    import sysconfig
+    import torch
+    tag = hashlib.sha256(repr((torch.__version__, torch.version.git_version, sysconfig.get_config_var("SOABI"))).encode())
+    for path in (os.path.join(INCLUDE, "grpo.h"), FASTCALL_SOURCE):
+        with open(path, "rb") as f:
+            tag.update(f.read())
+    return os.path.join(_PKG, "_fastcall.%s.so" % tag.hexdigest()[:16])
+
+
 def build_fastcall(verbose: bool = False) -> str:
-    """Compiles the binding's native part and returns its path."""
-    compile_fastcall(os.path.join(_PKG, "csrc", "fastcall.cpp"), FASTCALL_PATH, verbose)
-    return FASTCALL_PATH
+    """Compiles the binding's native part, removes those of other sources, and returns its path."""
+    path = fastcall_path()
+    compile_fastcall(FASTCALL_SOURCE, path, verbose)
+    for old in glob.glob(os.path.join(_PKG, "_fastcall*.so")):
+        if old != path:
+            try:
+                os.unlink(old)
+            except FileNotFoundError:  # another process has built at the same time
+                pass
+    return path
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(fastcall_path()):
         return True
     t = os.path.getmtime(LIB_PATH)
     deps = SOURCES + [os.path.join(_PKG, "csrc", f) for f in ("lmhead.hpp", "lm_plan.hpp")] + [os.path.join(INCLUDE, "grpo.h")]
