@@ -1,11 +1,12 @@
 """Sizes at which the head's products change how they divide their work: rows around 128 and 256 (whole, thin and
-halved tiles), vocabularies around the 64 columns of a wavefront's part and the 256 of a tile, one and two K steps,
+halved tiles, thin ones two to a place), vocabularies around the 64 columns of a wavefront's part and the 256 of a tile, one and two K steps,
 contractions that are cut and that are not.  Against the fp64 oracle, element by element (run_case)."""
 import pytest
 import torch
 
 import paper_2505_07291_amd as grpo
 import paper_2505_07291_amd.workloads as wl
+from helpers import lm_plan
 from test_gpu_lmhead_parity import DEV, run_case
 
 pytestmark = pytest.mark.gpu
@@ -27,9 +28,19 @@ def test_every_element_around_tile_edges(rows, vocab, d):
     run_case(cfg, d, label="%dx%dx%d" % (rows, vocab, d), products="library" if rows * vocab * d > 10 ** 8 else "loops")
 
 
-# results whose rows do not lie on 16 (dL/dW) or 8 bytes (dL/dH) are stored element by element: the same bits
-@pytest.mark.parametrize("rows,vocab,d", [(130, 300, 128), (300, 700, 64)])
-def test_results_at_odd_pitches_and_offsets(rows, vocab, d):
+# more thin tiles than places that are free in the round of the last whole ones: two of them to a place
+@pytest.mark.parametrize("rows,vocab,d", [(384, 35840, 64), (512 + 96, 44600, 64)])
+def test_thin_tiles_two_to_a_place(rows, vocab, d):
+    assert lm_plan(rows, vocab, d)["pairs"] > 0  # no row of this recipe is masked
+    cfg = wl.CONFIGS["numerics_stress"].scaled(n_prompts=1, seq_len=rows // 2, vocab=vocab, group_size=2)
+    run_case(cfg, d, label="%dx%dx%d" % (rows, vocab, d), products="library")
+
+
+# results whose rows do not lie on 16 (dL/dW) or 8 bytes (dL/dH) are stored element by element: the same bits, in
+# lm_gemm_nt and, where the contraction of dL/dH is cut, for thin tiles or for whole and thin ones, in lm_split_reduce
+@pytest.mark.parametrize("rows,vocab,d,cut", [(130, 300, 128, ()), (300, 700, 64, ()), (120, 5000, 64, ("thin",)),
+                                              (600, 20000, 128, ("rest", "thin"))])
+def test_results_at_odd_pitches_and_offsets(rows, vocab, d, cut):
     g = torch.Generator(device=DEV).manual_seed(rows)
     h = torch.randn(rows, d, generator=g, device=DEV).bfloat16()
     w = (torch.randn(vocab, d, generator=g, device=DEV) * 0.2).bfloat16()
@@ -38,6 +49,9 @@ def test_results_at_odd_pitches_and_offsets(rows, vocab, d):
     old = grpo.grpo_lmhead_logprobs_fwd(h, w, tokens) + 0.1 * torch.randn(rows, generator=g, device=DEV)
     call = lambda **kw: grpo.grpo_lmhead_loss_fwd_bwd(h, w, tokens, old, adv, **kw)  # noqa: E731
     *_, gh, gw = call()
+    ldz = (vocab + 63) // 64 * 64
+    plan = lm_plan(int((gh != 0).any(1).sum()), d, ldz, (rows + 255) // 256 * 256 * ldz // 65536)
+    assert (plan["s2"] > 1) == bool(cut) and all(plan[kind] > 0 for kind in cut) and ("thin" not in cut or plan["t2"] > 1)
     odd_h = torch.full((rows, d + 1), 7.0, dtype=torch.bfloat16, device=DEV)
     odd_w = torch.full((vocab, d + 3), 7.0, device=DEV)
     call(grad_hidden=odd_h[:, 1:], grad_weight=odd_w[:, 1:d + 1])
