@@ -36,14 +36,17 @@
 // chunk ^ ((row >> 1) & 7), applied on the global-address side, so that 16 consecutive rows of one logical chunk (a
 // quarter of a ds_read_b128 fragment read) fall on 16 different groups of four banks.
 // What bounds it is power: the chip lowers its clock until the products of random data fit.  In registers alone,
-// 16 x 16 x 32 products of normally distributed values reach 2040 TFLOP/s and 32 x 32 x 16 ones 1810 (both 2460 on
-// zeros): half of the accumulator traffic per product.  Fragments from LDS bring that to 1670, operand tiles
-// from the L2 caches to about 1500, from memory to 1400 (2048 rows, 65536 x 4096: 634, 777 and 826 us).  With the
+// 16 x 16 x 32 products of normally distributed values reach 2065 TFLOP/s and 32 x 32 x 16 ones 1780 (both about 2480 on
+// zeros): half of the accumulator traffic per product.  Fragments from LDS bring that to 1670 (profiles/mfma_rates.txt).
+// Log-probs of 2048 x 65536 x 4096 take 635 us (1730 TFLOP/s) on copies of this kernel whose operand tiles are loaded once
+// and for all, 766 (1435) where every load finds its tile in the L2 cache, 813 (1350) as it is.  With the
 // products in this form, their loads issued at the beginning of a half step and wavefronts in the middle of their products
 // preferred over others (1.3 and 2.3 % of a call), the three products of about 2560 live rows with [152064, 5120]
 // went from 3.11 / 2.72 / 2.72 ms (logits with their fp32 copy, dL/dH, dL/dW) to 2.75 / 2.36 / 2.66.  Because power
 // bounds it, a wait costs little by itself: with workgroups started out of step, so that the bursts of stores between
-// tiles meet others' products, that call took 2 % longer.
+// tiles meet others' products, that call took 2 % longer.  What the form costs: log-probs of d_model 64, whose second K step
+// does not exist and is multiplied as zeros, take 3 to 9 % longer than before (32768 x 4096: 78 and 85 us; products
+// left out behind the loop, 82, but those of d_model 5120 then took 1 % more).
 
 #include <algorithm>
 #include <type_traits>
@@ -1050,6 +1053,8 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
 // LDS and leave 256 bytes at a time, each to its place among the gradient rows.  Padding is written as zeros: the
 // columns V .. ldg (dL/dH runs over whole K steps of the vocabulary) and the rows n_grad .. the next
 // multiple of 64 (dL/dW runs over whole K steps of rows).
+// Reading Z in that order costs this kernel something (10066 rows of 152064: 648 us, 584 with Z row by row; 992 and 901 with
+// the auxiliary terms) and saves the product in front 5 us of a CU's time per tile, 0.46 ms of those rows.
 constexpr int LM_GL_COLS = 512, LM_GL_ROWS = 16;
 template <bool AUX>
 __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long ldz, int V, LmRows w,
