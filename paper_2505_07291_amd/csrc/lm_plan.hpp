@@ -76,7 +76,7 @@ struct LmPlan {
 // cut): nanoseconds to rank the parts of one product by, not its time.  A K step is 1200 in a whole tile, 700 in a thin
 // one; a part 6000 more; its 256 KB of fp32 results (128 KB of a thin tile), written and read again, 40 each 128 KB.  That is
 // a K step with operands in the caches at a clock that short products hold; the whole chip at it for milliseconds lowers
-// its clock to 1640 (1949 rows of 152064 x 5120: 2429 us and 72 for the sum, 1914 by this; 612 of 50304 x 768: 61 and 12,
+// its clock to 1610 (1949 rows of 152064 x 5120: 2385 us and 72 for the sum, 1914 by this; 612 of 50304 x 768: 60 and 12,
 // and 52).  Which number of parts wins is a matter of rounds, which all take the same clock: 128 rows of 152064 x 1024,
 // 510 us a call with an earlier rule, take 341.
 __host__ __device__ inline long long lm_split_cost(int S, int T, int over, int thin, int k_tiles, int max_items, int n_cu)
