@@ -15,6 +15,7 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import threading
 import warnings
 
 import torch  # imported first so that the HIP runtime torch ships is the one in the process
@@ -26,6 +27,7 @@ GRPO_F32, GRPO_BF16 = 0, 1
 COUNT_NAMES = ("tokens", "clip_high", "clip_low", "delta", "out_of_band")
 
 _lib = None
+_lib_lock = threading.Lock()
 
 
 class _NoFastcall:
@@ -67,63 +69,69 @@ class GrpoError(RuntimeError):
 
 def lib():
     """The loaded C library with argument types declared, and with it the binding's native part.  Builds them only if absent."""
-    global _lib, _fast
     if _lib is None:
-        path = _build.LIB_PATH
-        if not os.path.exists(path):
-            path = _build.build_library()
-        L = ctypes.CDLL(path)
-        vp, i64, i32, f32, f64, sz = (ctypes.c_void_p, ctypes.c_int64, ctypes.c_int,
-                                      ctypes.c_float, ctypes.c_double, ctypes.c_size_t)
-        L.grpo_status_string.restype = ctypes.c_char_p
-        L.grpo_status_string.argtypes = [i32]
-        L.grpo_workspace_bytes.restype = sz
-        L.grpo_workspace_bytes.argtypes = [i64]
-        L.grpo_row_kernel_plan.restype = i32
-        L.grpo_row_kernel_plan.argtypes = [i32, i64, ctypes.POINTER(RowPlan)]
-        L.grpo_group_advantages.restype = i32
-        L.grpo_group_advantages.argtypes = [vp, i64, vp, i64, i64, f32, i32, vp, vp, i64, vp, vp]
-        L.grpo_logprobs_fwd.restype = i32
-        L.grpo_logprobs_fwd.argtypes = [vp, i32, i64, i64, i64, vp, vp, f32, vp, vp, sz, vp]
-        L.grpo_loss_fwd_bwd.restype = i32
-        L.grpo_loss_fwd_bwd.argtypes = [vp, i32, i64, i64, i64, vp, vp, vp, vp, f32, f32, f32, f32,
-                                        f64, f32, vp, vp, vp, vp, vp, sz, vp]
-        L.grpo_loss_fwd_bwd_noalloc.restype = i32
-        L.grpo_loss_fwd_bwd_noalloc.argtypes = [vp, i32, i64, i64, i64, vp, vp, vp, vp, f32, f32, f32, f32,
-                                                f64, f32, vp, vp, vp, vp, vp, vp]
-        L.grpo_loss_aux_fwd_bwd.restype = i32
-        L.grpo_loss_aux_fwd_bwd.argtypes = [vp, i32, i64, i64, i64, vp, vp, vp, vp, vp, vp, f32, f32, f32,
-                                            f32, f32, f32, f64, f32, vp, vp, vp, vp, vp, vp, sz, vp]
-        L.grpo_total_rewards.restype = i32
-        L.grpo_total_rewards.argtypes = [vp, vp, vp, i64, f32, vp, vp]
-        L.grpo_filter_groups.restype = i32
-        L.grpo_filter_groups.argtypes = [vp, i64, vp, i64, i64, vp, vp, vp, vp, vp]
-        L.grpo_packed_layout.restype = i32
-        L.grpo_packed_layout.argtypes = [vp, i64, i64, i32, vp, vp, vp]
-        L.grpo_workspace_error.restype = i32
-        L.grpo_workspace_error.argtypes = [vp, vp, vp]
-        L.grpo_lmhead_workspace_bytes.restype = sz
-        L.grpo_lmhead_workspace_bytes.argtypes = [i64, i64, i64, i32]
-        L.grpo_lmhead_workspace_bytes_for_chunk.restype = sz
-        L.grpo_lmhead_workspace_bytes_for_chunk.argtypes = [i64, i64, i64, i64]
-        L.grpo_lmhead_logprobs_fwd.restype = i32
-        L.grpo_lmhead_logprobs_fwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, f32, vp, vp, sz, vp]
-        L.grpo_lmhead_loss_fwd_bwd.restype = i32
-        L.grpo_lmhead_loss_fwd_bwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, vp, vp, f32, f32,
-                                               f32, f32, f64, f32, vp, vp, vp, vp, i64, vp, i64, i32,
-                                               vp, sz, vp]
-        L.grpo_lmhead_loss_aux_fwd_bwd.restype = i32
-        L.grpo_lmhead_loss_aux_fwd_bwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, vp, vp, vp, vp,
-                                                   f32, f32, f32, f32, f32, f32, f64, f32, vp, vp, vp, vp,
-                                                   vp, i64, vp, i64, i32, vp, sz, vp]
-        _lib = L
-        fast = _load_fastcall()
-        if fast is not None:
-            fast.bind(*[ctypes.cast(f, vp).value for f in (
-                L.grpo_workspace_bytes, L.grpo_group_advantages, L.grpo_logprobs_fwd, L.grpo_loss_fwd_bwd,
-                L.grpo_loss_aux_fwd_bwd, L.grpo_total_rewards, L.grpo_filter_groups, L.grpo_packed_layout)])
-            _fast = fast
+        with _lib_lock:  # one thread builds and loads
+            if _lib is None:
+                _load_lib()
     return _lib
+
+
+def _load_lib():
+    global _lib, _fast
+    path = _build.LIB_PATH
+    if not os.path.exists(path):
+        path = _build.build_library()
+    L = ctypes.CDLL(path)
+    vp, i64, i32, f32, f64, sz = (ctypes.c_void_p, ctypes.c_int64, ctypes.c_int,
+                                  ctypes.c_float, ctypes.c_double, ctypes.c_size_t)
+    L.grpo_status_string.restype = ctypes.c_char_p
+    L.grpo_status_string.argtypes = [i32]
+    L.grpo_workspace_bytes.restype = sz
+    L.grpo_workspace_bytes.argtypes = [i64]
+    L.grpo_row_kernel_plan.restype = i32
+    L.grpo_row_kernel_plan.argtypes = [i32, i64, ctypes.POINTER(RowPlan)]
+    L.grpo_group_advantages.restype = i32
+    L.grpo_group_advantages.argtypes = [vp, i64, vp, i64, i64, f32, i32, vp, vp, i64, vp, vp]
+    L.grpo_logprobs_fwd.restype = i32
+    L.grpo_logprobs_fwd.argtypes = [vp, i32, i64, i64, i64, vp, vp, f32, vp, vp, sz, vp]
+    L.grpo_loss_fwd_bwd.restype = i32
+    L.grpo_loss_fwd_bwd.argtypes = [vp, i32, i64, i64, i64, vp, vp, vp, vp, f32, f32, f32, f32,
+                                    f64, f32, vp, vp, vp, vp, vp, sz, vp]
+    L.grpo_loss_fwd_bwd_noalloc.restype = i32
+    L.grpo_loss_fwd_bwd_noalloc.argtypes = [vp, i32, i64, i64, i64, vp, vp, vp, vp, f32, f32, f32, f32,
+                                            f64, f32, vp, vp, vp, vp, vp, vp]
+    L.grpo_loss_aux_fwd_bwd.restype = i32
+    L.grpo_loss_aux_fwd_bwd.argtypes = [vp, i32, i64, i64, i64, vp, vp, vp, vp, vp, vp, f32, f32, f32,
+                                        f32, f32, f32, f64, f32, vp, vp, vp, vp, vp, vp, sz, vp]
+    L.grpo_total_rewards.restype = i32
+    L.grpo_total_rewards.argtypes = [vp, vp, vp, i64, f32, vp, vp]
+    L.grpo_filter_groups.restype = i32
+    L.grpo_filter_groups.argtypes = [vp, i64, vp, i64, i64, vp, vp, vp, vp, vp]
+    L.grpo_packed_layout.restype = i32
+    L.grpo_packed_layout.argtypes = [vp, i64, i64, i32, vp, vp, vp]
+    L.grpo_workspace_error.restype = i32
+    L.grpo_workspace_error.argtypes = [vp, vp, vp]
+    L.grpo_lmhead_workspace_bytes.restype = sz
+    L.grpo_lmhead_workspace_bytes.argtypes = [i64, i64, i64, i32]
+    L.grpo_lmhead_workspace_bytes_for_chunk.restype = sz
+    L.grpo_lmhead_workspace_bytes_for_chunk.argtypes = [i64, i64, i64, i64]
+    L.grpo_lmhead_logprobs_fwd.restype = i32
+    L.grpo_lmhead_logprobs_fwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, f32, vp, vp, sz, vp]
+    L.grpo_lmhead_loss_fwd_bwd.restype = i32
+    L.grpo_lmhead_loss_fwd_bwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, vp, vp, f32, f32,
+                                           f32, f32, f64, f32, vp, vp, vp, vp, i64, vp, i64, i32,
+                                           vp, sz, vp]
+    L.grpo_lmhead_loss_aux_fwd_bwd.restype = i32
+    L.grpo_lmhead_loss_aux_fwd_bwd.argtypes = [vp, i64, vp, i64, i64, i64, i64, vp, vp, vp, vp, vp, vp,
+                                               f32, f32, f32, f32, f32, f32, f64, f32, vp, vp, vp, vp,
+                                               vp, i64, vp, i64, i32, vp, sz, vp]
+    fast = _load_fastcall()
+    if fast is not None:
+        fast.bind(*[ctypes.cast(f, vp).value for f in (
+            L.grpo_workspace_bytes, L.grpo_group_advantages, L.grpo_logprobs_fwd, L.grpo_loss_fwd_bwd,
+            L.grpo_loss_aux_fwd_bwd, L.grpo_total_rewards, L.grpo_filter_groups, L.grpo_packed_layout)])
+        _fast = fast
+    _lib = L
 
 
 def _fast_result(out, where):

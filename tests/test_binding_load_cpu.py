@@ -31,6 +31,9 @@ USE = """
 import paper_2505_07291_amd as grpo
 from paper_2505_07291_amd import binding
 assert binding.__file__.startswith(%r), binding.__file__
+import threading
+threads = [threading.Thread(target=grpo.grpo_workspace_bytes, args=(1,)) for _ in range(4)]  # one of them loads
+[t.start() for t in threads], [t.join() for t in threads]
 assert grpo.grpo_workspace_bytes(1) > 0
 print("native" if binding._fast.__class__.__name__ == "module" else binding._fast.total_rewards(1, 2, 3, 4))
 grpo.lib()
