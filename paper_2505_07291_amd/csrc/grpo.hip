@@ -87,7 +87,20 @@ struct RowParams {
     // small batches of narrow rows: the row kernel counts the rows that take part itself (kCountRows)
     int count_here;
     double denom;  // the caller's denominator, or <= 0: that count
+    // where gradient rows start inside a 128-byte line, in 16-byte vectors: row r at (shift0 + r shift_step) mod 8
+    // (both 0: rows are processed from their first vector on, see row_shift)
+    unsigned shift0, shift_step;
 };
+
+// How many vectors in front of row r its first 128-byte line of gradients begins: rows are taken from there on, so that every
+// store of a wavefront covers whole lines.  A store that begins inside a line leaves its first and its last line to be
+// written in two parts, by two wavefronts, and the memory writes each part by itself: 4096 x 152064 bf16, a third of the
+// rows masked, 359 us a step at a pitch of 152064 and 409 at 152072, where it now takes 367; 4096 x 50257 fp32 257 at 50304
+// and 283 at 50260, now 261 (loads do not care: the log-probs pass takes the same time at either pitch).
+__device__ __forceinline__ unsigned row_shift(const RowParams &p, long long r)
+{
+    return (p.shift0 + (unsigned)r * p.shift_step) & 7u;
+}
 
 template <grpo_dtype DT>
 struct Elem;
@@ -198,7 +211,9 @@ template <grpo_dtype DT, int BLOCK>
 __device__ __forceinline__ void zero_row(char *row, int nvec_full, int tail, int tid)
 {
     const u32x4 z = {0u, 0u, 0u, 0u};
-    for (int v = tid; v < nvec_full; v += BLOCK) st16(row + (unsigned)v * 16u, z);
+    const int s = (int)(((unsigned long long)row >> 4) & 7u);  // whole lines, as in row_shift
+    if (tid >= s && tid - s < nvec_full) st16(row + (unsigned)(tid - s) * 16u, z);
+    for (int v = BLOCK + tid - s; v < nvec_full; v += BLOCK) st16(row + (unsigned)v * 16u, z);
     if (tail && tid < tail) store_elem<DT>(row, (long long)nvec_full * Elem<DT>::EPV + tid, 0.f);
 }
 
@@ -859,12 +874,16 @@ constexpr int row_stash_slots(int block, int nv, int nl = 0)
 // REM: the row may be wider still; what lies beyond slot NV + NL is streamed from memory, once
 // for an online (max, sum) pass that is merged into the resident part's statistics and once
 // more for the gradient: 2 reads + 1 write for that remainder only.
+// SHIFT: gradient rows begin inside a 128-byte line (row_shift).  An instantiation of its own: on rows that begin with a
+// line the conditions it adds per slot cost 1 to 2 % of a step and 5 to 8 % of a log-probs pass (4096 x 128256 bf16 297 -> 304
+// us, 129 -> 139), where rows that do not gain 7 to 14 % (128264 apart 339 -> 305, 16384 x 32001 bf16 361 -> 322, 8192 x 50304
+// 267 -> 247, 32768 x 8001 204 -> 174).
 // COUNT: a small batch of narrow rows.  Every workgroup counts the rows that take part (up to four bytes a
 // lane, on their way while the first row is looked up), and the first one writes the header, error word
 // included, for grpo_finalize: no grpo_prepare in front, which is one of four launches of a step on 512 fp32 rows
 // of 1024 (figures at kCountRows).
 // ---------------------------------------------------------------------------
-template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false>
+template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false, bool SHIFT = false>
 // 4 wavefronts per SIMD and 128 registers each; the widest instantiations 2 and 256
 __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowParams p)
 {
@@ -873,6 +892,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     constexpr unsigned SLAB = BLOCK * 16u;  // bytes one pass of the workgroup covers
     static_assert(NL == 0 || !TAIL, "LDS-resident slots come without the ragged-tail slot");
     static_assert(!REM || !TAIL, "the streamed remainder comes without the ragged-tail slot");
+    static_assert(!SHIFT || NL == 0, "rows are held further back in registers only");
     constexpr int RU = AUX ? 2 : 4;  // vectors per lane in flight in the remainder loops (what the registers leave)
     // Gradient vectors of the first STASH slots wait in LDS (each lane its own 16 bytes per
     // slot, no sharing), those of the next RSTASH slots in registers, and all of them are
@@ -891,6 +911,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     __shared__ float lds_max[BLOCK / 64];
     __shared__ float lds_sum[BLOCK / 64];
     __shared__ float lds_sumw[BLOCK / 64];
+    __shared__ float lds_turn[SHIFT && AUX ? 2 : 1][SHIFT ? BLOCK : 1];
     __shared__ long long lds_row[2];
     __shared__ int lds_count[COUNT ? BLOCK / 64 : 1], lds_bad[COUNT ? BLOCK / 64 : 1];
     __shared__ float lds_inv_D;
@@ -999,14 +1020,18 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         if constexpr (NL > 0 || GRPO_OPAQUE_LANE) asm volatile("" : "+v"(t));
         return t;
     };
+    unsigned noff = toff;  // byte offset of this lane inside a slab, as used by the refills
     auto lane_off = [&]() __attribute__((always_inline)) {
-        unsigned o = toff;
+        unsigned o = SHIFT ? noff : toff;  // (held apart they would cost the row a register)
         if constexpr (NL > 0 || GRPO_OPAQUE_LANE) asm volatile("" : "+v"(o));
         return o;
     };
-    unsigned noff = toff;  // byte offset of this lane inside a slab, as used by the refills
-    auto fetch_slot = [&](const char *zrow, int i) __attribute__((always_inline)) {
-        if (i * BLOCK + lane() < nvec_full) buf[i] = ld16(zrow + (size_t)i * SLAB + noff);
+    // A row that begins s vectors into a line of its gradient is held s vectors further back (row_shift): vector v of the
+    // row sits at position v + s, position q in slot q / BLOCK of lane q % BLOCK.  Slot addresses are relative to
+    // position 0 (rows' addresses less 16 s); the first s lanes have nothing in slot 0.
+    auto shift_of = [&](long long r) __attribute__((always_inline)) -> int { return SHIFT ? (int)row_shift(p, r) : 0; };
+    auto fetch_slot = [&](const char *zpos, int i, int s) __attribute__((always_inline)) {
+        if (i * BLOCK + lane() < nvec_full + s && (!SHIFT || i > 0 || lane() >= s)) buf[i] = ld16(zpos + (size_t)i * SLAB + noff);
     };
     // LDS-resident slot j (slot NV + j of the row): lane tid owns the 16 bytes at j * SLAB + toff,
     // which is also where the load puts them (wavefront base in M0, 16 bytes per lane).  Lanes
@@ -1040,11 +1065,11 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         __builtin_amdgcn_sched_barrier(0);
     };
     // (always inlined: as a function of its own it would take the row out of the registers)
-    auto fetch_all = [&](const char *zrow) __attribute__((always_inline)) {
+    auto fetch_all = [&](const char *zpos, int s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) fetch_slot(zrow, i);
+        for (int i = 0; i < NV; ++i) fetch_slot(zpos, i, s);
 #pragma unroll
-        for (int j = 0; j < NL; ++j) fetch_lds_slot(zrow, j);
+        for (int j = 0; j < NL; ++j) fetch_lds_slot(zpos, j);
     };
     auto fetch_rest = [&](const char *zrow, long long y) {
         if (ragged && tid < tail) tz = load_elem<DT>(zrow, (long long)nvec_full * EPV + tid);
@@ -1060,9 +1085,10 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
 
     long long y = 0, y_next = 0;
     long long row = acquire(y);
+    int sh = shift_of(row);
     if (row < p.n_tokens) {
         const char *zrow = (const char *)p.logits + row * p.row_stride * BYTES;
-        fetch_all(zrow);
+        fetch_all(zrow - sh * 16, sh);
         fetch_rest(zrow, y);
     }
     if constexpr (COUNT) {
@@ -1096,21 +1122,35 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         const long long next = acquire(y_next);
         const bool has_next = next < p.n_tokens;
         const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
+        const int sh_next = shift_of(next);
+        const char *zpos_next = zrow_next - sh_next * 16;
 
-        const int vy = (int)(y / EPV);
+        const int vy = (int)(y / EPV) + sh;  // the sampled token's position
         const int ey = (int)(y % EPV);
+        const int npos = nvec_full + sh;
+        if constexpr (SHIFT) {
+            // Where this row has nothing, the one before it may have had something: in front of its first vector and up to
+            // the last position any row has.
+            if (tid < sh) buf[0] = neg_inf_vec<DT>();
+            const int q = npos + ((tid - npos) & (BLOCK - 1));  // this lane's first position behind the row
+            if (q < nvec_full + 7) {
+#pragma unroll
+                for (int i = 0; i < NV; ++i)
+                    if (i == q / BLOCK) buf[i] = neg_inf_vec<DT>();
+            }
+        }
         // The sampled token's logit is taken out of the resident row (replaced by -inf):
         // the sum below is then s_excl = sum_{j != y}, which keeps 1 - p_y = s_excl / s
         // accurate on near-one-hot rows where it would cancel to 0 in fp32.  One lane
         // of one wavefront does this once per row.
-        if (tid == (vy & (BLOCK - 1)) && vy < nvec_full) {
+        if (tid == (vy & (BLOCK - 1)) && vy < npos) {
 #pragma unroll
             for (int i = 0; i < NV; ++i)
                 if (i == vy / BLOCK) set_neg_inf<DT>(buf[i], ey);
         }
         if (ragged) {
             keep_branch(tz);
-            if (vy == nvec_full && tid == ey) tz = -INFINITY;
+            if (vy == npos && tid == ey) tz = -INFINITY;
         }
 
         // reference maximum over j != y, then joined with z_y
@@ -1172,7 +1212,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                 acc += exp_sum_vec<DT>(buf[i], p.k, mk);
             if (!p.bwd && has_next) {
                 order_after(noff, acc);
-                fetch_slot(zrow_next, i);
+                fetch_slot(zpos_next, i, sh_next);
             }
             VECTOR_FENCE();
         }
@@ -1186,9 +1226,17 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             asm volatile("" : "+v"(acc));  // done with this slot before the next one is read
             if (!p.bwd && has_next) {
                 order_after(noff, acc);  // the slot has been read: its refill may start
-                fetch_lds_slot(zrow_next, j);
+                fetch_lds_slot(zpos_next, j);
             }
             VECTOR_FENCE();
+        }
+        if (SHIFT && sh != 0) {  // the lanes' sums to the lanes that have them for a row that begins with a line: the same order of summation
+            const int at = (tid - sh) & (BLOCK - 1);
+            lds_turn[0][SHIFT ? at : 0] = acc;
+            if constexpr (AUX) lds_turn[SHIFT ? 1 : 0][SHIFT ? at : 0] = accw;
+            lds_barrier();
+            acc = lds_turn[0][SHIFT ? tid : 0];
+            if constexpr (AUX) accw = lds_turn[SHIFT ? 1 : 0][SHIFT ? tid : 0];
         }
         if (ragged) {
             keep_branch(tz);
@@ -1224,7 +1272,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             if (sc.c == 0.f && (!AUX || sc.b == 0.f)) {
                 // the gradient of this row is cut: fetch the next row, then zero-fill
                 if (has_next) {
-                    fetch_all(zrow_next);
+                    fetch_all(zpos_next, sh_next);
                     fetch_rest(zrow_next, y_next);
                 }
                 zero_row<DT, BLOCK>(grow, nvec_full, tail, tid);
@@ -1259,6 +1307,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                         }
                     }
                 }
+                char *const gpos = grow - sh * 16;
                 u32x4 rstash[RSTASH > 0 ? RSTASH : 1];
 #pragma unroll
                 for (int i = 0; i < NV; ++i) {
@@ -1277,9 +1326,9 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                     // the slot's gradient waits (LDS, then registers) or, for the last slots, is
                     // stored at once, but in every case behind the next row's load into the slot
                     if (i < STASH) *(u32x4 *)(grad_stash + (size_t)i * SLAB + lane_off()) = packed;
-                    if (has_next) fetch_slot(zrow_next, i);
+                    if (has_next) fetch_slot(zpos_next, i, sh_next);
                     if (i >= STASH && i < STASH + RSTASH) rstash[i - STASH < 0 ? 0 : i - STASH] = packed;
-                    if (i >= STASH + RSTASH && v < nvec_full) st16(grow + (size_t)i * SLAB + lane_off(), packed);
+                    if (i >= STASH + RSTASH && v < npos && (!SHIFT || i > 0 || lane() >= sh)) st16(gpos + (size_t)i * SLAB + lane_off(), packed);
                     VECTOR_FENCE();
                 }
 #pragma unroll
@@ -1296,8 +1345,8 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                         packed = pack<DT>(g);
                     }
                     order_after(noff, packed);  // the slot has been read: its refill may start
-                    if (has_next) fetch_lds_slot(zrow_next, j);
-                    if (v < nvec_full) st16(grow + (size_t)(NV + j) * SLAB + lane_off(), packed);
+                    if (has_next) fetch_lds_slot(zpos_next, j);
+                    if (v < npos) st16(gpos + (size_t)(NV + j) * SLAB + lane_off(), packed);
                     VECTOR_FENCE();
                 }
                 if (ragged && tid < tail) {
@@ -1309,22 +1358,23 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                     } else {
                         g = __builtin_amdgcn_exp2f(fmaf(tz, p.k, -sc.shift)) * q;
                     }
-                    if (vy == nvec_full && tid == ey) g = gy;
+                    if (vy == npos && tid == ey) g = gy;
                     store_elem<DT>(grow, (long long)nvec_full * EPV + tid, g);
                 }
                 if (has_next) fetch_rest(zrow_next, y_next);
 #pragma unroll
                 for (int i = 0; i < STASH; ++i) {
                     const u32x4 packed = *(const u32x4 *)(grad_stash + (size_t)i * SLAB + lane_off());
-                    if (i * BLOCK + lane() < nvec_full) st16(grow + (size_t)i * SLAB + lane_off(), packed);
+                    if (i * BLOCK + lane() < npos && (!SHIFT || i > 0 || lane() >= sh)) st16(gpos + (size_t)i * SLAB + lane_off(), packed);
                 }
 #pragma unroll
                 for (int i = STASH; i < STASH + RSTASH; ++i)
-                    if (i * BLOCK + lane() < nvec_full) st16(grow + (size_t)i * SLAB + lane_off(), rstash[i - STASH]);
+                    if (i * BLOCK + lane() < npos && (!SHIFT || i > 0 || lane() >= sh)) st16(gpos + (size_t)i * SLAB + lane_off(), rstash[i - STASH]);
             }
         }
         row = next;
         y = y_next;
+        sh = sh_next;
     }
 }
 
@@ -2171,7 +2221,7 @@ int cu_count()
     return n;
 }
 
-template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false>
+template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false, bool SHIFT = false>
 void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
 {
     RowParams p = p_in;
@@ -2191,12 +2241,12 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
         static std::atomic<bool> attr_done[64];  // setting the attribute twice is harmless
         int dev = 0;
         if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !attr_done[dev].load()) {
-            if (hipFuncSetAttribute((const void *)grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT>,
+            if (hipFuncSetAttribute((const void *)grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT, SHIFT>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) == hipSuccess)
                 attr_done[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT>), dim3((unsigned)grid), dim3(BLOCK),
+    hipLaunchKernelGGL((grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT, SHIFT>), dim3((unsigned)grid), dim3(BLOCK),
                        lds_bytes, st, p);
 }
 
@@ -2294,6 +2344,15 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
 #define GRPO_ROW_CASE(ID, BLOCK, NV, TAIL, NL, RSTP, RSTA, REM, PERCU)                              \
     case ID:                                                                                       \
         static_assert(PERCU == row_blocks_per_cu(BLOCK, NV), "workgroups per CU");                \
+        /* gradient rows that begin inside a line, if the slots hold a row seven vectors further back */ \
+        if constexpr (NL == 0) {                                                                   \
+            /* 512 lanes of 26 and 32 slots: the kernel for ragged rows serves whole ones too */   \
+            constexpr bool T = TAIL || (BLOCK == 512 && (NV == 26 || NV == 32));                   \
+            if ((p.shift0 | p.shift_step) != 0 && p.vocab / Elem<DT>::EPV + 7 <= BLOCK * NV) {     \
+                launch_cached<DT, BLOCK, NV, AUX, T, 0, (AUX ? RSTA : RSTP), false, false, true>(p, PERCU, st); \
+                break;                                                                             \
+            }                                                                                      \
+        }                                                                                          \
         launch_cached<DT, BLOCK, NV, AUX, TAIL, NL, (AUX ? RSTA : RSTP), REM>(p, PERCU, st);      \
         break;
         GRPO_ROW_KERNELS(GRPO_ROW_CASE)
@@ -2430,6 +2489,8 @@ grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens,
         p.delta = delta;
         p.grad_scale = grad_scale;
         p.bwd = 1;
+        p.shift0 = (unsigned)((uintptr_t)grad_logits >> 4) & 7u;
+        p.shift_step = (unsigned)(row_stride * (dtype == GRPO_BF16 ? 2 : 4) >> 4) & 7u;
         p.order = order;
         if (aux) {
             p.ref_lp = kl_coef != 0.f ? ref_logprobs : nullptr;

@@ -125,3 +125,45 @@ def test_rows_counted_by_the_row_kernel(aux, dtype, vocab, rows, bad):
             got.append([t[:rows] if t.dim() > 0 and t.shape[0] == n else t for t in out])
         for a, b in zip(*got):
             assert torch.equal(a, b)
+
+
+# gradient rows that begin with a 128-byte line, or anywhere inside one: the resident kernels then hold a row up to seven
+# vectors further back, and sum in the same order: the same bits, nothing written outside the rows.  Every resident width,
+# whole and ragged rows, the last widths that leave room for it and the first that do not.
+@pytest.mark.parametrize("aux", [False, True])
+@pytest.mark.parametrize("dtype,epv", [(torch.bfloat16, 8), (torch.float32, 4)])
+@pytest.mark.parametrize("vectors", [1, 5, 249, 250, 1017, 1018, 4000, 6649, 8185, 8186, 10233, 13305, 16377, 16378, 19449,
+                                     22521, 22522])
+def test_rows_that_begin_inside_a_line(aux, dtype, epv, vectors):
+    rows = 23
+    for tail in (0, epv - 1) if vectors <= 16384 else (0,):
+        vocab = vectors * epv + tail
+        g = torch.Generator(device="cuda").manual_seed(vocab)
+        z = (torch.randn(rows, vocab, generator=g, device="cuda") * 3).to(dtype)
+        z[1, : vocab // 2] = float("-inf")
+        tokens = torch.randint(0, vocab, (rows,), generator=g, device="cuda")
+        tokens[0], tokens[1], tokens[2] = 0, vocab - 1, min(vocab - 1, 3 * epv)
+        old, adv, ref = (torch.randn(rows, generator=g, device="cuda") for _ in range(3))
+        mask = (torch.rand(rows, generator=g, device="cuda") < 0.7).to(torch.uint8)
+        mask[:4] = 1
+        want = None
+        for start, apart in ((0, 8), (0, 1), (3, 8), (5, 3), (7, 7)):   # of the first row, between rows: in vectors mod 8
+            pitch = ((vectors + 1 + 7) // 8 * 8 + apart % 8) * epv
+            size = rows * pitch + 8 * epv + pitch
+            bufs = [torch.full((size,), 3.0, dtype=dtype, device="cuda") for _ in range(2)]
+            views = [b[start * epv:].as_strided((rows, vocab), (pitch, 1)) for b in bufs]
+            views[0].copy_(z)
+            for b in bufs:
+                assert b.data_ptr() % 128 == 0
+            if aux:
+                out = grpo.grpo_loss_aux_fwd_bwd(views[0], tokens, old, ref, adv, mask, kl_coef=0.1, entropy_coef=0.01,
+                                                 grad_logits=views[1])
+            else:
+                out = grpo.grpo_loss_fwd_bwd(views[0], tokens, old, adv, mask, grad_logits=views[1])
+            got = [views[1].clone()] + [t for t in out[:-1]]
+            views[1].fill_(3.0)
+            assert bool((bufs[1] == 3.0).all()), "written outside the rows"
+            if want is None:
+                want = got
+            for a, b in zip(got, want):
+                assert torch.equal(a.nan_to_num(nan=77.0), b.nan_to_num(nan=77.0)), (vocab, start, apart)
