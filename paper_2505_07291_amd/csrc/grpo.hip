@@ -1435,6 +1435,9 @@ __device__ __forceinline__ void online_batch(u32x4 (&z)[U], float k, float &m, f
 // Whole step in turn on one card, against one vector in flight per lane and rows strided over the grid (which
 // gave some workgroups the live head of every response and others its masked tail): 2048 x 100003 fp32
 // 317 -> 270 us, 4096 x 152069 bf16 550 -> 466 us.  Batches of five and six: 270 and 286, 473 and 486.
+// Rows whose gradient begins inside a line are stored in whole lines by lanes turned by that much (4096 x 152069 bf16 step
+// 462 -> 412 us, what it takes at a pitch of whole lines; 2048 x 100003 fp32 333 -> 301).  Two more batches of a row
+// held in LDS between the passes saved 1 %: the second reads are served by the caches.
 // ---------------------------------------------------------------------------
 constexpr int kStreamBlock = 512, kStreamPerCu = 2, kStreamBatch = 4;
 template <grpo_dtype DT, bool AUX>
@@ -1445,6 +1448,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     __shared__ float lds_max[BLOCK / 64];
     __shared__ float lds_sum[BLOCK / 64];
     __shared__ float lds_sumw[BLOCK / 64];
+    __shared__ float lds_turn[AUX ? 2 : 1][BLOCK];
     __shared__ long long lds_row[2];
     const int tid = threadIdx.x;
     const int nvec_full = (int)(p.vocab / EPV);
@@ -1472,38 +1476,50 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     };
     u32x4 A[U], B[U];
     float zy = 0.f, tz = -INFINITY;  // the sampled token's logit; lane i < tail: entry i of the ragged last vector
-    // the lane's number and byte offset, opaque at every use (see the resident kernel: kept for every
-    // slot of every batch they would fill the registers)
-    auto lane = [&]() __attribute__((always_inline)) {
-        int t = tid;
-        asm volatile("" : "+v"(t));
-        return t;
-    };
+    // Lanes are turned by as many vectors as the row's gradient begins inside a line (row_shift): lane t has the vectors
+    // (t - s) mod BLOCK of every slot, so that a wavefront's stores are whole lines but for the one at a slot's border.  The
+    // lane's byte offset in a slot is opaque at every use (see the resident kernel: kept for every
+    // slot of every batch it would fill the registers).
     unsigned noff = (unsigned)tid * 16u;
-    auto load_slot = [&](u32x4 &z, const char *zrow, int slot) __attribute__((always_inline)) {
+    auto offset = [&](int s) __attribute__((always_inline)) -> unsigned {
+        unsigned o = noff;
+        asm volatile("" : "+v"(o));
+        return (o - 16u * (unsigned)s) & (SLAB - 1u);
+    };
+    auto first_vector = [&](int s) __attribute__((always_inline)) -> int { return (int)(offset(s) >> 4); };
+    // how far into slot `slot` the row's vectors reach, in bytes
+    auto reach = [&](int slot) __attribute__((always_inline)) -> int { return (nvec_full - slot * BLOCK) * 16; };
+    auto load_slot = [&](u32x4 &z, const char *zrow, int s, int slot) __attribute__((always_inline)) {
         z = neg_inf_vec<DT>();
-        if (slot * BLOCK + lane() < nvec_full) z = *(const u32x4 *)(zrow + (size_t)slot * SLAB + noff);
+        const unsigned o = offset(s);
+        if ((int)o < reach(slot)) z = *(const u32x4 *)(zrow + (size_t)slot * SLAB + o);
     };
-    auto load_batch = [&](u32x4 (&buf)[U], const char *zrow, int b) __attribute__((always_inline)) {
+    auto load_batch = [&](u32x4 (&buf)[U], const char *zrow, int s, int b) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) load_slot(buf[u], zrow, b * U + u);
+        for (int u = 0; u < U; ++u) load_slot(buf[u], zrow, s, b * U + u);
     };
-    auto load_first = [&](const char *zrow, long long y) __attribute__((always_inline)) {
-        load_batch(A, zrow, 0);
-        load_batch(B, zrow, 1);
+    auto load_last = [&](const char *zrow, int s, long long y) __attribute__((always_inline)) {
         zy = load_elem<DT>(zrow, y);
-        if (tid < tail) tz = load_elem<DT>(zrow, (long long)nvec_full * EPV + tid);
+        const int l = first_vector(s);
+        if (l < tail) tz = load_elem<DT>(zrow, (long long)nvec_full * EPV + l);
+    };
+    auto load_first = [&](const char *zrow, int s, long long y) __attribute__((always_inline)) {
+        load_batch(A, zrow, s, 0);
+        load_batch(B, zrow, s, 1);
+        load_last(zrow, s, y);
     };
 
     long long y = 0, y_next = 0;
     long long row = acquire(y);
-    if (row < p.n_tokens) load_first((const char *)p.logits + row * p.row_stride * BYTES, y);
+    int sh = (int)row_shift(p, row);
+    if (row < p.n_tokens) load_first((const char *)p.logits + row * p.row_stride * BYTES, sh, y);
 
     while (row < p.n_tokens) {
         const char *zrow = (const char *)p.logits + row * p.row_stride * BYTES;
         const long long next = acquire(y_next);
         const bool has_next = next < p.n_tokens;
         const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
+        const int sh_next = (int)row_shift(p, next);
         const int vy = (int)(y / EPV);
         const int ey = (int)(y % EPV);
 
@@ -1511,24 +1527,37 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
         auto stat_step = [&](u32x4 (&buf)[U], int b) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < U; ++u)  // the sampled token's logit stays out of the sums
-                if ((b * U + u) == vy / BLOCK && lane() == vy % BLOCK && vy < nvec_full) set_neg_inf<DT>(buf[u], ey);
+                if ((b * U + u) == vy / BLOCK && offset(sh) == (unsigned)(vy % BLOCK) * 16u && vy < nvec_full) set_neg_inf<DT>(buf[u], ey);
             online_batch<DT, AUX, U>(buf, p.k, m, s, w);
-            if (b + 2 < nb) load_batch(buf, zrow, b + 2);
+            if (b + 2 < nb) load_batch(buf, zrow, sh, b + 2);
         };
         for (int b = 0; b < nb; b += 2) {
             stat_step(A, b);
             if (b + 1 < nb) stat_step(B, b + 1);
         }
-        u32x4 tv[1] = {neg_inf_vec<DT>()};  // the ragged last vector, one entry per lane
+        // the ragged last vector, one entry per lane: its word (the rest of the lane's vector is -inf)
+        unsigned tword = kNegInfF32;
+        if (DT == GRPO_BF16) tword = kNegInfBf16x2;
         if (tail) {
-            if (tid < tail && !(vy == nvec_full && tid == ey))
-                tv[0][0] = DT == GRPO_BF16 ? (kNegInfF32 | (as_u32(tz) >> 16)) : as_u32(tz);
+            const int l = first_vector(sh);
+            if (l < tail && !(vy == nvec_full && l == ey))
+                tword = DT == GRPO_BF16 ? (kNegInfF32 | (as_u32(tz) >> 16)) : as_u32(tz);
+            u32x4 tv[1] = {neg_inf_vec<DT>()};
+            tv[0][0] = tword;
             online_batch<DT, AUX, 1>(tv, p.k, m, s, w);
         }
         const float mx = fmaxf(block_max<BLOCK>(m, lds_max), zy);
         const float mk = mx * p.k;
         float scaled, scaledw;
         online_rescale<AUX>(m, s, w, mx, p.k, scaled, scaledw);
+        if (sh != 0) {  // the lanes' sums in the order of an unturned row
+            const int l = first_vector(sh);
+            lds_turn[0][l] = scaled;
+            if constexpr (AUX) lds_turn[AUX ? 1 : 0][l] = scaledw;
+            lds_barrier();
+            scaled = lds_turn[0][tid];
+            if constexpr (AUX) scaledw = lds_turn[AUX ? 1 : 0][tid];
+        }
         RowScalars sc;
         if constexpr (AUX) {
             block_sum2<BLOCK>(scaled, scaledw, lds_sum, lds_sumw);
@@ -1546,7 +1575,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
 
         char *grow = (char *)p.grad + row * p.row_stride * BYTES;
         if (!p.bwd || (sc.c == 0.f && (!AUX || sc.b == 0.f))) {
-            if (has_next) load_first(zrow_next, y_next);
+            if (has_next) load_first(zrow_next, sh_next, y_next);
             if (p.bwd) zero_row<DT, BLOCK>(grow, nvec_full, tail, tid);
         } else {
             const float q = -sc.c * p.inv_T;
@@ -1565,41 +1594,43 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
                 u32x4 out[U];
                 const bool more = b >= 2 || has_next;  // A is done with batch 0, B with batch 1: the next row's
                 const char *from = b >= 2 ? zrow : zrow_next;
-                const int b_load = b >= 2 ? b - 2 : b;
+                const int b_load = b >= 2 ? b - 2 : b, s_load = b >= 2 ? sh : sh_next;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     forget(buf[u]);
                     out[u] = buf[u];
-                    grad_of(out[u], (b * U + u) * BLOCK + lane() == vy, ey);
+                    grad_of(out[u], (int)offset(sh) == (vy - (b * U + u) * BLOCK) * 16, ey);
                     order_after(noff, out[u]);
-                    if (more) load_slot(buf[u], from, b_load * U + u);
+                    if (more) load_slot(buf[u], from, s_load, b_load * U + u);
                     VECTOR_FENCE();
                 }
 #pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if ((b * U + u) * BLOCK + lane() < nvec_full)
-                        st16(grow + (size_t)(b * U + u) * SLAB + noff, out[u]);
+                for (int u = 0; u < U; ++u) {
+                    const unsigned o = offset(sh);
+                    if ((int)o < reach(b * U + u)) st16(grow + (size_t)(b * U + u) * SLAB + o, out[u]);
+                }
             };
             for (int b = (nb - 1) | 1; b > 0; b -= 2) {
                 if (b < nb) grad_step(B, b);
                 grad_step(A, b - 1);
             }
             if (tail) {
-                grad_of(tv[0], vy == nvec_full && tid == ey, 0);
-                if (tid < tail) {
+                const int l = first_vector(sh);
+                u32x4 tv = neg_inf_vec<DT>();
+                tv[0] = tword;
+                grad_of(tv, vy == nvec_full && l == ey, 0);
+                if (l < tail) {
                     if constexpr (DT == GRPO_BF16)
-                        ((unsigned short *)grow)[(long long)nvec_full * EPV + tid] = (unsigned short)(tv[0][0] & 0xffffu);
+                        ((unsigned short *)grow)[(long long)nvec_full * EPV + l] = (unsigned short)(tv[0] & 0xffffu);
                     else
-                        ((unsigned *)grow)[(long long)nvec_full * EPV + tid] = tv[0][0];
+                        ((unsigned *)grow)[(long long)nvec_full * EPV + l] = tv[0];
                 }
             }
-            if (has_next) {
-                zy = load_elem<DT>(zrow_next, y_next);
-                if (tid < tail) tz = load_elem<DT>(zrow_next, (long long)nvec_full * EPV + tid);
-            }
+            if (has_next) load_last(zrow_next, sh_next, y_next);
         }
         row = next;
         y = y_next;
+        sh = sh_next;
     }
 }
 

@@ -128,15 +128,16 @@ def test_rows_counted_by_the_row_kernel(aux, dtype, vocab, rows, bad):
 
 
 # gradient rows that begin with a 128-byte line, or anywhere inside one: the resident kernels then hold a row up to seven
-# vectors further back, and sum in the same order: the same bits, nothing written outside the rows.  Every resident width,
-# whole and ragged rows, the last widths that leave room for it and the first that do not.
+# vectors further back, the streaming one turns its lanes, and both sum in the same order: the same bits, nothing written
+# outside the rows.  Every resident width, whole and ragged rows, the last widths that leave room for it and the first that
+# do not; streamed ragged rows (those of more than 16384 vectors).
 @pytest.mark.parametrize("aux", [False, True])
 @pytest.mark.parametrize("dtype,epv", [(torch.bfloat16, 8), (torch.float32, 4)])
 @pytest.mark.parametrize("vectors", [1, 5, 249, 250, 1017, 1018, 4000, 6649, 8185, 8186, 10233, 13305, 16377, 16378, 19449,
                                      22521, 22522])
 def test_rows_that_begin_inside_a_line(aux, dtype, epv, vectors):
     rows = 23
-    for tail in (0, epv - 1) if vectors <= 16384 else (0,):
+    for tail in (0, epv - 1):
         vocab = vectors * epv + tail
         g = torch.Generator(device="cuda").manual_seed(vocab)
         z = (torch.randn(rows, vocab, generator=g, device="cuda") * 3).to(dtype)
