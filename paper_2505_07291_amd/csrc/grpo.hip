@@ -989,13 +989,23 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         }
     };
     // next row that needs the full treatment; rows that do not (masked, bad token id)
-    // are finished on the way
-    auto acquire = [&](long long &y) -> long long {
+    // are finished on the way.  With a live row in hand whose loads are under way (`holding`) and live rows handed out first,
+    // one such row is: under its zeros the loads arrive, more of them would keep every workgroup's last live row waiting for the
+    // end of the batch (8192 x 128256 bf16 with the auxiliary terms 650 -> 637 us, 1000 x 152064 bf16 of which 106 are live
+    // 81 -> 72; not even one costs batches of few rows, whose only loads it is: 512 x 152064, half of them live, 54 -> 57).
+    // Rows with a streamed remainder gain nothing.
+    bool none_left = false;
+    const bool masked_last = !REM && queued && p.order;
+    auto acquire = [&](long long &y, bool holding) -> long long {
         for (;;) {
             long long r = grab();
-            if (r >= p.n_tokens) return p.n_tokens;
+            if (r >= p.n_tokens) {
+                none_left = true;
+                return p.n_tokens;
+            }
             if (p.order) r = uniform((long long)p.order[r]);  // position in the hand-out order -> row
             if (row_is_live<DT, BLOCK, COUNT>(p, r, nvec_full, tail, y)) return r;
+            if (holding && masked_last) return p.n_tokens;
         }
     };
 
@@ -1083,9 +1093,11 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         }
     };
 
-    long long y = 0, y_next = 0;
-    long long row = acquire(y);
-    int sh = shift_of(row);
+    long long y = 0, y_next = 0, row;
+    int sh;
+rows_from_none:
+    row = acquire(y, false);
+    sh = shift_of(row);
     if (row < p.n_tokens) {
         const char *zrow = (const char *)p.logits + row * p.row_stride * BYTES;
         fetch_all(zrow - sh * 16, sh);
@@ -1119,7 +1131,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     while (row < p.n_tokens) {
         // Take the following row now: its loads are issued while this row's last pass
         // still computes, into the registers that pass has just finished with.
-        const long long next = acquire(y_next);
+        const long long next = acquire(y_next, true);
         const bool has_next = next < p.n_tokens;
         const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
         const int sh_next = shift_of(next);
@@ -1376,6 +1388,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
         y = y_next;
         sh = sh_next;
     }
+    if (masked_last && !none_left) goto rows_from_none;
 }
 
 // One batch of vectors joined into a lane's online statistics: running maximum m (in logit units),
@@ -1457,7 +1470,9 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     const bool queued = p.queued != 0;
     long long strided_next = blockIdx.x;
     unsigned grabs = 0;
-    auto acquire = [&](long long &y) -> long long {
+    bool none_left = false;  // as in the resident kernel
+    const bool masked_last = queued && p.order;
+    auto acquire = [&](long long &y, bool holding) -> long long {
         for (;;) {
             long long r;
             if (queued) {
@@ -1469,9 +1484,13 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
                 r = strided_next;
                 strided_next += gridDim.x;
             }
-            if (r >= p.n_tokens) return p.n_tokens;
+            if (r >= p.n_tokens) {
+                none_left = true;
+                return p.n_tokens;
+            }
             if (p.order) r = uniform((long long)p.order[r]);
             if (row_is_live<DT, BLOCK>(p, r, nvec_full, tail, y)) return r;
+            if (holding && masked_last) return p.n_tokens;
         }
     };
     u32x4 A[U], B[U];
@@ -1509,14 +1528,16 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
         load_last(zrow, s, y);
     };
 
-    long long y = 0, y_next = 0;
-    long long row = acquire(y);
-    int sh = (int)row_shift(p, row);
+    long long y = 0, y_next = 0, row;
+    int sh;
+rows_from_none:
+    row = acquire(y, false);
+    sh = (int)row_shift(p, row);
     if (row < p.n_tokens) load_first((const char *)p.logits + row * p.row_stride * BYTES, sh, y);
 
     while (row < p.n_tokens) {
         const char *zrow = (const char *)p.logits + row * p.row_stride * BYTES;
-        const long long next = acquire(y_next);
+        const long long next = acquire(y_next, true);
         const bool has_next = next < p.n_tokens;
         const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
         const int sh_next = (int)row_shift(p, next);
@@ -1632,6 +1653,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
         y = y_next;
         sh = sh_next;
     }
+    if (masked_last && !none_left) goto rows_from_none;
 }
 
 // ---------------------------------------------------------------------------
