@@ -78,6 +78,8 @@ struct RowParams {
     int queued;       // rows come from the queue in the workspace (0: strided over the grid)
     int queue_chunk;  // rows taken from the queue per increment
     int queue_parts;  // counters in use (1 or kQueueParts)
+    int queue_more;   // log-probs only: how many at once while a counter has not passed more_until
+    long long more_until;
     // auxiliary terms (kernels instantiated with AUX only)
     const float *ref_lp;  // reference-policy log-probs, or NULL (no KL term)
     const float *token_w; // per-token weights omega_t, or NULL (all ones); 0 = masked row
@@ -369,6 +371,22 @@ __device__ __forceinline__ void block_sum2(float &a, float &b, float *lds_a, flo
     }
 }
 
+// Reads what no kernel of this call writes while it runs, through the scalar cache where the address is uniform.  A vector
+// load's wait is a wait for everything older in the memory queue too, the gradient stores of the row before among it.
+template <typename T>
+__device__ __forceinline__ T fixed_load(const T *p)
+{
+    return *(const __attribute__((address_space(4))) T *)(unsigned long long)p;
+}
+// A byte of an array of n: the four bytes around it where they are all inside the array.
+__device__ __forceinline__ bool fixed_byte_set(const unsigned char *a, long long i, long long n)
+{
+    const unsigned long long at = (unsigned long long)(a + i), word = at & ~3ull;
+    if (word >= (unsigned long long)a && word + 4 <= (unsigned long long)(a + n))
+        return (fixed_load((const unsigned *)word) >> (8 * (unsigned)(at & 3))) & 0xffu;
+    return a[i] != 0;
+}
+
 // Per-row scalars once the row statistics are known.
 //   mk     = (max_j z_j) * k                      (k = log2 e / T)
 //   s_excl = sum_{j != y} exp2(z_j k - mk)        (the sampled token is left out so that
@@ -445,8 +463,8 @@ __device__ __forceinline__ RowScalars row_scalars(const RowParams &p, long long 
     if (!p.bwd) return o;
 
     float dJ;
-    surrogate(p, hw_exp(o.logp - p.old_lp[row]), p.adv[row], o.J, dJ, o.flags);
-    o.c = -(p.grad_scale * dJ) * (inv_D ? *inv_D : (float)p.hdr->inv_D);
+    surrogate(p, hw_exp(o.logp - fixed_load(p.old_lp + row)), fixed_load(p.adv + row), o.J, dJ, o.flags);
+    o.c = -(p.grad_scale * dJ) * (inv_D ? *inv_D : (float)fixed_load(&p.hdr->inv_D));
     return o;
 }
 
@@ -721,16 +739,16 @@ __device__ __forceinline__ void write_row_aux(const RowParams &p, long long row,
 // Decides whether a row takes part; handles the rows that do not (masked, or with a
 // token id outside the vocabulary).  Returns true when the row must be processed.
 // COUNT: the header's error word is not the rows' business (see grpo_rows_cached).
-template <grpo_dtype DT, int BLOCK, bool COUNT = false>
+template <grpo_dtype DT, int BLOCK, bool COUNT = false, bool FIXED = false>
 __device__ __forceinline__ bool row_is_live(const RowParams &p, long long row, int nvec_full,
                                             int tail, long long &y)
 {
-    bool live = p.mask ? (p.mask[row] != 0) : true;
+    bool live = p.mask ? (FIXED ? fixed_byte_set(p.mask, row, p.n_tokens) : p.mask[row] != 0) : true;
     if (live && p.token_w) live = p.token_w[row] != 0.f;
     bool bad = false;
     y = 0;
     if (live) {
-        y = p.tokens[row];
+        y = FIXED ? fixed_load(p.tokens + row) : p.tokens[row];
         if (y < 0 || y >= p.vocab) {
             live = false;
             bad = true;
@@ -906,6 +924,9 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     // further slots that wait in registers
     constexpr int RSTASH = RST < 0 ? row_reg_stash_slots(BLOCK, NV) : RST < NV - STASH ? RST : NV - STASH;
     static_assert(STASH + RSTASH <= NV, "more waiting slots than register slots");
+    // The next row is asked for before the passes over this one; not where the registers are short (256 lanes of 26 and 32
+    // slots: 8192 x 32000 fp32 step 304 us, 312 with it; the auxiliary terms -1 to +2 %).
+    constexpr bool AHEAD = !AUX && !REM && !(BLOCK == 256 && NV > 19);
     extern __shared__ __attribute__((aligned(16))) char row_stash[];
     char *const grad_stash = row_stash + (size_t)NL * SLAB;  // behind the LDS-resident part of the row
     __shared__ float lds_max[BLOCK / 64];
@@ -950,12 +971,27 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     long long strided_base = 0;
     unsigned turn = blockIdx.x, grabs = 0;
     // very narrow rows are also handed out several at a time
-    const long long chunk = p.queue_chunk;
+    long long chunk = p.queue_chunk;
     long long chunk_next = 0, chunk_end = 0;  // positions inside the current partition
     // consecutive workgroups sit on different XCDs; dividing by 8 first spreads every
     // partition over all XCDs (tying a partition to one XCD measured 4 % slower)
     const int nparts = p.queue_parts;
     int part = (int)((blockIdx.x / 8) % nparts), parts_done = 0;
+    // The counter is asked before the passes over a row (ask) and its answer shared with one of their barriers (tell).  Asked
+    // when it was needed, counter, mask, order and token were four loads in a chain between two rows, and each wait was for
+    // everything in flight (the next three now go through the scalar cache).  Log-probs of 8192 x 128256 bf16
+    // 251 -> 238 us, of 4096 x 50304 fp32 98 -> 94; steps on rows of several workgroups to a CU 340 -> 308 (30000 x 16384 bf16)
+    // and 333 -> 322 (16384 x 32000), on wider ones, which HBM bounds, as before.
+    bool asked = false;
+    unsigned long long answer = 0;
+    auto ask = [&]() __attribute__((always_inline)) {
+        asked = AHEAD && queued && chunk_next >= chunk_end && parts_done < nparts;
+        if (!AUX && !REM && !p.bwd) chunk = chunk_end < p.more_until ? p.queue_more : p.queue_chunk;
+        if (asked && tid == 0) answer = atomicAdd(queue_counters(p.hdr) + part * kQueueStride, (unsigned long long)chunk);
+    };
+    auto tell = [&]() __attribute__((always_inline)) {
+        if (asked && tid == 0) lds_row[grabs & 1u] = (long long)answer;
+    };
     auto grab = [&]() -> long long {
         if (!queued) {
             const long long r = strided_base + turn;
@@ -974,10 +1010,14 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             // two LDS slots used alternately: the barrier of grab k+1 separates the reads
             // of grab k from the write of grab k+2 into the same slot
             const unsigned slot = grabs++ & 1u;
-            if (tid == 0)
-                lds_row[slot] = (long long)atomicAdd(queue_counters(p.hdr) + part * kQueueStride,
-                                                     (unsigned long long)chunk);
-            lds_barrier();
+            if (!asked) {
+                if (!AUX && !REM && !p.bwd) chunk = chunk_end < p.more_until ? p.queue_more : p.queue_chunk;
+                if (tid == 0)
+                    lds_row[slot] = (long long)atomicAdd(queue_counters(p.hdr) + part * kQueueStride,
+                                                         (unsigned long long)chunk);
+                lds_barrier();
+            }
+            asked = false;
             const long long base = uniform(lds_row[slot]);
             if (part + (long long)nparts * base >= p.n_tokens) {
                 part = (part + 1) % nparts;  // this partition is exhausted: help with the next
@@ -1003,8 +1043,8 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
                 none_left = true;
                 return p.n_tokens;
             }
-            if (p.order) r = uniform((long long)p.order[r]);  // position in the hand-out order -> row
-            if (row_is_live<DT, BLOCK, COUNT>(p, r, nvec_full, tail, y)) return r;
+            if (p.order) r = uniform((long long)(AHEAD ? fixed_load(p.order + r) : p.order[r]));  // position in the hand-out order -> row
+            if (row_is_live<DT, BLOCK, COUNT, AHEAD>(p, r, nvec_full, tail, y)) return r;
             if (holding && masked_last) return p.n_tokens;
         }
     };
@@ -1129,14 +1169,23 @@ rows_from_none:
     }
 
     while (row < p.n_tokens) {
-        // Take the following row now: its loads are issued while this row's last pass
+        // Take the following row: its loads are issued while this row's last pass
         // still computes, into the registers that pass has just finished with.
-        const long long next = acquire(y_next, true);
-        const bool has_next = next < p.n_tokens;
-        const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
-        const int sh_next = shift_of(next);
-        const char *zpos_next = zrow_next - sh_next * 16;
-
+        long long next;
+        bool has_next;
+        const char *zrow_next, *zpos_next;
+        int sh_next;
+        auto take_next = [&]() __attribute__((always_inline)) {
+            next = acquire(y_next, true);
+            has_next = next < p.n_tokens;
+            zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
+            sh_next = shift_of(next);
+            zpos_next = zrow_next - sh_next * 16;
+        };
+        if constexpr (AHEAD)
+            ask();
+        else
+            take_next();
         const int vy = (int)(y / EPV) + sh;  // the sampled token's position
         const int ey = (int)(y % EPV);
         const int npos = nvec_full + sh;
@@ -1209,8 +1258,11 @@ rows_from_none:
             }
             mx = fmaxf(mx, rem_m);
         }
+        if constexpr (AHEAD) tell();
         mx = fmaxf(block_max<BLOCK>(mx, lds_max), zy);
         const float mk = mx * p.k;
+
+        if constexpr (AHEAD) take_next();
 
         // sum of exponentials over j != y; in log-probs-only mode this is the last use
         // of the row, so the next row is fetched slot by slot behind it
@@ -2288,6 +2340,12 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
     // 126 and 114) but wider ones lose (32000 of 4000 126 and 140, 10000 fp32 rows of 7001, ten rounds, 107 and 113).
     if (p.n_tokens <= grid || (p.queue_chunk > 1 && p.n_tokens <= 8 * grid)) p.queued = 0;
     if (grid > p.n_tokens) grid = p.n_tokens;
+    // The log-probs pass asks for twice as many rows at once while two rounds of that are left, if there is a mask: a masked
+    // row, which it only looks at, costs it the counter's answer all the same.  A third of the rows masked, 16384 x 152064 bf16:
+    // one at a time 526 us, two 502, four 495, eight 490; 8192 x 128256 238, 224, 219, 234; 4096 x 50304 fp32 95, 92, 94, 96.
+    // None masked, 16384 x 152064: 735, 755, 780, 767.
+    p.queue_more = p.queue_chunk * (p.mask ? 2 : 1);
+    p.more_until = (p.n_tokens - 2 * grid * p.queue_more) / p.queue_parts;
     // dynamic LDS: the waiting gradient slots, or the LDS-resident part of the row
     constexpr unsigned lds_bytes = (unsigned)(NL + row_stash_slots(BLOCK, NV, NL)) * BLOCK * 16u;
     if constexpr (lds_bytes > 0) {
