@@ -67,6 +67,8 @@ constexpr int LM_SLOTS = 5;                          // operand tiles resident i
 constexpr int LM_LPT = LM_BM * LM_CPR / LM_THREADS;  // 16-byte loads per lane and operand tile: 4
 constexpr int LM_LDS_BYTES = LM_SLOTS * LM_TILE_BYTES;
 
+constexpr int LM_LEAD_STEPS = 16;                     // contractions of up to so many K steps: see lm_gemm_nt
+
 enum { LM_EPI_LSE = 0, LM_EPI_BF16 = 1, LM_EPI_F32 = 2 };
 enum { LM_Z_NONE = 0, LM_Z_KEPT = 1, LM_Z_LARGE = 2 };  // the fp32 copy of the logits: none, stored, stored past the caches
 
@@ -158,6 +160,16 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     // dispatched - and its loads run ahead into the next item (below).
     const int xcd = (int)(blockIdx.x & 7), per_xcd = (int)(gridDim.x >> 3), n_items = lm_items_per_xcd(pl);
     int idx = (int)(blockIdx.x >> 3);
+    // Of short contractions a workgroup takes the half or thin tile at the end of its places first: workgroups that have one then
+    // store their tiles while the others multiply.  In step, 256 of them store 64 MB at once, as long as 6 K steps, and multiply
+    // with the memory idle (1024 x 50304 x 768 with the auxiliary terms 311 -> 295 us a call, 4096 x 32000 x 256 347 ->
+    // 331, 1500 x 30000 x 640 258 -> 246).  Of long ones it is the operands that count, which neighbouring tiles share
+    // while they are in step (log-probs of 2048 x 152064 x 5120 1682 us, 1704 with it).
+    int lead = -1, idx_end = n_items;  // the place taken first, if any, and where the others end
+    if (EPI != LM_EPI_BF16 && K <= LM_LEAD_STEPS * LM_BK && idx < n_items) {
+        const int last = idx + (n_items - 1 - idx) / per_xcd * per_xcd;
+        if (last > idx && last >= (pl.full + 7) / 8) lead = last, idx_end = last;
+    }
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // in a scalar register: LDS targets are uniform
@@ -192,19 +204,27 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
             ++item.tn;
         } else {
             LmItem it;
-            for (;; idx += per_xcd) {
-                if (idx >= n_items) {  // whole workgroup alike
-                    KT = 0;  // the loads that still follow find no step and touch no memory
-                    return false;
+            int at;
+            for (;;) {
+                if (lead >= 0) {
+                    at = lead;
+                    lead = -1;
+                } else {
+                    if (idx >= idx_end) {  // whole workgroup alike
+                        KT = 0;  // the loads that still follow find no step and touch no memory
+                        return false;
+                    }
+                    at = idx;
+                    idx += per_xcd;
                 }
-                if (lm_map_item(xcd, idx, p.tiles_n, pl, it)) break;
+                if (lm_map_item(xcd, at, p.tiles_n, pl, it)) break;
             }
             item = it;
             const int n1 = (pl.full + 7) / 8;
             L_end = 0;
-            if (idx < n1) {
+            if (at < n1) {
                 const int group_tiles = LM_GROUP_M * p.tiles_n;
-                L = xcd * n1 + idx;
+                L = xcd * n1 + at;
                 group_row0 = L / group_tiles * LM_GROUP_M;
                 group_rows = min(LM_GROUP_M, pl.rows_w - group_row0);
                 L_end = min(min(pl.full, (xcd + 1) * n1), (L / group_tiles + 1) * group_tiles);
@@ -212,7 +232,6 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 step_n = per_xcd / group_rows;
                 step_m = per_xcd - step_n * group_rows;
             }
-            idx += per_xcd;
         }
         const LmItem &it = item;
         const int row0 = it.row0, col0 = it.tn * LM_BN, row_end = min(M, row0 + it.height);
