@@ -1900,13 +1900,29 @@ constexpr size_t fin_partials_bytes(long long n)
     return (((size_t)((n + 4095) / 4096) * sizeof(FinPartial)) + 255) / 256 * 256;
 }
 
-__global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const float *KL_ws,
-                                                      const float *H_ws,
-                                                      const unsigned char *flags_ws, long long n,
-                                                      WsHeader *hdr, FinPartial *partials, float kl_coef,
-                                                      float ent_coef, float *loss_out,
-                                                      long long *counts_out, int *error_out)
+struct FinParams {
+    const float *J_ws, *KL_ws, *H_ws;
+    const unsigned char *flags_ws;
+    long long n;
+    WsHeader *hdr;
+    FinPartial *partials;
+    float kl_coef, ent_coef;
+    float *loss_out;
+    long long *counts_out;
+    int *error_out;
+};
+// What workgroup `block` of the segments' does; 1024 lanes.
+__device__ __forceinline__ void finalize_segment(const FinParams &f, unsigned block)
 {
+    const float *J_ws = f.J_ws, *KL_ws = f.KL_ws, *H_ws = f.H_ws;
+    const unsigned char *flags_ws = f.flags_ws;
+    const long long n = f.n;
+    WsHeader *hdr = f.hdr;
+    FinPartial *partials = f.partials;
+    const float kl_coef = f.kl_coef, ent_coef = f.ent_coef;
+    float *loss_out = f.loss_out;
+    long long *counts_out = f.counts_out;
+    int *error_out = f.error_out;
     __shared__ double lds_s[3][16];
     __shared__ int lds_c[2][16];
     __shared__ long long lds_c4[4][16];
@@ -1916,7 +1932,7 @@ __global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const f
     const long long nseg = (n + kFinSegment - 1) / kFinSegment;  // 0 for an empty batch: one block, no rows
     // this block's segment, four consecutive rows per lane and step (the arrays start on 256-byte
     // boundaries and a segment is a multiple of four rows), the batch's last n % 4 rows one by one
-    const long long seg0 = (long long)blockIdx.x * kFinSegment;
+    const long long seg0 = (long long)block * kFinSegment;
     const long long seg1 = seg0 + kFinSegment < n ? seg0 + kFinSegment : n;
     constexpr int STEPS = kFinSegment / 4096;
     f32x4 j[STEPS], kl[STEPS], h[STEPS];
@@ -2003,7 +2019,7 @@ __global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const f
 #pragma unroll
             for (int q = 0; q < 4; ++q) pt.c[q] = c[q];
             pt.pad = 0;
-            partials[blockIdx.x] = pt;
+            partials[block] = pt;
             __threadfence();  // the partial is visible before the ticket is
             lds_ticket = atomicAdd(&hdr->fin_ticket, 1u);
         }
@@ -2055,6 +2071,8 @@ __global__ void __launch_bounds__(1024) grpo_finalize(const float *J_ws, const f
         }
     }
 }
+
+__global__ void __launch_bounds__(1024) grpo_finalize(FinParams f) { finalize_segment(f, blockIdx.x); }
 
 // One wavefront per group: mean, then spread around the mean, both in fp64.
 __global__ void __launch_bounds__(64) grpo_group_adv(const float *rewards, long long n_rollouts,
@@ -2633,9 +2651,9 @@ grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens,
                 launch_rows<GRPO_F32, false>(p, st);
         }
     }
-    hipLaunchKernelGGL(grpo_finalize, dim3(fin_blocks(n_tokens)), dim3(1024), 0, st, J_ws,
-                       aux ? KL_ws : (const float *)nullptr, H_ws, flags_ws, (long long)n_tokens, hdr, partials,
-                       kl_coef, entropy_coef, loss_out, (long long *)counts_out, (int *)error_out);
+    const FinParams fin = {J_ws, aux ? KL_ws : nullptr, H_ws, flags_ws, (long long)n_tokens, hdr, partials, kl_coef,
+                           entropy_coef, loss_out, (long long *)counts_out, (int *)error_out};
+    hipLaunchKernelGGL(grpo_finalize, dim3(fin_blocks(n_tokens)), dim3(1024), 0, st, fin);
     return hipGetLastError() == hipSuccess ? GRPO_OK : GRPO_ERR_HIP;
 }
 

@@ -1164,17 +1164,24 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
 
 // Sum of the parts of the tiles lm_gemm_nt has cut: C[c_rows[r]][:] = bf16(sum over s of the
 // tile's partial blocks) for the rows present, parts in order.  Does nothing when no tile was cut.
-__global__ void __launch_bounds__(256) lm_split_reduce(const float *ws, const int *M_dev, int M, int N, int tiles_n,
+// The workgroups behind its own are grpo_finalize's: neither waits for anything of the other, and a launch of its own costs
+// the sums of a small call what they take (724 x 12331 x 1152 134 -> 130 us a call).
+constexpr int LM_REDUCE_BLOCKS = 512;
+__global__ void __launch_bounds__(1024) lm_split_reduce(const float *ws, const int *M_dev, int M, int N, int tiles_n,
                                                        int k_tiles, int max_items, int n_cu,
-                                                       const int *c_rows, __bf16 *C, long long ldc)
+                                                       const int *c_rows, __bf16 *C, long long ldc, FinParams fin)
 {
+    if (blockIdx.x >= LM_REDUCE_BLOCKS) {  // whole workgroup alike
+        finalize_segment(fin, blockIdx.x - LM_REDUCE_BLOCKS);
+        return;
+    }
     const int rows = M_dev ? min(*M_dev, M) : M;
     const LmPlan pl = lm_plan(rows, tiles_n, k_tiles, true, max_items, n_cu);
     if (pl.s2 == 1) return;
     // 16 bytes a lane, as lm_gemm_nt's wavefronts have stored them; whole tiles first, then thin ones (wavefronts 0 .. 3)
     constexpr int quads = LM_BM * LM_BN / 4;
     const long long rest = (long long)pl.rest * quads, total = rest + (long long)pl.thin * (quads / 2);
-    for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < total; e += (long long)gridDim.x * 256) {
+    for (long long e = (long long)blockIdx.x * 1024 + threadIdx.x; e < total; e += LM_REDUCE_BLOCKS * 1024ll) {
         int row, col, parts, q;
         const float *src;
         if (e < rest) {
@@ -1388,6 +1395,9 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
     float *H_ws = (float *)(ws + kHeaderBytes + 2 * col);
     unsigned char *flags_ws = (unsigned char *)(ws + kHeaderBytes + 3 * col);
     FinPartial *partials = (FinPartial *)(ws + kHeaderBytes + 3 * col + align_up((size_t)n_tokens, 256));
+    const FinParams fin = {J_ws, aux ? KL_ws : nullptr, H_ws, flags_ws, (long long)n_tokens, hdr, partials, kl_coef,
+                           entropy_coef, loss_out, (long long *)counts_out, nullptr};
+    bool finalized = false;
 
     const bool take = n_tokens > 0 && n_tokens <= LM_TAKE_MAX;
     if (bwd && !take)
@@ -1547,11 +1557,14 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             gh.split_ws = (float *)(ws + L.Z);
             e = lm_launch_gemm<LM_EPI_BF16, LM_Z_NONE, false, false, true>(gh, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
-            if (gh.split_items > 0)
-                hipLaunchKernelGGL(lm_split_reduce, dim3(2048), dim3(256), 0, st, (const float *)gh.split_ws,
-                                   (const int *)w.n_grad, Mc, D, (D + LM_BN - 1) / LM_BN, (int)(L.ldg / LM_BK),
-                                   gh.split_items, n_cu, (const int *)w.orig2, (__bf16 *)grad_hidden,
-                                   (long long)grad_hidden_stride);
+            if (gh.split_items > 0) {
+                const bool last = c == n_chunks - 1;  // every row's objective is there
+                hipLaunchKernelGGL(lm_split_reduce, dim3(LM_REDUCE_BLOCKS + (last ? fin_blocks(n_tokens) : 0)), dim3(1024), 0, st,
+                                   (const float *)gh.split_ws, (const int *)w.n_grad, Mc, D, (D + LM_BN - 1) / LM_BN,
+                                   (int)(L.ldg / LM_BK), gh.split_items, n_cu, (const int *)w.orig2, (__bf16 *)grad_hidden,
+                                   (long long)grad_hidden_stride, fin);
+                finalized = last;
+            }
 
             GemmParams gw = {};  // dL/dW [V][d] (+)= G^T . H over the chunk's gradient rows; G is read as it lies,
                                  // [rows][ldg]: K-major
@@ -1575,10 +1588,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
         hipLaunchKernelGGL(lm_zero<float>, dim3(4096), dim3(256), 0, st, grad_weight, (long long)vocab,
                            (long long)d_model, (long long)grad_weight_stride);
     }
-    if (bwd)
-        hipLaunchKernelGGL(grpo_finalize, dim3(fin_blocks(n_tokens)), dim3(1024), 0, st, J_ws,
-                           aux ? KL_ws : (const float *)nullptr, H_ws, flags_ws, (long long)n_tokens, hdr, partials,
-                           kl_coef, entropy_coef, loss_out, (long long *)counts_out, (int *)nullptr);
+    if (bwd && !finalized) hipLaunchKernelGGL(grpo_finalize, dim3(fin_blocks(n_tokens)), dim3(1024), 0, st, fin);
     return hipGetLastError() == hipSuccess ? GRPO_OK : GRPO_ERR_HIP;
 }
 
