@@ -726,11 +726,13 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
 // Per-row arrays the fused path keeps between its kernels.  Rows that take part (mask 1,
 // token id inside the vocabulary) are compacted: "compact row i" is original row rows[i],
 // i < *n_live.  Of those, the ones with a gradient (c != 0) are compacted once more for
-// the backward: row i of the chunk is gradient row pos2[i] (-1: none), gradient row j is original row orig2[j], j < *n_grad.
+// the backward, in order: bit i % 16 of gmask[i / 16] says whether row i of the chunk is one, gradient row j is original row
+// orig2[j], j < *n_grad.
 // The masked tail of every rollout and the clipped tokens then cost no matrix work at all.
 struct LmRows {
     int *rows, *tokens32, *n_live;   // [n], [n] (by compact row), [1]
-    int *pos2, *orig2, *n_grad;      // [cap] (by row inside the chunk), [cap], [1]
+    int *orig2, *n_grad;             // [cap], [1]
+    unsigned *gmask;                 // [cap / 16]
     float *zy;     // by compact row: logit of the sampled token (fp32 accumulator)
     float *shift;  // max k + log2(sum): p_j = exp2(z_j k - shift)
     float *q;      // c / T
@@ -901,25 +903,6 @@ __global__ void __launch_bounds__(LM_TAKE_THREADS) lm_take_rows(RowParams p, LmR
     }
 }
 
-// Compact rows of the current chunk with a gradient -> pos2[] (by row of the chunk: its place among them, or -1),
-// orig2[] (original row), *n_grad.
-__global__ void __launch_bounds__(1024) lm_select_grad_rows(LmRows w)
-{
-    int base, count;
-    lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, base, count);
-    const int total = lm_ordered_select(
-        count,
-        [&](long long j) {
-            w.pos2[j] = -1;
-            return w.q[base + j] != 0.f || (w.bq && w.bq[base + j] != 0.f);
-        },
-        [&](int pos, long long j) {
-            w.pos2[j] = pos;
-            w.orig2[pos] = w.rows[base + j];
-        });
-    if (threadIdx.x == 0) *w.n_grad = total;
-}
-
 // out[i][:] = in[rowmap[i]][:] for i < *count: d bf16 values per row, 16 bytes per lane.
 __global__ void __launch_bounds__(256) lm_gather_rows(const __bf16 *in, long long ldi, const int *rowmap,
                                                       const int *count, int d, __bf16 *out, long long ldo)
@@ -1006,6 +989,7 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
         if constexpr (AUX) w_excl += sh_w[l][rl];
     }
     const long long row = w.rows[i];
+    bool has_grad = false;
     if constexpr (AUX) {
         float kl, H;
         const RowScalars o = row_scalars_aux(p, row, zy, mx, s_excl, w_excl, kl, H);
@@ -1018,6 +1002,7 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
         w.log2s[i] = o.log2s;
         w.q2[i] = o.q2;
         w.bq[i] = o.bq;
+        has_grad = q != 0.f || o.bq != 0.f;
     } else {
         const RowScalars o = row_scalars(p, row, zy, mk, s_excl);
         write_row_outputs(p, row, o.logp, o.J, o.flags);
@@ -1026,11 +1011,16 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
             w.q[i] = q;
             w.gy[i] = q * (o.s_excl / o.s);
             w.shift[i] = o.shift;
+            has_grad = q != 0.f;
         }
+    }
+    if (p.bwd) {  // the workgroup's 16 rows are lanes 0 .. 15, those that exist
+        const unsigned grads = (unsigned)__ballot(has_grad) & 0xffffu;
+        if (rl == 0) w.gmask[il / LM_CMB_ROWS] = grads;
     }
 }
 
-// One 64 x 64 tile of out[c][r] = in[rowmap[r]][c], r < R, c < C, at (r0, c0); the
+// One 64 x 64 tile of out[c][r] = in[rowmap[r - r0]][c], r < R, c < C, at (r0, c0); the
 // columns R .. of out are zero-filled.  Through LDS, four consecutive
 // elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
 // 8-byte aligned (the operands of this path: d_model is a multiple of 64, rows 16-byte aligned).
@@ -1045,7 +1035,7 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
         const int rl = ty + 16 * i, r = r0 + rl, c = c0 + tx * 4;
         unsigned lo = 0, hi = 0;
         if (r < R && c < C) {
-            const unsigned *q = (const unsigned *)(src + (long long)rowmap[r] * ldi + c);
+            const unsigned *q = (const unsigned *)(src + (long long)rowmap[rl] * ldi + c);
             lo = q[0];
             hi = q[1];
         }
@@ -1074,7 +1064,12 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
 // multiple of 64 (dL/dW runs over whole K steps of rows).
 // Reading Z in that order costs this kernel something (10066 rows of 152064: 648 us, 584 with Z row by row; 992 and 901 with
 // the auxiliary terms) and saves the product in front 5 us of a CU's time per tile, 0.46 ms of those rows.
+// Which rows have a gradient, and so where theirs go, every workgroup takes from gmask: a word for 16 rows, a load or three a
+// lane while its logits are on their way.  The list in order, and their number, which the products read, come from here
+// too (a kernel of one workgroup in front of this one made them: 4096 x 32000 x 256 332 -> 323 us a call, 100 x 3000 x 256
+// 62.4 -> 60.3, 1024 x 50304 x 768 291.5 -> 290).
 constexpr int LM_GL_COLS = 512, LM_GL_ROWS = 16;
+static_assert(LM_GL_ROWS == LM_CMB_ROWS, "a word of gmask to a workgroup's rows");
 template <bool AUX>
 __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long ldz, int V, LmRows w,
                                                       float k, __bf16 *G, long long ldg, int col_groups, unsigned gl_blocks,
@@ -1083,21 +1078,45 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
     constexpr int WAVE_COLS = LM_GL_COLS / 4, PITCH = WAVE_COLS * 2 + 16;  // bytes: 16-byte aligned rows, 4 banks apart
     __shared__ __attribute__((aligned(16))) char turn_all[4 * LM_GL_ROWS * PITCH];
     static_assert(sizeof(turn_all) >= 64 * 66 * 2, "the tile that is turned round for H^T fits");
-    if (blockIdx.x >= gl_blocks) {  // H^T of the chunk's gradient rows, [d][ldht]: independent of G, in the same launch
-        const int t = (int)(blockIdx.x - gl_blocks), across = (int)(ldht / 64);
-        const int n = *w.n_grad;
-        // columns past the rows that exist are read as zeros up to the next whole K step, and not at all beyond it
-        if (t % across * 64 < (n + 63) / 64 * 64)
-            lm_transpose_tile(t % across * 64, t / across * 64, hidden, ldh, n, w.orig2, d, Ht, ldht,
-                              (unsigned short(*)[66])turn_all);
-        return;
-    }
-    const int n2 = *w.n_grad, n2_pad = (n2 + 63) / 64 * 64;
-    const int r0 = (int)(blockIdx.x / (unsigned)col_groups) * LM_GL_ROWS;
+    __shared__ int lds_n[2][4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
     int zbase, zcount;  // Z holds the current chunk's rows only
     lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, zbase, zcount);
-    if (r0 >= zcount && r0 >= n2_pad) return;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, n = lane & 15, g = lane >> 4;
+    const int groups = (zcount + LM_GL_ROWS - 1) / LM_GL_ROWS;
+    if (blockIdx.x >= gl_blocks) {  // H^T of the chunk's gradient rows, [d][ldht]: independent of G, in the same launch
+        __shared__ int rowmap[64];
+        const int t = (int)(blockIdx.x - gl_blocks), across = (int)(ldht / 64), first = t % across * 64;
+        int total = 0;
+        for (int q0 = 0; q0 < groups; q0 += 256) {  // whole workgroup alike
+            const int q = q0 + (int)threadIdx.x;
+            unsigned bits = q < groups ? w.gmask[q] : 0u;
+            int incl = __builtin_popcount(bits);  // inclusive scan inside the wavefront
+            const int own = incl;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int up = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += up;
+            }
+            if (lane == 63) lds_n[0][wv] = incl;
+            __syncthreads();
+            int pos = total + incl - own - first;
+            for (int i = 0; i < 4; ++i) {
+                if (i < wv) pos += lds_n[0][i];
+                total += lds_n[0][i];
+            }
+            if (pos < 64 && pos + own > 0)
+                for (; bits != 0u; bits &= bits - 1u, ++pos)
+                    if (pos >= 0 && pos < 64) rowmap[pos] = w.rows[zbase + q * LM_GL_ROWS + __builtin_ctz(bits)];
+            __syncthreads();
+        }
+        // columns past the rows that exist are read as zeros up to the next whole K step, and not at all beyond it
+        if (first < (total + 63) / 64 * 64)
+            lm_transpose_tile(first, t / across * 64, hidden, ldh, total, rowmap, d, Ht, ldht, (unsigned short(*)[66])turn_all);
+        return;
+    }
+    const int r0 = (int)(blockIdx.x / (unsigned)col_groups) * LM_GL_ROWS;
+    // rows n_grad and up of the chunk, of which there are no more than it has: at most up to the next multiple of 64
+    if (r0 >= (zcount + 63) / 64 * 64 && blockIdx.x != 0) return;
     const int c0 = (int)(blockIdx.x % (unsigned)col_groups) * LM_GL_COLS + wv * WAVE_COLS;  // this wavefront's columns
     char *turn = turn_all + wv * (LM_GL_ROWS * PITCH);
     const int ci = zbase + r0 + n;  // this lane's compact row
@@ -1112,7 +1131,23 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
                     ? __builtin_nontemporal_load((const f32x4 *)(Z + lm_z_part(r0, c, ldz) + lm_z_in_part(r0 + n, c)))
                     : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const int pos = r0 + n < zcount ? w.pos2[r0 + n] : -1;
+    int before = 0, n2 = 0;  // gradient rows ahead of this workgroup's, and in the chunk
+    for (int q = threadIdx.x; q < groups; q += 256) {
+        const int c = __builtin_popcount(w.gmask[q]);
+        n2 += c;
+        before += q < r0 / LM_GL_ROWS ? c : 0;
+    }
+    before = wave_sum(before);
+    n2 = wave_sum(n2);
+    if (lane == 0) lds_n[0][wv] = before, lds_n[1][wv] = n2;
+    __syncthreads();
+    before = lds_n[0][0] + lds_n[0][1] + lds_n[0][2] + lds_n[0][3];
+    n2 = lds_n[1][0] + lds_n[1][1] + lds_n[1][2] + lds_n[1][3];
+    const int n2_pad = (n2 + 63) / 64 * 64;
+    const unsigned grads = r0 < zcount ? w.gmask[r0 / LM_GL_ROWS] : 0u;
+    const int pos = (grads >> n) & 1u ? before + __builtin_popcount(grads & ((1u << n) - 1u)) : -1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *w.n_grad = n2;
+    if (blockIdx.x % (unsigned)col_groups == 0 && threadIdx.x < LM_GL_ROWS && pos >= 0) w.orig2[pos] = w.rows[zbase + r0 + n];
     float q = 0.f, sh = 0.f, mxr = 0.f, l2s = 0.f, q2 = 0.f, bq = 0.f, gy = 0.f;
     int y = -1;
     if (r0 + n < zcount) {  // (of a row without a gradient nothing is stored)
@@ -1254,7 +1289,7 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
 }
 
 struct LmLayout {
-    size_t rows, tokens32, pos2, orig2, counts, zy, shift, q, gy, mx, log2s, q2, bq, part_m, part_s, part_w, Hc, Z, G, Ht,
+    size_t rows, tokens32, gmask, orig2, counts, zy, shift, q, gy, mx, log2s, q2, bq, part_m, part_s, part_w, Hc, Z, G, Ht,
         total;
     long long ldz, ldg, ldgt;  // vocab and chunk rows rounded up to whole K steps
     int tiles_n;
@@ -1292,7 +1327,7 @@ LmLayout lm_layout(int64_t n, int64_t V, int64_t d, bool bwd, int64_t cap)
     L.part_s = take((size_t)L.tiles_n * cap * 4);
     L.Hc = take((size_t)n * d * 2);
     if (bwd) {
-        L.pos2 = take((size_t)cap * 4);
+        L.gmask = take((size_t)cap * 4);
         L.orig2 = take((size_t)cap * 4);
         L.shift = take((size_t)n * 4);
         L.q = take((size_t)n * 4);
@@ -1426,7 +1461,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             w.bq = (float *)(ws + L.bq);
         }
         if (bwd) {
-            w.pos2 = (int *)(ws + L.pos2);
+            w.gmask = (unsigned *)(ws + L.gmask);
             w.orig2 = (int *)(ws + L.orig2);
             w.shift = (float *)(ws + L.shift);
             w.q = (float *)(ws + L.q);
@@ -1526,7 +1561,6 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
                 hipLaunchKernelGGL((few ? lm_combine<false, 16> : lm_combine<false, 64>), cmb_grid, cmb_block, 0, st, p, w);
             if (!bwd) continue;
 
-            hipLaunchKernelGGL(lm_select_grad_rows, dim3(1), dim3(1024), 0, st, w);
             const int gl_cols = (int)((L.ldg + LM_GL_COLS - 1) / LM_GL_COLS);
             // rows up to the next multiple of 64: the padding rows are written too (G has cap >= 256 rows)
             const unsigned gl_blocks = (unsigned)((long long)gl_cols * ((Mc + 63) / 64 * (64 / LM_GL_ROWS)));
