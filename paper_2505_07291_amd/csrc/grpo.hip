@@ -1516,7 +1516,7 @@ __device__ __forceinline__ void online_batch(u32x4 (&z)[U], float k, float &m, f
 // held in LDS between the passes saved 1 %: the second reads are served by the caches.
 // ---------------------------------------------------------------------------
 constexpr int kStreamBlock = 512, kStreamPerCu = 2, kStreamBatch = 4;
-template <grpo_dtype DT, bool AUX>
+template <grpo_dtype DT, bool AUX, bool SHIFT>
 __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams p)
 {
     constexpr int EPV = Elem<DT>::EPV, BYTES = Elem<DT>::BYTES, BLOCK = kStreamBlock, U = kStreamBatch;
@@ -1524,7 +1524,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     __shared__ float lds_max[BLOCK / 64];
     __shared__ float lds_sum[BLOCK / 64];
     __shared__ float lds_sumw[BLOCK / 64];
-    __shared__ float lds_turn[AUX ? 2 : 1][BLOCK];
+    __shared__ float lds_turn[SHIFT && AUX ? 2 : 1][SHIFT ? BLOCK : 1];
     __shared__ long long lds_row[2];
     const int tid = threadIdx.x;
     const int nvec_full = (int)(p.vocab / EPV);
@@ -1566,7 +1566,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     auto offset = [&](int s) __attribute__((always_inline)) -> unsigned {
         unsigned o = noff;
         asm volatile("" : "+v"(o));
-        return (o - 16u * (unsigned)s) & (SLAB - 1u);
+        return SHIFT ? (o - 16u * (unsigned)s) & (SLAB - 1u) : o;
     };
     auto first_vector = [&](int s) __attribute__((always_inline)) -> int { return (int)(offset(s) >> 4); };
     // how far into slot `slot` the row's vectors reach, in bytes
@@ -1595,7 +1595,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     int sh;
 rows_from_none:
     row = acquire(y, false);
-    sh = (int)row_shift(p, row);
+    sh = (SHIFT ? (int)row_shift(p, row) : 0);
     if (row < p.n_tokens) load_first((const char *)p.logits + row * p.row_stride * BYTES, sh, y);
 
     while (row < p.n_tokens) {
@@ -1603,7 +1603,7 @@ rows_from_none:
         const long long next = acquire(y_next, true);
         const bool has_next = next < p.n_tokens;
         const char *zrow_next = (const char *)p.logits + (has_next ? next : row) * p.row_stride * BYTES;
-        const int sh_next = (int)row_shift(p, next);
+        const int sh_next = (SHIFT ? (int)row_shift(p, next) : 0);
         const int vy = (int)(y / EPV);
         const int ey = (int)(y % EPV);
 
@@ -1634,13 +1634,13 @@ rows_from_none:
         const float mk = mx * p.k;
         float scaled, scaledw;
         online_rescale<AUX>(m, s, w, mx, p.k, scaled, scaledw);
-        if (sh != 0) {  // the lanes' sums in the order of an unturned row
+        if (SHIFT && sh != 0) {  // the lanes' sums in the order of an unturned row
             const int l = first_vector(sh);
-            lds_turn[0][l] = scaled;
-            if constexpr (AUX) lds_turn[AUX ? 1 : 0][l] = scaledw;
+            lds_turn[0][SHIFT ? l : 0] = scaled;
+            if constexpr (AUX) lds_turn[SHIFT && AUX ? 1 : 0][SHIFT ? l : 0] = scaledw;
             lds_barrier();
-            scaled = lds_turn[0][tid];
-            if constexpr (AUX) scaledw = lds_turn[AUX ? 1 : 0][tid];
+            scaled = lds_turn[0][SHIFT ? tid : 0];
+            if constexpr (AUX) scaledw = lds_turn[SHIFT && AUX ? 1 : 0][SHIFT ? tid : 0];
         }
         RowScalars sc;
         if constexpr (AUX) {
@@ -2499,11 +2499,17 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
 #undef GRPO_ROW_CASE
     default: {
         long long grid = (long long)cu_count() * kStreamPerCu;
+        // turned lanes cost a row instructions (59 fp32 rows of 126615 35.2 and 36.8 us a step): not where each workgroup has
+        // one row at most, whose time no memory bounds
+        const bool shift = (p.shift0 | p.shift_step) != 0 && p.n_tokens > grid;
         if (p.n_tokens <= grid) {
             p.queued = 0;
             grid = p.n_tokens;
         }
-        hipLaunchKernelGGL((grpo_rows_streamed<DT, AUX>), dim3((unsigned)grid), dim3(kStreamBlock), 0, st, p);
+        if (shift)
+            hipLaunchKernelGGL((grpo_rows_streamed<DT, AUX, true>), dim3((unsigned)grid), dim3(kStreamBlock), 0, st, p);
+        else
+            hipLaunchKernelGGL((grpo_rows_streamed<DT, AUX, false>), dim3((unsigned)grid), dim3(kStreamBlock), 0, st, p);
     }
     }
 }
