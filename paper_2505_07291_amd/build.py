@@ -1,6 +1,7 @@
 """Builds libgrpo.so (the C-ABI library with the gfx950 HIP kernels) and the binding's native part in-tree."""
 from __future__ import annotations
 
+import concurrent.futures
 import glob
 import hashlib
 import os
@@ -16,8 +17,10 @@ FASTCALL_SOURCE = os.path.join(_PKG, "csrc", "fastcall.cpp")
 
 # -packed-fp32-ops is switched off on purpose: packed fp32 forms generated from plain
 # float code have produced wrong results on the test machines.
-HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+# the parts of grpo.hip, compiled at the same time
+PARTS = [["-DGRPO_ROWS_APART"]] + [["-DGRPO_ROWS_OF=%s, %s" % (dt, aux)] for dt in ("GRPO_BF16", "GRPO_F32") for aux in ("false", "true")]
 
 
 def find_hipcc() -> str:
@@ -30,12 +33,26 @@ def find_hipcc() -> str:
 def build_library(verbose: bool = False) -> str:
     """Compiles the library unconditionally and returns its path."""
     tmp = LIB_PATH + ".tmp.%d" % os.getpid()
-    cmd = [find_hipcc()] + HIPCC_FLAGS + ["-I", INCLUDE, "-o", tmp] + SOURCES
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    objects = ["%s.%d.o" % (tmp, i) for i in range(len(PARTS))]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        return subprocess.run(cmd, capture_output=True, text=True)
+
+    base = [find_hipcc()] + HIPCC_FLAGS
+    try:
+        with concurrent.futures.ThreadPoolExecutor(len(PARTS)) as pool:
+            results = list(pool.map(lambda part: run(base + part[0] + ["-I", INCLUDE, "-c", "-o", part[1]] + SOURCES),
+                                    zip(PARTS, objects)))
+        results.append(run(base + ["-shared", "-o", tmp] + objects) if all(r.returncode == 0 for r in results) else results[0])
+        for res in results:
+            if res.returncode != 0:
+                raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
+    finally:
+        for path in objects:
+            if os.path.exists(path):
+                os.unlink(path)
     os.replace(tmp, LIB_PATH)
     return LIB_PATH
 

@@ -18,7 +18,10 @@
 
 #include "grpo.h"
 
-namespace {
+// The row kernels' instantiations take most of the compiler's time: build.py compiles this file once for each element type
+// with and without the auxiliary terms (GRPO_ROWS_OF: the arguments of launch_rows) and once for everything else
+// (GRPO_ROWS_APART), at the same time.  With neither defined it is the whole library.
+namespace grpo_impl {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -1752,7 +1755,7 @@ __device__ __forceinline__ int count_live(const unsigned char *mask, const float
 
 // The rows of each segment of 4096 that take part, for batches too long for every workgroup of
 // grpo_prepare to count them all itself.
-__global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned char *mask, const float *token_w, long long n,
+static __global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned char *mask, const float *token_w, long long n,
                                                         int *live_of)
 {
     __shared__ int lds[16];
@@ -1780,7 +1783,7 @@ __global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned char *mas
 // atomics on the way.  That work grows with the square of the batch: in longer batches (prepare_counts_itself)
 // grpo_count_rows has counted each segment (live_of) and only those numbers are added up here.
 // order[0 .. M) are the live rows in increasing order, order[M .. n) the masked ones (written from the end).
-__global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask, const float *token_w, long long n,
+static __global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask, const float *token_w, long long n,
                                                      double denom, WsHeader *hdr, int *order, const int *live_of)
 {
     __shared__ long long lds_before[16], lds_rest[16];
@@ -1864,7 +1867,7 @@ __global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask, 
 }
 
 // Log-probs-only calls that bring a workspace use it for the row queue alone.
-__global__ void grpo_reset_queue(WsHeader *hdr)
+static __global__ void grpo_reset_queue(WsHeader *hdr)
 {
     if (threadIdx.x < kQueueParts) queue_counters(hdr)[threadIdx.x * kQueueStride] = 0ull;
     if (threadIdx.x == 0) {
@@ -2072,10 +2075,10 @@ __device__ __forceinline__ void finalize_segment(const FinParams &f, unsigned bl
     }
 }
 
-__global__ void __launch_bounds__(1024) grpo_finalize(FinParams f) { finalize_segment(f, blockIdx.x); }
+static __global__ void __launch_bounds__(1024) grpo_finalize(FinParams f) { finalize_segment(f, blockIdx.x); }
 
 // One wavefront per group: mean, then spread around the mean, both in fp64.
-__global__ void __launch_bounds__(64) grpo_group_adv(const float *rewards, long long n_rollouts,
+static __global__ void __launch_bounds__(64) grpo_group_adv(const float *rewards, long long n_rollouts,
                                                      const int *offsets, long long n_groups,
                                                      long long group_size, double eps_std, int ddof,
                                                      float *adv_out)
@@ -2104,7 +2107,7 @@ __global__ void __launch_bounds__(64) grpo_group_adv(const float *rewards, long 
     }
 }
 
-__global__ void __launch_bounds__(256) grpo_adv_to_tokens(const float *adv, long long n_rollouts,
+static __global__ void __launch_bounds__(256) grpo_adv_to_tokens(const float *adv, long long n_rollouts,
                                                           const int *rollout_of_token,
                                                           long long n_tokens, float *adv_tok)
 {
@@ -2122,7 +2125,7 @@ __global__ void __launch_bounds__(256) grpo_adv_to_tokens(const float *adv, long
 // them the repeated work costs more than the launch.  Neither output may overlap the rewards: a workgroup may
 // still be reading them when another one writes (in place, the two launches above are taken).
 constexpr int kAdvRollouts = 1024, kAdvTokens = 4096;
-__global__ void __launch_bounds__(1024) grpo_adv_fused(const float *rewards, int n_rollouts, int n_groups, int group_size,
+static __global__ void __launch_bounds__(1024) grpo_adv_fused(const float *rewards, int n_rollouts, int n_groups, int group_size,
                                                        double eps_std, int ddof, float *adv_out,
                                                        const int *rollout_of_token, long long n_tokens, float *adv_tok)
 {
@@ -2174,7 +2177,7 @@ __global__ void __launch_bounds__(1024) grpo_adv_fused(const float *rewards, int
 
 // r_total = r_task - alpha |l_target - l_y| (section 3.1).  The length difference is formed
 // in integers, so it is exact.
-__global__ void __launch_bounds__(256) grpo_total_rewards_k(const float *task, const int *len,
+static __global__ void __launch_bounds__(256) grpo_total_rewards_k(const float *task, const int *len,
                                                             const int *target, long long n,
                                                             float alpha, float *out)
 {
@@ -2186,7 +2189,7 @@ __global__ void __launch_bounds__(256) grpo_total_rewards_k(const float *task, c
 
 // Online filter (section 3.3): flags the groups whose rewards are not all equal.  One
 // wavefront per group.
-__global__ void __launch_bounds__(64) grpo_filter_flag(const float *rewards, long long n_rollouts,
+static __global__ void __launch_bounds__(64) grpo_filter_flag(const float *rewards, long long n_rollouts,
                                                        const int *offsets, long long n_groups,
                                                        long long group_size, unsigned char *keep,
                                                        unsigned char *rollout_keep)
@@ -2215,7 +2218,7 @@ __global__ void __launch_bounds__(64) grpo_filter_flag(const float *rewards, lon
 // call; the two kernels around this one take 13 us at any of these sizes): 1024 groups of 16 10 us, of 24 13,
 // of 32 19, of 48 26, of 64 36; 64, 128 and 256 groups of 64 10, 10 and 12.
 constexpr int kFilterGroups = 1024, kFilterSize = 64, kFilterRollouts = 16384;
-__global__ void __launch_bounds__(kFilterGroups) grpo_filter_fused(const float *rewards, int n_groups, int group_size,
+static __global__ void __launch_bounds__(kFilterGroups) grpo_filter_fused(const float *rewards, int n_groups, int group_size,
                                                                    unsigned char *keep, unsigned char *rollout_keep,
                                                                    int *kept_groups, int *n_kept)
 {
@@ -2247,7 +2250,7 @@ __global__ void __launch_bounds__(kFilterGroups) grpo_filter_fused(const float *
 
 // Ordered compaction of the kept group indices: one workgroup walks the flags in chunks
 // of 1024 with a running offset, so the output order is the input order.
-__global__ void __launch_bounds__(1024) grpo_filter_compact(const unsigned char *keep, long long n_groups,
+static __global__ void __launch_bounds__(1024) grpo_filter_compact(const unsigned char *keep, long long n_groups,
                                                             int *kept_groups, int *n_kept)
 {
     __shared__ int wave_tot[16];
@@ -2300,7 +2303,7 @@ __device__ __forceinline__ long long count_le(const long long *cu, long long R, 
         if (len > step) len = step;
     }
 }
-__global__ void __launch_bounds__(256) grpo_packed_rows(const long long *cu, long long n_rollouts, long long n_tokens,
+static __global__ void __launch_bounds__(256) grpo_packed_rows(const long long *cu, long long n_rollouts, long long n_tokens,
                                                         int sample_level, float *weights, int *rollout_of_token)
 {
     const int lane = threadIdx.x & 63;
@@ -2341,7 +2344,7 @@ __global__ void __launch_bounds__(256) grpo_packed_rows(const long long *cu, lon
 // Host side
 // ---------------------------------------------------------------------------
 
-int cu_count()
+static int cu_count()
 {
     static std::atomic<int> cached[64];          // zero-initialised; host threads may race here
     int dev = 0;
@@ -2426,7 +2429,7 @@ constexpr int kRowStreaming = -1;  // the plan's id for grpo_rows_streamed
 // use one workgroup per CU: 512 lanes with twice the registers, the spare ones holding
 // gradient vectors back behind the next row's loads (ragged rows of up to 10 slots of 1024 lanes
 // take those).
-int plan_rows(long long nvec, bool ragged)
+static int plan_rows(long long nvec, bool ragged)
 {
     if (nvec <= 256 * 1) return 0;
     if (nvec <= 256 * 4) return 1;
@@ -2514,6 +2517,17 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
     }
 }
 
+#ifdef GRPO_ROWS_OF
+template void launch_rows<GRPO_ROWS_OF>(const RowParams &, hipStream_t);
+}  // namespace grpo_impl
+#else
+#ifdef GRPO_ROWS_APART
+extern template void launch_rows<GRPO_BF16, false>(const RowParams &, hipStream_t);
+extern template void launch_rows<GRPO_BF16, true>(const RowParams &, hipStream_t);
+extern template void launch_rows<GRPO_F32, false>(const RowParams &, hipStream_t);
+extern template void launch_rows<GRPO_F32, true>(const RowParams &, hipStream_t);
+#endif
+
 // The integer a C caller put into an enum parameter.  The C ABI passes enums as ints and a C caller
 // may pass any int; in C++ merely reading an enum object that holds no enumerator's value is
 // undefined, so the boundary reads the bytes instead and validates the integer.
@@ -2526,7 +2540,7 @@ int raw_enum(const E &e)
     return v;
 }
 
-grpo_status check_logits_args(const void *logits, int dtype, int64_t n_tokens, int64_t vocab,
+static grpo_status check_logits_args(const void *logits, int dtype, int64_t n_tokens, int64_t vocab,
                               int64_t row_stride, const int64_t *tokens, float temperature)
 {
     if (dtype != GRPO_F32 && dtype != GRPO_BF16) return GRPO_ERR_DTYPE;
@@ -2539,8 +2553,8 @@ grpo_status check_logits_args(const void *logits, int dtype, int64_t n_tokens, i
     return GRPO_OK;
 }
 
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-unsigned fin_blocks(int64_t n) { return (unsigned)(n > 0 ? (n + kFinSegment - 1) / kFinSegment : 1); }
+static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+static unsigned fin_blocks(int64_t n) { return (unsigned)(n > 0 ? (n + kFinSegment - 1) / kFinSegment : 1); }
 // header | J, KL estimate, entropy per row (f32 each) | indicator bits per row (u8) | partial sums per
 // segment | the order the rows are handed out in (i32 per row)
 constexpr size_t loss_workspace_bytes(long long n)
@@ -2560,7 +2574,7 @@ constexpr long long kCountRows = 1024, kCountVectors = 1024;
 // of 32768 13.7 and of 4194304 3300 (mask and weights 5200).
 constexpr bool prepare_counts_itself(long long n, bool weights) { return n <= (weights ? 16384 : 131072); }
 
-grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens, int64_t vocab,
+static grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_tokens, int64_t vocab,
                       int64_t row_stride, const int64_t *tokens, const float *old_logprobs,
                       const float *ref_logprobs, const float *advantages, const uint8_t *mask,
                       const float *token_weights, float eps_low, float eps_high, float delta,
@@ -2675,7 +2689,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 // The device address of `scratch` on the current device.  In host code the array's name is
 // only a handle for the runtime, not an address a kernel can use: the address comes from
 // hipGetSymbolAddress, once per device, with that device current, and is kept per device.
-void *scratch_address()
+static void *scratch_address()
 {
     static std::atomic<void *> cached[64];  // zero-initialised; racing host threads store the same value
     int dev = 0;
@@ -2691,7 +2705,8 @@ void *scratch_address()
     return ptr;
 }
 
-}  // namespace
+}  // namespace grpo_impl
+using namespace grpo_impl;
 
 extern "C" {
 
@@ -2974,3 +2989,4 @@ grpo_status grpo_workspace_error(const void *workspace, int32_t *flag_out, void 
 }  // extern "C"
 
 #include "lmhead.hpp"
+#endif  // GRPO_ROWS_OF
