@@ -141,7 +141,7 @@ __device__ __forceinline__ int lm_z_in_part(int row, int col)
     return ((((row >> 4) & 7) * 4 + ((col >> 4) & 3)) * 64 + (row & 15) + 16 * ((col >> 2) & 3)) * 4;
 }
 
-template <int EPI, int Z, bool AUX = false, bool AKM = false, bool BKM = false>
+template <int EPI, int Z, bool AUX = false, bool AKM = false, bool BKM = false, bool LEAD = false>
 __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
 {
     extern __shared__ __attribute__((aligned(1024))) char lm_smem[];
@@ -164,9 +164,10 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     // store their tiles while the others multiply.  In step, 256 of them store 64 MB at once, as long as 6 K steps, and multiply
     // with the memory idle (1024 x 50304 x 768 with the auxiliary terms 311 -> 295 us a call, 4096 x 32000 x 256 347 ->
     // 331, 1500 x 30000 x 640 258 -> 246).  Of long ones it is the operands that count, which neighbouring tiles share
-    // while they are in step (log-probs of 2048 x 152064 x 5120 1682 us, 1704 with it).
+    // while they are in step (log-probs of 2048 x 152064 x 5120 1682 us, 1704 with it); even the possibility costs them
+    // 0.5 %, so it is an instantiation of its own (LEAD) where the host knows the length.
     int lead = -1, idx_end = n_items;  // the place taken first, if any, and where the others end
-    if (EPI != LM_EPI_BF16 && K <= LM_LEAD_STEPS * LM_BK && idx < n_items) {
+    if (LEAD && K <= LM_LEAD_STEPS * LM_BK && idx < n_items) {
         const int last = idx + (n_items - 1 - idx) / per_xcd * per_xcd;
         if (last > idx && last >= (pl.full + 7) / 8) lead = last, idx_end = last;
     }
@@ -205,17 +206,17 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
         } else {
             LmItem it;
             int at;
-            for (;;) {
-                if (lead >= 0) {
+            for (;; idx += per_xcd) {
+                if (LEAD && lead >= 0) {
                     at = lead;
                     lead = -1;
+                    idx -= per_xcd;  // the first place is still to come
                 } else {
                     if (idx >= idx_end) {  // whole workgroup alike
                         KT = 0;  // the loads that still follow find no step and touch no memory
                         return false;
                     }
                     at = idx;
-                    idx += per_xcd;
                 }
                 if (lm_map_item(xcd, at, p.tiles_n, pl, it)) break;
             }
@@ -232,6 +233,7 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
                 step_n = per_xcd / group_rows;
                 step_m = per_xcd - step_n * group_rows;
             }
+            idx += per_xcd;
         }
         const LmItem &it = item;
         const int row0 = it.row0, col0 = it.tn * LM_BN, row_end = min(M, row0 + it.height);
@@ -1268,7 +1270,7 @@ __global__ void __launch_bounds__(256) lm_zero(T *out, long long rows, long long
 // Host side
 // ---------------------------------------------------------------------------
 
-template <int EPI, int Z, bool AUX = false, bool AKM = false, bool BKM = false>
+template <int EPI, int Z, bool AUX = false, bool AKM = false, bool BKM = false, bool LEAD = false>
 hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
 {
     static std::atomic<bool> attr_done[64];      // setting the attribute twice is harmless
@@ -1276,7 +1278,7 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev >= 0 && dev < 64 && !attr_done[dev].load()) {
-        e = hipFuncSetAttribute((const void *)lm_gemm_nt<EPI, Z, AUX, AKM, BKM>,
+        e = hipFuncSetAttribute((const void *)lm_gemm_nt<EPI, Z, AUX, AKM, BKM, LEAD>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LM_LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done[dev].store(true);
@@ -1284,7 +1286,7 @@ hipError_t lm_launch_gemm(GemmParams p, hipStream_t st)
     p.tiles_n = (p.N + LM_BN - 1) / LM_BN;
     p.n_cu = cu_count();
     const unsigned grid = 8u * (unsigned)lm_workgroups_per_xcd(p.M, p.tiles_n, EPI == LM_EPI_BF16 && p.split_items > 0, p.n_cu);
-    hipLaunchKernelGGL((lm_gemm_nt<EPI, Z, AUX, AKM, BKM>), dim3(grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
+    hipLaunchKernelGGL((lm_gemm_nt<EPI, Z, AUX, AKM, BKM, LEAD>), dim3(grid), dim3(LM_THREADS), LM_LDS_BYTES, st, p);
     return hipGetLastError();
 }
 
@@ -1545,11 +1547,15 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             // 1003 past it, 3000 x 50304 x 768 with auxiliary terms 759 and 744; on 1000 x 30000 x 512 153 and 157, on
             // 2000 x 20000 x 1024 264 and 268.
             const bool large = (long long)Mc * L.ldz > (256ll << 20) / 4;
-            hipError_t e = aux   ? large ? lm_launch_gemm<LM_EPI_LSE, LM_Z_LARGE, true>(g, st)
-                                         : lm_launch_gemm<LM_EPI_LSE, LM_Z_KEPT, true>(g, st)
-                           : !bwd ? lm_launch_gemm<LM_EPI_LSE, LM_Z_NONE>(g, st)
-                           : large ? lm_launch_gemm<LM_EPI_LSE, LM_Z_LARGE>(g, st)
-                                   : lm_launch_gemm<LM_EPI_LSE, LM_Z_KEPT>(g, st);
+            auto logits = [&](auto lead) {
+                constexpr bool LD = decltype(lead)::value;
+                return aux   ? large ? lm_launch_gemm<LM_EPI_LSE, LM_Z_LARGE, true, false, false, LD>(g, st)
+                                     : lm_launch_gemm<LM_EPI_LSE, LM_Z_KEPT, true, false, false, LD>(g, st)
+                       : !bwd ? lm_launch_gemm<LM_EPI_LSE, LM_Z_NONE, false, false, false, LD>(g, st)
+                       : large ? lm_launch_gemm<LM_EPI_LSE, LM_Z_LARGE, false, false, false, LD>(g, st)
+                               : lm_launch_gemm<LM_EPI_LSE, LM_Z_KEPT, false, false, false, LD>(g, st);
+            };
+            hipError_t e = D <= LM_LEAD_STEPS * LM_BK ? logits(std::true_type{}) : logits(std::false_type{});
             if (e != hipSuccess) return GRPO_ERR_HIP;
 
             const dim3 cmb_grid((unsigned)((Mc + LM_CMB_ROWS - 1) / LM_CMB_ROWS));
@@ -1614,7 +1620,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             gw.C = grad_weight;
             gw.ldc = grad_weight_stride;
             gw.accumulate = (accumulate_grad_weight || c > 0) ? 1 : 0;  // the first chunk starts the sum
-            e = lm_launch_gemm<LM_EPI_F32, LM_Z_NONE, false, true, false>(gw, st);
+            e = lm_launch_gemm<LM_EPI_F32, LM_Z_NONE, false, true, false, true>(gw, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
         }
     } else if (bwd && !accumulate_grad_weight && vocab > 0) {
