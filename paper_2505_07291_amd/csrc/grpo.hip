@@ -500,6 +500,7 @@ __device__ __forceinline__ RowScalars row_scalars_aux(const RowParams &p, long l
     o.s = s;
     o.s_excl = s_excl;
     o.mx = mx;
+    o.log2s = log2s;
     const float ay_f = fmaxf(ay, kExpFloor);
     const float abar = fmaf(e_y, ay_f, w_excl) / s;
     const float H = fmaf(-kLn2, abar, ln_s);
@@ -523,7 +524,13 @@ __device__ __forceinline__ RowScalars row_scalars_aux(const RowParams &p, long l
     o.bq = o.b * p.inv_T * kLn2;
     o.q2 = fmaf(o.bq, log2s - abar, -o.c * p.inv_T);
     o.gy_ent = o.bq * ((e_y / s) * (ay_f - abar));
-    o.log2s = fabsf(o.q2) < INFINITY ? log2s : NAN;  // also probabilities of 0 are poisoned then (grad_vec_aux)
+    // A coefficient that is no finite number: p_j q2 is infinite, or NaN, and NaN where p_j is 0, which the product of
+    // grad_vec_aux hides.  Against a maximum of -inf a logit of -inf is NaN and every other one +inf, and so are the
+    // exponent, the probability and, with bq of the sign of q2, the product.
+    if (!(fabsf(o.q2) < INFINITY)) {
+        o.mx = -INFINITY;
+        o.bq = copysignf(1.f, o.q2);
+    }
     if (p.token_w) {  // the reductions sum omega_t J_t, omega_t kl_t, omega_t H_t
         const float w = p.token_w[row];
         o.J *= w;

@@ -406,3 +406,45 @@ def test_aux_nan_and_inf_poison_their_row(dtype, V):
         assert bool(torch.isnan(loss).all()), what
         gn = torch.isnan(grad.float())
         assert bool(gn[5].all()) and int(gn.sum()) == V, what
+
+
+@pytest.mark.parametrize("shifted", [False, True])
+@pytest.mark.parametrize("dtype,V", [("bf16", 1999), ("bf16", 50304), ("bf16", 81925), ("bf16", 152064), ("bf16", 262144),
+                                     ("bf16", 600000), ("bf16", 200003), ("f32", 50257), ("f32", 100003), ("f32", 152064)])
+def test_aux_coefficients_that_are_no_finite_numbers(dtype, V, shifted):
+    """An advantage or a KL term that is infinite makes the gradient of its row infinite where the probability is not 0 and NaN
+    where it is (a logit of -inf), with the sign that the product has; one that is NaN makes all of the row NaN.  No other
+    row sees it.  Every kind of row: registers, last slots in LDS, streamed remainder, streamed, each with gradients
+    that begin with a 128-byte line or inside one."""
+    N, inf, nan = 8, float("inf"), float("nan")
+    g = torch.Generator().manual_seed(V)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    pitch = (V + 63) // 64 * 64 + (8 if shifted else 0)
+    store = torch.zeros((N, pitch), dtype=dt)
+    store[:, :V] = (torch.randn((N, V), generator=g) * 2).to(dt)
+    store[5, 7:V // 2] = -inf
+    z = store.to(DEV)[:, :V]
+    tokens = torch.randint(0, 7, (N,), generator=g).to(DEV)
+    lp = grpo.grpo_logprobs_fwd(z, tokens)
+    zero = z[5] == -inf
+    at_y = torch.arange(V, device=DEV) == tokens[5]
+    # what is set in row 5 (advantage, reference, old log-prob), and the sign of the gradient off the sampled token (0: NaN)
+    for adv5, ref5, old5, sign in ((inf, 0.0, 0.0, 1), (-inf, 0.0, 0.0, -1), (1.0, inf, 0.0, 1), (nan, 0.0, 0.0, 0),
+                                   (1.0, nan, 0.0, 0), (1.0, 0.0, nan, 0)):
+        adv, ref, old = torch.randn(N, generator=g).to(DEV), lp - 0.1, lp + 0.05
+        adv[5] = adv5
+        ref[5] = lp[5] - 0.1 + ref5
+        old[5] = lp[5] + 0.05 + old5
+        for in_place in (False, True):
+            buf = torch.empty_strided((N, V), (pitch, 1), dtype=dt, device=DEV)
+            zz = torch.empty_strided((N, V), (pitch, 1), dtype=dt, device=DEV).copy_(z)
+            grad = grpo.grpo_loss_aux_fwd_bwd(zz, tokens, old, ref, adv, None, kl_coef=0.01, entropy_coef=0.01,
+                                              grad_logits=zz if in_place else buf)[-1].float()
+            what = (adv5, ref5, old5, in_place)
+            assert bool(torch.isfinite(grad[:5]).all()) and bool(torch.isfinite(grad[6:]).all()), what
+            if sign == 0:
+                assert bool(torch.isnan(grad[5]).all()), what
+            else:
+                assert bool(torch.isnan(grad[5][zero]).all()), what
+                assert bool((grad[5][~zero & ~at_y] == sign * inf).all()), what
+                assert bool((grad[5][at_y] == -sign * inf).all()), what

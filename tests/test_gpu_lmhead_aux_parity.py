@@ -267,3 +267,27 @@ def test_nan_in_the_weights_reaches_every_row(first, last):
     assert bool(torch.isnan(lp).all()) and bool(torch.isnan(loss).all()) and bool(torch.isnan(dH.float()).all())
     assert bool(torch.isnan(aux[1]).all()) and bool(torch.isnan(aux[2]).all()) and bool(torch.isnan(aux[0]).all())
     assert bool(torch.isnan(aux[4].float()).all())
+
+
+@pytest.mark.parametrize("adv,ref,sign", [(float("inf"), 0.0, 1), (float("-inf"), 0.0, -1), (1.0, float("inf"), 1),
+                                          (float("nan"), 0.0, 0)])
+def test_coefficients_that_are_no_finite_numbers(adv, ref, sign):
+    """An infinite advantage or KL term makes dL/dz of its row infinite, with the sign that it has off the sampled token, and so
+    dL/dW off that token's entry; one that is NaN makes it NaN."""
+    n, v, d = 5, 700, 64
+    g = torch.Generator(device="cuda").manual_seed(3)
+    h = torch.randn((n, d), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((v, d), generator=g, device="cuda") * 0.1).to(torch.bfloat16)
+    tok = torch.randint(0, v, (n,), generator=g, device="cuda")
+    lp = grpo.grpo_lmhead_logprobs_fwd(h, w, tok)
+    a, r = torch.ones(n, device="cuda"), lp - 0.1
+    a[2], r[2] = adv, lp[2] + ref
+    out = grpo.grpo_lmhead_loss_aux_fwd_bwd(h, w, tok, lp + 0.05, r, a, None, kl_coef=0.01, entropy_coef=0.01)
+    dH, dW = out[-2].float(), out[-1]
+    assert bool(torch.isfinite(dH[[0, 1, 3, 4]]).all()) and not bool(torch.isfinite(dH[2]).any())
+    off = torch.arange(v, device="cuda") != tok[2]
+    if sign == 0:
+        assert bool(torch.isnan(dW).all())
+    else:
+        assert bool((h[2] != 0).all())
+        assert torch.equal(dW[off], (h[2].float() * sign * float("inf")).expand(int(off.sum()), d))
