@@ -20,8 +20,9 @@
 
 // The row kernels' instantiations take most of the compiler's time: build.py compiles this file once for each element type
 // with and without the auxiliary terms (GRPO_ROWS_OF: the arguments of launch_rows) and once for everything else
-// (GRPO_ROWS_APART), at the same time.  With neither defined it is the whole library.
-namespace grpo_impl {
+// (GRPO_ROWS_APART), at the same time.  With neither defined it is the whole library.  The parts find each other's names, and
+// nothing outside the library does: two builds of it in one process would otherwise call each other's.
+namespace __attribute__((visibility("hidden"))) grpo_impl {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));

@@ -3,6 +3,7 @@ every bad argument into its status code before touching the device."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -28,6 +29,14 @@ def test_library_exports_every_declared_symbol():
     L = grpo.lib()
     for n in names:
         assert hasattr(L, n), n
+
+
+def test_library_exports_nothing_else():
+    """Two builds of the library in one process must not find each other's kernels, launch functions or flags."""
+    out = subprocess.run(["nm", "-D", "--defined-only", os.path.join(ROOT, "paper_2505_07291_amd", "libgrpo.so")],
+                         capture_output=True, text=True, check=True).stdout
+    names = [line.split()[-1] for line in out.splitlines()]
+    assert sorted(n for n in names if not n.startswith("__hip_cuid_")) == declared_functions()  # (those are the compiler's marks)
 
 
 def test_status_strings_and_workspace_size():
