@@ -54,6 +54,7 @@ struct WsHeader {
 constexpr int kOrderRows = 4096;    // rows one workgroup of grpo_prepare orders: four per lane
 constexpr int kFinSegment = 16384;  // rows one workgroup of grpo_finalize takes: sixteen per lane
 constexpr int kQueueParts = 8;
+constexpr long long kOrderMinRowBytes = 32768;  // narrower rows are handed out several at a time, in index order
 constexpr int kQueueStride = 16;  // in unsigned long long: 128 bytes
 constexpr size_t kHeaderBytes = 256 + (size_t)kQueueParts * kQueueStride * 8;
 __device__ __forceinline__ unsigned long long *queue_counters(WsHeader *hdr)
@@ -78,7 +79,7 @@ struct RowParams {
     float inv_T;  // 1 / T
     float lo, hi, delta, grad_scale;
     int bwd;  // 0: log-probs only (grpo_logprobs_fwd), 1: objective + gradient
-    const int *order;  // optional: the rows in the order they are handed out (grpo_prepare), else 0, 1, 2, ...
+    const int *order;  // optional: the rows in the order they are handed out (grpo_prepare, row_of), else 0, 1, 2, ...
     int queued;       // rows come from the queue in the workspace (0: strided over the grid)
     int queue_chunk;  // rows taken from the queue per increment
     int queue_parts;  // counters in use (1 or kQueueParts)
@@ -901,6 +902,13 @@ constexpr int row_stash_slots(int block, int nv, int nl = 0)
     return fit < 0 ? 0 : fit < nv ? fit : nv;
 }
 
+// Position in the hand-out order -> row.  late: a masked row of which a workgroup with a live row in hand fills one only.
+__device__ __forceinline__ long long row_of(int entry, bool &late)
+{
+    late = entry < 0;
+    return late ? ~entry : entry;
+}
+
 // ---------------------------------------------------------------------------
 // Register-resident row kernel: requires ceil(vocab / EPV) <= BLOCK * (NV + NL).
 // One workgroup per row at a time, rows strided over a persistent grid.
@@ -949,6 +957,7 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     // The next row is asked for before the passes over this one; not where the registers are short (256 lanes of 26 and 32
     // slots: 8192 x 32000 fp32 step 304 us, 312 with it; the auxiliary terms -1 to +2 %).
     constexpr bool AHEAD = !AUX && !REM && !(BLOCK == 256 && NV > 19);
+    constexpr bool ORDERED = BLOCK * NV * 16ll >= kOrderMinRowBytes;  // serves rows that come in an order
     extern __shared__ __attribute__((aligned(16))) char row_stash[];
     char *const grad_stash = row_stash + (size_t)NL * SLAB;  // behind the LDS-resident part of the row
     __shared__ float lds_max[BLOCK / 64];
@@ -1050,24 +1059,20 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
             chunk_end = base + chunk;
         }
     };
-    // next row that needs the full treatment; rows that do not (masked, bad token id)
-    // are finished on the way.  With a live row in hand whose loads are under way (`holding`) and live rows handed out first,
-    // one such row is: under its zeros the loads arrive, more of them would keep every workgroup's last live row waiting for the
-    // end of the batch (8192 x 128256 bf16 with the auxiliary terms 650 -> 637 us, 1000 x 152064 bf16 of which 106 are live
-    // 81 -> 72; not even one costs batches of few rows, whose only loads it is: 512 x 152064, half of them live, 54 -> 57).
-    // Rows with a streamed remainder gain nothing.
-    bool none_left = false;
-    const bool masked_last = !REM && queued && p.order;
+    // next row that needs the full treatment; rows that do not (masked, bad token id) are finished on the way.  With a live row
+    // in hand (`holding`) and live rows handed out first, of masked rows that are marked as late only one is: LateRule.
+    bool rows_left = false;
     auto acquire = [&](long long &y, bool holding) -> long long {
         for (;;) {
             long long r = grab();
-            if (r >= p.n_tokens) {
-                none_left = true;
+            if (r >= p.n_tokens) return p.n_tokens;
+            bool late = false;
+            if (p.order) r = row_of(uniform(AHEAD ? fixed_load(p.order + r) : p.order[r]), late);
+            if (row_is_live<DT, BLOCK, COUNT, AHEAD>(p, r, nvec_full, tail, y)) return r;
+            if (ORDERED && !REM && holding && late) {
+                rows_left = true;
                 return p.n_tokens;
             }
-            if (p.order) r = uniform((long long)(AHEAD ? fixed_load(p.order + r) : p.order[r]));  // position in the hand-out order -> row
-            if (row_is_live<DT, BLOCK, COUNT, AHEAD>(p, r, nvec_full, tail, y)) return r;
-            if (holding && masked_last) return p.n_tokens;
         }
     };
 
@@ -1468,7 +1473,10 @@ rows_from_none:
         y = y_next;
         sh = sh_next;
     }
-    if (masked_last && !none_left) goto rows_from_none;
+    if (rows_left) {
+        rows_left = false;
+        goto rows_from_none;
+    }
 }
 
 // One batch of vectors joined into a lane's online statistics: running maximum m (in logit units),
@@ -1550,8 +1558,7 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
     const bool queued = p.queued != 0;
     long long strided_next = blockIdx.x;
     unsigned grabs = 0;
-    bool none_left = false;  // as in the resident kernel
-    const bool masked_last = queued && p.order;
+    bool rows_left = false;  // as in the resident kernel
     auto acquire = [&](long long &y, bool holding) -> long long {
         for (;;) {
             long long r;
@@ -1564,13 +1571,14 @@ __global__ void __launch_bounds__(kStreamBlock, 4) grpo_rows_streamed(RowParams 
                 r = strided_next;
                 strided_next += gridDim.x;
             }
-            if (r >= p.n_tokens) {
-                none_left = true;
+            if (r >= p.n_tokens) return p.n_tokens;
+            bool late = false;
+            if (p.order) r = row_of(uniform(p.order[r]), late);
+            if (row_is_live<DT, BLOCK>(p, r, nvec_full, tail, y)) return r;
+            if (holding && late) {
+                rows_left = true;
                 return p.n_tokens;
             }
-            if (p.order) r = uniform((long long)p.order[r]);
-            if (row_is_live<DT, BLOCK>(p, r, nvec_full, tail, y)) return r;
-            if (holding && masked_last) return p.n_tokens;
         }
     };
     u32x4 A[U], B[U];
@@ -1733,7 +1741,10 @@ rows_from_none:
         y = y_next;
         sh = sh_next;
     }
-    if (masked_last && !none_left) goto rows_from_none;
+    if (rows_left) {
+        rows_left = false;
+        goto rows_from_none;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1785,6 +1796,25 @@ static __global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned ch
     }
 }
 
+// When a workgroup with a live row in hand, whose loads are under way, fills only one of the masked rows that it comes to, then takes
+// its row and fills the others behind it (late), and when it fills them first until none is left.  Late, a workgroup's last
+// live row is not kept waiting for the end of the batch, but the workgroup asks the queue once more when that row's gradient is
+// stored.  That pays where each has several masked rows (1000 x 152064 bf16, 900 masked, 80 -> 71 us, 3000 of which 1125 277 -> 275;
+// with the auxiliary terms, whose passes are longer, 1400 of which 525 163 -> 159; 1400 x 32000, 1260 masked, 38 -> 36), or
+// where it has one live row at most and shares its CU (1400 x 32000, 525 masked, with the auxiliary terms 52 -> 46).  Fewer masked rows
+// are filled by workgroups that are out of live rows while others have one more (700 x 152064, 263 masked, with the
+// auxiliary terms 82 us, late 91; 1400 x 65536, 525 masked, 71 and 76; 400 x 81920, 150 masked, 41 and 45).
+struct LateRule {
+    long long grid;  // the row kernel's workgroups; 0: never
+    int few;         // masked rows to a workgroup up to which they are filled first
+    bool shared;     // several workgroups to a CU
+    __host__ __device__ bool late(long long n, long long live) const
+    {
+        const long long masked = n - live;
+        return grid > 0 && (masked > few * grid || (masked > grid && masked > 4 * live) || (shared && live <= grid));
+    }
+};
+
 // Counts the unmasked rows, fixes the denominator and resets the queue before any row is processed;
 // with `order`, also writes the order in which the row kernels hand out the rows of a batch with
 // masked rows: first the rows that take part (mask 1 and weight not 0), then the masked ones, which
@@ -1796,9 +1826,10 @@ static __global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned ch
 // 16384 rows that is one step, against a launch of its own for the counting (2 to 5 us) and two
 // atomics on the way.  That work grows with the square of the batch: in longer batches (prepare_counts_itself)
 // grpo_count_rows has counted each segment (live_of) and only those numbers are added up here.
-// order[0 .. M) are the live rows in increasing order, order[M .. n) the masked ones (written from the end).
+// order[0 .. M) are the live rows in increasing order, order[M .. n) the masked ones (written from the end), by their complements
+// where the rule says that they are late.
 static __global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char *mask, const float *token_w, long long n,
-                                                     double denom, WsHeader *hdr, int *order, const int *live_of)
+                                                     double denom, WsHeader *hdr, int *order, const int *live_of, LateRule rule)
 {
     __shared__ long long lds_before[16], lds_rest[16];
     __shared__ int wave_l[16], wave_m[16];
@@ -1869,6 +1900,7 @@ static __global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char 
             before_m += wave_m[w];
         }
     }
+    const int mark = rule.late(n, before + rest) ? -1 : 0;
     long long pl = before + before_l + (il - cl);
     long long pm = (seg0 - before) + before_m + (im - cm);
 #pragma unroll
@@ -1876,7 +1908,7 @@ static __global__ void __launch_bounds__(1024) grpo_prepare(const unsigned char 
         if (live[e])
             order[pl++] = (int)(r0 + e);
         else if (valid[e])
-            order[n - 1 - pm++] = (int)(r0 + e);
+            order[n - 1 - pm++] = (int)(r0 + e) ^ mark;
     }
 }
 
@@ -2575,7 +2607,6 @@ constexpr size_t loss_workspace_bytes(long long n)
 {
     return kHeaderBytes + 4 * (((size_t)n * 4 + 255) / 256 * 256) + ((size_t)n + 255) / 256 * 256 + fin_partials_bytes(n);
 }
-constexpr long long kOrderMinRowBytes = 32768;  // narrower rows are handed out several at a time, in index order
 // Up to how many rows, of at most how many vectors, the row kernel counts the rows itself and grpo_prepare is not
 // launched.  Every workgroup then reads the whole mask, and the weights.  Step with and without grpo_prepare: 512 rows of
 // 1000 fp32 21.4 and 18.1 us, 1024 rows of 8000 bf16 21.0 and 18.6, with weights and auxiliary terms 28.4 and 27.0
@@ -2627,6 +2658,14 @@ static grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_
     if (!((mask || (aux && token_weights)) && n_tokens <= 0x7fffffffll && n_tokens > cu_count() &&
           vocab * (dtype == GRPO_BF16 ? 2 : 4) >= kOrderMinRowBytes))
         order = nullptr;
+    LateRule rule = {};
+    if (order) {
+        grpo_row_plan plan;
+        grpo_row_kernel_plan((grpo_dtype)dtype, vocab, &plan);
+        const long long grid = (long long)cu_count() * plan.workgroups_per_cu;
+        // (from the queue only; rows with a streamed remainder gain nothing)
+        if (n_tokens > grid && !plan.streamed_remainder) rule = {grid, aux ? 2 : 4, plan.workgroups_per_cu > 1};
+    }
     const float *weights = aux ? token_weights : nullptr;
     const dim3 segments(order ? (unsigned)((n_tokens + kOrderRows - 1) / kOrderRows) : 1u);
     int *live_of = nullptr;
@@ -2638,7 +2677,7 @@ static grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_
     const bool count_here = n_tokens > 0 && n_tokens <= kCountRows && (vocab + epv - 1) / epv <= kCountVectors;
     if (!count_here)
         hipLaunchKernelGGL(grpo_prepare, segments, dim3(1024), 0, st, mask, weights, (long long)n_tokens, denom, hdr, order,
-                           (const int *)live_of);
+                           (const int *)live_of, rule);
     if (n_tokens > 0) {
         RowParams p = {};
         p.count_here = count_here ? 1 : 0;

@@ -1439,7 +1439,7 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
     const bool take = n_tokens > 0 && n_tokens <= LM_TAKE_MAX;
     if (bwd && !take)
         hipLaunchKernelGGL(grpo_prepare, dim3(1), dim3(1024), 0, st, mask, aux ? token_weights : (const float *)nullptr,
-                           (long long)n_tokens, denom, hdr, (int *)nullptr, (const int *)nullptr);
+                           (long long)n_tokens, denom, hdr, (int *)nullptr, (const int *)nullptr, LateRule{});
     if (n_tokens > 0) {
         const int M = (int)n_tokens, V = (int)vocab, D = (int)d_model;
         const int Mc = (int)std::min<int64_t>(cap, n_tokens);  // most rows a chunk can have

@@ -168,3 +168,47 @@ def test_rows_that_begin_inside_a_line(aux, dtype, epv, vectors):
                 want = got
             for a, b in zip(got, want):
                 assert torch.equal(a.nan_to_num(nan=77.0), b.nan_to_num(nan=77.0)), (vocab, start, apart)
+
+
+# masked rows behind the live ones, filled in front of a workgroup's last live row or behind it: batches on either side of each
+# condition of the rule, by the live ones of their rows, in each kind of kernel (one, two and four workgroups to a CU, rows
+# with LDS slots, a streamed remainder, streamed).  Every row's values are those it has in a batch without an order (as many
+# rows as CUs at most), masked rows are zeros, and nothing is written outside the rows.
+@pytest.mark.parametrize("aux", [False, True])
+@pytest.mark.parametrize("dtype,vocab,rows", [("bf16", 152064, 700), ("bf16", 81925, 700), ("bf16", 200064, 600), ("bf16", 65536, 1100),
+                                              ("bf16", 16384, 1300), ("f32", 50304, 700), ("bf16", 300000, 520), ("bf16", 152069, 1100)])
+def test_masked_rows_before_and_behind_live_ones(dtype, vocab, rows, aux):
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    pitch = (vocab + 7) // 8 * 8
+    z = torch.empty((rows, pitch), dtype=dt, device="cuda")
+    for a in range(0, rows, 100):
+        z[a:a + 100] = torch.randn((len(z[a:a + 100]), pitch), generator=g, device="cuda") * 3
+    tokens = torch.randint(0, vocab, (rows,), generator=g, device="cuda")
+    old = -12 + torch.randn(rows, generator=g, device="cuda")
+    adv, ref = (torch.randn(rows, generator=g, device="cuda") for _ in range(2))
+    order = torch.randperm(rows, generator=torch.Generator().manual_seed(rows))
+
+    def step(part, mask):
+        n = len(tokens[part])
+        grad = torch.full((n, pitch), 3.0, dtype=dt, device="cuda")
+        ws = torch.full((grpo.grpo_workspace_bytes(n),), 255, dtype=torch.uint8, device="cuda")
+        kw = dict(denom=50.0, grad_logits=grad[:, :vocab], workspace=ws)
+        if aux:
+            out = grpo.grpo_loss_aux_fwd_bwd(z[part][:, :vocab], tokens[part], old[part], ref[part], adv[part], mask[part],
+                                             kl_coef=0.1, entropy_coef=0.01, **kw)
+        else:
+            out = grpo.grpo_loss_fwd_bwd(z[part][:, :vocab], tokens[part], old[part], adv[part], mask[part], **kw)
+        assert bool((grad[:, vocab:] == 3.0).all()), "written outside the rows"
+        return [grad[:, :vocab]] + [t for t in out[1:-1] if t.shape[0] == n]
+
+    for live in sorted({0, 1, 40, rows // 5, max(0, rows - 2 * cus - 1), rows * 5 // 8, rows - 1}):
+        mask = torch.zeros(rows, dtype=torch.uint8)
+        mask[order[:live]] = 1
+        mask = mask.to("cuda")
+        whole = step(slice(0, rows), mask)
+        assert bool((whole[0][mask == 0] == 0).all())
+        for a in range(0, rows, cus):
+            for t, part in zip(whole, step(slice(a, a + cus), mask)):
+                assert torch.equal(t[a:a + cus], part), (live, a)
