@@ -926,12 +926,13 @@ __device__ __forceinline__ long long row_of(int entry, bool &late)
 // line the conditions it adds per slot cost 1 to 2 % of a step and 5 to 8 % of a log-probs pass (4096 x 128256 bf16 297 -> 304
 // us, 129 -> 139), where rows that do not gain 7 to 14 % (128264 apart 339 -> 305, 16384 x 32001 bf16 361 -> 322, 8192 x 50304
 // 267 -> 247, 32768 x 8001 204 -> 174).
+// FEW: a batch of few rows, see few_rounds.
 // COUNT: a small batch of narrow rows.  Every workgroup counts the rows that take part (up to four bytes a
 // lane, on their way while the first row is looked up), and the first one writes the header, error word
 // included, for grpo_finalize: no grpo_prepare in front, which is one of four launches of a step on 512 fp32 rows
 // of 1024 (figures at kCountRows).
 // ---------------------------------------------------------------------------
-template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false, bool SHIFT = false>
+template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false, bool SHIFT = false, bool FEW = false>
 // 4 wavefronts per SIMD and 128 registers each; the widest instantiations 2 and 256
 __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowParams p)
 {
@@ -955,8 +956,8 @@ __global__ void __launch_bounds__(BLOCK, NV > 19 ? 2 : 4) grpo_rows_cached(RowPa
     constexpr int RSTASH = RST < 0 ? row_reg_stash_slots(BLOCK, NV) : RST < NV - STASH ? RST : NV - STASH;
     static_assert(STASH + RSTASH <= NV, "more waiting slots than register slots");
     // The next row is asked for before the passes over this one; not where the registers are short (256 lanes of 26 and 32
-    // slots: 8192 x 32000 fp32 step 304 us, 312 with it; the auxiliary terms -1 to +2 %).
-    constexpr bool AHEAD = !AUX && !REM && !(BLOCK == 256 && NV > 19);
+    // slots: 8192 x 32000 fp32 step 304 us, 312 with it; the auxiliary terms -1 to +2 %), and not in batches of few rows.
+    constexpr bool AHEAD = !FEW && !AUX && !REM && !(BLOCK == 256 && NV > 19);
     constexpr bool ORDERED = BLOCK * NV * 16ll >= kOrderMinRowBytes;  // serves rows that come in an order
     extern __shared__ __attribute__((aligned(16))) char row_stash[];
     char *const grad_stash = row_stash + (size_t)NL * SLAB;  // behind the LDS-resident part of the row
@@ -2404,7 +2405,7 @@ static int cu_count()
     return n;
 }
 
-template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false, bool SHIFT = false>
+template <grpo_dtype DT, int BLOCK, int NV, bool AUX, bool TAIL, int NL = 0, int RST = -1, bool REM = false, bool COUNT = false, bool SHIFT = false, bool FEW = false>
 void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
 {
     RowParams p = p_in;
@@ -2430,12 +2431,12 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
         static std::atomic<bool> attr_done[64];  // setting the attribute twice is harmless
         int dev = 0;
         if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64 && !attr_done[dev].load()) {
-            if (hipFuncSetAttribute((const void *)grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT, SHIFT>,
+            if (hipFuncSetAttribute((const void *)grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT, SHIFT, FEW>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) == hipSuccess)
                 attr_done[dev].store(true);
         }
     }
-    hipLaunchKernelGGL((grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT, SHIFT>), dim3((unsigned)grid), dim3(BLOCK),
+    hipLaunchKernelGGL((grpo_rows_cached<DT, BLOCK, NV, AUX, TAIL, NL, RST, REM, COUNT, SHIFT, FEW>), dim3((unsigned)grid), dim3(BLOCK),
                        lds_bytes, st, p);
 }
 
@@ -2509,6 +2510,12 @@ static int plan_rows(long long nvec, bool ragged)
     return kRowStreaming;
 }
 
+// Batches of which a workgroup that has its CU to itself takes a live row or two (of padded responses five eighths of the rows are
+// live): the masked ones that a workgroup without a second live row fills it fills under its first one's loads, not behind
+// its first pass (FEW).  600 x 152064 bf16, a third of them masked, 77 -> 73.5 us, 512 x 200064 97.5 -> 94.5, 420 x 107001 53 -> 50.  With one live row at most
+// to each the other way is 1 to 3 % ahead (400 x 152064), from 1000 rows on both are even, then it is 1 to 2 %.
+constexpr bool few_rounds(long long n, long long cus) { return 5 * n > 8 * cus && n <= 3 * cus; }
+
 template <grpo_dtype DT, bool AUX>
 void launch_rows(const RowParams &p_in, hipStream_t st)
 {
@@ -2539,6 +2546,12 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
             constexpr bool T = TAIL || (BLOCK == 512 && (NV == 26 || NV == 32));                   \
             if ((p.shift0 | p.shift_step) != 0 && p.vocab / Elem<DT>::EPV + 7 <= BLOCK * NV) {     \
                 launch_cached<DT, BLOCK, NV, AUX, T, 0, (AUX ? RSTA : RSTP), false, false, true>(p, PERCU, st); \
+                break;                                                                             \
+            }                                                                                      \
+        }                                                                                          \
+        if constexpr (!AUX && !REM && PERCU == 1) {                                                \
+            if (p.order && few_rounds(p.n_tokens, cu_count())) {                                   \
+                launch_cached<DT, BLOCK, NV, AUX, TAIL, NL, RSTP, false, false, false, true>(p, PERCU, st); \
                 break;                                                                             \
             }                                                                                      \
         }                                                                                          \
