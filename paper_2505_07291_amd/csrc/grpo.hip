@@ -2516,6 +2516,17 @@ static int plan_rows(long long nvec, bool ragged)
 // to each the other way is 1 to 3 % ahead (400 x 152064), from 1000 rows on both are even, then it is 1 to 2 %.
 constexpr bool few_rounds(long long n, long long cus) { return 5 * n > 8 * cus && n <= 3 * cus; }
 
+// Where rows held further back, whose stores are whole lines, pay (SHIFT): wide ones in batches of any length (256 x 107001 bf16
+// 33.5 -> 30.3 us, 2048 x 32001 58 -> 53); not the narrow ones, whose time the additional conditions per slot are rather
+// than the memory (16384 x 1619 bf16 55.9 us, 58.8 with, x 4001 72.5 and 78, with the auxiliary terms 100 and 118) up to where the
+// memory is (16384 x 8001 109 and 103, 32768 x 4001 fp32 199 and 169), and with the auxiliary terms not where few rows
+// of middling width go to a workgroup (1400 x 16001 38.3 and 40.3, 2048 x 8001 fp32 36.0 and 38.5; 9000 x 16001 137 with).
+constexpr bool shift_pays(int vectors, bool aux, long long row_bytes, long long n, long long cus)
+{
+    if (vectors <= 1024) return !aux && row_bytes >= 12288;
+    return !aux || vectors > 4096 || row_bytes >= 40960 || n > 8 * cus;
+}
+
 template <grpo_dtype DT, bool AUX>
 void launch_rows(const RowParams &p_in, hipStream_t st)
 {
@@ -2544,7 +2555,8 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
         if constexpr (NL == 0) {                                                                   \
             /* 512 lanes of 26 and 32 slots: the kernel for ragged rows serves whole ones too */   \
             constexpr bool T = TAIL || (BLOCK == 512 && (NV == 26 || NV == 32));                   \
-            if ((p.shift0 | p.shift_step) != 0 && p.vocab / Elem<DT>::EPV + 7 <= BLOCK * NV) {     \
+            if ((p.shift0 | p.shift_step) != 0 && p.vocab / Elem<DT>::EPV + 7 <= BLOCK * NV &&     \
+                shift_pays(BLOCK * NV, AUX, p.vocab * Elem<DT>::BYTES, p.n_tokens, cu_count())) {  \
                 launch_cached<DT, BLOCK, NV, AUX, T, 0, (AUX ? RSTA : RSTP), false, false, true>(p, PERCU, st); \
                 break;                                                                             \
             }                                                                                      \
