@@ -1801,7 +1801,8 @@ static __global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned ch
 // its row and fills the others behind it (late), and when it fills them first until none is left.  Late, a workgroup's last
 // live row is not kept waiting for the end of the batch, but the workgroup asks the queue once more when that row's gradient is
 // stored.  That pays where each has several masked rows (1000 x 152064 bf16, 900 masked, 80 -> 71 us, 3000 of which 1125 277 -> 275;
-// with the auxiliary terms, whose passes are longer, 1400 of which 525 163 -> 159; 1400 x 32000, 1260 masked, 38 -> 36), or
+// with the auxiliary terms, whose passes are longer, 1400 of which 525 163 -> 159 and, sharing CUs, 4096 x 16384 of which
+// 1536 80 -> 74; 1400 x 32000, 1260 masked, 38 -> 36), or
 // where it has one live row at most and shares its CU (1400 x 32000, 525 masked, with the auxiliary terms 52 -> 46).  Fewer masked rows
 // are filled by workgroups that are out of live rows while others have one more (700 x 152064, 263 masked, with the
 // auxiliary terms 82 us, late 91; 1400 x 65536, 525 masked, 71 and 76; 400 x 81920, 150 masked, 41 and 45).
@@ -2689,7 +2690,10 @@ static grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_
         grpo_row_kernel_plan((grpo_dtype)dtype, vocab, &plan);
         const long long grid = (long long)cu_count() * plan.workgroups_per_cu;
         // (from the queue only; rows with a streamed remainder gain nothing)
-        if (n_tokens > grid && !plan.streamed_remainder) rule = {grid, aux ? 2 : 4, plan.workgroups_per_cu > 1};
+        if (n_tokens > grid && !plan.streamed_remainder) {
+            const bool shared = plan.workgroups_per_cu > 1;
+            rule = {grid, !aux ? 4 : shared ? 1 : 2, shared};
+        }
     }
     const float *weights = aux ? token_weights : nullptr;
     const dim3 segments(order ? (unsigned)((n_tokens + kOrderRows - 1) / kOrderRows) : 1u);
