@@ -67,6 +67,7 @@ constexpr int LM_SLOTS = 5;                          // operand tiles resident i
 constexpr int LM_LPT = LM_BM * LM_CPR / LM_THREADS;  // 16-byte loads per lane and operand tile: 4
 constexpr int LM_LDS_BYTES = LM_SLOTS * LM_TILE_BYTES;
 
+constexpr int LM_CHUNK_MAX = 1 << 20;  // rows of a chunk; keeps every per-chunk grid extent and 32-bit offset in range
 constexpr int LM_LEAD_STEPS = 16;                     // contractions of up to so many K steps: see lm_gemm_nt
 
 enum { LM_EPI_LSE = 0, LM_EPI_BF16 = 1, LM_EPI_F32 = 2 };
@@ -735,6 +736,7 @@ struct LmRows {
     int *rows, *tokens32, *n_live;   // [n], [n] (by compact row), [1]
     int *orig2, *n_grad;             // [cap], [1]
     unsigned *gmask;                 // [cap / 16]
+    int *gsum;                       // gradient rows of every LM_SUM_WORDS words of gmask, in chunks of more than LM_SUM_FROM rows
     float *zy;     // by compact row: logit of the sampled token (fp32 accumulator)
     float *shift;  // max k + log2(sum): p_j = exp2(z_j k - shift)
     float *q;      // c / T
@@ -1022,6 +1024,20 @@ __global__ void __launch_bounds__(LM_CMB_ROWS * LM_CMB_LANES) lm_combine(RowPara
     }
 }
 
+// The gradient rows of every LM_SUM_WORDS words of gmask.
+constexpr int LM_SUM_WORDS = 256;
+__global__ void __launch_bounds__(LM_SUM_WORDS) lm_count_grads(LmRows w)
+{
+    __shared__ int lds_n[LM_SUM_WORDS / 64];
+    int base, count;
+    lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, base, count);
+    const int q = (int)(blockIdx.x * LM_SUM_WORDS + threadIdx.x);
+    const int n = wave_sum(q * LM_CMB_ROWS < count ? __builtin_popcount(w.gmask[q]) : 0);
+    if ((threadIdx.x & 63) == 0) lds_n[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) w.gsum[blockIdx.x] = lds_n[0] + lds_n[1] + lds_n[2] + lds_n[3];
+}
+
 // One 64 x 64 tile of out[c][r] = in[rowmap[r - r0]][c], r < R, c < C, at (r0, c0); the
 // columns R .. of out are zero-filled.  Through LDS, four consecutive
 // elements (8 bytes) per lane on both sides; C and ldo are multiples of 4 and both matrices
@@ -1072,7 +1088,14 @@ __device__ __forceinline__ void lm_transpose_tile(int r0, int c0, const __bf16 *
 // 62.4 -> 60.3, 1024 x 50304 x 768 291.5 -> 290).
 constexpr int LM_GL_COLS = 512, LM_GL_ROWS = 16;
 static_assert(LM_GL_ROWS == LM_CMB_ROWS, "a word of gmask to a workgroup's rows");
-template <bool AUX>
+static_assert(LM_SUM_WORDS == 256 && LM_CHUNK_MAX / LM_GL_ROWS / LM_SUM_WORDS <= 256, "a lane to every word of gsum");
+// Every workgroup looking at all of the words costs chunks of many rows more and more of the launch (the rows of a default
+// chunk are 640 words, a caller's workspace may hold 65536 of them): of chunks of more than LM_SUM_FROM rows lm_count_grads has
+// counted the gradient rows of every 256 words (SUMS; an instantiation of its own: the choice inside cost 4096 x 32000 x 256
+// 4 us), and only the words of a workgroup's own 4096 rows are looked at.  Call on one chunk of 1048576 x 256 x 64: 15100 us without,
+// 13800 with, 65536 x 4000 x 512 1422 and 1382, 65536 x 1000 x 256 857 and 842, 20480 x 1000 x 256 287 and 289.
+constexpr int LM_SUM_FROM = 32768;
+template <bool AUX, bool SUMS>
 __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long ldz, int V, LmRows w,
                                                       float k, __bf16 *G, long long ldg, int col_groups, unsigned gl_blocks,
                                                       const __bf16 *hidden, long long ldh, int d, __bf16 *Ht, long long ldht)
@@ -1086,14 +1109,11 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
     lm_chunk_range(*w.n_live, w.chunk_cap, w.chunk, zbase, zcount);
     const int groups = (zcount + LM_GL_ROWS - 1) / LM_GL_ROWS;
     if (blockIdx.x >= gl_blocks) {  // H^T of the chunk's gradient rows, [d][ldht]: independent of G, in the same launch
-        __shared__ int rowmap[64];
+        __shared__ int rowmap[64], lds_from[2], lds_to;
         const int t = (int)(blockIdx.x - gl_blocks), across = (int)(ldht / 64), first = t % across * 64;
-        int total = 0;
-        for (int q0 = 0; q0 < groups; q0 += 256) {  // whole workgroup alike
-            const int q = q0 + (int)threadIdx.x;
-            unsigned bits = q < groups ? w.gmask[q] : 0u;
-            int incl = __builtin_popcount(bits);  // inclusive scan inside the wavefront
-            const int own = incl;
+        // what the lanes before this one have, added to `pos`, and what all of them have, added to `sum` (read before a barrier)
+        auto scan = [&](int own, int &pos, int &sum) {
+            int incl = own;  // inclusive scan inside the wavefront
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const int up = __shfl_up(incl, o, 64);
@@ -1101,19 +1121,39 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
             }
             if (lane == 63) lds_n[0][wv] = incl;
             __syncthreads();
-            int pos = total + incl - own - first;
+            pos += incl - own;
             for (int i = 0; i < 4; ++i) {
                 if (i < wv) pos += lds_n[0][i];
-                total += lds_n[0][i];
+                sum += lds_n[0][i];
             }
+        };
+        int total = 0, n2 = 0, q_from = 0, q_to = groups;
+        if constexpr (SUMS) {  // only the words that hold rows first .. first + 63
+            const int own = (int)threadIdx.x * LM_SUM_WORDS < groups ? w.gsum[threadIdx.x] : 0;
+            int pos = 0;
+            scan(own, pos, n2);
+            if (first >= n2) return;  // whole workgroup alike
+            if (pos <= first && first < pos + own) lds_from[0] = (int)threadIdx.x * LM_SUM_WORDS, lds_from[1] = pos;
+            const int last = min(first + 64, n2);
+            if (pos < last && last <= pos + own) lds_to = min(((int)threadIdx.x + 1) * LM_SUM_WORDS, groups);
+            __syncthreads();
+            q_from = lds_from[0], total = lds_from[1], q_to = lds_to;
+        }
+        for (int q0 = q_from; q0 < q_to; q0 += 256) {  // whole workgroup alike
+            const int q = q0 + (int)threadIdx.x;
+            unsigned bits = q < groups ? w.gmask[q] : 0u;
+            const int own = __builtin_popcount(bits);
+            int pos = total - first;
+            scan(own, pos, total);
             if (pos < 64 && pos + own > 0)
                 for (; bits != 0u; bits &= bits - 1u, ++pos)
                     if (pos >= 0 && pos < 64) rowmap[pos] = w.rows[zbase + q * LM_GL_ROWS + __builtin_ctz(bits)];
             __syncthreads();
         }
+        if constexpr (!SUMS) n2 = total;
         // columns past the rows that exist are read as zeros up to the next whole K step, and not at all beyond it
-        if (first < (total + 63) / 64 * 64)
-            lm_transpose_tile(first, t / across * 64, hidden, ldh, total, rowmap, d, Ht, ldht, (unsigned short(*)[66])turn_all);
+        if (first < (n2 + 63) / 64 * 64)
+            lm_transpose_tile(first, t / across * 64, hidden, ldh, n2, rowmap, d, Ht, ldht, (unsigned short(*)[66])turn_all);
         return;
     }
     const int r0 = (int)(blockIdx.x / (unsigned)col_groups) * LM_GL_ROWS;
@@ -1134,10 +1174,17 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
                     : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     int before = 0, n2 = 0;  // gradient rows ahead of this workgroup's, and in the chunk
-    for (int q = threadIdx.x; q < groups; q += 256) {
-        const int c = __builtin_popcount(w.gmask[q]);
-        n2 += c;
-        before += q < r0 / LM_GL_ROWS ? c : 0;
+    const int mine = r0 / LM_GL_ROWS;
+    if constexpr (SUMS) {
+        const int c = (int)threadIdx.x * LM_SUM_WORDS < groups ? w.gsum[threadIdx.x] : 0, q = mine / LM_SUM_WORDS * LM_SUM_WORDS + (int)threadIdx.x;
+        n2 = c;
+        before = ((int)threadIdx.x < mine / LM_SUM_WORDS ? c : 0) + (q < mine && q < groups ? __builtin_popcount(w.gmask[q]) : 0);
+    } else {
+        for (int q = threadIdx.x; q < groups; q += 256) {
+            const int c = __builtin_popcount(w.gmask[q]);
+            n2 += c;
+            before += q < mine ? c : 0;
+        }
     }
     before = wave_sum(before);
     n2 = wave_sum(n2);
@@ -1146,7 +1193,7 @@ __global__ void __launch_bounds__(256) lm_grad_logits(const float *Z, long long 
     before = lds_n[0][0] + lds_n[0][1] + lds_n[0][2] + lds_n[0][3];
     n2 = lds_n[1][0] + lds_n[1][1] + lds_n[1][2] + lds_n[1][3];
     const int n2_pad = (n2 + 63) / 64 * 64;
-    const unsigned grads = r0 < zcount ? w.gmask[r0 / LM_GL_ROWS] : 0u;
+    const unsigned grads = r0 < zcount ? w.gmask[mine] : 0u;
     const int pos = (grads >> n) & 1u ? before + __builtin_popcount(grads & ((1u << n) - 1u)) : -1;
     if (blockIdx.x == 0 && threadIdx.x == 0) *w.n_grad = n2;
     if (blockIdx.x % (unsigned)col_groups == 0 && threadIdx.x < LM_GL_ROWS && pos >= 0) w.orig2[pos] = w.rows[zbase + r0 + n];
@@ -1303,7 +1350,7 @@ struct LmLayout {
 // still fills the chip (40 tile rows: 23760 tiles of the logits product, 800 of dL/dH).  A caller
 // that brings more gets larger chunks.
 constexpr int64_t kLmChunkRows = 10240;
-constexpr int64_t kLmChunkMax = 1 << 20;  // rows; keeps every per-chunk grid extent and 32-bit offset in range
+constexpr int64_t kLmChunkMax = LM_CHUNK_MAX;
 
 int64_t lm_cap_limit(int64_t n) { return std::min<int64_t>(kLmChunkMax, std::max<int64_t>(256, (n + 255) / 256 * 256)); }
 
@@ -1567,11 +1614,18 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
                 hipLaunchKernelGGL((few ? lm_combine<false, 16> : lm_combine<false, 64>), cmb_grid, cmb_block, 0, st, p, w);
             if (!bwd) continue;
 
+            const bool sums = Mc > LM_SUM_FROM;
+            if (sums) {
+                w.gsum = (int *)(w.gmask + cap / LM_GL_ROWS);  // in the space behind the words
+                hipLaunchKernelGGL(lm_count_grads, dim3((unsigned)((Mc + LM_GL_ROWS * LM_SUM_WORDS - 1) / (LM_GL_ROWS * LM_SUM_WORDS))),
+                                   dim3(LM_SUM_WORDS), 0, st, w);
+            }
             const int gl_cols = (int)((L.ldg + LM_GL_COLS - 1) / LM_GL_COLS);
             // rows up to the next multiple of 64: the padding rows are written too (G has cap >= 256 rows)
             const unsigned gl_blocks = (unsigned)((long long)gl_cols * ((Mc + 63) / 64 * (64 / LM_GL_ROWS)));
             const dim3 gl_grid(gl_blocks + (unsigned)((L.ldgt / 64) * ((D + 63) / 64)));  // then the tiles of H^T
-            hipLaunchKernelGGL((aux ? lm_grad_logits<true> : lm_grad_logits<false>), gl_grid, dim3(256), 0, st,
+            hipLaunchKernelGGL((aux ? sums ? lm_grad_logits<true, true> : lm_grad_logits<true, false>
+                                    : sums ? lm_grad_logits<false, true> : lm_grad_logits<false, false>), gl_grid, dim3(256), 0, st,
                                (const float *)(ws + L.Z), L.ldz, V, w, k, G, L.ldg, gl_cols, gl_blocks,
                                (const __bf16 *)hidden, (long long)hidden_stride, D, Ht, L.ldgt);
 

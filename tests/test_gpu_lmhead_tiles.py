@@ -61,3 +61,47 @@ def test_results_at_odd_pitches_and_offsets(rows, vocab, d, cut):
     call(grad_weight=twice, accumulate_grad_weight=True)
     call(grad_weight=odd_w[:, 1:d + 1], accumulate_grad_weight=True)
     assert torch.equal(twice, gw + gw) and torch.equal(odd_w[:, 1:d + 1], twice)
+
+
+# chunks of more than 32768 rows: the rows with a gradient are found through counts per 4096 rows.  One chunk of all rows against the
+# default chunks of 10240: log-probs, loss and counters bit for bit, dL/dH to its bf16 rounding (2^-8; a row in another row's place
+# is off by its own size), dL/dW to the order of up to 5e4 fp32 sums (their rounding adds up to some sqrt(5e4) 2^-24 = 1.4e-5).
+# Gradients everywhere, in a few rows at the edges of those counts, in 64 rows across one, at the end only, and nowhere.
+@pytest.mark.parametrize("aux", [False, True])
+@pytest.mark.parametrize("rows", [32769, 70001])
+def test_gradient_rows_of_large_chunks(rows, aux):
+    v, d = 300, 64
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    h = torch.randn((rows, d), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((v, d), generator=g, device="cuda") * 0.3).to(torch.bfloat16)
+    tok = torch.randint(0, v, (rows,), generator=g, device="cuda")
+    mask = (torch.rand(rows, generator=g, device="cuda") < 0.8).to(torch.uint8)
+    zeros = torch.zeros(rows, device="cuda")
+    # the reference is this very call's log-probs: a KL term of a last bit, as against those of the forward alone, has a gradient too
+    lp = grpo.grpo_lmhead_loss_aux_fwd_bwd(h, w, tok, zeros, zeros, zeros, mask, kl_coef=0.1, entropy_coef=0.0)[1]
+    live = mask.nonzero()[:, 0]
+    n = len(live)
+    picks = {"all": live, "edges": live[[0, 15, 16, 4095, 4096, 4097, 8191, 20000, n - 1]], "across": live[4064:4128],
+             "end": live[n - 4000:], "none": live[:0]}
+    for name, pick in picks.items():
+        adv = torch.zeros(rows, device="cuda")
+        adv[pick] = torch.rand(len(pick), generator=g, device="cuda") + 0.5
+        got = []
+        for chunk in (10240, rows):
+            ws = torch.full((grpo.grpo_lmhead_workspace_bytes_for_chunk(rows, v, d, chunk),), 255, dtype=torch.uint8, device="cuda")
+            kw = dict(workspace=ws)
+            if aux:  # a gradient where the KL term has one too
+                out = grpo.grpo_lmhead_loss_aux_fwd_bwd(h, w, tok, lp + 0.05, lp - 0.1 * (adv != 0), adv, mask, kl_coef=0.1,
+                                                        entropy_coef=0.0, **kw)
+            else:
+                out = grpo.grpo_lmhead_loss_fwd_bwd(h, w, tok, lp + 0.05, adv, mask, **kw)
+            got.append(out)
+        for a, b in zip(got[0][:-2], got[1][:-2]):
+            assert torch.equal(a, b), name
+        (ha, wa), (hb, wb) = ([t.float() for t in out[-2:]] for out in got)
+        nothing = torch.ones(rows, dtype=torch.bool, device="cuda")
+        nothing[pick] = False
+        assert bool((hb[nothing] == 0).all()), name
+        assert bool(((ha - hb).norm(dim=1) <= ha.norm(dim=1) * 2.0 ** -8).all()), name
+        assert float((wa - wb).norm()) <= 1e-4 * float(wa.norm()), name
+        assert len(pick) == 0 or float(wb.norm()) > 0
