@@ -60,9 +60,11 @@ def test_head_partials_of_few_and_many_tiles(vocab):
 
 
 # rows strided over the grid, several rounds of it, where workgroups share a CU and where each has one to
-# itself: every row is taken once, whatever workgroup takes it
+# itself, or from the queue, the last four in batches long enough for two increments at once: every row is taken once, whatever
+# workgroup takes it
 @pytest.mark.parametrize("dtype,vocab,rows", [("f32", 1000, 9000), ("bf16", 8192, 5000), ("bf16", 50304, 1300),
-                                              ("bf16", 100352, 1030), ("f32", 50257, 700)])
+                                              ("bf16", 100352, 1030), ("f32", 50257, 700), ("bf16", 8192, 14000),
+                                              ("bf16", 16384, 6000), ("bf16", 107008, 2500), ("f32", 50257, 2400)])
 def test_strided_rows_equal_queued_rows(dtype, vocab, rows):
     g = torch.Generator(device="cuda").manual_seed(vocab)
     pitch = (vocab + 7) // 8 * 8
@@ -127,10 +129,11 @@ def test_rows_counted_by_the_row_kernel(aux, dtype, vocab, rows, bad):
             assert torch.equal(a, b)
 
 
-# gradient rows that begin with a 128-byte line, or anywhere inside one: the resident kernels then hold a row up to seven
+# gradient rows that begin with a 128-byte line, or anywhere inside one: the resident kernels may then hold a row up to seven
 # vectors further back, the streaming one turns its lanes, and both sum in the same order: the same bits, nothing written
 # outside the rows.  Every resident width, whole and ragged rows, the last widths that leave room for it and the first that
-# do not; streamed ragged rows (those of more than 16384 vectors).
+# do not; streamed ragged rows (those of more than 16384 vectors).  At most a row to a workgroup, where only the resident
+# kernels of wide rows do so.
 @pytest.mark.parametrize("aux", [False, True])
 @pytest.mark.parametrize("dtype,epv", [(torch.bfloat16, 8), (torch.float32, 4)])
 @pytest.mark.parametrize("vectors", [1, 5, 249, 250, 1017, 1018, 4000, 6649, 8185, 8186, 10233, 13305, 16377, 16378, 19449,
@@ -168,6 +171,55 @@ def test_rows_that_begin_inside_a_line(aux, dtype, epv, vectors):
                 want = got
             for a, b in zip(got, want):
                 assert torch.equal(a.nan_to_num(nan=77.0), b.nan_to_num(nan=77.0)), (vocab, start, apart)
+
+
+# the same with several rows to a workgroup, from the queue, and different places in a line from one row to the next: a
+# workgroup refills its registers in front of and behind what the row before had, lanes turn between rows.  Two masks: most
+# rows live, and few, so that masked rows are filled behind the last live ones.  Rows enough for every kernel by its workgroups
+# to a CU, more than eight rounds of those that take several narrow rows at once.
+@pytest.mark.parametrize("aux", [False, True])
+@pytest.mark.parametrize("dtype,epv", [(torch.bfloat16, 8), (torch.float32, 4)])
+@pytest.mark.parametrize("vectors", [200, 800, 1016, 1300, 2600, 4088, 6648, 8184, 8185, 10232, 10233, 13304, 13305, 16376,
+                                     16377, 19448, 19449, 22520])
+def test_several_rows_that_begin_inside_a_line(aux, dtype, epv, vectors):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tail = epv - 3 if vectors % 2 else 0
+    per_cu = 8 if vectors <= 1024 else 4 if vectors <= 4096 else 2 if vectors <= 8192 else 1  # streamed: 2, of four rounds' rows
+    rows = (8 if vectors * 16 < 32768 else 4 if per_cu == 1 else 3) * per_cu * cus + 37
+    vocab = vectors * epv + tail
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    pitches = [((vectors + 1 + 7) // 8 * 8 + apart) * epv for apart in (0, 1, 3, 4)]
+    z = torch.empty((rows, vocab), dtype=dtype, device="cuda")
+    for a in range(0, rows, 256):
+        z[a:a + 256] = torch.randn((len(z[a:a + 256]), vocab), generator=g, device="cuda") * 3
+    tokens = torch.randint(0, vocab, (rows,), generator=g, device="cuda")
+    tokens[::3], tokens[1::5] = 0, vocab - 1
+    old, adv, ref = (torch.randn(rows, generator=g, device="cuda") for _ in range(3))
+    old -= 12
+    bufs = [torch.empty(rows * pitches[-1] + 16 * epv, dtype=dtype, device="cuda") for _ in range(2)]
+    for share in (0.7, 0.15):
+        mask = (torch.rand(rows, generator=g, device="cuda") < share).to(torch.uint8)
+        want = None
+        for pitch, start in zip(pitches, (0, 3, 0, 7)):
+            for b in bufs:
+                b.fill_(3.0)
+                assert b.data_ptr() % 128 == 0
+            views = [b[start * epv:].as_strided((rows, vocab), (pitch, 1)) for b in bufs]
+            views[0].copy_(z)
+            ws = torch.full((grpo.grpo_workspace_bytes(rows),), 255, dtype=torch.uint8, device="cuda")
+            kw = dict(grad_logits=views[1], workspace=ws)
+            if aux:
+                out = grpo.grpo_loss_aux_fwd_bwd(views[0], tokens, old, ref - 12, adv, mask, kl_coef=0.1, entropy_coef=0.01, **kw)
+            else:
+                out = grpo.grpo_loss_fwd_bwd(views[0], tokens, old, adv, mask, **kw)
+            got = [views[1].clone()] + list(out[:-1])
+            views[1].fill_(3.0)
+            assert bool((bufs[1] == 3.0).all()), "written outside the rows"
+            if want is None:
+                want = got
+                assert bool((got[0][mask == 0] == 0).all()) and bool(got[0].isfinite().all())
+            for a, b in zip(got, want):
+                assert torch.equal(a, b), (vocab, start, pitch, share)
 
 
 # masked rows behind the live ones, filled in front of a workgroup's last live row or behind it: batches on either side of each
