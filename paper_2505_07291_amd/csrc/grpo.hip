@@ -925,7 +925,7 @@ __device__ __forceinline__ long long row_of(int entry, bool &late)
 // SHIFT: gradient rows begin inside a 128-byte line (row_shift).  An instantiation of its own: on rows that begin with a
 // line the conditions it adds per slot cost 1 to 2 % of a step and 5 to 8 % of a log-probs pass (4096 x 128256 bf16 297 -> 304
 // us, 129 -> 139), where rows that do not gain 7 to 14 % (128264 apart 339 -> 305, 16384 x 32001 bf16 361 -> 322, 8192 x 50304
-// 267 -> 247, 32768 x 8001 204 -> 174).
+// at a pitch of 50312 267 -> 247, 32768 x 8001 204 -> 174).
 // FEW: a batch of few rows, see few_rounds.
 // COUNT: a small batch of narrow rows.  Every workgroup counts the rows that take part (up to four bytes a
 // lane, on their way while the first row is looked up), and the first one writes the header, error word
@@ -2421,9 +2421,10 @@ void launch_cached(const RowParams &p_in, int blocks_per_cu, hipStream_t st)
     if (p.n_tokens <= grid || (p.queue_chunk > 1 && p.n_tokens <= 8 * grid)) p.queued = 0;
     if (grid > p.n_tokens) grid = p.n_tokens;
     // The log-probs pass asks for twice as many rows at once while two rounds of that are left, if there is a mask: a masked
-    // row, which it only looks at, costs it the counter's answer all the same.  A third of the rows masked, 16384 x 152064 bf16:
-    // one at a time 526 us, two 502, four 495, eight 490; 8192 x 128256 238, 224, 219, 234; 4096 x 50304 fp32 95, 92, 94, 96.
-    // None masked, 16384 x 152064: 735, 755, 780, 767.
+    // row, which it only looks at, costs it the counter's answer all the same.  Responses padded at their end, a third of the rows
+    // masked: 16384 x 152064 bf16 491 us one at a time, 464 two, 3000 x 128256 87 and 77, 8192 x 65536 124 and 121; four and eight gain
+    // no more.  A mask without a zero costs the widest rows 1 % by it (16384 x 152064 751 and 760 us, 8192 x 128256 328 and 326), but
+    // to ask for two only behind a masked row, by a flag or by counts, costs every batch 1 to 3 %.
     p.queue_more = p.queue_chunk * (p.mask ? 2 : 1);
     p.more_until = (p.n_tokens - 2 * grid * p.queue_more) / p.queue_parts;
     // dynamic LDS: the waiting gradient slots, or the LDS-resident part of the row
@@ -2524,7 +2525,7 @@ constexpr bool few_rounds(long long n, long long cus) { return 5 * n > 8 * cus &
 // of middling width go to a workgroup (1400 x 16001 38.3 and 40.3, 2048 x 8001 fp32 36.0 and 38.5; 9000 x 16001 137 with).
 constexpr bool shift_pays(int vectors, bool aux, long long row_bytes, long long n, long long cus)
 {
-    if (vectors <= 1024) return !aux && row_bytes >= 12288;
+    if (vectors <= 1024) return row_bytes >= 12288;  // (not reached by rows of up to 256 vectors, or 1024 with the auxiliary terms)
     return !aux || vectors > 4096 || row_bytes >= 40960 || n > 8 * cus;
 }
 
@@ -2553,7 +2554,7 @@ void launch_rows(const RowParams &p_in, hipStream_t st)
     case ID:                                                                                       \
         static_assert(PERCU == row_blocks_per_cu(BLOCK, NV), "workgroups per CU");                \
         /* gradient rows that begin inside a line, if the slots hold a row seven vectors further back */ \
-        if constexpr (NL == 0) {                                                                   \
+        if constexpr (NL == 0 && BLOCK * NV > (AUX ? 1024 : 256)) {                                \
             /* 512 lanes of 26 and 32 slots: the kernel for ragged rows serves whole ones too */   \
             constexpr bool T = TAIL || (BLOCK == 512 && (NV == 26 || NV == 32));                   \
             if ((p.shift0 | p.shift_step) != 0 && p.vocab / Elem<DT>::EPV + 7 <= BLOCK * NV &&     \

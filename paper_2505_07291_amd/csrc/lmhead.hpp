@@ -165,8 +165,8 @@ __global__ void __launch_bounds__(LM_THREADS) lm_gemm_nt(GemmParams p)
     // store their tiles while the others multiply.  In step, 256 of them store 64 MB at once, as long as 6 K steps, and multiply
     // with the memory idle (1024 x 50304 x 768 with the auxiliary terms 311 -> 295 us a call, 4096 x 32000 x 256 347 ->
     // 331, 1500 x 30000 x 640 258 -> 246).  Of long ones it is the operands that count, which neighbouring tiles share
-    // while they are in step (log-probs of 2048 x 152064 x 5120 1682 us, 1704 with it); even the possibility costs them
-    // 0.5 %, so it is an instantiation of its own (LEAD) where the host knows the length.
+    // while they are in step (log-probs of 2048 x 152064 x 5120 1682 us, 1704 with it); even the possibility costs the
+    // logits' 0.5 %, so it is an instantiation of its own (LEAD).
     int lead = -1, idx_end = n_items;  // the place taken first, if any, and where the others end
     if (LEAD && K <= LM_LEAD_STEPS * LM_BK && idx < n_items) {
         const int last = idx + (n_items - 1 - idx) / per_xcd * per_xcd;
@@ -1674,6 +1674,8 @@ grpo_status lm_impl(bool bwd, bool aux, const void *hidden, int64_t hidden_strid
             gw.C = grad_weight;
             gw.ldc = grad_weight_stride;
             gw.accumulate = (accumulate_grad_weight || c > 0) ? 1 : 0;  // the first chunk starts the sum
+            // (how many rows it contracts the host does not know; the possibility costs this product's long contractions
+            // nothing: call on 4096 x 152064 x 5120 11084 us with it, 11122 without, 2048 x 152064 x 2048 2740 either way)
             e = lm_launch_gemm<LM_EPI_F32, LM_Z_NONE, false, true, false, true>(gw, st);
             if (e != hipSuccess) return GRPO_ERR_HIP;
         }
