@@ -1803,17 +1803,22 @@ static __global__ void __launch_bounds__(1024) grpo_count_rows(const unsigned ch
 // stored.  That pays where each has several masked rows (1000 x 152064 bf16, 900 masked, 80 -> 71 us, 3000 of which 1125 277 -> 275;
 // with the auxiliary terms, whose passes are longer, 1400 of which 525 163 -> 159 and, sharing CUs, 4096 x 16384 of which
 // 1536 80 -> 74; 1400 x 32000, 1260 masked, 38 -> 36), or
-// where it has one live row at most and shares its CU (1400 x 32000, 525 masked, with the auxiliary terms 52 -> 46).  Fewer masked rows
-// are filled by workgroups that are out of live rows while others have one more (700 x 152064, 263 masked, with the
-// auxiliary terms 82 us, late 91; 1400 x 65536, 525 masked, 71 and 76; 400 x 81920, 150 masked, 41 and 45).
+// where it has one live row at most and shares its CU (1400 x 32000, 525 masked, with the auxiliary terms 52 -> 46), without the auxiliary
+// terms and four to a CU up to five rows on four of them (1741 x 17470, 564 masked, 44.5 -> 42.8, 461 masked 45.3 -> 44.7, 2600 of which
+// 1423 are 48.7 -> 47.9, 1500 x 32000, 272 masked, 48.4 -> 46.4; at thirteen on ten even, from there on it loses up to 8 %).  Fewer masked
+// rows are filled by workgroups that are out of live rows while others have one more (700 x 152064, 263 masked, with the auxiliary
+// terms 82 us, late 91; 1400 x 65536, 525 masked, 71 and 76; 400 x 81920, 150 masked, 41 and 45).  Streamed rows, of which
+// none is held, have them late in all long batches (4096 x 152069, 1452 masked, 423 -> 421, 2500 of which 334 are 306 -> 305; 1100 of which
+// 417 are 132 and 134).
 struct LateRule {
-    long long grid;  // the row kernel's workgroups; 0: never
-    int few;         // masked rows to a workgroup up to which they are filled first
-    bool shared;     // several workgroups to a CU
+    long long grid;   // the row kernel's workgroups; 0: never
+    int few;          // masked rows to a workgroup up to which they are filled first
+    long long up_to;  // late up to so many live rows
+    long long from;   // and with more than so many
     __host__ __device__ bool late(long long n, long long live) const
     {
         const long long masked = n - live;
-        return grid > 0 && (masked > few * grid || (masked > grid && masked > 4 * live) || (shared && live <= grid));
+        return grid > 0 && (masked > few * grid || (masked > grid && masked > 4 * live) || live <= up_to || live > from);
     }
 };
 
@@ -2693,7 +2698,8 @@ static grpo_status loss_impl(bool aux, const void *logits, int dtype, int64_t n_
         // (from the queue only; rows with a streamed remainder gain nothing)
         if (n_tokens > grid && !plan.streamed_remainder) {
             const bool shared = plan.workgroups_per_cu > 1;
-            rule = {grid, !aux ? 4 : shared ? 1 : 2, shared};
+            rule = {grid, !aux ? 4 : shared ? 1 : 2, !shared ? 0 : !aux && plan.workgroups_per_cu == 4 ? grid + grid / 4 : grid,
+                    plan.streaming ? 4 * grid : n_tokens};
         }
     }
     const float *weights = aux ? token_weights : nullptr;

@@ -229,7 +229,8 @@ def test_several_rows_that_begin_inside_a_line(aux, dtype, epv, vectors):
 @pytest.mark.parametrize("aux", [False, True])
 @pytest.mark.parametrize("dtype,vocab,rows", [("bf16", 152064, 700), ("bf16", 81925, 700), ("bf16", 200064, 600), ("bf16", 65536, 1100),
                                               ("bf16", 16384, 1300), ("f32", 50304, 700), ("bf16", 300000, 520), ("bf16", 152069, 1100),
-                                              ("bf16", 71616, 411), ("f32", 65533, 768), ("bf16", 240000, 700), ("f32", 75008, 769)])
+                                              ("bf16", 71616, 411), ("f32", 65533, 768), ("bf16", 240000, 700), ("f32", 75008, 769),
+                                              ("bf16", 17470, 1300), ("bf16", 131081, 2100)])
 def test_masked_rows_before_and_behind_live_ones(dtype, vocab, rows, aux):
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     cus = torch.cuda.get_device_properties(0).multi_processor_count
@@ -256,7 +257,8 @@ def test_masked_rows_before_and_behind_live_ones(dtype, vocab, rows, aux):
         assert bool((grad[:, vocab:] == 3.0).all()), "written outside the rows"
         return [grad[:, :vocab]] + [t for t in out[1:-1] if t.shape[0] == n]
 
-    for live in sorted({0, 1, 40, rows // 5, max(0, rows - 2 * cus - 1), rows * 5 // 8, rows - 1}):
+    edges = {cus * 5, cus * 5 + 1, cus * 8, cus * 8 + 1}  # five rows on four workgroups of four to a CU, four to one of two
+    for live in sorted({0, 1, 40, rows // 5, max(0, rows - 2 * cus - 1), rows * 5 // 8, rows - 1} | {e for e in edges if e < rows}):
         mask = torch.zeros(rows, dtype=torch.uint8)
         mask[order[:live]] = 1
         mask = mask.to("cuda")
